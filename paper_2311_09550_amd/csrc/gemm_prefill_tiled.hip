@@ -16,12 +16,22 @@
 //                    the conversion of Fig. 4(c) then lands in the activations' natural k order and the
 //                    activation bytes need no shuffling at all.
 //
-// The 32 lanes of an MFMA operand read 512 consecutive bytes of a block: no LDS bank conflicts, no swizzle.
+// The 16 lanes of a K group of an MFMA operand read 256 consecutive bytes of a block: no LDS bank conflicts, no swizzle.
+//
+// Matrix instruction: v_mfma_i32_16x16x64_i8.  At large M the chip holds its clock to a power limit, and per operation
+// the 16x16x64 form touches half the accumulator registers of the 32x32x32 form: a register-resident loop on random
+// int8 activations and multiples of 16 as weights runs at 4.5 POP/s with it and at 3.6 with 32x32x32 (4.8 and 4.6 on
+// constant operands, where power does not bind).  In this kernel, N = 8192, K = 28672, M = 2048: 326 us before (32x32x32),
+// 278 us now; N = 27648, K = 5120, M = 1024: 123 before, 102 now.  What bounds it then: in the 256 x 256 tile the matrix
+// cores, 80 % busy at 2.1 GHz; in the smaller tiles the vector issue slots of the conversion (6 operations per weight
+// fragment and wave, for MT MFMAs of four issue slots each) and the LDS reads.
 //
 // Kernel structure: a ring of STAGES stages of 128 k in LDS, filled by LDS-direct buffer loads (1 KB per wave
 // instruction: 8 activation rows x 128 B, or half a weight block).  Stage t + STAGES is requested as soon as every
 // wave has taken its last fragment of stage t, so STAGES - 1 stages are in flight while one is being multiplied.
-// One workgroup barrier per stage; fragments for the next MFMA step are always read during the current one.
+// One workgroup barrier per stage; fragments are always read a block of MFMAs ahead of their use.
+#include <type_traits>
+
 #include "common.hpp"
 #include "kernels.hpp"
 
@@ -29,12 +39,9 @@ namespace w4a8 {
 
 namespace {
 
-typedef int v16i __attribute__((ext_vector_type(16)));
 typedef __attribute__((address_space(3))) void *lds_ptr_t;
 
 constexpr int kStageK = kTiledBlockK;
-
-__device__ __forceinline__ v16i mfma32(v4i a, v4i b, v16i c) { return __builtin_amdgcn_mfma_i32_32x32x32_i8(a, b, c, 0, 0, 0); }
 
 // Swizzle of the eight 16-byte slots of a 128-byte activation row in LDS: 8 as well as 16 consecutive rows reading
 // the same logical slot fall into different banks.
@@ -104,9 +111,9 @@ __global__ __launch_bounds__(256) void tile_weights_kernel(const uint8_t *__rest
 // group, so every stage starts its integer sums from zero and ends by folding them, converted to fp32 and multiplied
 // by the group's scales, into a second, floating-point set of accumulators: per MFMA 8 extra VALU operations, twice
 // the accumulator registers (which rules out the 256 x 256 tile), and one more 16-byte load per wave and stage (each
-// wave brings in the 32 NTW scales it needs itself, next to its share of the operands).
+// wave brings in the 16 NT scales it needs itself, next to its share of the operands).
 // KS = 2 (signed int4, per-channel scales only): two sets of WM x WN waves share the output tile and split every
-// stage's k between them (set ks takes k = 64 ks .. 64 ks + 63 of the stage, i.e. MFMA steps 2 ks and 2 ks + 1); their
+// stage's k between them (set ks takes MFMA step ks); their
 // integer sums meet in LDS before the epilogue.  For tiles that a compute unit holds only once (N too small for
 // more workgroups) this doubles the waves per SIMD without shrinking the tile.
 // SWIGLU (signed int4, per-channel scales, fp16 output): the channels are gate and up projections interleaved
@@ -114,7 +121,7 @@ __global__ __launch_bounds__(256) void tile_weights_kernel(const uint8_t *__rest
 // two values: the glue between the gate+up and the down projection done where its inputs are produced (the fusion
 // across operators of Sec. 6.1).  p.out is then h [M][p.ldc], p.ldc = channels / 2; same bits as silu_mul_kernel
 // gives on the unfused output.
-template <int MTW, int NTW, int WM, int WN, int STAGES, bool ACC_OUT, int WBITS = 4, bool UNS = false, bool FG = false,
+template <int MT, int NT, int WM, int WN, int STAGES, bool ACC_OUT, int WBITS = 4, bool UNS = false, bool FG = false,
           int KS = 1, bool SWIGLU = false>
 __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kernel(PrefillArgs p) {
     static_assert(!SWIGLU || (WBITS == 4 && !UNS && !FG && !ACC_OUT), "fused SiLU * up: the plain W4A8 kernel, fp16 output");
@@ -128,8 +135,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
     constexpr int kParts = kBlock / 1024;                  // wave loads per block
     constexpr int kOutWaves = WM * WN;     // waves that own a part of the output tile
     constexpr int kWaves = kOutWaves * KS;
-    constexpr int BM = 32 * MTW * WM;
-    constexpr int BN = 32 * NTW * WN;
+    constexpr int BM = 16 * MT * WM;
+    constexpr int BN = 16 * NT * WN;
+    static_assert(BM % 32 == 0 && BN % 32 == 0, "the tile is whole weight blocks wide");
     constexpr int A_TOTAL = BM / 8;                 // wave loads (8 rows x 128 B) of an activation stage
     constexpr int B_TOTAL = (BN / 32) * kParts;     // wave loads (1 KB of a weight block) of a weight stage
     static_assert(A_TOTAL % kWaves == 0 && (kWaves & 1) == 0, "activation loads must split evenly over an even wave count");
@@ -141,11 +149,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
     constexpr int B_STAGE = (BN / 32) * kBlock;
     constexpr int kBBase = STAGES * A_STAGE;
     constexpr int kSpare = STAGES * (A_STAGE + B_STAGE);  // 1 KB that absorbs the surplus loads of an uneven split
-    constexpr int kScaleBase = kSpare + 1024;             // FG: per ring slot and wave, 32 NTW group scales
-    constexpr int kScaleWave = NTW * 128;
+    constexpr int kScaleBase = kSpare + 1024;             // FG: per ring slot and wave, 16 NT group scales
+    constexpr int kScaleWave = NT * 64;
+    constexpr int kSlabRows = MT % 2 == 0 ? 32 : 16;      // rows that a wave turns around in LDS at a time in the epilogue
     // behind everything else: the tile's s_a and s_w for the epilogue (see below); mirrors launch_one's layout
-    constexpr int kRingBytes = STAGES * (A_STAGE + B_STAGE) + 1024 + (FG ? STAGES * kOutWaves * NTW * 128 + 1024 : 0);
-    constexpr int kMeetBytes = KS == 2 ? kOutWaves * (32 * (64 * NTW + 16) + MTW * NTW * 16 * 256) : 0;
+    constexpr int kRingBytes = STAGES * (A_STAGE + B_STAGE) + 1024 + (FG ? STAGES * kOutWaves * NT * 64 + 1024 : 0);
+    constexpr int kMeetBytes = KS == 2 ? kOutWaves * (kSlabRows * (32 * NT + 16) + MT * NT * 4 * 256) : 0;
     constexpr int kEpiScales = kRingBytes > kMeetBytes ? kRingBytes : kMeetBytes;
     static_assert(kWaves * 64 >= BM && kWaves * 64 >= BN, "one thread per row and per channel of the tile");
     static_assert(STAGES >= 2 && (STAGES - 1) * kLoads < 64, "outstanding loads must fit the counter");
@@ -158,8 +167,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
     const int wsub = wave % kOutWaves;
     const int wm = wsub / WN;
     const int wn = wsub % WN;
-    const int idx = lane & 31;
-    const int g = lane >> 5;
+    const int idx = lane & 15;  // row of a 16-row operand tile
+    const int g = lane >> 4;    // K group
 
     // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs; consecutive tiles of one XCD share
     // their weight panel, so it is fetched into that XCD's L2 once
@@ -221,10 +230,10 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
                        ? ((unsigned)nb * (unsigned)st_all * kParts + (L % kParts)) * 1024u + lane * 16
                        : kNowhere;
     }
-    // FG: lane L < 8 NTW of every wave fetches the scales of channels n_wave + 4 L .. + 3 of the stage's group
+    // FG: lane L < 4 NT of every wave fetches the scales of channels n_wave + 4 L .. + 3 of the stage's group
     // (p.ldg is a multiple of 4, so a 16-byte run lies wholly inside a row of s_g or wholly outside)
     const v4i g_rsrc = FG ? make_rsrc(p.s_w, (size_t)st_all * (size_t)p.ldg * 4) : v4i{0, 0, 0, 0};
-    const int g_n = bn0 + wn * (32 * NTW) + 4 * lane;
+    const int g_n = bn0 + wn * (16 * NT) + 4 * lane;
     const unsigned g_off = (FG && g_n < p.ldg) ? (unsigned)g_n * 4u : kNowhere;
 
     // The load is written in assembly on purpose: the compiler orders LDS reads after every LDS-writing load it knows
@@ -252,90 +261,105 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
                 const int L = i * kWaves + wave;
                 const unsigned dst = (kRagged && L >= B_TOTAL) ? kSpare : kBBase + slot * B_STAGE + L * 1024;
                 dma16(b_rsrc, lds_base + dst, b_off[i], st * kBlock);
-            } else if (lane < 8 * NTW) {  // FG: the other lanes are masked off and write nothing
+            } else if (lane < 4 * NT) {  // FG: the other lanes are masked off and write nothing
                 dma16(g_rsrc, lds_base + kScaleBase + (slot * kWaves + wave) * kScaleWave, g_off, st * p.ldg * 4);
             }
         }
     };
 
-    v16i acc[MTW][NTW];
+    // The wave's part of the output tile: MT x NT tiles of 16 rows of X x 16 channels.
+    v4i acc[MT][NT];
 #pragma unroll
-    for (int mt = 0; mt < MTW; ++mt)
+    for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-        for (int t = 0; t < NTW; ++t)
-#pragma unroll
-            for (int v = 0; v < 16; ++v) acc[mt][t][v] = 0;
+        for (int t = 0; t < NT; ++t) acc[mt][t] = v4i{0, 0, 0, 0};
     // FG: sum over the groups of float(integer sum of the group) * group scale, sixteen-fold like the integer sums
-    float facc[FG ? MTW : 1][FG ? NTW : 1][16];
+    float facc[FG ? MT : 1][FG ? NT : 1][4];
     if (FG) {
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int t = 0; t < NTW; ++t)
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) facc[FG ? mt : 0][FG ? t : 0][v] = 0.f;
+                for (int v = 0; v < 4; ++v) facc[FG ? mt : 0][FG ? t : 0][v] = 0.f;
     }
 
-    // LDS offsets of this lane's fragments inside a stage.  MFMA step j = 0..3 of a stage covers k = 32 j .. 32 j + 31;
-    // lane (idx, g) supplies k = 32 j + 16 g .. + 15: activation chunk 2 j + g of its row, and dwords 2 (j % 2), +1
-    // of weight chunk ... (the weight chunk c = 32 k holds two steps: c = j / 2 ... see read_w).
-    // Steps are numbered so that one weight chunk serves two consecutive steps: step j uses weight chunk
-    // 2 (j / 2) + g, dwords 2 (j % 2) and 2 (j % 2) + 1, i.e. k = 64 (j/2) + 32 g + 16 (j%2) .. + 15, and the
-    // activation chunk with the same k: 4 (j / 2) + 2 g + (j % 2).
-    int xa[4];
+    // LDS offsets of this lane's fragments inside a stage.  A stage is two MFMA steps h = 0, 1 of 64 k.  int4: K group g of
+    // step h is k = 32 g + 16 h .. + 15, so that the 16 bytes of weight chunk g hold a lane's codes of both steps (dwords
+    // 2 h, 2 h + 1), and the activation chunk is 2 g + h.  int8: k = 64 h + 16 g .. + 15, chunk 4 h + g of both operands.
+    int xa[2];
     {
-        const int row = wm * (32 * MTW) + idx;  // rows of the other m tiles differ by 32: same swizzle
+        const int row = wm * (16 * MT) + idx;  // the other m tiles lie multiples of 16 rows further: same swizzle
 #pragma unroll
-        for (int j = 0; j < 4; ++j) {
-            // int8 weights: step j, lane group g holds k = 32 j + 16 g .. + 15, i.e. activation chunk 2 j + g
-            const int chunk = W8 ? 2 * j + g : 4 * (j >> 1) + 2 * g + (j & 1);
-            xa[j] = row * 128 + ((chunk ^ fx(row)) << 4);
-        }
+        for (int h = 0; h < 2; ++h) xa[h] = row * 128 + (((W8 ? 4 * h + g : 2 * g + h) ^ fx(row)) << 4);
     }
-    const int wa = kBBase + wn * (NTW * kBlock) + (g * 32 + idx) * 16;
-    auto read_x_at = [&](v4u(&dst)[MTW], int slot, int offset) {
+    // channel tile t of the wave is tile T = wn NT + t of the output tile, half T % 2 of weight block T / 2
+    const int tile0 = wn * NT;
+    const int wa_even = kBBase + (tile0 >> 1) * kBlock + (tile0 & 1) * 256 + (g * 32 + idx) * 16;
+    const int wa_odd = wa_even + ((tile0 & 1) ? kBlock - 256 : 256);
+    auto wa = [&](int t) { return (NT % 2 == 0 ? wa_even + (t & 1) * 256 : (t & 1) ? wa_odd : wa_even) + (t >> 1) * kBlock; };
+    // A block of MFMAs takes at most four m tiles, so that its fragments and those of the next one fit the registers.
+    constexpr int XF = MT > 4 ? MT / 2 : MT;
+    constexpr int kBlocksPerStep = MT / XF;
+    constexpr int kBlocks = 2 * kBlocksPerStep;  // per stage
+    static_assert(MT % XF == 0, "m tiles must split evenly over the blocks");
+    auto read_x = [&](v4u(&dst)[XF], int slot, int h, int m0) {
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) dst[mt] = *(const v4u *)(&lds[slot * A_STAGE + offset + mt * 4096]);
+        for (int i = 0; i < XF; ++i) dst[i] = *(const v4u *)(&lds[slot * A_STAGE + xa[h] + (m0 + i) * 2048]);
     };
-    auto read_x = [&](v4u(&dst)[MTW], int slot, int j) { read_x_at(dst, slot, xa[j]); };
-    // weight fragments of the pair of chunks q: int4 -> q = 0, 1 serves MFMA steps 2q and 2q + 1 (halves h = 0, 1 of
-    // the fragment); int8 -> q = 0 .. 3 serves MFMA step q
-    auto read_w = [&](v4u(&dst)[NTW], int slot, int q) {
-#pragma unroll
-        for (int t = 0; t < NTW; ++t) dst[t] = *(const v4u *)(&lds[slot * B_STAGE + wa + t * kBlock + q * 1024]);
+    // weight fragment of channel tile t: int4 -> both steps of the stage; int8 -> step h
+    auto read_w = [&](v4u &dst, int slot, int t, int h) {
+        dst = *(const v4u *)(&lds[slot * B_STAGE + wa(t) + (W8 ? h * 2048 : 0)]);
     };
     // the scales of this wave's channels for the group in ring slot `slot`, in accumulator order:
-    // register 4 q + e of block t belongs to channel 32 t + 8 q + 4 g + e
-    auto read_sg = [&](float(&dst)[NTW][16], int slot) {
+    // register v of tile t belongs to channel 16 t + 4 g + v
+    auto read_sg = [&](float(&dst)[NT][4], int slot) {
 #pragma unroll
-        for (int t = 0; t < NTW; ++t)
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const float4 v = *(const float4 *)(&lds[kScaleBase + (slot * kWaves + wave) * kScaleWave +
-                                                        (32 * t + 8 * q + 4 * g) * 4]);
-                dst[t][4 * q] = v.x;
-                dst[t][4 * q + 1] = v.y;
-                dst[t][4 * q + 2] = v.z;
-                dst[t][4 * q + 3] = v.w;
-            }
+        for (int t = 0; t < NT; ++t) {
+            const float4 v = *(const float4 *)(&lds[kScaleBase + (slot * kWaves + wave) * kScaleWave + (16 * t + 4 * g) * 4]);
+            dst[t][0] = v.x;
+            dst[t][1] = v.y;
+            dst[t][2] = v.z;
+            dst[t][3] = v.w;
+        }
     };
-    // fresh = true (FG, first step of a stage): the group's integer sums start from zero
-    auto mfma_step = [&](const v4u(&x)[MTW], const v4u(&w)[NTW], int h, bool fresh = false) {
+    auto w_op = [&](const v4u &w, int h) {
+        return W8    ? v4i{(int)w.x, (int)w.y, (int)w.z, (int)w.w}
+               : UNS ? (h == 0 ? u_operand_tiled(w.x, w.y) : u_operand_tiled(w.z, w.w))
+                     : (h == 0 ? w_operand_tiled(w.x, w.y) : w_operand_tiled(w.z, w.w));
+    };
+    // MFMAs of m tiles m0 .. m0 + XF - 1 with every channel tile, step h.  fresh = true (FG, first step of a stage): the
+    // group's integer sums start from zero.  behind(t) is issued behind the MFMAs of channel tile t.
+    // wk[t] holds the operands of channel tile t.  While the MFMAs of a tile run, the codes of the next tile are converted
+    // (CONVERT: the block is the first of its step; in the others the operands are there already), two vector operations
+    // to an MFMA, which issue while the matrix core is busy (N = 5120, K = 13824, M = 1024, tile 128 x 256: 67 us against 75
+    // with the conversion right in front of the MFMAs that use it); behind the last tile of a step (hn >= 0) those of the
+    // first tile of the next step, hn.
+    v4i wk[NT];
+    auto mfma_block = [&](const v4u(&x)[XF], v4u(&w)[NT], int h, int m0, bool fresh, bool convert, int hn, auto behind) {
 #pragma unroll
-        for (int t = 0; t < NTW; ++t) {
-            const v4i wop = W8    ? v4i{(int)w[t].x, (int)w[t].y, (int)w[t].z, (int)w[t].w}
-                            : UNS ? (h == 0 ? u_operand_tiled(w[t].x, w[t].y) : u_operand_tiled(w[t].z, w[t].w))
-                                  : (h == 0 ? w_operand_tiled(w[t].x, w[t].y) : w_operand_tiled(w[t].z, w[t].w));
+        for (int t = 0; t < NT; ++t) {
+            static_assert(NT >= 2, "the next step's first operand is converted before its fragment is replaced");
+            const v4i wop = wk[t];
+            if (convert && t + 1 < NT) wk[t + 1] = w_op(w[t + 1], h);
+            if (t + 1 == NT && hn >= 0) wk[0] = w_op(w[0], hn);
 #pragma unroll
-            for (int mt = 0; mt < MTW; ++mt)
-                acc[mt][t] = mfma32(wop, v4i{(int)x[mt].x, (int)x[mt].y, (int)x[mt].z, (int)x[mt].w},
-                                    fresh ? v16i{0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0, 0} : acc[mt][t]);
+            for (int i = 0; i < XF; ++i)
+                acc[m0 + i][t] = mfma_i8_16x16x64(wop, v4i{(int)x[i].x, (int)x[i].y, (int)x[i].z, (int)x[i].w},
+                                                  fresh ? v4i{0, 0, 0, 0} : acc[m0 + i][t]);
+            behind(t);
+#pragma unroll
+            for (int i = 0; i < XF; ++i) {
+                __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+                __builtin_amdgcn_sched_group_barrier(0x002, 2, 0);
+            }
+            __builtin_amdgcn_sched_barrier(0);
         }
     };
 
     // Two schedules.  Ring of two: stage st + 2 can only be requested once stage st has been read, i.e. in one burst
     // behind the barrier of stage st.  Ring of three or more (kSpread): the slot freed by the barrier of stage st - 1
-    // is refilled with stage st + STAGES - 1 in thirds, between the MFMA blocks of stage st; a burst of loads right
+    // is refilled with stage st + STAGES - 1 load by load, between the MFMAs of stage st; a burst of loads right
     // behind the barrier holds up the issuing wave for as long as the address unit needs to take them (measured: a
     // fifth of the loop time), spread out they cost an issue slot each.
     // Loads return in order, so "at most n outstanding" means all but the youngest n have landed; waiting for fewer
@@ -353,116 +377,115 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
         wait_vmcnt<0>();
     __builtin_amdgcn_s_barrier();
 
-    v4u x0[MTW], x1[MTW], w0[NTW], w1[NTW];
-    float sg[FG ? NTW : 1][16];
+    v4u x0[XF], x1[XF], w[NT];
     int slot = 0;
+    auto handover = [&](bool count_outstanding) {
+        if (count_outstanding)
+            wait_vmcnt<(STAGES - 2) * kLoads>();  // the stages behind st + 1 may still be in flight
+        else
+            wait_vmcnt<0>();
+        __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's last fragment reads of the slot have returned
+        __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
+        __builtin_amdgcn_s_barrier();
+        __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
+    };
     if constexpr (KS == 2) {
-        // Per stage and wave two MFMA steps (2 ks and 2 ks + 1, one weight fragment) with the barrier between them:
-        // by then this wave has every fragment of the stage in registers.  The target stage goes out in halves,
-        // one before and one behind the barrier, so behind the barrier's wait only the first half may be in flight.
-        static_assert(kSpread, "the k split uses the spread schedule");
-        constexpr int kFirstHalf = (kLoads + 1) / 2;
-        const int xa_first = ks ? xa[2] : xa[0], xa_second = ks ? xa[3] : xa[1];
-        read_x_at(x0, 0, xa_first);
-        read_w(w0, 0, ks);
+        // Wave set ks multiplies step ks of every stage, whose fragments it reads one stage ahead.
+        static_assert(kSpread && XF == MT, "the k split uses the spread schedule and one block per step");
+        auto read_half = [&](v4u &dst, int slot, int t) {  // the eight bytes of step ks
+            const v2u v = *(const v2u *)(&lds[slot * B_STAGE + wa(t) + 8 * ks]);
+            dst.x = v.x;
+            dst.y = v.y;
+        };
+        read_x(x0, 0, ks, 0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) read_half(w[t], 0, t);
+        wk[0] = w_op(w[0], 0);
         for (int st = 0; st < st_total; ++st) {
             const int next = slot + 1 == STAGES ? 0 : slot + 1;
             const int prev = slot == 0 ? STAGES - 1 : slot - 1;
-            const int target = st + STAGES - 1;
-            const bool have_target = target < st_total;
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-            read_x_at(x1, slot, xa_second);
-            if (have_target) issue(target, prev, 0, 2);
+            const int target = st + STAGES - 1;  // into the slot whose fragments every wave had before the last barrier
+            if (target < st_total) issue(target, prev, 0, 1);
+            handover(target < st_total);
+            const bool more = st + 1 < st_total;
+            if (more) read_x(x1, next, ks, 0);
             __builtin_amdgcn_sched_barrier(0);
-            mfma_step(x0, w0, 0);
-            __builtin_amdgcn_sched_barrier(0);
-            if (have_target)
-                wait_vmcnt<kFirstHalf>();
-            else
-                wait_vmcnt<0>();
-            __builtin_amdgcn_s_waitcnt(0xC07F);
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            if (have_target) issue(target, prev, 1, 2);
-            if (st + 1 < st_total) {
-                read_x_at(x0, next, xa_first);
-                read_w(w1, next, ks);
-            }
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_step(x1, w0, 1);
-            __builtin_amdgcn_sched_barrier(0);
+            mfma_block(x0, w, 0, 0, false, true, 0, [&](int t) {
+                if (more) read_half(w[t], next, t);
+            });
 #pragma unroll
-            for (int t = 0; t < NTW; ++t) w0[t] = w1[t];
+            for (int i = 0; i < XF; ++i) x0[i] = x1[i];
             slot = next;
         }
     } else {
-        read_x(x0, 0, 0);
-        read_w(w0, 0, 0);
-        for (int st = 0; st < st_total; ++st) {
+        read_x(x0, 0, 0, 0);
+#pragma unroll
+        for (int t = 0; t < NT; ++t) read_w(w[t], 0, t, 0);
+        wk[0] = w_op(w[0], 0);
+        float sg[FG ? NT : 1][4];
+        // One stage: kBlocks blocks of MFMAs, each reading the activation fragments of the block behind it; the scheduling
+        // fences keep those reads in front of the MFMAs they overlap with (left alone the compiler sinks them next to
+        // their first use and every block then starts with an exposed LDS wait).  A weight fragment is replaced by its
+        // successor right behind its last MFMAs.  TARGET: there is a stage left to request.
+        auto stage = [&](int st, auto target_c) {
+            constexpr bool TARGET = decltype(target_c)::value;
             const int next = slot + 1 == STAGES ? 0 : slot + 1;
             const int prev = slot == 0 ? STAGES - 1 : slot - 1;
-            const int target = st + STAGES - 1;            // kSpread: the stage requested during this one
-            const bool have_target = kSpread && target < st_total;
-            // The scheduling fences keep each block of LDS reads in front of the MFMA block it overlaps with; left alone
-            // the compiler sinks the reads next to their first use and every step then starts with an exposed LDS wait.
-            // The fragments of step 0 were requested eight MFMAs ago; waiting for them here, before the next reads go
-            // out, costs nothing and spares the wait the compiler would otherwise place behind those reads.
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0)
-            // Weight registers: int4 fragments hold two steps (w0: steps 0, 1; w1: steps 2, 3); int8 fragments one step
-            // each, w0 and w1 taking turns (w0: steps 0, 2; w1: steps 1, 3).
-            read_x(x1, slot, 1);
-            if (W8) read_w(w1, slot, 1);
-            if (have_target) issue(target, prev, 0, 3);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_step(x0, w0, 0, FG);
-            __builtin_amdgcn_sched_barrier(0);
-            read_x(x0, slot, 2);
-            if (W8)
-                read_w(w0, slot, 2);
-            else
-                read_w(w1, slot, 1);
-            if (have_target) issue(target, prev, 1, 3);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_step(x1, *(W8 ? &w1 : &w0), 1);
-            __builtin_amdgcn_sched_barrier(0);
-            read_x(x1, slot, 3);
-            if (W8) read_w(w1, slot, 3);
-            if constexpr (FG) read_sg(sg, slot);  // before the barrier that lets the slot be refilled
-            if (have_target) issue(target, prev, 2, 3);
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_step(x0, *(W8 ? &w0 : &w1), 0);
-            __builtin_amdgcn_sched_barrier(0);
-            // Every fragment of this stage is in registers once the reads above have returned, so after the barrier the
-            // slot can be refilled; stage st + 1 must be in LDS for every wave.
-            if (kSpread ? have_target : st + STAGES <= st_total)
-                wait_vmcnt<(STAGES - 2) * kLoads>();  // the stages behind st + 1 may still be in flight
-            else
-                wait_vmcnt<0>();
-            __builtin_amdgcn_s_waitcnt(0xC07F);  // lgkmcnt(0): this wave's last fragment reads of the slot have returned
-            __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
-            __builtin_amdgcn_s_barrier();
-            __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
-            if (!kSpread && st + STAGES < st_total) issue(st + STAGES, slot, 0, 1);
-            if (st + 1 < st_total) {
-                read_x(x0, next, 0);
-                read_w(w0, next, 0);
+#pragma unroll
+            for (int b = 0; b < kBlocks; ++b) {
+                const int h = b / kBlocksPerStep, m0 = (b % kBlocksPerStep) * XF;
+                const bool last = b + 1 == kBlocks;
+                v4u(&x)[XF] = (b & 1) ? x1 : x0;
+                v4u(&xn)[XF] = (b & 1) ? x0 : x1;
+                const bool more = TARGET || st + 1 < st_total;
+                if (!last) {
+                    read_x(xn, slot, (b + 1) / kBlocksPerStep, ((b + 1) % kBlocksPerStep) * XF);
+                    if constexpr (FG)
+                        if (b + 2 == kBlocks) read_sg(sg, slot);  // before the barrier that lets the slot be refilled
+                } else {
+                    // Every fragment of this stage is in registers once the reads above have returned, so after the
+                    // barrier the slot can be refilled; stage st + 1 must be in LDS for every wave.
+                    handover(TARGET || (!kSpread && st + STAGES <= st_total));
+                    if (!kSpread && TARGET) issue(st + STAGES, slot, 0, 1);
+                    if (more) read_x(xn, next, 0, 0);
+                }
+                __builtin_amdgcn_sched_barrier(0);
+                const bool step_ends = m0 + XF == MT;
+                mfma_block(x, w, h, m0, FG && h == 0, m0 == 0, step_ends ? 1 - h : -1, [&](int t) {
+                    // loads of the target stage, evenly over the channel tiles of every block but the last
+                    if constexpr (kSpread && TARGET) {
+                        constexpr int kPlaces = (kBlocks - 1) * NT;
+                        if (!last) {
+#pragma unroll
+                            for (int j = 0; j < kLoads; ++j)
+                                if (j * kPlaces / kLoads == b * NT + t) issue(st + STAGES - 1, prev, j, kLoads);
+                        }
+                    }
+                    if (step_ends) {
+                        if (last) {
+                            if (more) read_w(w[t], next, t, 0);
+                        } else if (W8) {
+                            read_w(w[t], slot, t, 1);
+                        }
+                    }
+                });
             }
-            __builtin_amdgcn_sched_barrier(0);
-            mfma_step(x1, w1, 1);
-            __builtin_amdgcn_sched_barrier(0);
             if constexpr (FG) {
                 // Dq of Eq. (5) for this group: a group's sums are below 2^24 in magnitude, so the conversion is exact
 #pragma unroll
-                for (int mt = 0; mt < MTW; ++mt)
+                for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                    for (int t = 0; t < NTW; ++t)
+                    for (int t = 0; t < NT; ++t)
 #pragma unroll
-                        for (int v = 0; v < 16; ++v)
+                        for (int v = 0; v < 4; ++v)
                             facc[mt][t][v] = __builtin_fmaf((float)acc[mt][t][v], sg[t][v], facc[mt][t][v]);
             }
             slot = next;
-        }
+        };
+        const int with_target = st_total - (kSpread ? STAGES - 1 : STAGES);
+        int st = 0;
+        for (; st < with_target; ++st) stage(st, std::true_type{});
+        for (; st < st_total; ++st) stage(st, std::false_type{});
     }
     wait_vmcnt<0>();
 
@@ -484,30 +507,30 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
     if constexpr (KS == 2) {
         // The two k halves meet: the ring is idle (the last barrier lies behind every wave's last fragment read and
         // every load has landed), the upper set parks its sums behind the area the epilogue's slabs will use and leaves.
-        constexpr int kRedBase = kOutWaves * 32 * (64 * NTW + 16);
-        int *part = (int *)(lds + kRedBase) + wsub * (MTW * NTW * 16 * 64) + lane;
+        constexpr int kRedBase = kOutWaves * kSlabRows * (32 * NT + 16);
+        int *part = (int *)(lds + kRedBase) + wsub * (MT * NT * 4 * 64) + lane;
         if (ks == 1) {
 #pragma unroll
-            for (int mt = 0; mt < MTW; ++mt)
+            for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-                for (int t = 0; t < NTW; ++t)
+                for (int t = 0; t < NT; ++t)
 #pragma unroll
-                    for (int v = 0; v < 16; ++v) part[((mt * NTW + t) * 16 + v) * 64] = acc[mt][t][v];
+                    for (int v = 0; v < 4; ++v) part[((mt * NT + t) * 4 + v) * 64] = acc[mt][t][v];
         }
         __builtin_amdgcn_fence(__ATOMIC_RELEASE, "workgroup", "local");
         __builtin_amdgcn_s_barrier();
         __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "workgroup", "local");
         if (ks == 1) return;
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt)
+        for (int mt = 0; mt < MT; ++mt)
 #pragma unroll
-            for (int t = 0; t < NTW; ++t)
+            for (int t = 0; t < NT; ++t)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[mt][t][v] += part[((mt * NTW + t) * 16 + v) * 64];
+                for (int v = 0; v < 4; ++v) acc[mt][t][v] += part[((mt * NT + t) * 4 + v) * 64];
     }
 
-    // Epilogue (Eq. (6),(7)).  A lane holds, per (mt, t, quad), four consecutive n of one m, so storing from the
-    // accumulator layout writes 16 bytes into each of 32 different rows per instruction.  Instead every wave turns
+    // Epilogue (Eq. (6),(7)).  A lane holds, per tile, four consecutive n of one m, so storing from the
+    // accumulator layout writes 32 bytes into each of 16 different rows per instruction.  Instead every wave turns
     // its 32-row slabs around in LDS (the ring is idle now: the last barrier of the loop lies behind every wave's
     // last fragment read and every load has landed) and stores whole 16-byte runs of 8 channels, 8 or more lanes per
     // row, i.e. whole cache lines.
@@ -522,35 +545,38 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
             return deq(acc[mt][t][v], s_a, s_w);
     };
     if (!ACC_OUT && (SWIGLU || (p.ldc & 7) == 0)) {  // the fused form is only launched with a pitch that allows this path
-        constexpr int kRowBytes = 64 * NTW;        // fp16 bytes of a slab row (32 NTW channels)
+        constexpr int kRowBytes = 32 * NT;         // fp16 bytes of a slab row (16 NT channels)
         constexpr int kPitch = kRowBytes + 16;     // padded: rows 16 apart, not 1 apart, share banks
-        constexpr int kChunksPerRow = 4 * NTW;     // 16-byte chunks
-        constexpr int kReads = (32 * kChunksPerRow + 63) / 64;
-        static_assert(kOutWaves * 32 * kPitch <= STAGES * (A_STAGE + B_STAGE), "slabs must fit the ring");
-        uint8_t *slab = lds + wsub * (32 * kPitch);
-        const int n_wave = bn0 + wn * (32 * NTW);
+        constexpr int kChunksPerRow = 2 * NT;      // 16-byte chunks
+        constexpr int kReads = (kSlabRows * kChunksPerRow + 63) / 64;
+        constexpr int kSlabTiles = kSlabRows / 16;
+        static_assert(kOutWaves * kSlabRows * kPitch <= STAGES * (A_STAGE + B_STAGE), "slabs must fit the ring");
+        uint8_t *slab = lds + wsub * (kSlabRows * kPitch);
+        const int n_wave = bn0 + wn * (16 * NT);
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt) {
-            const int m_slab = bm0 + wm * (32 * MTW) + 32 * mt;
-            const float sa = sa_lds[wm * (32 * MTW) + 32 * mt + idx];  // 0 for rows past M
+        for (int mt = 0; mt < MT; mt += kSlabTiles) {
+            const int m_slab = bm0 + wm * (16 * MT) + 16 * mt;
+            float sa[kSlabTiles];  // 0 for rows past M
 #pragma unroll
-            for (int t = 0; t < NTW; ++t) {
+            for (int e = 0; e < kSlabTiles; ++e) sa[e] = sa_lds[wm * (16 * MT) + 16 * (mt + e) + idx];
 #pragma unroll
-                for (int q = 0; q < 4; ++q) {
-                    const int nl = 32 * t + 8 * q + 4 * g;
-                    // channels past N carry scale 0: their values are formed but never stored
-                    const float4 sw = FG ? float4{0.f, 0.f, 0.f, 0.f} : *(const float4 *)(sw_lds + wn * (32 * NTW) + nl);
+            for (int t = 0; t < NT; ++t) {
+                const int nl = 16 * t + 4 * g;
+                // channels past N carry scale 0: their values are formed but never stored
+                const float4 sw = FG ? float4{0.f, 0.f, 0.f, 0.f} : *(const float4 *)(sw_lds + wn * (16 * NT) + nl);
+#pragma unroll
+                for (int e = 0; e < kSlabTiles; ++e) {
                     v2u o;
-                    o.x = pack_f16x2(value(mt, t, 4 * q, sa, sw.x), value(mt, t, 4 * q + 1, sa, sw.y));
-                    o.y = pack_f16x2(value(mt, t, 4 * q + 2, sa, sw.z), value(mt, t, 4 * q + 3, sa, sw.w));
-                    *(v2u *)(slab + idx * kPitch + nl * 2) = o;
+                    o.x = pack_f16x2(value(mt + e, t, 0, sa[e], sw.x), value(mt + e, t, 1, sa[e], sw.y));
+                    o.y = pack_f16x2(value(mt + e, t, 2, sa[e], sw.z), value(mt + e, t, 3, sa[e], sw.w));
+                    *(v2u *)(slab + (16 * e + idx) * kPitch + nl * 2) = o;
                 }
             }
 #pragma unroll
             for (int j = 0; j < kReads; ++j) {
                 const int c = j * 64 + lane;
                 const int row = c / kChunksPerRow, col = c - row * kChunksPerRow;
-                if (32 * kChunksPerRow % 64 != 0 && row >= 32) continue;
+                if (kSlabRows * kChunksPerRow % 64 != 0 && row >= kSlabRows) continue;
                 const v4u v = *(const v4u *)(slab + row * kPitch + col * 16);
                 const int mm = m_slab + row, n = n_wave + col * 8;
                 if (mm >= p.M || n >= p.N) continue;
@@ -585,43 +611,39 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
     // general epilogue: raw sums, or an output pitch that rules out 16-byte stores
     const bool vec_ok = (p.ldc & 3) == 0;
 #pragma unroll
-    for (int mt = 0; mt < MTW; ++mt) {
-        const int m = bm0 + wm * (32 * MTW) + 32 * mt + idx;
+    for (int mt = 0; mt < MT; ++mt) {
+        const int m = bm0 + wm * (16 * MT) + 16 * mt + idx;
         if (m >= p.M) continue;
-        const float sa = ACC_OUT ? 0.f : sa_lds[wm * (32 * MTW) + 32 * mt + idx];
+        const float sa = ACC_OUT ? 0.f : sa_lds[wm * (16 * MT) + 16 * mt + idx];
 #pragma unroll
-        for (int t = 0; t < NTW; ++t) {
-#pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const int n = bn0 + wn * (32 * NTW) + 32 * t + 8 * q + 4 * g;
-                if (n >= p.N) continue;
-                const v4i s = v4i{acc[mt][t][4 * q], acc[mt][t][4 * q + 1], acc[mt][t][4 * q + 2], acc[mt][t][4 * q + 3]};
-                if (ACC_OUT) {
-                    int *dst = p.acc_out + (size_t)m * p.ldc + n;
-                    if (p.splits > 1) dst += (size_t)blockIdx.y * (size_t)p.M * (size_t)p.ldc;
-                    constexpr int kShift = kTrueSums ? 0 : 4;  // signed int4: exact, every sum is a multiple of 16
-                    const v4i v = v4i{s.x >> kShift, s.y >> kShift, s.z >> kShift, s.w >> kShift};
-                    if (vec_ok && n + 3 < p.N) {
-                        *(v4i *)dst = v;
-                    } else {
-#pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (n + j < p.N) dst[j] = v[j];
-                    }
+        for (int t = 0; t < NT; ++t) {
+            const int n = bn0 + wn * (16 * NT) + 16 * t + 4 * g;
+            if (n >= p.N) continue;
+            if (ACC_OUT) {
+                int *dst = p.acc_out + (size_t)m * p.ldc + n;
+                if (p.splits > 1) dst += (size_t)blockIdx.y * (size_t)p.M * (size_t)p.ldc;
+                constexpr int kShift = kTrueSums ? 0 : 4;  // signed int4: exact, every sum is a multiple of 16
+                const v4i s = acc[mt][t];
+                const v4i v = v4i{s.x >> kShift, s.y >> kShift, s.z >> kShift, s.w >> kShift};
+                if (vec_ok && n + 3 < p.N) {
+                    *(v4i *)dst = v;
                 } else {
-                    unsigned short *dst = (unsigned short *)p.out + (size_t)m * p.ldc + n;
-                    if (vec_ok && n + 3 < p.N) {
-                        const float4 sw = FG ? float4{0.f, 0.f, 0.f, 0.f} : *(const float4 *)(sw_lds + (n - bn0));
-                        v2u o;
-                        o.x = pack_f16x2(value(mt, t, 4 * q, sa, sw.x), value(mt, t, 4 * q + 1, sa, sw.y));
-                        o.y = pack_f16x2(value(mt, t, 4 * q + 2, sa, sw.z), value(mt, t, 4 * q + 3, sa, sw.w));
-                        *(v2u *)dst = o;
-                    } else {
 #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-                            if (n + j < p.N)
-                                dst[j] = f32_to_f16_bits(value(mt, t, 4 * q + j, sa, FG ? 0.f : sw_lds[n + j - bn0]));
-                    }
+                    for (int j = 0; j < 4; ++j)
+                        if (n + j < p.N) dst[j] = v[j];
+                }
+            } else {
+                unsigned short *dst = (unsigned short *)p.out + (size_t)m * p.ldc + n;
+                if (vec_ok && n + 3 < p.N) {
+                    const float4 sw = FG ? float4{0.f, 0.f, 0.f, 0.f} : *(const float4 *)(sw_lds + (n - bn0));
+                    v2u o;
+                    o.x = pack_f16x2(value(mt, t, 0, sa, sw.x), value(mt, t, 1, sa, sw.y));
+                    o.y = pack_f16x2(value(mt, t, 2, sa, sw.z), value(mt, t, 3, sa, sw.w));
+                    *(v2u *)dst = o;
+                } else {
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        if (n + j < p.N) dst[j] = f32_to_f16_bits(value(mt, t, j, sa, FG ? 0.f : sw_lds[n + j - bn0]));
                 }
             }
         }
@@ -630,25 +652,25 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
 
 namespace {
 
-template <int MTW, int NTW, int WM, int WN, int STAGES, bool ACC_OUT, int WBITS, bool UNS, bool FG, int KS, bool SWIGLU = false>
+template <int MT, int NT, int WM, int WN, int STAGES, bool ACC_OUT, int WBITS, bool UNS, bool FG, int KS, bool SWIGLU = false>
 hipError_t launch_one(const PrefillArgs &p, dim3 grid, hipStream_t stream) {
-    constexpr int BM = 32 * MTW * WM, BN = 32 * NTW * WN;
-    // ring + spare KB; group scales: 128 NTW bytes per wave and ring slot, and a KB of slack behind them
-    constexpr int kRing = STAGES * (BM * 128 + BN * 16 * WBITS) + 1024 + (FG ? STAGES * WM * WN * NTW * 128 + 1024 : 0);
+    constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN;
+    // ring + spare KB; group scales: 64 NT bytes per wave and ring slot, and a KB of slack behind them
+    constexpr int kRing = STAGES * (BM * 128 + BN * 16 * WBITS) + 1024 + (FG ? STAGES * WM * WN * NT * 64 + 1024 : 0);
     // k split: the epilogue's slabs and, behind them, the parked sums of the upper wave set
-    constexpr int kMeet = KS == 2 ? WM * WN * (32 * (64 * NTW + 16) + MTW * NTW * 16 * 256) : 0;
+    constexpr int kMeet = KS == 2 ? WM * WN * ((MT % 2 == 0 ? 32 : 16) * (32 * NT + 16) + MT * NT * 4 * 256) : 0;
     constexpr int kLdsBytes = (kRing > kMeet ? kRing : kMeet) + (BM + BN) * 4;  // + the epilogue's s_a and s_w
     static_assert(kLdsBytes <= 160 * 1024, "a workgroup's ring must fit the compute unit's LDS");
-    constexpr auto kernel = gemm_prefill_tiled_kernel<MTW, NTW, WM, WN, STAGES, ACC_OUT, WBITS, UNS, FG, KS, SWIGLU>;
+    constexpr auto kernel = gemm_prefill_tiled_kernel<MT, NT, WM, WN, STAGES, ACC_OUT, WBITS, UNS, FG, KS, SWIGLU>;
     if (const hipError_t e = allow_lds<kernel>(kLdsBytes); e != hipSuccess) return e;
     if (p.prepare_only) return hipSuccess;
     hipLaunchKernelGGL(kernel, grid, dim3(64 * WM * WN * KS), kLdsBytes, stream, p);
     return hipGetLastError();
 }
 
-template <int MTW, int NTW, int WM, int WN, int STAGES, int WBITS = 4, bool UNS = false, bool FG = false, int KS = 1>
+template <int MT, int NT, int WM, int WN, int STAGES, int WBITS = 4, bool UNS = false, bool FG = false, int KS = 1>
 hipError_t launch_tile(PrefillArgs p, bool acc_out, hipStream_t stream) {
-    constexpr int BM = 32 * MTW * WM, BN = 32 * NTW * WN;
+    constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN;
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     const int total = p.tiles_m * p.tiles_n;
@@ -656,21 +678,21 @@ hipError_t launch_tile(PrefillArgs p, bool acc_out, hipStream_t stream) {
     if (p.splits > 1 && (!acc_out || FG)) return hipErrorInvalidValue;  // a split of K returns raw partial sums
     if constexpr (FG) {
         if (acc_out) return hipErrorInvalidValue;  // there is no single integer sum to return
-        return launch_one<MTW, NTW, WM, WN, STAGES, false, WBITS, UNS, true, 1>(p, grid, stream);
+        return launch_one<MT, NT, WM, WN, STAGES, false, WBITS, UNS, true, 1>(p, grid, stream);
     } else {
-        return acc_out ? launch_one<MTW, NTW, WM, WN, STAGES, true, WBITS, UNS, false, KS>(p, grid, stream)
-                       : launch_one<MTW, NTW, WM, WN, STAGES, false, WBITS, UNS, false, KS>(p, grid, stream);
+        return acc_out ? launch_one<MT, NT, WM, WN, STAGES, true, WBITS, UNS, false, KS>(p, grid, stream)
+                       : launch_one<MT, NT, WM, WN, STAGES, false, WBITS, UNS, false, KS>(p, grid, stream);
     }
 }
 
 // The fused SiLU * up form of a tile: one launch covers the problem (byte offsets below 2^32 are the caller's check).
-template <int MTW, int NTW, int WM, int WN, int STAGES>
+template <int MT, int NT, int WM, int WN, int STAGES>
 hipError_t launch_tile_swiglu(PrefillArgs p, hipStream_t stream) {
-    constexpr int BM = 32 * MTW * WM, BN = 32 * NTW * WN;
+    constexpr int BM = 16 * MT * WM, BN = 16 * NT * WN;
     p.tiles_m = (p.M + BM - 1) / BM;
     p.tiles_n = (p.N + BN - 1) / BN;
     const int total = p.tiles_m * p.tiles_n;
-    return launch_one<MTW, NTW, WM, WN, STAGES, false, 4, false, false, 1, true>(p, dim3(8 * ((total + 7) / 8)), stream);
+    return launch_one<MT, NT, WM, WN, STAGES, false, 4, false, false, 1, true>(p, dim3(8 * ((total + 7) / 8)), stream);
 }
 
 // One thread per 16-byte chunk of the tiled int8 array (W8A8 variant): a plain gather, no reordering inside a chunk.
@@ -758,55 +780,55 @@ hipError_t launch_gemm_prefill_tiled(const PrefillArgs &p, bool acc_out, int til
             hipError_t e;
             if (wbits == 4) {
                 switch (tile) {
-                    case kTiled256x256: e = launch_tile<4, 2, 2, 4, 3>(q, acc_out, stream); break;
-                    case kTiled256x256Square: e = launch_tile<2, 4, 4, 2, 3>(q, acc_out, stream); break;
-                    case kTiled128x256: e = launch_tile<4, 2, 1, 4, 2>(q, acc_out, stream); break;
-                    case kTiled128x160: e = launch_tile<1, 5, 4, 1, 3>(q, acc_out, stream); break;
-                    case kTiled128x128: e = launch_tile<2, 2, 2, 2, 3>(q, acc_out, stream); break;
-                    case kTiled64x128: e = launch_tile<1, 2, 2, 2, 4>(q, acc_out, stream); break;
-                    case kTiled64x64: e = launch_tile<1, 1, 2, 2, 4>(q, acc_out, stream); break;
-                    case kTiled32x128: e = launch_tile<1, 1, 1, 4, 4>(q, acc_out, stream); break;
-                    case kTiled128x160K2: e = launch_tile<1, 5, 4, 1, 3, 4, false, false, 2>(q, acc_out, stream); break;
-                    case kTiled128x128K2: e = launch_tile<2, 2, 2, 2, 3, 4, false, false, 2>(q, acc_out, stream); break;
-                    case kTiled256x192: e = launch_tile<2, 3, 4, 2, 3>(q, acc_out, stream); break;
-                    case kTiled128x256W8: e = launch_tile<2, 2, 2, 4, 3>(q, acc_out, stream); break;
+                    case kTiled256x256: e = launch_tile<8, 4, 2, 4, 3>(q, acc_out, stream); break;
+                    case kTiled256x256Square: e = launch_tile<4, 8, 4, 2, 3>(q, acc_out, stream); break;
+                    case kTiled128x256: e = launch_tile<8, 4, 1, 4, 2>(q, acc_out, stream); break;
+                    case kTiled128x160: e = launch_tile<2, 10, 4, 1, 3>(q, acc_out, stream); break;
+                    case kTiled128x128: e = launch_tile<4, 4, 2, 2, 3>(q, acc_out, stream); break;
+                    case kTiled64x128: e = launch_tile<2, 4, 2, 2, 4>(q, acc_out, stream); break;
+                    case kTiled64x64: e = launch_tile<2, 2, 2, 2, 4>(q, acc_out, stream); break;
+                    case kTiled32x128: e = launch_tile<2, 2, 1, 4, 4>(q, acc_out, stream); break;
+                    case kTiled128x160K2: e = launch_tile<2, 10, 4, 1, 3, 4, false, false, 2>(q, acc_out, stream); break;
+                    case kTiled128x128K2: e = launch_tile<4, 4, 2, 2, 3, 4, false, false, 2>(q, acc_out, stream); break;
+                    case kTiled256x192: e = launch_tile<4, 6, 4, 2, 3>(q, acc_out, stream); break;
+                    case kTiled128x256W8: e = launch_tile<4, 4, 2, 4, 3>(q, acc_out, stream); break;
                     default: e = hipErrorInvalidConfiguration;
                 }
             } else if (wbits == 8) {
                 // int8 weight stages are twice as large: shallower rings for the same LDS
                 switch (tile) {
-                    case kTiled256x256: e = launch_tile<4, 2, 2, 4, 2, 8>(q, acc_out, stream); break;
-                    case kTiled256x256Square: e = launch_tile<2, 4, 4, 2, 2, 8>(q, acc_out, stream); break;
-                    case kTiled128x256: e = launch_tile<4, 2, 1, 4, 2, 8>(q, acc_out, stream); break;
-                    case kTiled128x160: e = launch_tile<1, 5, 4, 1, 2, 8>(q, acc_out, stream); break;
-                    case kTiled128x128: e = launch_tile<2, 2, 2, 2, 2, 8>(q, acc_out, stream); break;
-                    case kTiled64x128: e = launch_tile<1, 2, 2, 2, 3, 8>(q, acc_out, stream); break;
-                    case kTiled64x64: e = launch_tile<1, 1, 2, 2, 4, 8>(q, acc_out, stream); break;
-                    case kTiled32x128: e = launch_tile<1, 1, 1, 4, 3, 8>(q, acc_out, stream); break;
+                    case kTiled256x256: e = launch_tile<8, 4, 2, 4, 2, 8>(q, acc_out, stream); break;
+                    case kTiled256x256Square: e = launch_tile<4, 8, 4, 2, 2, 8>(q, acc_out, stream); break;
+                    case kTiled128x256: e = launch_tile<8, 4, 1, 4, 2, 8>(q, acc_out, stream); break;
+                    case kTiled128x160: e = launch_tile<2, 10, 4, 1, 2, 8>(q, acc_out, stream); break;
+                    case kTiled128x128: e = launch_tile<4, 4, 2, 2, 2, 8>(q, acc_out, stream); break;
+                    case kTiled64x128: e = launch_tile<2, 4, 2, 2, 3, 8>(q, acc_out, stream); break;
+                    case kTiled64x64: e = launch_tile<2, 2, 2, 2, 4, 8>(q, acc_out, stream); break;
+                    case kTiled32x128: e = launch_tile<2, 2, 1, 4, 3, 8>(q, acc_out, stream); break;
                     default: e = hipErrorInvalidConfiguration;
                 }
             } else if (wbits == kWeightsUnsigned4) {
                 switch (tile) {
-                    case kTiled256x256: e = launch_tile<4, 2, 2, 4, 3, 4, true>(q, acc_out, stream); break;
-                    case kTiled256x256Square: e = launch_tile<2, 4, 4, 2, 3, 4, true>(q, acc_out, stream); break;
-                    case kTiled128x256: e = launch_tile<4, 2, 1, 4, 2, 4, true>(q, acc_out, stream); break;
-                    case kTiled128x160: e = launch_tile<1, 5, 4, 1, 3, 4, true>(q, acc_out, stream); break;
-                    case kTiled128x128: e = launch_tile<2, 2, 2, 2, 3, 4, true>(q, acc_out, stream); break;
-                    case kTiled64x128: e = launch_tile<1, 2, 2, 2, 4, 4, true>(q, acc_out, stream); break;
-                    case kTiled64x64: e = launch_tile<1, 1, 2, 2, 4, 4, true>(q, acc_out, stream); break;
-                    case kTiled32x128: e = launch_tile<1, 1, 1, 4, 4, 4, true>(q, acc_out, stream); break;
+                    case kTiled256x256: e = launch_tile<8, 4, 2, 4, 3, 4, true>(q, acc_out, stream); break;
+                    case kTiled256x256Square: e = launch_tile<4, 8, 4, 2, 3, 4, true>(q, acc_out, stream); break;
+                    case kTiled128x256: e = launch_tile<8, 4, 1, 4, 2, 4, true>(q, acc_out, stream); break;
+                    case kTiled128x160: e = launch_tile<2, 10, 4, 1, 3, 4, true>(q, acc_out, stream); break;
+                    case kTiled128x128: e = launch_tile<4, 4, 2, 2, 3, 4, true>(q, acc_out, stream); break;
+                    case kTiled64x128: e = launch_tile<2, 4, 2, 2, 4, 4, true>(q, acc_out, stream); break;
+                    case kTiled64x64: e = launch_tile<2, 2, 2, 2, 4, 4, true>(q, acc_out, stream); break;
+                    case kTiled32x128: e = launch_tile<2, 2, 1, 4, 4, 4, true>(q, acc_out, stream); break;
                     default: e = hipErrorInvalidConfiguration;
                 }
             } else if (wbits == kWeightsFineGrained4) {
                 // one problem, one launch: the group scales are addressed with the whole problem's pitch
                 if (q.M != p.M || q.N != p.N) return hipErrorInvalidValue;
                 switch (tile) {
-                    case kFine128x256: e = launch_tile<2, 2, 2, 4, 3, 4, false, true>(q, acc_out, stream); break;
-                    case kFine256x128: e = launch_tile<2, 2, 4, 2, 3, 4, false, true>(q, acc_out, stream); break;
-                    case kFine128x128: e = launch_tile<2, 2, 2, 2, 3, 4, false, true>(q, acc_out, stream); break;
-                    case kFine64x128: e = launch_tile<1, 2, 2, 2, 4, 4, false, true>(q, acc_out, stream); break;
-                    case kFine64x64: e = launch_tile<1, 1, 2, 2, 4, 4, false, true>(q, acc_out, stream); break;
-                    case kFine32x128: e = launch_tile<1, 1, 1, 4, 4, 4, false, true>(q, acc_out, stream); break;
+                    case kFine128x256: e = launch_tile<4, 4, 2, 4, 3, 4, false, true>(q, acc_out, stream); break;
+                    case kFine256x128: e = launch_tile<4, 4, 4, 2, 3, 4, false, true>(q, acc_out, stream); break;
+                    case kFine128x128: e = launch_tile<4, 4, 2, 2, 3, 4, false, true>(q, acc_out, stream); break;
+                    case kFine64x128: e = launch_tile<2, 4, 2, 2, 4, 4, false, true>(q, acc_out, stream); break;
+                    case kFine64x64: e = launch_tile<2, 2, 2, 2, 4, 4, false, true>(q, acc_out, stream); break;
+                    case kFine32x128: e = launch_tile<2, 2, 1, 4, 4, 4, false, true>(q, acc_out, stream); break;
                     default: e = hipErrorInvalidConfiguration;
                 }
             } else {
@@ -827,11 +849,11 @@ hipError_t launch_gemm_prefill_tiled_swiglu(const PrefillArgs &p, int tile, hipS
         (long long)((p.N + 31) / 32) * kb_total * kTiledBlockBytes > kMaxBytes)
         return hipErrorInvalidValue;
     switch (tile) {
-        case kTiled256x256: return launch_tile_swiglu<4, 2, 2, 4, 3>(p, stream);
-        case kTiled256x192: return launch_tile_swiglu<2, 3, 4, 2, 3>(p, stream);
-        case kTiled128x256: return launch_tile_swiglu<4, 2, 1, 4, 2>(p, stream);
-        case kTiled128x256W8: return launch_tile_swiglu<2, 2, 2, 4, 3>(p, stream);
-        case kTiled128x128: return launch_tile_swiglu<2, 2, 2, 2, 3>(p, stream);
+        case kTiled256x256: return launch_tile_swiglu<8, 4, 2, 4, 3>(p, stream);
+        case kTiled256x192: return launch_tile_swiglu<4, 6, 4, 2, 3>(p, stream);
+        case kTiled128x256: return launch_tile_swiglu<8, 4, 1, 4, 2>(p, stream);
+        case kTiled128x256W8: return launch_tile_swiglu<4, 4, 2, 4, 3>(p, stream);
+        case kTiled128x128: return launch_tile_swiglu<4, 4, 2, 2, 3>(p, stream);
         default: return hipErrorInvalidConfiguration;
     }
 }
