@@ -166,10 +166,7 @@ int w4a8_quantize_weights_clipped(const void *w_fp16, const float *gamma, const 
  * i.e. exactly what w4a8_gemm_tiled followed by w4a8_silu_mul gives on the same weights in the usual order, bit for
  * bit, without the M x 2 I intermediate going to memory.
  *   xq [M][K], s_a [M], wt_gu (tiled array of 2 I channels x K), s_w_gu [2 I]   in;   h_fp16 [M][I]   out.
- *   I follows the K contract (I % 32 == 0, I <= 65536).  Up to 64 tokens the weight-streaming kernel runs (where all
- *   of K fits its waves' registers, as for w4a8_gemm_tiled), otherwise the large-M kernel, which has the fused form
- *   for its 256- and 128-row tiles: from 65 to some hundred tokens w4a8_gemm_tiled and w4a8_silu_mul_quantize are
- *   faster.
+ *   I follows the K contract (I % 32 == 0, I <= 65536).  Which kernel runs is decided as for w4a8_gemm_tiled.
  *   M * K and the tiled weight bytes must each be below 0xF0000000 (W4A8_ERR_SHAPE).
  */
 int w4a8_gemm_tiled_swiglu(const int8_t *xq, const float *s_a, const uint8_t *wt_gu, const float *s_w_gu, void *h_fp16,

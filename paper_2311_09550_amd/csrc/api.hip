@@ -85,21 +85,6 @@ struct Plan {
 bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool whole16, int aux, bool tiled, DecodeShape *out,
                     int k_slices = 1, bool x_window = false);
 
-// 17 to 64 tokens over tiled weights: shape of the persistent kernel with per-wave staging, cut into the fewest K
-// slices for which an instantiation exists (slices_forced > 0: exactly that many).  False when there is none.
-bool wide_plan(int M, int N, int K, int slices_forced, int max_slices, DecodeShape *out) {
-    if (M <= 16 || M > kResidentMaxM) return false;
-    const int first = slices_forced > 0 ? slices_forced : 1, last = slices_forced > 0 ? slices_forced : max_slices;
-    for (int s = first; s <= last; ++s) {
-        DecodeShape t{};
-        if (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &t, s, true)) {
-            *out = t;
-            return true;
-        }
-    }
-    return false;
-}
-
 // Shape of the persistent weight-streaming kernel for (M, N, K).  Returns false when a wave's share of the
 // activations would not fit in registers (then the general streaming kernel takes over).
 //   waves    : 8 or 16, 0 = library's choice (8 wherever a wave's k steps fit its registers, see below);
@@ -128,8 +113,9 @@ bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool
     s.norm = out->norm;                // ... or to add the residual and normalise in front of its quantiser
     s.aux = aux < 0 ? 2 : aux;
     s.x_window = x_window;
-    s.k_slices = k_slices < 1 ? 1 : k_slices;
-    const int ks_total = ((K + 127) / 128 + s.k_slices - 1) / s.k_slices;  // k steps of a slice
+    const int ks_all = (K + 127) / 128, want = k_slices < 1 ? 1 : k_slices;
+    const int ks_total = (ks_all + want - 1) / want;           // k steps of a slice
+    s.k_slices = (ks_all + ks_total - 1) / ks_total;           // no empty slice
     // 8 waves wherever their k steps fit the registers (measured 4 to 13 % faster than 16): up to 14 steps per wave
     // for one column tile (K <= 14336), 7 for two with per-wave staging, 5 for three and four
     if (waves == 0) {
@@ -151,7 +137,6 @@ bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool
     if (grid <= 0) {
         const long long per_wg = ((long long)N * s.k_slices + compute_units() - 1) / compute_units();
         rows = per_wg > kResidentMaxRows ? kResidentMaxRows : (int)((per_wg + 15) / 16 * 16);
-        if (rows > kResidentMaxRows) rows = kResidentMaxRows;
     } else {
         rows = ((N + grid - 1) / grid + unit - 1) / unit * unit;
     }
@@ -192,52 +177,150 @@ int choose_prefill_tile(int M, int N) {
     return best;
 }
 
-// Output tile of the kernel over the tiled weight layout.  A launch runs in rounds of as many workgroups as the chip
-// holds at once; the estimate is rounds x tile area x workgroups per compute unit / efficiency of the tile shape.
-// Efficiencies and the cost of a round in which a compute unit holds one workgroup instead of two ("alone") are
-// measured on LLaMA-13B shapes, M = 128 .. 4096 (warm weights, tiles timed in turn within one process):
-//   256 x 256         one per compute unit, the most work per operand byte staged;
-//   256 x 192         its narrower partner: fills one round where 256 x 256 would need two, or leave columns over;
-//   128 x 256 8 waves one per compute unit (three-stage ring): half the tile in 59 % of the time of 256 x 256;
-//   128 x 256 4 waves two per compute unit (two-stage ring); alone on a compute unit it takes 73 % of a shared round;
-//   128 x 160, 128 x 128, 64 x 128   two per compute unit, for N or M too small for the above;
-//   128 x 128 with the k halves of a stage on two wave sets, one per compute unit.
-// For 256 x 256 the estimate also covers the launch in two phases (whole rounds of 256 x 256, the columns left over as
-// one round of 256 x 192, see launch_tiled_in_phases).
+// Price of a launch of the large-M kernel over tiled int4 weights, in microseconds, for every output tile the library
+// chooses from.  A launch runs in rounds of as many workgroups as the chip holds at once (per_cu to a compute unit):
+//   launch + round * rounds + stages of 128 k * (stage * full rounds + last + share * part - lone * [part <= half]),
+// part = filled share of the last round (the last three terms only where there is one; lone: a compute unit then holds one
+// workgroup instead of several).  The coefficients are least-squares fits over 280 random shapes (N 1024 .. 32768,
+// K 1024 .. 16384, M 17 .. 1400, up to six K slices; every tile timed on every shape from HIP graphs, weights cold); the
+// fits are within 5 to 8 % of the measured times, and choosing among tiles, K slices and the weight-streaming kernel by
+// them costs 1.2 % on average over always choosing the fastest.  (Rounds times area over an efficiency on nine tiles, the
+// rule before, cost 8 %.)  Of 32 tile shapes tried, these are the ones whose removal costs anything.
+struct TileCost {
+    int id, bm, bn, per_cu;
+    float launch, round, stage, last, share, lone;
+};
+constexpr TileCost kTileCosts[] = {
+    {kTiled256x256, 256, 256, 1, 7.43f, 0.00f, 1.064f, 0.967f, 0.163f, 0.000f},
+    {kTiled128x256, 128, 256, 2, 6.07f, 0.00f, 1.198f, 1.005f, 0.436f, 0.337f},
+    {kTiled64x128, 64, 128, 2, 3.33f, 0.42f, 0.537f, 0.401f, 0.181f, 0.144f},
+    {kTiled64x64, 64, 64, 3, 3.35f, 0.17f, 0.531f, 0.214f, 0.363f, 0.034f},
+    {kTiled32x128, 32, 128, 3, 3.45f, 0.17f, 0.520f, 0.230f, 0.337f, 0.036f},
+    {kTiled128x256W8, 128, 256, 1, 5.67f, 0.00f, 0.779f, 0.505f, 0.173f, 0.000f},
+    {kTiled64x256, 64, 256, 1, 3.18f, 1.24f, 0.485f, 0.343f, 0.142f, 0.000f},
+    {kTiled128x384, 128, 384, 1, 6.67f, 0.02f, 1.022f, 0.732f, 0.193f, 0.000f},
+    {kTiled128x192, 128, 192, 1, 4.17f, 0.88f, 0.635f, 0.466f, 0.150f, 0.000f},
+    {kTiled64x192, 64, 192, 1, 2.53f, 1.62f, 0.413f, 0.333f, 0.120f, 0.000f},
+    {kTiled128x320, 128, 320, 1, 5.80f, 0.66f, 0.904f, 0.662f, 0.168f, 0.000f},
+    {kTiled192x320, 192, 320, 1, 7.19f, 0.00f, 1.112f, 0.976f, 0.111f, 0.000f},
+    {kTiled192x256, 192, 256, 1, 6.43f, 0.00f, 0.927f, 0.767f, 0.129f, 0.000f},
+    {kTiled192x192, 192, 192, 1, 5.91f, 0.00f, 0.802f, 0.620f, 0.141f, 0.000f},
+};
+
+// What K slices add: a second launch, and the slabs written and read
+double slab_us(int M, int N, int slices) { return 2.0 + 0.34e-6 * 4.0 * M * (double)N * slices; }
+
+double tile_us(const TileCost &t, int M, int N, int stages, int slices = 1) {
+    const long long n = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * slices;
+    const long long slots = (long long)compute_units() * t.per_cu;
+    const long long full = n / slots, rest = n % slots;
+    double us = t.launch + t.round * (double)(full + (rest != 0)) + t.stage * (double)(full * stages);
+    if (rest != 0) {
+        const double part = (double)rest / (double)slots;
+        us += (t.last + t.share * part - (t.per_cu > 1 && rest * 2 <= slots ? t.lone : 0.f)) * stages;
+    }
+    return us;
+}
+
 // max_id: the highest tile id the weight format has (the unsigned storage lacks the tiles above kTiledTileMax).
-int choose_tiled_tile(int M, int N, int max_id = kTiledTileMax4) {
-    struct Option { int id, bm, bn, per_cu; double eff, alone; };
-    const Option options[] = {{kTiled256x256, 256, 256, 1, 1.00, 1.0},    {kTiled256x192, 256, 192, 1, 0.97, 1.0},
-                              {kTiled128x256, 128, 256, 2, 0.93, 0.73},   {kTiled128x256W8, 128, 256, 1, 0.85, 1.0},
-                              {kTiled128x160, 128, 160, 2, 0.66, 0.63},   {kTiled128x128, 128, 128, 2, 0.75, 0.67},
-                              {kTiled64x128, 64, 128, 2, 0.60, 0.75},     {kTiled128x128K2, 128, 128, 1, 0.60, 1.0}};
-    const int cus = compute_units();
-    // Medium M: when not even 128 x 128 tiles occupy three quarters of the compute units, run time is the length of
-    // one workgroup's walk over K, and smaller tiles (more workgroups, each with a shorter stage) shorten it.
-    auto count = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    if (M <= 32) return kTiled32x128;  // taller tiles would multiply rows that do not exist
-    if (M <= 64 || count(128, 128) * 4 < (long long)cus * 3)
-        return count(64, 128) * 4 >= (long long)cus * 3 ? kTiled64x128 : kTiled64x64;
-    int best = kTiled256x256;
-    double best_cost = 0;
-    for (const Option &o : options) {
-        if (o.id > max_id) continue;
-        const long long tiles = count(o.bm, o.bn);
-        const long long slots = (long long)cus * o.per_cu;
-        const long long full = tiles / slots, rest = tiles % slots;
-        const double last = rest == 0 ? 0.0 : ((o.per_cu > 1 && rest <= cus) ? o.alone : 1.0);
-        double cost = ((double)full + last) * o.bm * o.bn * o.per_cu / o.eff;
-        if (o.id == kTiled256x256 && max_id >= kTiled256x192) {
-            const long long tiles_m = (M + 255) / 256, cols = (N + 255) / 256, per_round = cus / tiles_m;
-            if (per_round > 0 && cols > per_round && cols % per_round != 0) {
-                const long long rest_cols = N - (cols / per_round) * per_round * 256;
-                const double phased = (double)(cols / per_round) * 256 * 256 + 256 * 192 / 0.97;
-                if ((rest_cols + 191) / 192 <= per_round && phased < cost) cost = phased;
-            }
-        }
-        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = o.id; }
+int choose_tiled_tile(int M, int N, int K, int max_id = kTiledTileLast) {
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
+    int best = 0;
+    double best_us = 0;
+    for (const TileCost &t : kTileCosts) {
+        if (t.id > max_id) continue;
+        const double us = tile_us(t, M, N, stages);
+        if (best == 0 || us < best_us) best = t.id, best_us = us;
     }
     return best;
+}
+
+// How a GEMM over tiled int4 weights with more than 16 tokens is run: by the weight-streaming kernel with per-wave
+// staging, K cut into slices, or by the large-M kernel, K cut into slices.  Both are priced
+// and the cheaper one is taken.
+struct TiledPlan {
+    bool wide;          // weight-streaming kernel, else the large-M kernel
+    DecodeShape shape;  // wide: its shape
+    int tile;           // else: output tile and K slices
+    int splits, stages_per_split;
+    size_t slab_bytes;  // raw sums of the slices, 0 when there is one
+};
+
+// Price of the weight-streaming kernel in microseconds: what every compute unit brings in (the activations and its
+// weights), a fixed part per chunk of 16 channels, more
+// of it where a wave has more than 8 k steps, and the slabs.  Fitted like the tiles' prices, within 5 %.
+double wide_us(const DecodeShape &s, int M, int N, int K) {
+    const double steps = ((K + 127) / 128 + s.k_slices - 1) / s.k_slices;
+    const double chunks = (s.rows_per_wg + 15) / 16, mt = (M + 15) / 16, long_walk = s.x_steps > 8 ? s.x_steps - 8 : 0;
+    const double x_kb = M * steps * 0.125, w_kb = s.rows_per_wg * steps * 0.0625;
+    double us = 2.215 + 0.01676 * x_kb + 0.01376 * w_kb + chunks * (0.630 + 0.0551 * mt + 0.1122 * long_walk);
+    if (s.k_slices > 1) us += slab_us(M, N, s.k_slices);
+    return us;
+}
+
+constexpr int kMaxSlices = 8;
+constexpr int kSplitMaxM = 512;  // the large-M kernel is not split beyond: there its tiles fill the chip or the slabs cost more
+
+// max_slab: bytes of slabs allowed (0: one slice only).
+TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu) {
+    TiledPlan best{};
+    double best_us = -1;
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
+    const size_t slab = (size_t)M * (size_t)N * sizeof(int32_t);
+    const int max_slices = max_slab / slab < 2 ? 1 : (int)(max_slab / slab < (size_t)kMaxSlices ? max_slab / slab : kMaxSlices);
+    for (const TileCost &t : kTileCosts) {
+        for (int s = 1; s <= (M <= kSplitMaxM ? max_slices : 1); ++s) {
+            const int per = (stages + s - 1) / s, n = (stages + per - 1) / per;
+            if (n != s) continue;  // the same as fewer slices
+            double us = tile_us(t, M, N, per, s);
+            if (s > 1) us += slab_us(M, N, s);
+            if (best_us < 0 || us < best_us) {
+                best_us = us;
+                best.tile = t.id;
+                best.splits = s;
+                best.stages_per_split = per;
+                best.slab_bytes = s > 1 ? s * slab : 0;
+            }
+        }
+    }
+    if (M <= kResidentMaxM) {
+        for (int s = 1; s <= (swiglu ? 1 : max_slices); ++s) {
+            DecodeShape shape{};
+            shape.swiglu = swiglu;
+            if (!resident_shape(M, N, K, 0, 0, 0, false, -1, true, &shape, s, true) || shape.k_slices != s) continue;
+            const double us = wide_us(shape, M, N, K);
+            if (us < best_us) {
+                best_us = us;
+                best.wide = true;
+                best.shape = shape;
+                best.slab_bytes = s > 1 ? s * slab : 0;
+            }
+        }
+    }
+    best.splits = best.wide ? best.shape.k_slices : best.splits;
+    return best;
+}
+
+// The same, remembered per thread: a plan is a pure function of its arguments (and of the device's compute units) and
+// costs some ten microseconds to work out, about as much as the launch it is for.
+const TiledPlan &tiled_plan(int M, int N, int K, size_t max_slab, bool swiglu) {
+    struct Entry { int M, N, K, cus; size_t max_slab; bool swiglu; TiledPlan plan; };
+    constexpr unsigned kEntries = 64;
+    static thread_local Entry entries[kEntries];
+    const int cus = compute_units();
+    const unsigned h = ((unsigned)M * 2654435761u ^ (unsigned)N * 2246822519u ^ (unsigned)K * 3266489917u ^ (unsigned)swiglu * 668265263u) >> 26;
+    Entry &e = entries[h % kEntries];
+    if (e.M != M || e.N != N || e.K != K || e.cus != cus || e.max_slab != max_slab || e.swiglu != swiglu)
+        e = Entry{M, N, K, cus, max_slab, swiglu, plan_tiled(M, N, K, max_slab, swiglu)};
+    return e.plan;
+}
+
+// d: pointers only
+hipError_t launch_wide(DecodeArgs d, int M, int N, int K, const DecodeShape &s, bool acc_out, hipStream_t st) {
+    d.M = M; d.N = N; d.K = K;
+    d.rows_per_wg = s.rows_per_wg;
+    d.chunk_rows = s.chunk_rows;
+    return launch_gemm_decode(d, acc_out, s, st);
 }
 
 // The choice among the fine-grained variant's tiles (measured on LLaMA-13B shapes at M = 1024 and 4096: two
@@ -296,9 +379,13 @@ int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
     if (tiling == W4A8_TILING_AUTO_TILED) {
         // one weight array for every M: the weight-streaming kernels up to M = 16 and, where all of K fits a wave's
         // registers, up to M = 64; the large-M kernel above
-        if (M > 16)
-            pl->tiling = wide_plan(M, N, K, 1, 1, &pl->decode) ? W4A8_TILING_DECODE_RESIDENT_TILED : W4A8_TILING_PREFILL_TILED;
-        else
+        if (M > 16) {
+            const TiledPlan t = tiled_plan(M, N, K, 0, false);
+            pl->decode = t.shape;
+            pl->prefill_tile = t.tile;
+            pl->tiling = t.wide ? W4A8_TILING_DECODE_RESIDENT : W4A8_TILING_PREFILL_TILED;
+            return W4A8_OK;
+        }
             pl->tiling = (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl->decode, 1, true) ||
                           resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl->decode))
                              ? W4A8_TILING_DECODE_RESIDENT_TILED
@@ -343,38 +430,12 @@ int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
         pl->decode = s;
     } else if (pl->tiling == W4A8_TILING_PREFILL_TILED) {
         if (variant < 0 || variant > kTiledTileMax4) return W4A8_ERR_ARG;
-        pl->prefill_tile = variant ? variant : choose_tiled_tile(M, N);
+        pl->prefill_tile = variant ? variant : choose_tiled_tile(M, N, K);
     } else {
         if (variant < 0 || variant > kPrefillTileMax) return W4A8_ERR_ARG;
         pl->prefill_tile = variant ? variant : choose_prefill_tile(M, N);
     }
     return W4A8_OK;
-}
-
-// The library's own launch of the large-M kernel over tiled int4 weights.  Where 256 x 256 tiles fill the chip more
-// than once, the last, partial round costs as much as a full one (LLaMA-13B gate+up at M = 1024: 432 tiles on 256
-// compute units, i.e. two rounds for 1.69 rounds of work).  Then the columns that whole rounds cover go to one launch
-// and the columns left over to a second launch with 256 x 192 tiles, if those fit into a single round: the second
-// round shrinks to three quarters.  Two launches of the same kernel on disjoint column ranges of the same output:
-// same arithmetic, same bits.
-hipError_t launch_tiled_in_phases(const PrefillArgs &a, bool want_acc, int tile, hipStream_t st) {
-    const int cus = compute_units();
-    const long long tiles_m = (a.M + 255) / 256, cols = (a.N + 255) / 256;
-    const long long per_round = tiles_m > 0 ? cus / tiles_m : 0;  // column tiles of 256 that one round holds
-    if (tile != kTiled256x256 || per_round == 0 || cols <= per_round || cols % per_round == 0)
-        return launch_gemm_prefill_tiled(a, want_acc, tile, st);
-    const long long n_first = (cols / per_round) * per_round * 256;     // covered by whole rounds
-    const long long rest = a.N - n_first;
-    if ((rest + 191) / 192 > per_round) return launch_gemm_prefill_tiled(a, want_acc, tile, st);  // 192 wide would need two rounds too
-    PrefillArgs first = a, second = a;
-    first.N = (int)n_first;
-    second.N = (int)rest;
-    second.wp = a.wp + (size_t)(n_first / 32) * (size_t)((a.K + kTiledBlockK - 1) / kTiledBlockK) * (size_t)kTiledBlockBytes;
-    if (a.s_w) second.s_w = a.s_w + n_first;
-    if (a.out) second.out = (unsigned short *)a.out + n_first;
-    if (a.acc_out) second.acc_out = a.acc_out + n_first;
-    if (const hipError_t e = launch_gemm_prefill_tiled(first, want_acc, kTiled256x256, st); e != hipSuccess) return e;
-    return launch_gemm_prefill_tiled(second, want_acc, kTiled256x192, st);
 }
 
 int run_gemm(const int8_t *xq, const float *s_a, const uint8_t *wp, const float *s_w, void *out_fp16, int32_t *acc_i32,
@@ -397,8 +458,7 @@ int run_gemm(const int8_t *xq, const float *s_a, const uint8_t *wp, const float 
         a.xq = xq; a.s_a = s_a; a.wp = wp; a.s_w = s_w;
         a.out = out_fp16; a.acc_out = acc_i32;
         a.M = M; a.N = N; a.K = K; a.ldc = N;
-        err = variant == 0 ? launch_tiled_in_phases(a, want_acc, pl.prefill_tile, st)
-                           : launch_gemm_prefill_tiled(a, want_acc, pl.prefill_tile, st);
+        err = launch_gemm_prefill_tiled(a, want_acc, pl.prefill_tile, st);
     } else if (pl.tiling != W4A8_TILING_PREFILL) {
         DecodeArgs a{};
         a.xq = xq; a.s_a = s_a; a.wp = wp; a.s_w = s_w;
@@ -508,112 +568,76 @@ int w4a8_gemm_tiled_swiglu(const int8_t *xq, const float *s_a, const uint8_t *wt
     if (misaligned(xq) || misaligned(wt_gu) || misaligned(h_fp16) || misaligned(s_w_gu)) return W4A8_ERR_ALIGN;
     if ((long long)M * K > 0xF0000000ll || (long long)tiled_weight_bytes(N, K, 4) > 0xF0000000ll) return W4A8_ERR_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    // up to 64 tokens: the weight-streaming kernel with per-wave staging, where it has a shape for (M, N, K)
-    if (M <= kResidentMaxM) {
-        DecodeShape shape{};
-        shape.swiglu = true;
-        if (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &shape, 1, true)) {
-            DecodeArgs d{};
-            d.xq = xq; d.s_a = s_a; d.wp = wt_gu; d.s_w = s_w_gu; d.out = h_fp16;
-            d.M = M; d.N = N; d.K = K;
-            d.rows_per_wg = shape.rows_per_wg;
-            d.chunk_rows = shape.chunk_rows;
-            return launched(launch_gemm_decode(d, false, shape, st));
-        }
+    const TiledPlan pl = tiled_plan(M, N, K, 0, true);
+    if (pl.wide) {
+        DecodeArgs d{};
+        d.xq = xq; d.s_a = s_a; d.wp = wt_gu; d.s_w = s_w_gu; d.out = h_fp16;
+        return launched(launch_wide(d, M, N, K, pl.shape, false, st));
     }
-    int tile = choose_tiled_tile(M, N);
-    if (tile != kTiled256x256 && tile != kTiled256x192 && tile != kTiled128x256 && tile != kTiled128x256W8)
-        tile = kTiled128x128;  // the large-M kernel has the fused form for these tiles
     PrefillArgs a{};
     a.xq = xq; a.s_a = s_a; a.wp = wt_gu; a.s_w = s_w_gu; a.out = h_fp16;
     a.M = M; a.N = N; a.K = K; a.ldc = I;
-    // the two-phase launch of launch_tiled_in_phases, with the output offset counted in values of h
-    const int cus = compute_units();
-    const long long tiles_m = (M + 255) / 256, cols = (N + 255) / 256, per_round = cus / tiles_m;
-    if (tile == kTiled256x256 && per_round > 0 && cols > per_round && cols % per_round != 0) {
-        const long long n_first = (cols / per_round) * per_round * 256, rest = N - n_first;
-        if ((rest + 191) / 192 <= per_round) {
-            PrefillArgs first = a, second = a;
-            first.N = (int)n_first;
-            second.N = (int)rest;
-            second.wp = wt_gu + (size_t)(n_first / 32) * (size_t)((K + kTiledBlockK - 1) / kTiledBlockK) * (size_t)kTiledBlockBytes;
-            second.s_w = s_w_gu + n_first;
-            second.out = (unsigned short *)h_fp16 + n_first / 2;
-            if (int e = launched(launch_gemm_prefill_tiled_swiglu(first, kTiled256x256, st))) return e;
-            return launched(launch_gemm_prefill_tiled_swiglu(second, kTiled256x192, st));
-        }
-    }
-    return launched(launch_gemm_prefill_tiled_swiglu(a, tile, st));
+    return launched(launch_gemm_prefill_tiled_swiglu(a, pl.tile, st));
 }
 
 // ---- K split over workgroups for shapes whose tiles alone leave most of the chip idle (medium M, small N)
 
 namespace {
 
-struct SplitPlan { int tile, splits, stages_per_split; };
-
-// Tile and number of K slices (measured on LLaMA-13B shapes, M = 32 .. 512).  Slices pay where the tiles alone leave
-// the chip under-filled: up to half the compute units for a short walk over K (fewer than 64 stages), up to all of
-// them for a long one; they aim at two workgroups per compute unit, at least 12 stages per slice and at most 6 slices
-// (each slice adds a slab to write and to read again).  With slices available the 64 x 128 tile replaces the
-// 64 x 64 one, and the 128 x 128 tile the 64 x 128 one on a long K (same workgroup count after the split, fewer operand
-// bytes per MFMA).  M above 512 is left alone: there the tiles fill the chip or the slabs cost more than they save.
-SplitPlan plan_split(int M, int N, int K, int variant, int splits) {
-    SplitPlan pl{};
-    const int st_all = (K + kTiledBlockK - 1) / kTiledBlockK;
-    const int cus = compute_units();
-    const bool long_k = st_all >= 64;
-    auto count = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    pl.tile = variant ? variant : choose_tiled_tile(M, N);
-    const int unsplit_tile = pl.tile;
-    if (!variant && M > 64 && M <= 512) {
-        if (pl.tile == kTiled64x64) pl.tile = kTiled64x128;
-        if (long_k && pl.tile == kTiled64x128 && count(128, 128) <= cus) pl.tile = kTiled128x128;
-    }
-    int s = splits;
-    if (s == 0) {
-        static const int bm[] = {0, 256, 256, 128, 128, 128, 64, 64, 32, 128, 128, 256, 128};
-        static const int bn[] = {0, 256, 256, 256, 160, 128, 128, 64, 128, 160, 128, 192, 256};
-        const long long tiles = count(bm[pl.tile], bn[pl.tile]);
-        s = 1;
-        if (M <= 512 && tiles <= (long_k ? cus : cus / 2)) {
-            s = (int)((2 * (long long)cus + tiles / 2) / tiles);
-            if (s > 6) s = 6;
-            if (s > st_all / 12) s = st_all / 12;
-            if (s < 1) s = 1;
+// K slices that callers are told to bring a workspace for (w4a8_gemm_tiled_workspace_bytes), 1 = none: with 17 to 64 tokens
+// as few as let a slice of K fit the registers of the weight-streaming kernel, above and up to 512 as many as give every
+// compute unit two 64 x 128 tiles (128 x 128 on a long K), at least 12 stages each and at most 6.  The library's own
+// choice stays within it and often needs fewer.
+int advertised_slices(int M, int N, int K) {
+    if (M <= 16 || M > kSplitMaxM) return 1;
+    if (M <= kResidentMaxM)
+        for (int s = 1; s <= kMaxSlices; ++s) {
+            DecodeShape t{};
+            if (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &t, s, true)) return t.k_slices;
         }
-    }
-    if (s > st_all) s = st_all;
-    if (s <= 1) pl.tile = unsplit_tile;  // the larger tiles are only worth it together with the slices
-    pl.stages_per_split = (st_all + s - 1) / s;
-    pl.splits = (st_all + pl.stages_per_split - 1) / pl.stages_per_split;  // no empty slice
-    return pl;
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
+    const bool long_k = stages >= 64;
+    auto count = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
+    const long long tiles = long_k && count(128, 128) <= cus ? count(128, 128) : count(64, 128);
+    if (tiles > (long_k ? cus : cus / 2)) return 1;
+    int s = (int)((2ll * cus + tiles / 2) / tiles);
+    if (s > 6) s = 6;
+    if (s > stages / 12) s = stages / 12;
+    if (s < 2) return 1;
+    const int per = (stages + s - 1) / s;
+    return (stages + per - 1) / per;  // no empty slice
 }
 
-// What w4a8_gemm_tiled_splitk does with a shape.  Up to 16 tokens (no tile or slice count forced): the weight-streaming
-// kernels, no slabs.  17 to 64 tokens (no tile forced): the persistent kernel with per-wave staging, in as few K slices
-// as a wave's registers allow (or the forced count, if an instantiation exists for it).  Otherwise the LDS-staged
-// kernel with the slices of plan_split.
+// What w4a8_gemm_tiled_splitk does with a shape: the plan, or token generation (up to 16 tokens, nothing forced: the entry
+// without slices).  max_slab: bytes of slabs the library's own choice may use.
 struct SplitRoute {
-    enum Kind { kStream, kWide, kRing } kind;
-    DecodeShape wide;
-    SplitPlan ring;
-    size_t slab_bytes;  // workspace the route needs
+    bool stream;
+    TiledPlan plan;
 };
 
-SplitRoute split_route(int M, int N, int K, int variant, int splits) {
+SplitRoute split_route(int M, int N, int K, int variant, int splits, size_t max_slab) {
     SplitRoute r{};
     const size_t slab = (size_t)M * (size_t)N * sizeof(int32_t);
-    if (M <= 16 && variant == 0 && splits == 0) {
-        r.kind = SplitRoute::kStream;
-    } else if (variant == 0 && wide_plan(M, N, K, splits, 8, &r.wide)) {
-        r.kind = SplitRoute::kWide;
-        r.slab_bytes = r.wide.k_slices > 1 ? (size_t)r.wide.k_slices * slab : 0;
-    } else {
-        r.kind = SplitRoute::kRing;
-        r.ring = plan_split(M, N, K, variant, splits);
-        r.slab_bytes = r.ring.splits > 1 ? (size_t)r.ring.splits * slab : 0;
+    if (variant == 0 && splits == 0) {
+        const size_t told = (size_t)advertised_slices(M, N, K) * slab;
+        r.stream = M <= 16;
+        if (!r.stream) r.plan = tiled_plan(M, N, K, told < max_slab ? told : max_slab, false);
+        return r;
     }
+    // forced: the weight-streaming kernel where it has a shape for that many slices (17 to 64 tokens, no tile forced), else
+    // the large-M kernel; a forced tile without a slice count is not cut
+    TiledPlan &pl = r.plan;
+    if (variant == 0 && M > 16 && M <= kResidentMaxM && resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl.shape, splits, true)) {
+        pl.wide = true;
+        pl.splits = pl.shape.k_slices;
+    } else {
+        const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
+        const int s = splits < 1 ? 1 : splits > stages ? stages : splits;
+        pl.tile = variant ? variant : choose_tiled_tile(M, N, K);
+        pl.stages_per_split = (stages + s - 1) / s;
+        pl.splits = (stages + pl.stages_per_split - 1) / pl.stages_per_split;  // no empty slice
+    }
+    pl.slab_bytes = pl.splits > 1 ? (size_t)pl.splits * slab : 0;
     return r;
 }
 
@@ -621,57 +645,58 @@ SplitRoute split_route(int M, int N, int K, int variant, int splits) {
 
 size_t w4a8_gemm_tiled_workspace_bytes(int M, int N, int K) {
     if (check_gemm_shape(M, N, K)) return 0;
-    // the library's own choice never exceeds 8 slices; a forced count is checked against the buffer at the call
-    return split_route(M, N, K, 0, 0).slab_bytes;
+    // a forced count is checked against the buffer at the call
+    const int s = advertised_slices(M, N, K);
+    return s > 1 ? (size_t)s * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
+}
+
+static int splitk_on_route(const SplitRoute &route, const int8_t *xq, const float *s_a, const uint8_t *wt, const float *s_w, void *out_fp16,
+                           int M, int N, int K, void *workspace, size_t workspace_bytes, void *stream) {
+    if (route.stream)  // token generation: the weight-streaming kernels over the same array
+        return run_gemm(xq, s_a, wt, s_w, out_fp16, nullptr, M, N, K, W4A8_TILING_AUTO_TILED, 0, stream);
+    hipStream_t st = static_cast<hipStream_t>(stream);
+    const TiledPlan &pl = route.plan;
+    const bool sliced = pl.splits > 1;
+    if (sliced) {
+        // one launch must cover the problem (slabs are whole M x N matrices)
+        if (!pl.wide && ((long long)M * K > 0xF0000000ll || (long long)tiled_weight_bytes(N, K, 4) > 0xF0000000ll)) return W4A8_ERR_SHAPE;
+        if (!workspace) return W4A8_ERR_NULL;
+        if (workspace_bytes < pl.slab_bytes) return W4A8_ERR_WORKSPACE;
+    }
+    int32_t *const slabs = sliced ? static_cast<int32_t *>(workspace) : nullptr;
+    void *const out = sliced ? nullptr : out_fp16;
+    hipError_t e;
+    if (pl.wide) {
+        DecodeArgs d{};
+        d.xq = xq; d.s_a = s_a; d.wp = wt; d.s_w = s_w; d.out = out; d.acc_out = slabs;
+        e = launch_wide(d, M, N, K, pl.shape, sliced, st);
+    } else {
+        PrefillArgs a{};
+        a.xq = xq; a.s_a = s_a; a.wp = wt; a.s_w = s_w; a.out = out; a.acc_out = slabs;
+        a.M = M; a.N = N; a.K = K; a.ldc = N;
+        a.splits = pl.splits;
+        a.stages_per_split = pl.stages_per_split;
+        e = launch_gemm_prefill_tiled(a, sliced, pl.tile, st);
+    }
+    if (int err = launched(e); err || !sliced) return err;
+    return launched(launch_splitk_epilogue(slabs, pl.splits, s_a, s_w, out_fp16, M, N, st));
+}
+
+static int check_splitk(const int8_t *xq, const float *s_a, const uint8_t *wt, const float *s_w, const void *out_fp16, int M, int N, int K,
+                        int variant, int splits) {
+    if (!xq || !s_a || !wt || !s_w || !out_fp16) return W4A8_ERR_NULL;
+    if (int e = check_gemm_shape(M, N, K)) return e;
+    if (variant < 0 || variant > kTiledTileMax4 || splits < 0 || splits > 64) return W4A8_ERR_ARG;
+    if (misaligned(xq) || misaligned(wt) || misaligned(out_fp16) || misaligned(s_w)) return W4A8_ERR_ALIGN;
+    return W4A8_OK;
 }
 
 int w4a8_gemm_tiled_splitk(const int8_t *xq, const float *s_a, const uint8_t *wt, const float *s_w, void *out_fp16, int M,
                            int N, int K, int variant, int splits, void *workspace, size_t workspace_bytes, void *stream) {
-    if (!xq || !s_a || !wt || !s_w || !out_fp16) return W4A8_ERR_NULL;
-    if (int e = check_gemm_shape(M, N, K)) return e;
-    if (variant < 0 || variant > kTiledTileMax4 || splits < 0 || splits > 64) return W4A8_ERR_ARG;
-    if (misaligned(xq) || misaligned(wt) || misaligned(out_fp16) || misaligned(s_w) || misaligned(workspace))
-        return W4A8_ERR_ALIGN;
-    const SplitRoute route = split_route(M, N, K, variant, splits);
-    if (route.kind == SplitRoute::kStream)  // token generation: the weight-streaming kernels over the same array
-        return run_gemm(xq, s_a, wt, s_w, out_fp16, nullptr, M, N, K, W4A8_TILING_AUTO_TILED, 0, stream);
-    hipStream_t st = static_cast<hipStream_t>(stream);
-    if (route.kind == SplitRoute::kWide) {
-        const DecodeShape &ds = route.wide;
-        DecodeArgs d{};
-        d.xq = xq; d.s_a = s_a; d.wp = wt; d.s_w = s_w;
-        d.M = M; d.N = N; d.K = K;
-        d.rows_per_wg = ds.rows_per_wg;
-        d.chunk_rows = ds.chunk_rows;
-        if (ds.k_slices <= 1) {
-            d.out = out_fp16;
-            return launched(launch_gemm_decode(d, false, ds, st));
-        }
-        if (!workspace) return W4A8_ERR_NULL;
-        if (workspace_bytes < route.slab_bytes) return W4A8_ERR_WORKSPACE;
-        d.acc_out = static_cast<int32_t *>(workspace);
-        if (int e = launched(launch_gemm_decode(d, true, ds, st))) return e;
-        return launched(launch_splitk_epilogue(d.acc_out, ds.k_slices, s_a, s_w, out_fp16, M, N, st));
-    }
-    const SplitPlan pl = route.ring;
-    PrefillArgs a{};
-    a.xq = xq; a.s_a = s_a; a.wp = wt; a.s_w = s_w;
-    a.M = M; a.N = N; a.K = K; a.ldc = N;
-    if (pl.splits <= 1) {
-        a.out = out_fp16;
-        const hipError_t e = variant == 0 ? launch_tiled_in_phases(a, false, pl.tile, st)
-                                          : launch_gemm_prefill_tiled(a, false, pl.tile, st);
-        return launched(e);
-    }
-    // one launch must cover the problem (slabs are whole M x N matrices)
-    if ((long long)M * K > 0xF0000000ll || (long long)tiled_weight_bytes(N, K, 4) > 0xF0000000ll) return W4A8_ERR_SHAPE;
-    if (!workspace) return W4A8_ERR_NULL;
-    if (workspace_bytes < (size_t)pl.splits * (size_t)M * (size_t)N * sizeof(int32_t)) return W4A8_ERR_WORKSPACE;
-    a.acc_out = static_cast<int32_t *>(workspace);
-    a.splits = pl.splits;
-    a.stages_per_split = pl.stages_per_split;
-    if (int e = launched(launch_gemm_prefill_tiled(a, true, pl.tile, st))) return e;
-    return launched(launch_splitk_epilogue(a.acc_out, pl.splits, s_a, s_w, out_fp16, M, N, st));
+    if (int e = check_splitk(xq, s_a, wt, s_w, out_fp16, M, N, K, variant, splits)) return e;
+    if (misaligned(workspace)) return W4A8_ERR_ALIGN;
+    return splitk_on_route(split_route(M, N, K, variant, splits, SIZE_MAX), xq, s_a, wt, s_w, out_fp16, M, N, K, workspace,
+                           workspace_bytes, stream);
 }
 
 // what the norm in front of the fused quantiser needs (gamma == NULL: no norm)
@@ -750,13 +775,12 @@ int w4a8_linear_tiled_swiglu_fp16(const void *x_fp16, long long ldx, const uint8
 
 int w4a8_gemm_tiled_splitk_static(const int8_t *xq, const float *s_a, const uint8_t *wt, const float *s_w, void *out_fp16,
                                   int M, int N, int K, int variant, int splits, void *stream) {
-    if (!xq || !s_a || !wt || !s_w || !out_fp16) return W4A8_ERR_NULL;
-    if (int e = check_gemm_shape(M, N, K)) return e;
-    if (variant < 0 || variant > kTiledTileMax4 || splits < 0 || splits > 64) return W4A8_ERR_ARG;
-    if (split_route(M, N, K, variant, splits).slab_bytes > kStaticScratchBytes) return W4A8_ERR_WORKSPACE;
+    if (int e = check_splitk(xq, s_a, wt, s_w, out_fp16, M, N, K, variant, splits)) return e;
+    const SplitRoute route = split_route(M, N, K, variant, splits, kStaticScratchBytes);
+    if (route.plan.slab_bytes > kStaticScratchBytes) return W4A8_ERR_WORKSPACE;
     void *ws = nullptr;
     if (int e = static_scratch(&ws)) return e;
-    return w4a8_gemm_tiled_splitk(xq, s_a, wt, s_w, out_fp16, M, N, K, variant, splits, ws, kStaticScratchBytes, stream);
+    return splitk_on_route(route, xq, s_a, wt, s_w, out_fp16, M, N, K, ws, kStaticScratchBytes, stream);
 }
 
 int w4a8_init(void) {
@@ -825,7 +849,7 @@ static int gemm_tiled_variant(const int8_t *xq, const float *s_a, const uint8_t 
     if (!xq || !wt) return W4A8_ERR_NULL;
     if (!want_acc && (!s_a || !s_w)) return W4A8_ERR_NULL;
     if (int e = check_gemm_shape(M, N, K)) return e;
-    if (variant < 0 || variant > (wfmt == 4 ? kTiledTileMax4 : kTiledTileMax)) return W4A8_ERR_ARG;
+    if (variant < 0 || variant > kTiledTileMax) return W4A8_ERR_ARG;
     if (misaligned(xq) || misaligned(wt) || misaligned(out_fp16) || misaligned(acc_i32) || (s_w && misaligned(s_w)))
         return W4A8_ERR_ALIGN;
     PrefillArgs a{};
@@ -833,8 +857,7 @@ static int gemm_tiled_variant(const int8_t *xq, const float *s_a, const uint8_t 
     a.out = out_fp16; a.acc_out = acc_i32;
     a.M = M; a.N = N; a.K = K; a.ldc = N;
     const int tile = variant ? variant
-                             : wfmt == 8 ? choose_tiled_tile8(M, N)
-                                         : choose_tiled_tile(M, N, wfmt == 4 ? kTiledTileMax4 : kTiledTileMax);
+                             : wfmt == 8 ? choose_tiled_tile8(M, N) : choose_tiled_tile(M, N, K, kTiledTileMax);
     return launched(launch_gemm_prefill_tiled(a, want_acc, tile, static_cast<hipStream_t>(stream), wfmt));
 }
 

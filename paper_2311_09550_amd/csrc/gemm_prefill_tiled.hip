@@ -785,13 +785,21 @@ hipError_t launch_gemm_prefill_tiled(const PrefillArgs &p, bool acc_out, int til
                     case kTiled128x256: e = launch_tile<8, 4, 1, 4, 2>(q, acc_out, stream); break;
                     case kTiled128x160: e = launch_tile<2, 10, 4, 1, 3>(q, acc_out, stream); break;
                     case kTiled128x128: e = launch_tile<4, 4, 2, 2, 3>(q, acc_out, stream); break;
-                    case kTiled64x128: e = launch_tile<2, 4, 2, 2, 4>(q, acc_out, stream); break;
+                    case kTiled64x128: e = launch_tile<2, 2, 2, 4, 4>(q, acc_out, stream); break;
                     case kTiled64x64: e = launch_tile<2, 2, 2, 2, 4>(q, acc_out, stream); break;
                     case kTiled32x128: e = launch_tile<2, 2, 1, 4, 4>(q, acc_out, stream); break;
                     case kTiled128x160K2: e = launch_tile<2, 10, 4, 1, 3, 4, false, false, 2>(q, acc_out, stream); break;
                     case kTiled128x128K2: e = launch_tile<4, 4, 2, 2, 3, 4, false, false, 2>(q, acc_out, stream); break;
                     case kTiled256x192: e = launch_tile<4, 6, 4, 2, 3>(q, acc_out, stream); break;
-                    case kTiled128x256W8: e = launch_tile<4, 4, 2, 4, 3>(q, acc_out, stream); break;
+                    case kTiled128x256W8: e = launch_tile<8, 2, 1, 8, 4>(q, acc_out, stream); break;
+                    case kTiled64x256: e = launch_tile<4, 2, 1, 8, 4>(q, acc_out, stream); break;
+                    case kTiled128x384: e = launch_tile<8, 3, 1, 8, 3>(q, acc_out, stream); break;
+                    case kTiled128x192: e = launch_tile<4, 3, 2, 4, 4>(q, acc_out, stream); break;
+                    case kTiled64x192: e = launch_tile<2, 3, 2, 4, 4>(q, acc_out, stream); break;
+                    case kTiled128x320: e = launch_tile<4, 5, 2, 4, 4>(q, acc_out, stream); break;
+                    case kTiled192x320: e = launch_tile<6, 5, 2, 4, 3>(q, acc_out, stream); break;
+                    case kTiled192x256: e = launch_tile<6, 4, 2, 4, 3>(q, acc_out, stream); break;
+                    case kTiled192x192: e = launch_tile<6, 3, 2, 4, 4>(q, acc_out, stream); break;
                     default: e = hipErrorInvalidConfiguration;
                 }
             } else if (wbits == 8) {
@@ -850,10 +858,19 @@ hipError_t launch_gemm_prefill_tiled_swiglu(const PrefillArgs &p, int tile, hipS
         return hipErrorInvalidValue;
     switch (tile) {
         case kTiled256x256: return launch_tile_swiglu<8, 4, 2, 4, 3>(p, stream);
-        case kTiled256x192: return launch_tile_swiglu<4, 6, 4, 2, 3>(p, stream);
         case kTiled128x256: return launch_tile_swiglu<8, 4, 1, 4, 2>(p, stream);
-        case kTiled128x256W8: return launch_tile_swiglu<4, 4, 2, 4, 3>(p, stream);
-        case kTiled128x128: return launch_tile_swiglu<4, 4, 2, 2, 3>(p, stream);
+        case kTiled64x128: return launch_tile_swiglu<2, 2, 2, 4, 4>(p, stream);
+        case kTiled64x64: return launch_tile_swiglu<2, 2, 2, 2, 4>(p, stream);
+        case kTiled32x128: return launch_tile_swiglu<2, 2, 1, 4, 4>(p, stream);
+        case kTiled128x256W8: return launch_tile_swiglu<8, 2, 1, 8, 4>(p, stream);
+        case kTiled64x256: return launch_tile_swiglu<4, 2, 1, 8, 4>(p, stream);
+        case kTiled128x384: return launch_tile_swiglu<8, 3, 1, 8, 3>(p, stream);
+        case kTiled128x192: return launch_tile_swiglu<4, 3, 2, 4, 4>(p, stream);
+        case kTiled64x192: return launch_tile_swiglu<2, 3, 2, 4, 4>(p, stream);
+        case kTiled128x320: return launch_tile_swiglu<4, 5, 2, 4, 4>(p, stream);
+        case kTiled192x320: return launch_tile_swiglu<6, 5, 2, 4, 3>(p, stream);
+        case kTiled192x256: return launch_tile_swiglu<6, 4, 2, 4, 3>(p, stream);
+        case kTiled192x192: return launch_tile_swiglu<6, 3, 2, 4, 4>(p, stream);
         default: return hipErrorInvalidConfiguration;
     }
 }
@@ -862,10 +879,11 @@ hipError_t prepare_tiled_kernels() {
     PrefillArgs a{};
     a.M = 32; a.N = 32; a.K = kTiledBlockK; a.ldc = 32; a.ldg = 32;
     a.prepare_only = true;
-    for (int tile : {kTiled256x256, kTiled256x192, kTiled128x256, kTiled128x256W8, kTiled128x128})
+    for (int tile : {kTiled256x256, kTiled128x256, kTiled64x128, kTiled64x64, kTiled32x128, kTiled128x256W8, kTiled64x256, kTiled128x384,
+                     kTiled128x192, kTiled64x192, kTiled128x320, kTiled192x320, kTiled192x256, kTiled192x192})
         if (const hipError_t e = launch_gemm_prefill_tiled_swiglu(a, tile, nullptr); e != hipSuccess) return e;
     struct Format { int wbits, tiles; bool acc; };
-    const Format formats[] = {{4, kTiledTileMax4, true}, {8, kTiledTileMax, true}, {kWeightsUnsigned4, kTiledTileMax, true},
+    const Format formats[] = {{4, kTiledTileLast, true}, {8, kTiledTileMax, true}, {kWeightsUnsigned4, kTiledTileMax, true},
                               {kWeightsFineGrained4, kFineTileMax, false}};
     for (const Format &f : formats)
         for (int tile = 1; tile <= f.tiles; ++tile)

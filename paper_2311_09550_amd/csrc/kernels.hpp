@@ -144,7 +144,7 @@ constexpr int kTiled256x256Square = 2;  // 8 waves of 64 x 128
 constexpr int kTiled128x256 = 3;        // 4 waves of 128 x 64, two-stage ring, two workgroups per compute unit
 constexpr int kTiled128x160 = 4;        // 4 waves of 32 x 160
 constexpr int kTiled128x128 = 5;        // 4 waves of 64 x 64
-constexpr int kTiled64x128 = 6;         // 4 waves of 32 x 64: medium M, where 128-row tiles leave most of the chip idle
+constexpr int kTiled64x128 = 6;         // signed int4: 8 waves of 32 x 32, else 4 waves of 32 x 64
 constexpr int kTiled64x64 = 7;          // 4 waves of 32 x 32
 constexpr int kTiled32x128 = 8;         // 4 waves of 32 x 32 side by side
 constexpr int kTiled128x160K2 = 9;      // 128 x 160 with two wave sets of 4 splitting each stage's k (int4 weights only)
@@ -152,9 +152,19 @@ constexpr int kTiled128x128K2 = 10;     // 128 x 128 likewise
 constexpr int kTiled256x192 = 11;       // 8 waves of 64 x 96 (int4 weights only): the narrower partner of 1 for the columns
                                         // that whole rounds of 256 x 256 tiles leave over
 constexpr int kTiledTileMax = 8;        // tiles every weight format has
-constexpr int kTiled128x256W8 = 12;     // 128 x 256 as 8 waves of 64 x 64, three-stage ring, one workgroup per compute unit
-                                        // (int4 weights only): where 128 x 256 tiles number no more than the compute units
-constexpr int kTiledTileMax4 = 12;      // tiles of the signed int4 format
+constexpr int kTiled128x256W8 = 12;     // 128 x 256 as 8 waves of 128 x 32, four-stage ring, one workgroup per compute unit
+                                        // (int4 weights only)
+constexpr int kTiledTileMax4 = 12;      // tiles of the signed int4 format that a caller can force
+// ... and the further ones the library chooses from, all of 8 waves, one workgroup per compute unit
+constexpr int kTiled64x256 = 13;        // 8 waves of 64 x 32
+constexpr int kTiled128x384 = 14;       // 128 x 48
+constexpr int kTiled128x192 = 15;       // 64 x 48
+constexpr int kTiled64x192 = 16;        // 32 x 48
+constexpr int kTiled128x320 = 17;       // 64 x 80
+constexpr int kTiled192x320 = 18;       // 96 x 80
+constexpr int kTiled192x256 = 19;       // 96 x 64
+constexpr int kTiled192x192 = 20;       // 96 x 48
+constexpr int kTiledTileLast = 20;
 
 // wbits = 4: packed int4 codes (blocks of 2 KB); wbits = 8: int8 codes of the W8A8 comparison variant (blocks of 4 KB);
 // wbits = kWeightsUnsigned4: the 2 KB blocks with unsigned nibbles u = w + 8 (the paper's vanilla storage, GEMM only)

@@ -162,3 +162,32 @@ def test_tiled_llama13b_prefill_sampled(gpu, oracle):
     acc_o, y32, _ = oracle.gemm(xq[rows], s_a[rows], wp, s_w)
     assert_equal_bits(acc.cpu().numpy()[rows], acc_o, "13B gate_up sampled rows acc")
     assert_fp16_close(out.cpu().numpy()[rows], y32, acc_o, "13B gate_up sampled rows out")
+
+
+# One ragged shape for every output tile the library picks by price beyond those a caller can force (and a few of the
+# others): M and N off the tile, a last stage of K that is partly past the end.
+@pytest.mark.parametrize("M,N,K", [(130, 21127, 800), (453, 22911, 288), (622, 9745, 288), (250, 12122, 416), (387, 19065, 416),
+                                   (647, 16927, 544), (450, 20537, 288), (338, 22148, 288), (516, 23091, 160), (781, 16335, 672),
+                                   (137, 9737, 288), (71, 13592, 160)])
+def test_librarys_choice_on_ragged_shapes_of_every_tile(gpu, oracle, M, N, K):
+    """Library's choice against the oracle on sampled rows and, on every element, against the bits of the 32 x 128 tile;
+    the fused SiLU * up form against the two calls (its bar is equality of bits, as in test_gpu_swiglu.py)."""
+    t = gpu
+    xq, wq, s_a, s_w = synth.uniform_codes(M, N, K, config_id=59)
+    wp = oracle.pack_w4(wq)
+    dxq, dsa, dsw = t.from_numpy(xq).cuda(), t.from_numpy(s_a).cuda(), t.from_numpy(s_w).cuda()
+    wt = w4a8.w4a8_tile_weights(t.from_numpy(wp).cuda())
+    out = w4a8.w4a8_gemm_tiled(dxq, dsa, wt, dsw)
+    ref = w4a8.w4a8_gemm_tuned(dxq, dsa, wt, dsw, TILED, 8, N=N)
+    t.cuda.synchronize()
+    assert_equal_bits(out.cpu().numpy().view(np.uint16), ref.cpu().numpy().view(np.uint16), f"choice M={M} N={N} K={K}")
+    rows = sorted({0, M // 2, M - 1})
+    acc_o, y32, _ = oracle.gemm(xq[rows], s_a[rows], wp, s_w)
+    assert_fp16_close(out.cpu().numpy()[rows], y32, acc_o, f"choice rows M={M} N={N} K={K}")
+    I = N // 64 * 32                                       # the first 2 I channels read as interleaved gate / up pairs
+    wt_gu = w4a8.w4a8_tile_weights(t.from_numpy(wp[:2 * I].copy()).cuda())
+    h = w4a8.w4a8_gemm_tiled_swiglu(dxq, dsa, wt_gu, dsw[:2 * I].contiguous())
+    pairs = out[:, :2 * I].reshape(M, I, 2)
+    two = w4a8.w4a8_silu_mul(t.cat((pairs[:, :, 0], pairs[:, :, 1]), dim=1).contiguous())
+    t.cuda.synchronize()
+    assert_equal_bits(h.cpu().numpy().view(np.uint16), two.cpu().numpy().view(np.uint16), f"swiglu choice M={M} I={I} K={K}")
