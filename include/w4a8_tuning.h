@@ -27,9 +27,9 @@ extern "C" {
  *                      its own k steps through a window of LDS: tiled weights only, 17 to 64 tokens, 8 waves (or 16
  *                      for up to 32 tokens and K <= 8192), one or two chunks in flight);
  *   DECODE_STREAM:   row_tiles * 100 + waves, row_tiles in {1, 2}, waves in {4, 8};
- *   PREFILL:         output tile (rows of X x channels): 1 = 128 x 256 as 1 x 4 waves, 2 = 128 x 128,
- *                    3 = 128 x 160, 4 = 128 x 256 as 2 x 2 waves (operands staged through registers);
- *                    5..8 = the shapes of 1, 4, 3, 2 with LDS-direct loads and a four-stage ring;
+ *   PREFILL:         output tile (rows of X x channels): 1 = 256 x 256, 2 = 192 x 320, 3 = 192 x 192, 4 = 128 x 256,
+ *                    5 = 64 x 192, 6 = 64 x 128, 7 = 64 x 64, 8 = 32 x 128; the library chooses among these and
+ *                    three further tiles;
  *   PREFILL_TILED:   `wp` is the TILED weight array of w4a8_tile_weights; output tile 1 = 256 x 256 as
  *                    2 x 4 waves, 2 = 256 x 256 as 4 x 2 waves, 3 = 128 x 256, 4 = 128 x 160, 5 = 128 x 128,
  *                    6 = 64 x 128, 7 = 64 x 64, 8 = 32 x 128 (the small tiles are for medium M);
@@ -46,7 +46,7 @@ extern "C" {
                                          with K <= 8192, M <= 64 with K <= 5120); at most 512 channels per
                                          workgroup                                                         */
 #define W4A8_TILING_DECODE_STREAM 2   /* general weight-streaming kernel, M <= 64                         */
-#define W4A8_TILING_PREFILL 3         /* LDS-staged output tiles on 32x32x32 int8 MFMA, for large M       */
+#define W4A8_TILING_PREFILL 3         /* output tiles through a ring of stages in LDS, any M (large M)    */
 #define W4A8_TILING_PREFILL_TILED 4   /* the same over the tiled weight layout (any M; meant for large M)  */
 #define W4A8_TILING_DECODE_RESIDENT_TILED 5 /* tilings 1 and 2 reading the TILED weight array (`wp` = wt);        */
 #define W4A8_TILING_DECODE_STREAM_TILED 6   /* same limits and variants as 1 and 2                                 */

@@ -154,29 +154,6 @@ bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool
     return true;
 }
 
-// Output tile of the LDS-staged kernel.  A launch runs in rounds of as many workgroups as the chip holds at once,
-// so the estimate is rounds x tile area / relative efficiency of the tile shape (measured on LLaMA-13B shapes): the
-// big tile does the most work per byte staged, the smaller ones fill the chip when N is small.
-int choose_prefill_tile(int M, int N) {
-    struct Option { int id, bm, bn, per_cu; double eff; };
-    const Option options[] = {{kPrefillTile128x256, 128, 256, 2, 1.00},
-                              {kPrefillDma128x160, 128, 160, 2, 0.80},  // the LDS-direct variant is the faster 128 x 160
-                              {kPrefillTile128x128, 128, 128, 3, 0.78}};
-    const int cus = compute_units();
-    int best = kPrefillTile128x256;
-    double best_cost = 0;
-    for (const Option &o : options) {
-        const long long tiles = (long long)((M + o.bm - 1) / o.bm) * ((N + o.bn - 1) / o.bn);
-        const long long slots = (long long)cus * o.per_cu;
-        const long long full = tiles / slots, rest = tiles % slots;
-        // a partial last round costs at least half a round: its workgroups no longer share their compute unit
-        const double rounds = (double)full + (rest == 0 ? 0.0 : (rest * 2 <= slots ? 0.5 : (double)rest / slots * 0.5 + 0.5));
-        const double cost = rounds * o.bm * o.bn * o.per_cu / o.eff;
-        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = o.id; }
-    }
-    return best;
-}
-
 // Price of a launch of the large-M kernel over tiled int4 weights, in microseconds, for every output tile the library
 // chooses from.  A launch runs in rounds of as many workgroups as the chip holds at once (per_cu to a compute unit):
 //   launch + round * rounds + stages of 128 k * (stage * full rounds + last + share * part - lone * [part <= half]),
@@ -233,6 +210,46 @@ int choose_tiled_tile(int M, int N, int K, int max_id = kTiledTileLast) {
         if (best == 0 || us < best_us) best = t.id, best_us = us;
     }
     return best;
+}
+
+// The same kernel over row-major weights.  Its stages take longer, a weight stage being half a cache line of every
+// channel: 1.2 times the prices above up to 64 tokens, 1.1 at large M, much the same for every tile.  So the prices serve
+// to choose among its tiles as they are (within 0.6 % of always taking the fastest on 200 random shapes).
+struct RowTile {
+    int id;
+    double us;
+};
+
+RowTile choose_row_tile(int M, int N, int K) {
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
+    RowTile best{0, 0};
+    for (const TileCost &t : kTileCosts) {
+        bool there = false;
+        for (const int id : kRowTiles) there |= id == t.id;
+        if (!there) continue;
+        const double us = tile_us(t, M, N, stages);
+        if (best.id == 0 || us < best.us) best = {t.id, us};
+    }
+    return best;
+}
+
+// Over row-major weights the weight-streaming kernels are priced against the tiles up to 32 tokens; beyond, a tile is the
+// faster one on every shape (1.05 to 2.3 times, 80 random shapes with 33 to 64 tokens; within 2 % where they are level).
+// The prices, in microseconds, are least-squares fits over 100 random shapes: the persistent kernel's within 5 to 6 %; the
+// general one (more than 16 tokens and K > 8192; up to 16 tokens it is always taken where K > 16384) walks all of K in every workgroup, 1.8 us per 1000 k and round of 8192
+// channels.  Choosing by them costs 0.2 % (up to 16 tokens) and 0.7 % on average over always choosing the faster; the
+// streaming kernels alone cost 1.3 % and 6.3 %.  (N = 24896, K = 3296, M = 18: 15.7 us streaming, 11.6 tiled; N = 3200,
+// K = 8160, M = 9: 7.3 and 20.1.)
+constexpr int kRowDecodeMaxM = 32;
+constexpr double kRowOverTiled = 1.2;
+
+double row_decode_us(int M, int N, int K, bool resident) {
+    if (!resident) return 1.8e-3 * K * ((N + 8191) / 8192);
+    const int rows = ((N + compute_units() - 1) / compute_units() + 15) / 16 * 16;
+    const double chunks = rows / 16, w_kb = rows * (K / 2048.0), x_kb = M * (K / 1024.0);
+    const int steps = ((K + 127) / 128 + (M <= 16 ? 7 : 15)) / (M <= 16 ? 8 : 16);
+    return M <= 16 ? 2.696 + 0.2546 * chunks + 0.0505 * w_kb + 0.0177 * x_kb + 0.0003 * steps * chunks
+                   : 2.971 + 0.6039 * chunks + 0.0316 * w_kb + 0.0263 * x_kb + 0.0730 * steps * chunks;
 }
 
 // How a GEMM over tiled int4 weights with more than 16 tokens is run: by the weight-streaming kernel with per-wave
@@ -395,11 +412,12 @@ int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
     if (pl->tiling == W4A8_TILING_DECODE_RESIDENT_TILED) pl->tiling = W4A8_TILING_DECODE_RESIDENT;
     if (pl->tiling == W4A8_TILING_DECODE_STREAM_TILED) pl->tiling = W4A8_TILING_DECODE_STREAM;
     if (tiling == W4A8_TILING_AUTO) {
-        if (M > kDecodeMaxM)
+        const bool resident = M <= kRowDecodeMaxM && resident_shape(M, N, K, 0, 0, 0, false, -1, false, &pl->decode);
+        const bool priced = M <= kRowDecodeMaxM && (resident || M > 16);
+        if (M > kRowDecodeMaxM || (priced && row_decode_us(M, N, K, resident) > kRowOverTiled * choose_row_tile(M, N, K).us))
             pl->tiling = W4A8_TILING_PREFILL;
         else
-            pl->tiling = resident_shape(M, N, K, 0, 0, 0, false, -1, false, &pl->decode) ? W4A8_TILING_DECODE_RESIDENT
-                                                                                          : W4A8_TILING_DECODE_STREAM;
+            pl->tiling = resident ? W4A8_TILING_DECODE_RESIDENT : W4A8_TILING_DECODE_STREAM;
     }
     if (pl->tiling == W4A8_TILING_DECODE_RESIDENT) {
         if (M > kResidentMaxM) return W4A8_ERR_ARG;
@@ -433,7 +451,7 @@ int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
         pl->prefill_tile = variant ? variant : choose_tiled_tile(M, N, K);
     } else {
         if (variant < 0 || variant > kPrefillTileMax) return W4A8_ERR_ARG;
-        pl->prefill_tile = variant ? variant : choose_prefill_tile(M, N);
+        pl->prefill_tile = variant ? kRowTiles[variant - 1] : choose_row_tile(M, N, K).id;
     }
     return W4A8_OK;
 }
@@ -473,7 +491,7 @@ int run_gemm(const int8_t *xq, const float *s_a, const uint8_t *wp, const float 
         a.xq = xq; a.s_a = s_a; a.wp = wp; a.s_w = s_w;
         a.out = out_fp16; a.acc_out = acc_i32;
         a.M = M; a.N = N; a.K = K; a.ldc = N;
-        err = launch_gemm_prefill(a, want_acc, pl.prefill_tile, st);
+        err = launch_gemm_prefill_row(a, want_acc, pl.prefill_tile, st);
     }
     return launched(err);
 }
@@ -788,6 +806,7 @@ int w4a8_init(void) {
     if (int e = static_scratch(&ws)) return e;
     (void)compute_units();
     if (int e = launched(prepare_tiled_kernels())) return e;
+    if (int e = launched(prepare_row_kernels())) return e;
     return launched(prepare_decode_kernels());
 }
 

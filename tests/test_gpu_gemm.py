@@ -118,7 +118,7 @@ def test_back_to_back_calls_share_nothing(gpu, oracle):
         assert_equal_bits(acc.cpu().numpy(), jobs[i // 2][2], f"call {i}")
 
 
-PREFILL_TILES = [1, 2, 3, 4, 5, 6, 7, 8]   # register-staged 128x256 (1x4 waves), 128x128, 128x160, 128x256 (2x2 waves); 5..8: the same four shapes, LDS-direct loads
+PREFILL_TILES = [1, 2, 3, 4, 5, 6, 7, 8]   # 256x256, 192x320, 192x192, 128x256, 64x192, 64x128, 64x64, 32x128
 
 
 @pytest.mark.parametrize("tile", PREFILL_TILES)
@@ -134,6 +134,23 @@ def test_prefill_tiling_all_m(gpu, oracle, M, tile):
 def test_prefill_tiling_ragged_shapes(gpu, oracle, M, N, K, tile):
     xq, wq, s_a, s_w = _codes(M, N, K, tag=41)
     _run_both(gpu, oracle, xq, wq, s_a, s_w, PREFILL, tile, f"prefill tile={tile} M={M} N={N} K={K}")
+
+
+@pytest.mark.parametrize("M,N,K", [(451, 20579, 288), (225, 17008, 544), (129, 19635, 1056),   # 192x256, 128x192, 64x256
+                                   (32, 1024, 544), (33, 1024, 544), (17, 1216, 96), (16, 29000, 160), (17, 29000, 160),
+                                   (20, 9000, 8224), (32, 700, 8224)])
+def test_row_major_routes(gpu, M, N, K):
+    """The library's own choice over row-major weights: the output tiles that cannot be forced, and both sides of the lines
+    between the weight-streaming kernels and the tiles (token count, price, K beyond the persistent kernel's registers)."""
+    xq, wq, s_a, s_w = _codes(M, N, K, tag=43)
+    # exact in fp32: |sum| <= 128 * 8 * K < 2^24
+    acc_ref = (xq.astype(np.float32) @ wq.astype(np.float32).T).astype(np.int32)
+    t = gpu
+    wp = ((wq[:, 0::2] & 15) | ((wq[:, 1::2] & 15) << 4)).astype(np.uint8)
+    dx, dw, dsa, dsw = (t.from_numpy(a).cuda() for a in (xq, wp, s_a, s_w))
+    assert_equal_bits(w4a8.w4a8_gemm_acc_i32(dx, dw).cpu().numpy(), acc_ref, "acc")
+    y32 = acc_ref.astype(np.float32) * (s_a[:, None] * s_w[None])
+    assert_fp16_close(w4a8.w4a8_gemm(dx, dsa, dw, dsw).cpu().numpy(), y32, acc_ref, "out")
 
 
 @pytest.mark.parametrize("tiling,M", [(STREAM, 2), (STREAM, 40), (PREFILL, 130)])
