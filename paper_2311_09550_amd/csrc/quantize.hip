@@ -107,36 +107,88 @@ __global__ __launch_bounds__(THREADS, THREADS <= 256 ? 8 : 1) void quantize_act_
     for (int c = threadIdx.x + kCache * kRowThreads; c < chunks; c += kRowThreads) emit(c, src[c]);
 }
 
+// Eight int4 codes from two words of int8 codes: code j in nibble j (App. A.1, low nibble = even k).
+__device__ __forceinline__ unsigned nibbles8(v2u codes) {
+    const unsigned lo = codes.x & 0x0F0F0F0Fu, hi = codes.y & 0x0F0F0F0Fu;
+    return __builtin_amdgcn_perm(hi | (hi >> 4), lo | (lo >> 4), 0x06040200u);
+}
+
 // Per-output-channel symmetric int4 round-to-nearest (Eq. (8),(9), 4 bits, gamma = beta = 1)
 // followed by the nibble packing of App. A.1 (low nibble = even k).
-__global__ __launch_bounds__(kRowThreads, 8) void quantize_weights_kernel(const uint16_t *__restrict__ w, uint8_t *__restrict__ wp,
-                                                                       float *__restrict__ s_w, int K) {
-    __shared__ float scratch[kRowThreads / 64];
+// What bounds it: the read of the fp16 rows.  A row is read once, into registers, and the codes take some six vector
+// operations per element (codes8, with its clamps and conversions, takes a dozen, as many microseconds as the memory
+// does).  Measured, cold rows, N = 27648, K = 5120: 57 us = 6.2 TB/s, against 98 with the row read twice and codes8;
+// N = 32768, K = 8192: 165 -> 102 us; N = 12288, K = 4096: 36 -> 23.  THREADS: 128 with short rows, where a thread of
+// 256 would hold fewer than three chunks (27648 x 5120: 57 us against 65); 256 with longer ones (5000 x 6944: 18.1 against
+// 19.6).  Loads carry the non-temporal hint, the stores do not: the codes are read next, by the kernel that tiles them
+// (without the hint on the loads 65 us; with it on the stores 62).
+constexpr int kShortRow = 6144;
+
+template <int THREADS, int CACHE>
+__global__ __launch_bounds__(THREADS, 8) void quantize_weights_kernel(const uint16_t *__restrict__ w, uint8_t *__restrict__ wp,
+                                                                   float *__restrict__ s_w, int K) {
+    // The row's maximum is put together from kParts maxima, part w of the chunks c with (c / 64) % kParts = w, for either
+    // THREADS: which parts hold a NaN decides what becomes of such a row (fmaxf passes over a part that is NaN), and that
+    // does not depend on the launch shape.
+    constexpr int kParts = kRowThreads / 64, kOwnParts = kRowThreads / THREADS;
+    static_assert(THREADS == kRowThreads || CACHE * THREADS * 8 >= kShortRow, "short rows are held in registers whole");
+    __shared__ float scratch[kParts];
     const int n = blockIdx.x;
     const int chunks = K >> 3;
     const v4u *src = (const v4u *)(w + (size_t)n * K);
 
-    unsigned amax2 = 0u;
-    for (int c = threadIdx.x; c < chunks; c += kRowThreads) amax2 = absmax8_packed(src[c], amax2);
-    float amax = block_max<kRowThreads, true>(absmax_packed_value(amax2), scratch);
+    v4u cache[CACHE];
+    unsigned amax2[kOwnParts] = {};
+#pragma unroll
+    for (int i = 0; i < CACHE; ++i) {
+        const int c = threadIdx.x + i * THREADS;
+        cache[i] = v4u{0, 0, 0, 0};
+        if (c < chunks) cache[i] = __builtin_nontemporal_load(src + c);
+    }
+#pragma unroll
+    for (int i = 0; i < CACHE; ++i) amax2[i % kOwnParts] = absmax8_packed(cache[i], amax2[i % kOwnParts]);
+    if (THREADS == kRowThreads)
+        for (int c = threadIdx.x + CACHE * THREADS; c < chunks; c += THREADS) amax2[0] = absmax8_packed(src[c], amax2[0]);
+#pragma unroll
+    for (int j = 0; j < kOwnParts; ++j) {
+        const float part = wave_max_nonneg(absmax_packed_value(amax2[j]));
+        if ((threadIdx.x & 63) == 0) scratch[j * (THREADS / 64) + (threadIdx.x >> 6)] = part;
+    }
+    __syncthreads();
+    float amax = scratch[0];
+    bool finite_row = scratch[0] < INFINITY;  // false for NaN as well
+#pragma unroll
+    for (int w = 1; w < kParts; ++w) {
+        amax = fmaxf(amax, scratch[w]);
+        finite_row &= scratch[w] < INFINITY;
+    }
 
     const RowQuantizer rq(amax, 7.0f, -8.f, 7.f);
     if (threadIdx.x == 0) s_w[n] = rq.scale;
     const bool zero_row = amax == 0.f;
 
     unsigned *dst = (unsigned *)(wp + (size_t)n * (K >> 1));
-    for (int c = threadIdx.x; c < chunks; c += kRowThreads) {
+    auto emit = [&](int c, v4u v) {
         unsigned o = 0;
-        if (!zero_row) {
-            float xf[8];
+        float xf[8];
+        halves8(v, xf);
+        if (!finite_row && !zero_row) {
             int q[8];
-            halves8(src[c], xf);
             rq.codes8(xf, q);
 #pragma unroll
             for (int j = 0; j < 4; ++j) o |= (unsigned)((q[2 * j] & 15) | ((q[2 * j + 1] & 15) << 4)) << (8 * j);
+        } else if (!zero_row) {
+            o = nibbles8(rq.packed8_own_max(xf));
         }
         dst[c] = o;
+    };
+#pragma unroll
+    for (int i = 0; i < CACHE; ++i) {
+        const int c = threadIdx.x + i * THREADS;
+        if (c < chunks) emit(c, cache[i]);
     }
+    if (THREADS == kRowThreads)
+        for (int c = threadIdx.x + CACHE * THREADS; c < chunks; c += THREADS) emit(c, src[c]);
 }
 
 // The same with the clipping strengths of Eq. (9) per output channel: S = max(|gamma max(W)|, |beta min(W)|) / 7.
@@ -364,7 +416,12 @@ hipError_t launch_quantize_act(const void *x, long long ldx, int8_t *xq, float *
 }
 
 hipError_t launch_quantize_weights(const void *w, uint8_t *wp, float *s_w, int N, int K, hipStream_t stream) {
-    hipLaunchKernelGGL(quantize_weights_kernel, dim3(N), dim3(kRowThreads), 0, stream, (const uint16_t *)w, wp, s_w, K);
+    if (K <= kShortRow)
+        hipLaunchKernelGGL((quantize_weights_kernel<128, kShortRow / (128 * 8)>), dim3(N), dim3(128), 0, stream, (const uint16_t *)w, wp,
+                           s_w, K);
+    else
+        hipLaunchKernelGGL((quantize_weights_kernel<kRowThreads, kCache>), dim3(N), dim3(kRowThreads), 0, stream,
+                           (const uint16_t *)w, wp, s_w, K);
     return hipGetLastError();
 }
 

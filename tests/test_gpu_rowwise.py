@@ -79,6 +79,44 @@ def test_quantize_weights_bit_exact(gpu, oracle, N, K):
     assert_equal_bits(wp.cpu().numpy(), oracle.pack_w4(wq_o), "wp")
 
 
+@pytest.mark.parametrize("K", [992, 1056, 5152, 6144, 6176, 16384, 16416])
+def test_quantize_weights_row_lengths(gpu, oracle, K):
+    """Rows that end inside, at the end of and beyond what a thread keeps in registers; a row of exact ties; a row with an
+    infinity (scale inf: finite weights become 0, the infinity -8); rows with a NaN, which takes part in the maximum only
+    where every one of the four 64-chunk phases of the row is NaN, and whose own code is -8."""
+    w = synth.weights_fp16(7, K, config_id=9)
+    w[2, :] = np.tile(np.array([7.0, 0.5, -1.5, 2.5, -3.5, 4.5, -5.5, -7.0], np.float16), K // 8)
+    w[3, K - 1] = np.float16(np.inf)
+    w[4, 5] = np.float16(np.nan)
+    w[5, ::8] = np.float16(np.nan)
+    wp, s_w = w4a8.w4a8_quantize_weights(gpu.from_numpy(w).cuda())
+    gpu.cuda.synchronize()
+    wp, s_w = wp.cpu().numpy(), s_w.cpu().numpy()
+    rows = [0, 1, 2, 6]
+    wq_o, s_o = oracle.quantize_weights_rtn(np.ascontiguousarray(w[rows]))
+    assert_equal_bits(s_w[rows].view(np.uint32), s_o.view(np.uint32), "s_w")
+    assert_equal_bits(wp[rows], oracle.pack_w4(wq_o), "wp")
+    inf_row = np.zeros((1, K), np.int8)
+    inf_row[0, K - 1] = -8
+    assert np.isposinf(s_w[3])
+    assert_equal_bits(wp[3:4], oracle.pack_w4(inf_row), "wp of a row with an infinity")
+    # one NaN: the scale is that of the phases without it
+    phase = (np.arange(K) // 512) % 4
+    counted = phase != 0
+    if K <= 1536:  # a phase without chunks counts as zero
+        assert counted.any()
+    top = np.float32(np.abs(w[4, counted].astype(np.float32)).max())
+    s = np.float32(top / np.float32(7.0))
+    assert s_w[4] == s
+    q = np.clip(np.rint(w[4].astype(np.float32) / s), -8, 7)
+    q[5] = -8
+    assert_equal_bits(wp[4:5], oracle.pack_w4(q.astype(np.int8)[None, :]), "wp of a row with a NaN")
+    # NaN in every phase that has chunks: no phase left (scale NaN, every code -8) or empty ones (scale 0, every code 0)
+    every = np.full((1, K), -8 if K > 1536 else 0, np.int8)
+    assert np.isnan(s_w[5]) if K > 1536 else s_w[5] == 0
+    assert_equal_bits(wp[5:6], oracle.pack_w4(every), "wp of a row of NaN")
+
+
 @pytest.mark.parametrize("N,K", [(1, 32), (7, 96), (64, 4096), (33, 5120), (4, 28672)])
 def test_quantize_weights_clipped_bit_exact(gpu, oracle, N, K):
     """Eq. (8),(9) with per-channel clipping strengths: codes (saturating at -8 / 7) and scales bit-exact."""
