@@ -187,14 +187,15 @@ constexpr TileCost kTileCosts[] = {
 // What K slices add: a second launch, and the slabs written and read
 double slab_us(int M, int N, int slices) { return 2.0 + 0.34e-6 * 4.0 * M * (double)N * slices; }
 
-double tile_us(const TileCost &t, int M, int N, int stages, int slices = 1) {
+// lone_slots: up to how many workgroups of the last round each has a compute unit for itself; 0: half of what the chip holds
+double tile_us(const TileCost &t, int M, int N, int stages, int slices = 1, long long lone_slots = 0) {
     const long long n = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * slices;
     const long long slots = (long long)compute_units() * t.per_cu;
     const long long full = n / slots, rest = n % slots;
     double us = t.launch + t.round * (double)(full + (rest != 0)) + t.stage * (double)(full * stages);
     if (rest != 0) {
         const double part = (double)rest / (double)slots;
-        us += (t.last + t.share * part - (t.per_cu > 1 && rest * 2 <= slots ? t.lone : 0.f)) * stages;
+        us += (t.last + t.share * part - (t.per_cu > 1 && rest <= (lone_slots ? lone_slots : slots / 2) ? t.lone : 0.f)) * stages;
     }
     return us;
 }
@@ -363,29 +364,27 @@ int choose_fine_tile(int M, int N) {
     return best;
 }
 
-// The same choice for the int8-weight variant, whose weight stages take twice the LDS (shallower rings, and the
-// 128 x 256 tile fits a compute unit only once).
-int choose_tiled_tile8(int M, int N) {
-    const int cus = compute_units();
-    auto count = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    if (M <= 32) return kTiled32x128;  // taller tiles would multiply rows that do not exist
-    if (M <= 64 || count(128, 128) * 4 < (long long)cus * 3)
-        return count(64, 128) * 4 >= (long long)cus * 3 ? kTiled64x128 : kTiled64x64;
-    struct Option { int id, bm, bn, per_cu; double eff; };
-    const Option options[] = {{kTiled256x256, 256, 256, 1, 1.00},
-                              {kTiled128x256, 128, 256, 1, 0.80},
-                              {kTiled128x160, 128, 160, 2, 0.95},
-                              {kTiled128x128, 128, 128, 2, 0.85}};
-    int best = kTiled256x256;
-    double best_cost = 0;
-    for (const Option &o : options) {
-        const long long tiles = count(o.bm, o.bn);
-        const long long slots = (long long)cus * o.per_cu;
-        const long long full = tiles / slots, rest = tiles % slots;
-        const double last = rest == 0 ? 0.0 : (o.per_cu == 1 || rest * 2 > slots ? 1.0 : 0.5);
-        const double cost = ((double)full + last) * o.bm * o.bn * o.per_cu / o.eff;
-        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = o.id; }
-    }
+// The choice for the int8-weight variant.  Its stages bring in twice the weight bytes, through rings one stage shallower,
+// and convert nothing: a launch takes 1.06 to 1.42 times the price of the same tile over int4 weights, most where the weight
+// stream is most of the work.  The factors are geometric means over 36 shapes (29 random, M 1 .. 1024; weights cold).
+// Choosing by them costs 0.6 % on average over always taking the fastest of fourteen tiles; rounds times area over an
+// efficiency on seven tiles, the rule before, cost 11 % (N = 5120, K = 13824, M = 512: 64 x 128 at 81 us, now 64 x 192 at 61;
+// N = 11722, K = 15648, M = 1: 54 us, now 38).  128 x 256 of 4 waves, 128 x 160 and 128 x 128 were never the fastest,
+// 64 x 256 and 192 x 256 neither.
+int choose_tiled_tile8(int M, int N, int K) {
+    struct Factor { int id; double over_int4; };
+    const Factor factors[] = {{kTiled256x256, 1.195}, {kTiled64x128, 1.333},  {kTiled64x64, 1.217},  {kTiled32x128, 1.411},
+                              {kTiled128x256W8, 1.252}, {kTiled128x192, 1.173}, {kTiled64x192, 1.277}, {kTiled192x192, 1.060}};
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
+    int best = 0;
+    double best_us = 0;
+    for (const Factor &f : factors)
+        for (const TileCost &t : kTileCosts) {
+            if (t.id != f.id) continue;
+            // a compute unit with two workgroups streams twice the weights: no discount for a lone one then
+            const double us = f.over_int4 * tile_us(t, M, N, stages, 1, compute_units());
+            if (best == 0 || us < best_us) best = t.id, best_us = us;
+        }
     return best;
 }
 
@@ -876,7 +875,7 @@ static int gemm_tiled_variant(const int8_t *xq, const float *s_a, const uint8_t 
     a.out = out_fp16; a.acc_out = acc_i32;
     a.M = M; a.N = N; a.K = K; a.ldc = N;
     const int tile = variant ? variant
-                             : wfmt == 8 ? choose_tiled_tile8(M, N) : choose_tiled_tile(M, N, K, kTiledTileMax);
+                             : wfmt == 8 ? choose_tiled_tile8(M, N, K) : choose_tiled_tile(M, N, K, kTiledTileMax);
     return launched(launch_gemm_prefill_tiled(a, want_acc, tile, static_cast<hipStream_t>(stream), wfmt));
 }
 

@@ -196,6 +196,10 @@ hipError_t launch_gemm_prefill_tiled(const PrefillArgs &p, bool acc_out, int til
                     case kTiled64x128: e = launch_tile<2, 4, 2, 2, 3, 8>(q, acc_out, stream); break;
                     case kTiled64x64: e = launch_tile<2, 2, 2, 2, 4, 8>(q, acc_out, stream); break;
                     case kTiled32x128: e = launch_tile<2, 2, 1, 4, 3, 8>(q, acc_out, stream); break;
+                    case kTiled128x256W8: e = launch_tile<8, 2, 1, 8, 3, 8>(q, acc_out, stream); break;
+                    case kTiled128x192: e = launch_tile<4, 3, 2, 4, 3, 8>(q, acc_out, stream); break;
+                    case kTiled64x192: e = launch_tile<2, 3, 2, 4, 4, 8>(q, acc_out, stream); break;
+                    case kTiled192x192: e = launch_tile<6, 3, 2, 4, 3, 8>(q, acc_out, stream); break;
                     default: e = hipErrorInvalidConfiguration;
                 }
             } else if (wbits == kWeightsUnsigned4) {
@@ -265,6 +269,9 @@ hipError_t prepare_tiled_kernels() {
     for (int tile : {kTiled256x256, kTiled128x256, kTiled64x128, kTiled64x64, kTiled32x128, kTiled128x256W8, kTiled64x256, kTiled128x384,
                      kTiled128x192, kTiled64x192, kTiled128x320, kTiled192x320, kTiled192x256, kTiled192x192})
         if (const hipError_t e = launch_gemm_prefill_tiled_swiglu(a, tile, nullptr); e != hipSuccess) return e;
+    for (int tile : {kTiled128x256W8, kTiled128x192, kTiled64x192, kTiled192x192})  // int8 weights, beside 1 .. kTiledTileMax
+        for (int acc = 0; acc <= 1; ++acc)
+            if (const hipError_t e = launch_gemm_prefill_tiled(a, acc != 0, tile, nullptr, 8); e != hipSuccess) return e;
     struct Format { int wbits, tiles; bool acc; };
     const Format formats[] = {{4, kTiledTileLast, true}, {8, kTiledTileMax, true}, {kWeightsUnsigned4, kTiledTileMax, true},
                               {kWeightsFineGrained4, kFineTileMax, false}};

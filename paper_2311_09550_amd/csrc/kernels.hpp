@@ -135,13 +135,13 @@ constexpr int kTiled64x64 = 7;          // 4 waves of 32 x 32
 constexpr int kTiled32x128 = 8;         // 4 waves of 32 x 32 side by side
 constexpr int kTiled128x160K2 = 9;      // 128 x 160 with two wave sets of 4 splitting each stage's k (int4 weights only)
 constexpr int kTiled128x128K2 = 10;     // 128 x 128 likewise
-constexpr int kTiled256x192 = 11;       // 8 waves of 64 x 96 (int4 weights only): the narrower partner of 1 for the columns
-                                        // that whole rounds of 256 x 256 tiles leave over
+constexpr int kTiled256x192 = 11;       // 8 waves of 64 x 96 (int4 weights only)
 constexpr int kTiledTileMax = 8;        // tiles every weight format has
-constexpr int kTiled128x256W8 = 12;     // 128 x 256 as 8 waves of 128 x 32, four-stage ring, one workgroup per compute unit
-                                        // (int4 weights only)
+constexpr int kTiled128x256W8 = 12;     // 128 x 256 as 8 waves of 128 x 32, one workgroup per compute unit; ring of four
+                                        // stages over int4 weights, of three over int8
 constexpr int kTiledTileMax4 = 12;      // tiles of the signed int4 format that a caller can force
-// ... and the further ones the library chooses from, all of 8 waves, one workgroup per compute unit
+// ... and the further ones the library chooses from, all of 8 waves, one workgroup per compute unit (15, 16 and 20 for
+// int8 weights too)
 constexpr int kTiled64x256 = 13;        // 8 waves of 64 x 32
 constexpr int kTiled128x384 = 14;       // 128 x 48
 constexpr int kTiled128x192 = 15;       // 64 x 48
@@ -170,7 +170,7 @@ hipError_t launch_tile_weights(const uint8_t *wp, uint8_t *wt, int N, int K, hip
 hipError_t launch_tile_weights8(const int8_t *w8, uint8_t *wt, int N, int K, hipStream_t stream);
 hipError_t launch_gemm_prefill_tiled(const PrefillArgs &p, bool acc_out, int tile, hipStream_t stream, int wbits = 4);
 // The same over gate and up channels interleaved, storing h = fp16(silu(gate) * up) (p.out = h, p.ldc = its pitch);
-// tiles 256 x 256, 256 x 192, 128 x 256 (both forms) and 128 x 128.
+// the tiles that the library chooses from.
 hipError_t launch_gemm_prefill_tiled_swiglu(const PrefillArgs &p, int tile, hipStream_t stream);
 // Per-device preparations (LDS allowance) of every instantiation of the tiled kernel, for the current device.
 hipError_t prepare_tiled_kernels();

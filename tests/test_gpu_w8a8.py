@@ -70,6 +70,24 @@ def test_w8a8_ragged_shapes(gpu, oracle, M, N, K, tile):
     _run(gpu, oracle, xq, w8, s_a, s_w, tile, f"w8a8 tile={tile} M={M} N={N} K={K}")
 
 
+@pytest.mark.parametrize("M,N,K", [(512, 5120, 13824), (450, 4927, 1056), (330, 12289, 160), (1023, 5120, 288), (512, 15363, 96),
+                                   (130, 32800, 96), (600, 27000, 64)])
+def test_w8a8_chosen_tiles(gpu, oracle, M, N, K):
+    """Sizes at which the library takes its 8-wave tiles (64 x 192, 128 x 192, 192 x 192, 128 x 256), with ragged edges:
+    the bits of the 64 x 64 tile, which the tests above hold against the oracle (integer sums, one rounding)."""
+    t = gpu
+    g = t.Generator(device="cuda").manual_seed(M + N + K)
+    xq = t.randint(-128, 128, (M, K), generator=g, device="cuda", dtype=t.int8)
+    wt = w4a8.w8a8_tile_weights(t.randint(-128, 128, (N, K), generator=g, device="cuda", dtype=t.int8))
+    s_a = t.rand(M, generator=g, device="cuda") * 1e-3
+    s_w = t.rand(N, generator=g, device="cuda") * 1e-3
+    acc, out = (w4a8.w8a8_gemm_tiled(xq, s_a, wt, s_w, want_acc=a) for a in (True, False))
+    acc64, out64 = (w4a8.w8a8_gemm_tiled(xq, s_a, wt, s_w, variant=7, want_acc=a) for a in (True, False))
+    t.cuda.synchronize()
+    assert t.equal(acc, acc64), "sums"
+    assert t.equal(out.view(t.int16), out64.view(t.int16)), "outputs"
+
+
 def test_w8a8_extremes_at_max_k(gpu, oracle):
     """a = -128, w = -128 along all of K = 65536: the sum is 2^30, inside int32."""
     M, K, N = 130, 65536, 48
