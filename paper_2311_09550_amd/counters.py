@@ -7,8 +7,7 @@ for `--kernel-trace --stats`).  This script reads them, never the GPU:
         HBM-side bytes per GEMM call of the kernel whose name contains NAME: FETCH_SIZE and WRITE_SIZE (KiB-like units
         per dispatch), each scaled by what the same counter reads for the 256 MiB `__amd_rocclr_copyBuffer` dispatches
         of `bench.py --copy-calibration` in the same run, summed over all dispatches of the kernel and divided by the
-        GEMM calls of the run = dispatches x F (a GEMM call may be more than one dispatch: the timed step makes 4 calls
-        in 5 dispatches, F = 0.8; default F = 1); with --by-grid instead the mean over the GEMM shapes of the mean per
+        GEMM calls of the run = dispatches x F (default F = 1; less where a GEMM call is more than one dispatch); with --by-grid instead the mean over the GEMM shapes of the mean per
         dispatch (the decode section: a shape is told by grid size and k steps per wave; equal weights).  Merges the result under KEY into
         profiles/traffic_counters.json together with the hash of the kernel sources, which `bench.py` checks before it
         reports the figure.  Prints a markdown table per (kernel, grid size).
