@@ -58,6 +58,26 @@ int w4a8_gemm_tuned(const int8_t *xq, const float *s_a, const uint8_t *wp, const
                     void *workspace, size_t workspace_bytes, void *stream);
 
 /*
+ * Which kernel the library's own choice runs for a shape: a host function that launches nothing and needs no GPU (without
+ * one it answers for 256 compute units).  For tests that must know which kernel they reach, and for benchmarks.
+ *   entry  : one of W4A8_ROUTE_*; N counts channels (2 I for SWIGLU);
+ *   variant, splits : as in w4a8_gemm_tiled_splitk, for SPLITK and SPLITK_STATIC only;
+ *   tiling : out, one of W4A8_TILING_* (never an AUTO one);
+ *   tile   : out, output tile of a PREFILL tiling, else 0.  1 .. 12 as for PREFILL_TILED above (for PREFILL as well); 13 = 64 x
+ *            256, 14 = 128 x 384, 15 = 128 x 192, 16 = 64 x 192, 17 = 128 x 320, 18 = 192 x 320, 19 = 192 x 256, 20 = 192 x 192;
+ *   slices : out, K slices.
+ * Returns what the entry returns for these sizes.
+ */
+#define W4A8_ROUTE_GEMM 0          /* w4a8_gemm, w4a8_gemm_acc_i32   */
+#define W4A8_ROUTE_GEMM_TILED 1    /* w4a8_gemm_tiled                */
+#define W4A8_ROUTE_SPLITK 2        /* w4a8_gemm_tiled_splitk         */
+#define W4A8_ROUTE_SPLITK_STATIC 3 /* w4a8_gemm_tiled_splitk_static  */
+#define W4A8_ROUTE_SWIGLU 4        /* w4a8_gemm_tiled_swiglu         */
+#define W4A8_ROUTE_W8A8 5          /* w8a8_gemm_tiled                */
+#define W4A8_ROUTE_UNSIGNED 6      /* w4a8_gemm_tiled_unsigned       */
+int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *tiling, int *tile, int *slices);
+
+/*
  * Two probes of what the chip sustains, for a benchmark to set its figures against (they are no part of the path and
  * compute nothing of use):
  * w4a8_probe_stream_read: a read-only streaming reduction over buf (device, `bytes` long, 16-byte aligned) by 8

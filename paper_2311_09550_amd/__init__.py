@@ -85,6 +85,8 @@ def lib():
         L.w4a8_add_rmsnorm_quantize.argtypes = [vp, vp, vp, ctypes.c_float, vp, vp, vp, vp, i, i, vp]
         L.w4a8_linear_tiled_swiglu_fp16.restype = i
         L.w4a8_linear_tiled_swiglu_fp16.argtypes = [vp, ctypes.c_longlong, vp, vp, vp, vp, i, i, i, vp]
+        L.w4a8_route.restype = i
+        L.w4a8_route.argtypes = [i] * 6 + [ctypes.POINTER(i)] * 3
         L.w4a8_init.restype = i
         L.w4a8_init.argtypes = []
         L.w4a8_probe_stream_read.restype = i
@@ -417,6 +419,16 @@ def w4a8_gemm_tiled_unsigned(xq, s_a, ut, s_w, N=None, variant: int = 0, want_ac
     _check(lib().w4a8_gemm_tiled_unsigned(_dev(xq, torch.int8, "xq"), sa, _dev(ut, torch.uint8, "ut"), sw, o16, o32, M, N, K,
                                           variant, _stream()))
     return out
+
+
+ROUTE_GEMM, ROUTE_GEMM_TILED, ROUTE_SPLITK, ROUTE_SPLITK_STATIC, ROUTE_SWIGLU, ROUTE_W8A8, ROUTE_UNSIGNED = range(7)
+
+
+def w4a8_route(entry: int, M: int, N: int, K: int, variant: int = 0, splits: int = 0):
+    """(tiling, tile, K slices) of the library's own choice for a shape; launches nothing, needs no GPU."""
+    out = [ctypes.c_int() for _ in range(3)]
+    _check(lib().w4a8_route(entry, M, N, K, variant, splits, *map(ctypes.byref, out)))
+    return tuple(o.value for o in out)
 
 
 def w4a8_gemm_tiled_workspace_bytes(M: int, N: int, K: int) -> int:

@@ -800,6 +800,51 @@ int w4a8_gemm_tiled_splitk_static(const int8_t *xq, const float *s_a, const uint
     return splitk_on_route(route, xq, s_a, wt, s_w, out_fp16, M, N, K, ws, kStaticScratchBytes, stream);
 }
 
+int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *tiling, int *tile, int *slices) {
+    if (!tiling || !tile || !slices) return W4A8_ERR_NULL;
+    if (int e = check_gemm_shape(M, N, K)) return e;
+    *tile = 0;
+    *slices = 1;
+    auto report = [&](const TiledPlan &pl) {
+        *tiling = pl.wide ? W4A8_TILING_DECODE_RESIDENT_TILED : W4A8_TILING_PREFILL_TILED;
+        *tile = pl.wide ? 0 : pl.tile;
+        *slices = pl.splits > 1 ? pl.splits : 1;
+        return (int)W4A8_OK;
+    };
+    auto plan = [&](int auto_tiling) {
+        Plan pl{};
+        if (int e = choose_plan(M, N, K, auto_tiling, 0, &pl)) return e;
+        const bool tiled = auto_tiling == W4A8_TILING_AUTO_TILED;
+        *tiling = !tiled                                      ? pl.tiling
+                  : pl.tiling == W4A8_TILING_DECODE_RESIDENT ? W4A8_TILING_DECODE_RESIDENT_TILED
+                  : pl.tiling == W4A8_TILING_DECODE_STREAM   ? W4A8_TILING_DECODE_STREAM_TILED
+                                                              : pl.tiling;
+        if (pl.tiling == W4A8_TILING_PREFILL || pl.tiling == W4A8_TILING_PREFILL_TILED) *tile = pl.prefill_tile;
+        return (int)W4A8_OK;
+    };
+    switch (entry) {
+        case W4A8_ROUTE_GEMM: return plan(W4A8_TILING_AUTO);
+        case W4A8_ROUTE_GEMM_TILED: return plan(W4A8_TILING_AUTO_TILED);
+        case W4A8_ROUTE_SPLITK:
+        case W4A8_ROUTE_SPLITK_STATIC: {
+            if (variant < 0 || variant > kTiledTileMax4 || splits < 0 || splits > 64) return W4A8_ERR_ARG;
+            const bool in_scratch = entry == W4A8_ROUTE_SPLITK_STATIC;
+            const SplitRoute r = split_route(M, N, K, variant, splits, in_scratch ? kStaticScratchBytes : SIZE_MAX);
+            if (in_scratch && r.plan.slab_bytes > kStaticScratchBytes) return W4A8_ERR_WORKSPACE;
+            return r.stream ? plan(W4A8_TILING_AUTO_TILED) : report(r.plan);
+        }
+        case W4A8_ROUTE_SWIGLU:
+            if (N % 64 != 0) return W4A8_ERR_SHAPE;
+            return report(tiled_plan(M, N, K, 0, true));
+        case W4A8_ROUTE_W8A8:
+        case W4A8_ROUTE_UNSIGNED:
+            *tiling = W4A8_TILING_PREFILL_TILED;
+            *tile = entry == W4A8_ROUTE_W8A8 ? choose_tiled_tile8(M, N, K) : choose_tiled_tile(M, N, K, kTiledTileMax);
+            return W4A8_OK;
+        default: return W4A8_ERR_ARG;
+    }
+}
+
 int w4a8_init(void) {
     void *ws = nullptr;
     if (int e = static_scratch(&ws)) return e;
