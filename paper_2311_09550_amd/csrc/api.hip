@@ -253,6 +253,11 @@ double row_decode_us(int M, int N, int K, bool resident) {
                    : 2.971 + 0.6039 * chunks + 0.0316 * w_kb + 0.0263 * x_kb + 0.0730 * steps * chunks;
 }
 
+// Whether one launch of the large-M kernel reaches every byte of both operands (32-bit byte offsets)
+bool one_launch_covers(int M, int N, int K) {
+    return (long long)M * K <= 0xF0000000ll && (long long)tiled_weight_bytes(N, K, 4) <= 0xF0000000ll;
+}
+
 // How a GEMM over tiled int4 weights with more than 16 tokens is run: by the weight-streaming kernel with per-wave
 // staging, K cut into slices, or by the large-M kernel, K cut into slices.  Both are priced
 // and the cheaper one is taken.
@@ -261,7 +266,6 @@ struct TiledPlan {
     DecodeShape shape;  // wide: its shape
     int tile;           // else: output tile and K slices
     int splits, stages_per_split;
-    size_t slab_bytes;  // raw sums of the slices, 0 when there is one
 };
 
 // Price of the weight-streaming kernel in microseconds: what every compute unit brings in (the activations and its
@@ -286,8 +290,9 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu) {
     const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
     const size_t slab = (size_t)M * (size_t)N * sizeof(int32_t);
     const int max_slices = max_slab / slab < 2 ? 1 : (int)(max_slab / slab < (size_t)kMaxSlices ? max_slab / slab : kMaxSlices);
+    const int ring_slices = M <= kSplitMaxM && one_launch_covers(M, N, K) ? max_slices : 1;
     for (const TileCost &t : kTileCosts) {
-        for (int s = 1; s <= (M <= kSplitMaxM ? max_slices : 1); ++s) {
+        for (int s = 1; s <= ring_slices; ++s) {
             const int per = (stages + s - 1) / s, n = (stages + per - 1) / per;
             if (n != s) continue;  // the same as fewer slices
             double us = tile_us(t, M, N, per, s);
@@ -297,7 +302,6 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu) {
                 best.tile = t.id;
                 best.splits = s;
                 best.stages_per_split = per;
-                best.slab_bytes = s > 1 ? s * slab : 0;
             }
         }
     }
@@ -311,7 +315,6 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu) {
                 best_us = us;
                 best.wide = true;
                 best.shape = shape;
-                best.slab_bytes = s > 1 ? s * slab : 0;
             }
         }
     }
@@ -583,7 +586,7 @@ int w4a8_gemm_tiled_swiglu(const int8_t *xq, const float *s_a, const uint8_t *wt
     const int N = 2 * I;
     if (int e = check_gemm_shape(M, N, K)) return e;
     if (misaligned(xq) || misaligned(wt_gu) || misaligned(h_fp16) || misaligned(s_w_gu)) return W4A8_ERR_ALIGN;
-    if ((long long)M * K > 0xF0000000ll || (long long)tiled_weight_bytes(N, K, 4) > 0xF0000000ll) return W4A8_ERR_SHAPE;
+    if (!one_launch_covers(M, N, K)) return W4A8_ERR_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
     const TiledPlan pl = tiled_plan(M, N, K, 0, true);
     if (pl.wide) {
@@ -601,60 +604,106 @@ int w4a8_gemm_tiled_swiglu(const int8_t *xq, const float *s_a, const uint8_t *wt
 
 namespace {
 
-// K slices that callers are told to bring a workspace for (w4a8_gemm_tiled_workspace_bytes), 1 = none: with 17 to 64 tokens
-// as few as let a slice of K fit the registers of the weight-streaming kernel, above and up to 512 as many as give every
-// compute unit two 64 x 128 tiles (128 x 128 on a long K), at least 12 stages each and at most 6.  The library's own
-// choice stays within it and often needs fewer.
-int advertised_slices(int M, int N, int K) {
-    if (M <= 16 || M > kSplitMaxM) return 1;
-    if (M <= kResidentMaxM)
+// What w4a8_gemm_tiled_splitk asks of its caller for a shape: how many slabs of raw sums the workspace has to hold, and by
+// that which calls are refused.  Callers size buffers by it (w4a8_gemm_tiled_workspace_bytes) and the static entry refuses by
+// it, so it is a rule of its own that does not move with the prices of plan_tiled; the library's choice stays within it and
+// often needs less.
+//   17 to 64 tokens: as few slices as let a slice of K fit the registers of the weight-streaming kernel, up to 8;
+//   else, and up to 512 tokens: where the tiles fill up to half the compute units (all of them on a long K), as many slices
+//   as bring two workgroups to every compute unit, at least 12 stages each and at most 6.  The tiles are those of a rule by
+//   rounds and area; a forced tile is cut by the same rule.
+struct SlabRule {
+    int slices;
+    bool ring;  // slices of the large-M kernel, whose one launch must cover the problem
+};
+
+long long tile_count(int M, int N, int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); }
+
+struct TileShape { int bm, bn; };
+constexpr TileShape kForcedTiles[] = {{0, 0},     {256, 256}, {256, 256}, {128, 256}, {128, 160}, {128, 128}, {64, 128},
+                                      {64, 64},   {32, 128},  {128, 160}, {128, 128}, {256, 192}, {128, 256}};
+static_assert(sizeof kForcedTiles / sizeof kForcedTiles[0] == kTiledTileMax4 + 1, "one shape per tile that can be forced");
+
+TileShape slab_rule_tile(int M, int N, bool long_k, int cus) {
+    auto count = [&](int bm, int bn) { return tile_count(M, N, bm, bn); };
+    if (M <= 32) return {32, 128};
+    if (M <= 64) return count(64, 128) * 4 >= cus * 3ll ? TileShape{64, 128} : TileShape{64, 64};
+    if (count(128, 128) * 4 < cus * 3ll) return long_k ? TileShape{128, 128} : TileShape{64, 128};
+    struct Option { int bm, bn, per_cu; double eff, alone; };
+    const Option options[] = {{256, 256, 1, 1.00, 1.0},  {256, 192, 1, 0.97, 1.0},  {128, 256, 2, 0.93, 0.73}, {128, 256, 1, 0.85, 1.0},
+                              {128, 160, 2, 0.66, 0.63}, {128, 128, 2, 0.75, 0.67}, {64, 128, 2, 0.60, 0.75},  {128, 128, 1, 0.60, 1.0}};
+    TileShape best{256, 256};
+    double best_cost = 0;
+    for (const Option &o : options) {
+        const long long tiles = count(o.bm, o.bn), slots = (long long)cus * o.per_cu, full = tiles / slots, rest = tiles % slots;
+        const double last = rest == 0 ? 0.0 : ((o.per_cu > 1 && rest <= cus) ? o.alone : 1.0);
+        const double cost = ((double)full + last) * o.bm * o.bn * o.per_cu / o.eff;
+        if (best_cost == 0 || cost < best_cost) { best_cost = cost; best = {o.bm, o.bn}; }
+    }
+    if (best.bm == 64 && long_k && count(128, 128) <= cus) best = {128, 128};
+    return best;
+}
+
+SlabRule slab_rule(int M, int N, int K, int variant) {
+    if (variant == 0 && M <= 16) return {1, false};
+    if (variant == 0 && M <= kResidentMaxM)
         for (int s = 1; s <= kMaxSlices; ++s) {
             DecodeShape t{};
-            if (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &t, s, true)) return t.k_slices;
+            if (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &t, s, true)) return {s, false};
         }
     const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
     const bool long_k = stages >= 64;
-    auto count = [&](int bm, int bn) { return (long long)((M + bm - 1) / bm) * ((N + bn - 1) / bn); };
-    const long long tiles = long_k && count(128, 128) <= cus ? count(128, 128) : count(64, 128);
-    if (tiles > (long_k ? cus : cus / 2)) return 1;
+    if (M > kSplitMaxM) return {1, true};
+    const TileShape t = variant ? kForcedTiles[variant] : slab_rule_tile(M, N, long_k, cus);
+    const long long tiles = tile_count(M, N, t.bm, t.bn);
+    if (tiles > (long_k ? cus : cus / 2)) return {1, true};
     int s = (int)((2ll * cus + tiles / 2) / tiles);
     if (s > 6) s = 6;
     if (s > stages / 12) s = stages / 12;
-    if (s < 2) return 1;
+    if (s < 1) s = 1;
     const int per = (stages + s - 1) / s;
-    return (stages + per - 1) / per;  // no empty slice
+    return {(stages + per - 1) / per, true};  // no empty slice
 }
 
 // What w4a8_gemm_tiled_splitk does with a shape: the plan, or token generation (up to 16 tokens, nothing forced: the entry
-// without slices).  max_slab: bytes of slabs the library's own choice may use.
+// without slices); and what it asks for.
 struct SplitRoute {
     bool stream;
     TiledPlan plan;
+    size_t need;      // bytes of workspace, 0 when one slice is asked for
+    bool one_launch;  // refused where one launch cannot address the problem (slabs are whole M x N matrices)
 };
 
-SplitRoute split_route(int M, int N, int K, int variant, int splits, size_t max_slab) {
+SplitRoute split_route(int M, int N, int K, int variant, int splits) {
     SplitRoute r{};
     const size_t slab = (size_t)M * (size_t)N * sizeof(int32_t);
-    if (variant == 0 && splits == 0) {
-        const size_t told = (size_t)advertised_slices(M, N, K) * slab;
-        r.stream = M <= 16;
-        if (!r.stream) r.plan = tiled_plan(M, N, K, told < max_slab ? told : max_slab, false);
-        return r;
-    }
-    // forced: the weight-streaming kernel where it has a shape for that many slices (17 to 64 tokens, no tile forced), else
-    // the large-M kernel; a forced tile without a slice count is not cut
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
     TiledPlan &pl = r.plan;
-    if (variant == 0 && M > 16 && M <= kResidentMaxM && resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl.shape, splits, true)) {
+    if (splits == 0) {
+        const SlabRule rule = slab_rule(M, N, K, variant);
+        r.need = rule.slices > 1 ? rule.slices * slab : 0;
+        r.one_launch = rule.ring && rule.slices > 1;
+        r.stream = variant == 0 && M <= 16;
+        if (r.stream) return r;
+        if (variant == 0) {
+            pl = tiled_plan(M, N, K, r.need, false);
+            return r;
+        }
+        splits = rule.slices;
+    } else if (variant == 0 && M > 16 && M <= kResidentMaxM && splits <= stages &&
+               resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl.shape, splits, true)) {
+        // a forced count without a tile: slices of the weight-streaming kernel where it has a shape for them
         pl.wide = true;
         pl.splits = pl.shape.k_slices;
-    } else {
-        const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
-        const int s = splits < 1 ? 1 : splits > stages ? stages : splits;
-        pl.tile = variant ? variant : choose_tiled_tile(M, N, K);
-        pl.stages_per_split = (stages + s - 1) / s;
-        pl.splits = (stages + pl.stages_per_split - 1) / pl.stages_per_split;  // no empty slice
+        r.need = splits > 1 ? splits * slab : 0;
+        return r;
     }
-    pl.slab_bytes = pl.splits > 1 ? (size_t)pl.splits * slab : 0;
+    if (splits > stages) splits = stages;
+    pl.tile = variant ? variant : choose_tiled_tile(M, N, K);
+    pl.stages_per_split = (stages + splits - 1) / splits;
+    pl.splits = (stages + pl.stages_per_split - 1) / pl.stages_per_split;  // no empty slice
+    r.one_launch = pl.splits > 1;
+    r.need = pl.splits > 1 ? pl.splits * slab : 0;
     return r;
 }
 
@@ -662,9 +711,7 @@ SplitRoute split_route(int M, int N, int K, int variant, int splits, size_t max_
 
 size_t w4a8_gemm_tiled_workspace_bytes(int M, int N, int K) {
     if (check_gemm_shape(M, N, K)) return 0;
-    // a forced count is checked against the buffer at the call
-    const int s = advertised_slices(M, N, K);
-    return s > 1 ? (size_t)s * (size_t)M * (size_t)N * sizeof(int32_t) : 0;
+    return split_route(M, N, K, 0, 0).need;  // a forced count is checked against the buffer at the call
 }
 
 static int splitk_on_route(const SplitRoute &route, const int8_t *xq, const float *s_a, const uint8_t *wt, const float *s_w, void *out_fp16,
@@ -674,11 +721,10 @@ static int splitk_on_route(const SplitRoute &route, const int8_t *xq, const floa
     hipStream_t st = static_cast<hipStream_t>(stream);
     const TiledPlan &pl = route.plan;
     const bool sliced = pl.splits > 1;
-    if (sliced) {
-        // one launch must cover the problem (slabs are whole M x N matrices)
-        if (!pl.wide && ((long long)M * K > 0xF0000000ll || (long long)tiled_weight_bytes(N, K, 4) > 0xF0000000ll)) return W4A8_ERR_SHAPE;
+    if (route.need) {
+        if (route.one_launch && !one_launch_covers(M, N, K)) return W4A8_ERR_SHAPE;
         if (!workspace) return W4A8_ERR_NULL;
-        if (workspace_bytes < pl.slab_bytes) return W4A8_ERR_WORKSPACE;
+        if (workspace_bytes < route.need) return W4A8_ERR_WORKSPACE;
     }
     int32_t *const slabs = sliced ? static_cast<int32_t *>(workspace) : nullptr;
     void *const out = sliced ? nullptr : out_fp16;
@@ -712,7 +758,7 @@ int w4a8_gemm_tiled_splitk(const int8_t *xq, const float *s_a, const uint8_t *wt
                            int N, int K, int variant, int splits, void *workspace, size_t workspace_bytes, void *stream) {
     if (int e = check_splitk(xq, s_a, wt, s_w, out_fp16, M, N, K, variant, splits)) return e;
     if (misaligned(workspace)) return W4A8_ERR_ALIGN;
-    return splitk_on_route(split_route(M, N, K, variant, splits, SIZE_MAX), xq, s_a, wt, s_w, out_fp16, M, N, K, workspace,
+    return splitk_on_route(split_route(M, N, K, variant, splits), xq, s_a, wt, s_w, out_fp16, M, N, K, workspace,
                            workspace_bytes, stream);
 }
 
@@ -793,8 +839,8 @@ int w4a8_linear_tiled_swiglu_fp16(const void *x_fp16, long long ldx, const uint8
 int w4a8_gemm_tiled_splitk_static(const int8_t *xq, const float *s_a, const uint8_t *wt, const float *s_w, void *out_fp16,
                                   int M, int N, int K, int variant, int splits, void *stream) {
     if (int e = check_splitk(xq, s_a, wt, s_w, out_fp16, M, N, K, variant, splits)) return e;
-    const SplitRoute route = split_route(M, N, K, variant, splits, kStaticScratchBytes);
-    if (route.plan.slab_bytes > kStaticScratchBytes) return W4A8_ERR_WORKSPACE;
+    const SplitRoute route = split_route(M, N, K, variant, splits);
+    if (route.need > kStaticScratchBytes) return W4A8_ERR_WORKSPACE;
     void *ws = nullptr;
     if (int e = static_scratch(&ws)) return e;
     return splitk_on_route(route, xq, s_a, wt, s_w, out_fp16, M, N, K, ws, kStaticScratchBytes, stream);
@@ -828,13 +874,13 @@ int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *til
         case W4A8_ROUTE_SPLITK:
         case W4A8_ROUTE_SPLITK_STATIC: {
             if (variant < 0 || variant > kTiledTileMax4 || splits < 0 || splits > 64) return W4A8_ERR_ARG;
-            const bool in_scratch = entry == W4A8_ROUTE_SPLITK_STATIC;
-            const SplitRoute r = split_route(M, N, K, variant, splits, in_scratch ? kStaticScratchBytes : SIZE_MAX);
-            if (in_scratch && r.plan.slab_bytes > kStaticScratchBytes) return W4A8_ERR_WORKSPACE;
+            const SplitRoute r = split_route(M, N, K, variant, splits);
+            if (entry == W4A8_ROUTE_SPLITK_STATIC && r.need > kStaticScratchBytes) return W4A8_ERR_WORKSPACE;
+            if (r.one_launch && !one_launch_covers(M, N, K)) return W4A8_ERR_SHAPE;
             return r.stream ? plan(W4A8_TILING_AUTO_TILED) : report(r.plan);
         }
         case W4A8_ROUTE_SWIGLU:
-            if (N % 64 != 0) return W4A8_ERR_SHAPE;
+            if (N % 64 != 0 || !one_launch_covers(M, N, K)) return W4A8_ERR_SHAPE;
             return report(tiled_plan(M, N, K, 0, true));
         case W4A8_ROUTE_W8A8:
         case W4A8_ROUTE_UNSIGNED:

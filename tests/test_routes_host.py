@@ -1,6 +1,7 @@
 """Which kernel the library's own choice runs, and which calls it refuses: pure functions of the shape (for the 256 compute
 units that are assumed where there is no GPU).  No kernel is launched here."""
 import ctypes
+from concurrent.futures import ThreadPoolExecutor
 
 import pytest
 
@@ -29,3 +30,59 @@ def test_route_answers_for_every_entry_and_refuses_what_the_entry_refuses():
         with pytest.raises(w4a8.W4A8Error) as e:
             w4a8_route(*bad)
         assert e.value.code == code, bad
+
+
+def _on_a_thread(call):
+    """The result of a call that may leave a HIP error behind, which the library keeps per thread."""
+    with ThreadPoolExecutor(1) as pool:
+        return pool.submit(call).result()
+
+
+def _splitk(M, N, K, variant, splits, slabs, static=False):
+    """Return code of the C entry with a workspace of `slabs` slabs (None: no workspace) at addresses that nothing reads: the
+    entry refuses before any launch, and what it does not refuse ends in -5, there being no GPU in the CPU tests."""
+    L = w4a8.lib()
+    if static:
+        return L.w4a8_gemm_tiled_splitk_static(P, P, P, P, P, M, N, K, variant, splits, None)
+    ws, size = (None, 0) if slabs is None else (P, slabs * M * N * 4)
+    return L.w4a8_gemm_tiled_splitk(P, P, P, P, P, M, N, K, variant, splits, ws, size, None)
+
+
+# Slabs of raw sums that the entry asks a workspace for (variant 0: the library's choice; else a forced tile), 1 = none.
+SLABS = [
+    (16, 5120, 13824, 0, 1), (32, 5120, 5120, 0, 1), (64, 512, 13824, 0, 3), (50, 4096, 11008, 0, 3), (44, 6244, 47168, 0, 5),
+    (61, 17674, 58112, 0, 1), (48, 24191, 55712, 0, 1),                     # no shape of the weight-streaming kernel in 8 slices
+    (128, 5120, 5120, 0, 3), (128, 5120, 13824, 0, 6), (333, 4096, 11008, 0, 5), (1024, 5120, 5120, 0, 1),
+    (140, 29215, 25248, 0, 2), (395, 20088, 22240, 0, 2),                   # long K, tiles up to the compute units
+    (289, 4258, 10528, 4, 6), (10, 179, 13952, 3, 6), (135, 5120, 5120, 12, 3), (5, 12288, 4096, 8, 2), (600, 5120, 5120, 7, 1),
+]
+
+
+@pytest.mark.parametrize("M,N,K,variant,slabs", SLABS)
+def test_splitk_asks_for_the_slabs_it_is_documented_to_ask_for(M, N, K, variant, slabs):
+    """splits = 0: the size reported, the refusal of less (and of none), the static entry's refusal of more than its array,
+    and that a forced tile is cut into as many slices; never more slices than slabs."""
+    if variant == 0:
+        assert w4a8.w4a8_gemm_tiled_workspace_bytes(M, N, K) == (slabs * M * N * 4 if slabs > 1 else 0)
+    tiling, tile, used = w4a8_route(ROUTE_SPLITK, M, N, K, variant, 0)
+    assert used <= slabs
+    if variant:
+        assert (tile, used) == (variant, slabs)
+    if slabs > 1:
+        assert _splitk(M, N, K, variant, 0, None) == -1
+        assert _splitk(M, N, K, variant, 0, slabs - 1) == -4
+    fits = slabs == 1 or slabs * M * N * 4 <= 16 << 20
+    if not fits:
+        assert _splitk(M, N, K, variant, 0, None, static=True) == -4
+    import torch
+    if not torch.cuda.is_available():  # accepted calls: only where nothing can be launched
+        assert _on_a_thread(lambda: _splitk(M, N, K, variant, 0, slabs if slabs > 1 else None)) == -5
+        assert not fits or _on_a_thread(lambda: _splitk(M, N, K, variant, 0, None, static=True)) == -5
+
+
+def test_forced_slice_counts_ask_for_what_was_forced():
+    assert _splitk(40, 1800, 10816, 0, 64, 63) == -4         # 43 slices are not empty, 64 slabs are asked for
+    assert _splitk(40, 1800, 10816, 0, 64, None, static=True) == -4
+    assert _splitk(100, 1800, 10816, 0, 64, 42) == -4        # the large-M kernel: 85 stages in 43 slices of two
+    assert w4a8_route(ROUTE_SPLITK, 100, 1800, 10816, 0, 64)[2] == 43
+    assert _splitk(64, 200000, 65536, 6, 2, 2) == -2         # sliced, and more than one launch can address
