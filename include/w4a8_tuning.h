@@ -78,6 +78,12 @@ int w4a8_gemm_tuned(const int8_t *xq, const float *s_a, const uint8_t *wp, const
 int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *tiling, int *tile, int *slices);
 
 /*
+ * How often the calling thread has worked out a plan for more than 16 tokens over tiled weights.  Plans are remembered, 64 a
+ * thread: a loop over a model's layers should make none after its first pass.
+ */
+unsigned long long w4a8_plans_made(void);
+
+/*
  * Two probes of what the chip sustains, for a benchmark to set its figures against (they are no part of the path and
  * compute nothing of use):
  * w4a8_probe_stream_read: a read-only streaming reduction over buf (device, `bytes` long, 16-byte aligned) by 8

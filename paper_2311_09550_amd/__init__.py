@@ -85,6 +85,8 @@ def lib():
         L.w4a8_add_rmsnorm_quantize.argtypes = [vp, vp, vp, ctypes.c_float, vp, vp, vp, vp, i, i, vp]
         L.w4a8_linear_tiled_swiglu_fp16.restype = i
         L.w4a8_linear_tiled_swiglu_fp16.argtypes = [vp, ctypes.c_longlong, vp, vp, vp, vp, i, i, i, vp]
+        L.w4a8_plans_made.restype = ctypes.c_ulonglong
+        L.w4a8_plans_made.argtypes = []
         L.w4a8_route.restype = i
         L.w4a8_route.argtypes = [i] * 6 + [ctypes.POINTER(i)] * 3
         L.w4a8_init.restype = i

@@ -188,9 +188,9 @@ constexpr TileCost kTileCosts[] = {
 double slab_us(int M, int N, int slices) { return 2.0 + 0.34e-6 * 4.0 * M * (double)N * slices; }
 
 // lone_slots: up to how many workgroups of the last round each has a compute unit for itself; 0: half of what the chip holds
-double tile_us(const TileCost &t, int M, int N, int stages, int slices = 1, long long lone_slots = 0) {
+double tile_us(const TileCost &t, int M, int N, int stages, int cus, int slices = 1, long long lone_slots = 0) {
     const long long n = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn) * slices;
-    const long long slots = (long long)compute_units() * t.per_cu;
+    const long long slots = (long long)cus * t.per_cu;
     const long long full = n / slots, rest = n % slots;
     double us = t.launch + t.round * (double)(full + (rest != 0)) + t.stage * (double)(full * stages);
     if (rest != 0) {
@@ -202,12 +202,12 @@ double tile_us(const TileCost &t, int M, int N, int stages, int slices = 1, long
 
 // max_id: the highest tile id the weight format has (the unsigned storage lacks the tiles above kTiledTileMax).
 int choose_tiled_tile(int M, int N, int K, int max_id = kTiledTileLast) {
-    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
     int best = 0;
     double best_us = 0;
     for (const TileCost &t : kTileCosts) {
         if (t.id > max_id) continue;
-        const double us = tile_us(t, M, N, stages);
+        const double us = tile_us(t, M, N, stages, cus);
         if (best == 0 || us < best_us) best = t.id, best_us = us;
     }
     return best;
@@ -222,13 +222,13 @@ struct RowTile {
 };
 
 RowTile choose_row_tile(int M, int N, int K) {
-    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
     RowTile best{0, 0};
     for (const TileCost &t : kTileCosts) {
         bool there = false;
         for (const int id : kRowTiles) there |= id == t.id;
         if (!there) continue;
-        const double us = tile_us(t, M, N, stages);
+        const double us = tile_us(t, M, N, stages, cus);
         if (best.id == 0 || us < best.us) best = {t.id, us};
     }
     return best;
@@ -284,7 +284,7 @@ constexpr int kMaxSlices = 8;
 constexpr int kSplitMaxM = 512;  // the large-M kernel is not split beyond: there its tiles fill the chip or the slabs cost more
 
 // max_slab: bytes of slabs allowed (0: one slice only).
-TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu) {
+TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu, int cus) {
     TiledPlan best{};
     double best_us = -1;
     const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
@@ -295,7 +295,7 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu) {
         for (int s = 1; s <= ring_slices; ++s) {
             const int per = (stages + s - 1) / s, n = (stages + per - 1) / per;
             if (n != s) continue;  // the same as fewer slices
-            double us = tile_us(t, M, N, per, s);
+            double us = tile_us(t, M, N, per, cus, s);
             if (s > 1) us += slab_us(M, N, s);
             if (best_us < 0 || us < best_us) {
                 best_us = us;
@@ -322,19 +322,43 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu) {
     return best;
 }
 
-// The same, remembered per thread: a plan is a pure function of its arguments (and of the device's compute units) and
-// costs some ten microseconds to work out, about as much as the launch it is for.
-const TiledPlan &tiled_plan(int M, int N, int K, size_t max_slab, bool swiglu) {
-    struct Entry { int M, N, K, cus; size_t max_slab; bool swiglu; TiledPlan plan; };
-    constexpr unsigned kEntries = 64;
-    static thread_local Entry entries[kEntries];
+// What the entries over tiled weights do with a shape: the plan, and what w4a8_gemm_tiled_splitk asks of its caller.
+struct Route {
+    TiledPlan plan;
+    size_t need;      // bytes of workspace, 0 when one slice is asked for
+    bool one_launch;  // refused where one launch cannot address the problem (slabs are whole M x N matrices)
+};
+enum RouteKind { kUnsliced, kSliced, kSwiglu };
+
+Route make_route(int M, int N, int K, RouteKind kind, int cus);
+
+thread_local unsigned long long plans_made = 0;
+
+// The library's own choice for more than 16 tokens, remembered per thread: it is a pure function of its arguments (and of the
+// device's compute units), and a loop over a model's layers asks for the same few again and again.  16 sets of four, the
+// oldest of a set replaced; the set comes from all bits of the shape (a sum or XOR of products with its top bits taken put
+// two linears of one layer into one place for every M).
+Route tiled_route(int M, int N, int K, RouteKind kind) {
+    struct Entry { int M, N, K, cus; RouteKind kind; Route route; };
+    constexpr unsigned kSets = 16, kWays = 4;
+    static thread_local Entry entries[kSets][kWays];
+    static thread_local unsigned char oldest[kSets];
     const int cus = compute_units();
-    const unsigned h = ((unsigned)M * 2654435761u ^ (unsigned)N * 2246822519u ^ (unsigned)K * 3266489917u ^ (unsigned)swiglu * 668265263u) >> 26;
-    Entry &e = entries[h % kEntries];
-    if (e.M != M || e.N != N || e.K != K || e.cus != cus || e.max_slab != max_slab || e.swiglu != swiglu)
-        e = Entry{M, N, K, cus, max_slab, swiglu, plan_tiled(M, N, K, max_slab, swiglu)};
-    return e.plan;
+    unsigned long long h = 0;
+    for (const unsigned v : {(unsigned)M, (unsigned)N, (unsigned)K, (unsigned)kind}) {
+        h = (h ^ v) * 0x9E3779B97F4A7C15ull;
+        h ^= h >> 29;
+    }
+    const unsigned set = (unsigned)(h >> 8) % kSets;
+    for (const Entry &e : entries[set])
+        if (e.M == M && e.N == N && e.K == K && e.cus == cus && e.kind == kind) return e.route;
+    Entry &e = entries[set][oldest[set]];
+    oldest[set] = (unsigned char)((oldest[set] + 1) % kWays);
+    ++plans_made;
+    return (e = Entry{M, N, K, cus, kind, make_route(M, N, K, kind, cus)}).route;
 }
+
+TiledPlan tiled_plan(int M, int N, int K, bool swiglu) { return tiled_route(M, N, K, swiglu ? kSwiglu : kUnsliced).plan; }
 
 // d: pointers only
 hipError_t launch_wide(DecodeArgs d, int M, int N, int K, const DecodeShape &s, bool acc_out, hipStream_t st) {
@@ -378,14 +402,14 @@ int choose_tiled_tile8(int M, int N, int K) {
     struct Factor { int id; double over_int4; };
     const Factor factors[] = {{kTiled256x256, 1.195}, {kTiled64x128, 1.333},  {kTiled64x64, 1.217},  {kTiled32x128, 1.411},
                               {kTiled128x256W8, 1.252}, {kTiled128x192, 1.173}, {kTiled64x192, 1.277}, {kTiled192x192, 1.060}};
-    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
     int best = 0;
     double best_us = 0;
     for (const Factor &f : factors)
         for (const TileCost &t : kTileCosts) {
             if (t.id != f.id) continue;
             // a compute unit with two workgroups streams twice the weights: no discount for a lone one then
-            const double us = f.over_int4 * tile_us(t, M, N, stages, 1, compute_units());
+            const double us = f.over_int4 * tile_us(t, M, N, stages, cus, 1, cus);
             if (best == 0 || us < best_us) best = t.id, best_us = us;
         }
     return best;
@@ -399,7 +423,7 @@ int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
         // one weight array for every M: the weight-streaming kernels up to M = 16 and, where all of K fits a wave's
         // registers, up to M = 64; the large-M kernel above
         if (M > 16) {
-            const TiledPlan t = tiled_plan(M, N, K, 0, false);
+            const TiledPlan t = tiled_plan(M, N, K, false);
             pl->decode = t.shape;
             pl->prefill_tile = t.tile;
             pl->tiling = t.wide ? W4A8_TILING_DECODE_RESIDENT : W4A8_TILING_PREFILL_TILED;
@@ -588,7 +612,7 @@ int w4a8_gemm_tiled_swiglu(const int8_t *xq, const float *s_a, const uint8_t *wt
     if (misaligned(xq) || misaligned(wt_gu) || misaligned(h_fp16) || misaligned(s_w_gu)) return W4A8_ERR_ALIGN;
     if (!one_launch_covers(M, N, K)) return W4A8_ERR_SHAPE;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const TiledPlan pl = tiled_plan(M, N, K, 0, true);
+    const TiledPlan pl = tiled_plan(M, N, K, true);
     if (pl.wide) {
         DecodeArgs d{};
         d.xq = xq; d.s_a = s_a; d.wp = wt_gu; d.s_w = s_w_gu; d.out = h_fp16;
@@ -644,14 +668,13 @@ TileShape slab_rule_tile(int M, int N, bool long_k, int cus) {
     return best;
 }
 
-SlabRule slab_rule(int M, int N, int K, int variant) {
-    if (variant == 0 && M <= 16) return {1, false};
+SlabRule slab_rule(int M, int N, int K, int variant, int cus) {
     if (variant == 0 && M <= kResidentMaxM)
         for (int s = 1; s <= kMaxSlices; ++s) {
             DecodeShape t{};
             if (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &t, s, true)) return {s, false};
         }
-    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
+    const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
     const bool long_k = stages >= 64;
     if (M > kSplitMaxM) return {1, true};
     const TileShape t = variant ? kForcedTiles[variant] : slab_rule_tile(M, N, long_k, cus);
@@ -665,39 +688,38 @@ SlabRule slab_rule(int M, int N, int K, int variant) {
     return {(stages + per - 1) / per, true};  // no empty slice
 }
 
-// What w4a8_gemm_tiled_splitk does with a shape: the plan, or token generation (up to 16 tokens, nothing forced: the entry
-// without slices); and what it asks for.
-struct SplitRoute {
+Route make_route(int M, int N, int K, RouteKind kind, int cus) {
+    Route r{};
+    if (kind == kSliced) {
+        const SlabRule rule = slab_rule(M, N, K, 0, cus);
+        r.need = rule.slices > 1 ? rule.slices * ((size_t)M * (size_t)N * sizeof(int32_t)) : 0;
+        r.one_launch = rule.ring && rule.slices > 1;
+    }
+    r.plan = plan_tiled(M, N, K, r.need, kind == kSwiglu, cus);
+    return r;
+}
+
+// What w4a8_gemm_tiled_splitk does with a shape and a forced tile or slice count, if any.  stream: token generation (up to 16
+// tokens, nothing forced), the entry without slices.
+struct SplitRoute : Route {
     bool stream;
-    TiledPlan plan;
-    size_t need;      // bytes of workspace, 0 when one slice is asked for
-    bool one_launch;  // refused where one launch cannot address the problem (slabs are whole M x N matrices)
 };
 
 SplitRoute split_route(int M, int N, int K, int variant, int splits) {
+    if (variant == 0 && splits == 0) return M <= 16 ? SplitRoute{{}, true} : SplitRoute{tiled_route(M, N, K, kSliced), false};
     SplitRoute r{};
     const size_t slab = (size_t)M * (size_t)N * sizeof(int32_t);
     const int stages = (K + kTiledBlockK - 1) / kTiledBlockK;
     TiledPlan &pl = r.plan;
-    if (splits == 0) {
-        const SlabRule rule = slab_rule(M, N, K, variant);
-        r.need = rule.slices > 1 ? rule.slices * slab : 0;
-        r.one_launch = rule.ring && rule.slices > 1;
-        r.stream = variant == 0 && M <= 16;
-        if (r.stream) return r;
-        if (variant == 0) {
-            pl = tiled_plan(M, N, K, r.need, false);
-            return r;
-        }
-        splits = rule.slices;
-    } else if (variant == 0 && M > 16 && M <= kResidentMaxM && splits <= stages &&
-               resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl.shape, splits, true)) {
+    if (variant == 0 && M > 16 && M <= kResidentMaxM && splits <= stages &&
+        resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl.shape, splits, true)) {
         // a forced count without a tile: slices of the weight-streaming kernel where it has a shape for them
         pl.wide = true;
         pl.splits = pl.shape.k_slices;
         r.need = splits > 1 ? splits * slab : 0;
         return r;
     }
+    if (splits == 0) splits = slab_rule(M, N, K, variant, compute_units()).slices;
     if (splits > stages) splits = stages;
     pl.tile = variant ? variant : choose_tiled_tile(M, N, K);
     pl.stages_per_split = (stages + splits - 1) / splits;
@@ -881,7 +903,7 @@ int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *til
         }
         case W4A8_ROUTE_SWIGLU:
             if (N % 64 != 0 || !one_launch_covers(M, N, K)) return W4A8_ERR_SHAPE;
-            return report(tiled_plan(M, N, K, 0, true));
+            return report(tiled_plan(M, N, K, true));
         case W4A8_ROUTE_W8A8:
         case W4A8_ROUTE_UNSIGNED:
             *tiling = W4A8_TILING_PREFILL_TILED;
@@ -890,6 +912,8 @@ int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *til
         default: return W4A8_ERR_ARG;
     }
 }
+
+unsigned long long w4a8_plans_made(void) { return plans_made; }
 
 int w4a8_init(void) {
     void *ws = nullptr;

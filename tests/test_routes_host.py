@@ -86,3 +86,18 @@ def test_forced_slice_counts_ask_for_what_was_forced():
     assert _splitk(100, 1800, 10816, 0, 64, 42) == -4        # the large-M kernel: 85 stages in 43 slices of two
     assert w4a8_route(ROUTE_SPLITK, 100, 1800, 10816, 0, 64)[2] == 43
     assert _splitk(64, 200000, 65536, 6, 2, 2) == -2         # sliced, and more than one launch can address
+
+
+@pytest.mark.parametrize("model", ["7b", "13b", "70b"])
+def test_plans_of_a_models_layers_are_remembered(model):
+    """One pass over the linears of a layer makes the plans, the second none, for every token count of the sizes in use."""
+    from paper_2311_09550_amd.synth import LLAMA_SHAPES
+    made = w4a8.lib().w4a8_plans_made
+    for M in [17, 24, 32, 33, 48, 50, 64, 100, 128, 200, 256, 333, 512, 700, 1024, 2048]:
+        for again in (False, True):
+            before = made()
+            for name, (N, K) in LLAMA_SHAPES[model].items():
+                w4a8_route(ROUTE_SPLITK, M, N, K)
+                if name == "gate_up":
+                    w4a8_route(ROUTE_SWIGLU, M, N, K)
+            assert not again or made() == before, M
