@@ -200,18 +200,36 @@ double tile_us(const TileCost &t, int M, int N, int stages, int cus, int slices 
     return us;
 }
 
-// max_id: the highest tile id the weight format has (the unsigned storage lacks the tiles above kTiledTileMax).
-int choose_tiled_tile(int M, int N, int K, int max_id = kTiledTileLast) {
+template <size_t TILES>
+int cheapest_tile(const TileCost (&costs)[TILES], int M, int N, int K) {
     const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
     int best = 0;
     double best_us = 0;
-    for (const TileCost &t : kTileCosts) {
-        if (t.id > max_id) continue;
+    for (const TileCost &t : costs) {
         const double us = tile_us(t, M, N, stages, cus);
         if (best == 0 || us < best_us) best = t.id, best_us = us;
     }
     return best;
 }
+
+int choose_tiled_tile(int M, int N, int K) { return cheapest_tile(kTileCosts, M, N, K); }
+
+// The unsigned storage has prices of its own: it lacks the tiles above kTiledTileMax, converts a weight fragment in 14
+// vector operations instead of 6, which the taller tiles spread over more MFMAs, and runs 64 x 128 on 4 waves.  Fits over 428
+// shapes (260 random, M 1 .. 2048, and the models' linears; weights cold) within 3 to 6 %; choosing by them costs 0.6 % on
+// average over always taking the fastest of the eight tiles, the signed prices 3.0 %, rounds times area over an efficiency
+// 4.0 %.  (N = K = 5120, M = 1024: 128 x 256 at 39.8 us, 64 x 128 at 47.6; N = 4096, K = 11008, M = 1024: 128 x 128 at 58.7, 64 x 128
+// at 67.7.)  The second 256 x 256 and 128 x 160 would gain nothing.
+constexpr TileCost kUnsignedTileCosts[] = {
+    {kTiled256x256, 256, 256, 1, 1.28f, 5.73f, 1.604f, 1.096f, 0.287f, 0.000f},
+    {kTiled128x256, 128, 256, 2, 1.96f, 4.34f, 1.607f, 1.283f, 0.308f, 0.503f},
+    {kTiled128x128, 128, 128, 2, 2.87f, 2.35f, 1.046f, 0.882f, 0.129f, 0.354f},
+    {kTiled64x128, 64, 128, 2, 3.32f, 1.21f, 0.681f, 0.621f, 0.090f, 0.175f},
+    {kTiled64x64, 64, 64, 3, 2.48f, 1.44f, 0.555f, 0.305f, 0.272f, 0.039f},
+    {kTiled32x128, 32, 128, 3, 2.95f, 1.19f, 0.546f, 0.353f, 0.226f, 0.078f},
+};
+
+int choose_unsigned_tile(int M, int N, int K) { return cheapest_tile(kUnsignedTileCosts, M, N, K); }
 
 // The same kernel over row-major weights.  Its stages take longer, a weight stage being half a cache line of every
 // channel: 1.2 times the prices above up to 64 tokens, 1.1 at large M, much the same for every tile.  So the prices serve
@@ -907,7 +925,7 @@ int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *til
         case W4A8_ROUTE_W8A8:
         case W4A8_ROUTE_UNSIGNED:
             *tiling = W4A8_TILING_PREFILL_TILED;
-            *tile = entry == W4A8_ROUTE_W8A8 ? choose_tiled_tile8(M, N, K) : choose_tiled_tile(M, N, K, kTiledTileMax);
+            *tile = entry == W4A8_ROUTE_W8A8 ? choose_tiled_tile8(M, N, K) : choose_unsigned_tile(M, N, K);
             return W4A8_OK;
         default: return W4A8_ERR_ARG;
     }
@@ -990,7 +1008,7 @@ static int gemm_tiled_variant(const int8_t *xq, const float *s_a, const uint8_t 
     a.out = out_fp16; a.acc_out = acc_i32;
     a.M = M; a.N = N; a.K = K; a.ldc = N;
     const int tile = variant ? variant
-                             : wfmt == 8 ? choose_tiled_tile8(M, N, K) : choose_tiled_tile(M, N, K, kTiledTileMax);
+                             : wfmt == 8 ? choose_tiled_tile8(M, N, K) : choose_unsigned_tile(M, N, K);
     return launched(launch_gemm_prefill_tiled(a, want_acc, tile, static_cast<hipStream_t>(stream), wfmt));
 }
 

@@ -101,3 +101,11 @@ def test_plans_of_a_models_layers_are_remembered(model):
                 if name == "gate_up":
                     w4a8_route(ROUTE_SWIGLU, M, N, K)
             assert not again or made() == before, M
+
+
+def test_unsigned_storage_is_priced_for_its_own_tiles():
+    """It has eight tiles, runs 64 x 128 on four waves and converts at twice the cost: the taller tiles pay earlier than over
+    signed weights, 128 x 128 among them."""
+    for (M, N, K), tile in {(1024, 5120, 5120): 3, (1024, 4096, 11008): 5, (256, 15360, 5120): 5, (64, 57344, 8192): 6,
+                            (812, 1168, 9920): 7, (512, 27648, 5120): 1, (16, 27648, 5120): 8}.items():
+        assert w4a8_route(ROUTE_UNSIGNED, M, N, K) == (TILING_PREFILL_TILED, tile, 1), (M, N, K)
