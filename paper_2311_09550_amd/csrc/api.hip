@@ -234,41 +234,37 @@ int choose_unsigned_tile(int M, int N, int K) { return cheapest_tile(kUnsignedTi
 // The same kernel over row-major weights.  Its stages take longer, a weight stage being half a cache line of every
 // channel: 1.2 times the prices above up to 64 tokens, 1.1 at large M, much the same for every tile.  So the prices serve
 // to choose among its tiles as they are (within 0.6 % of always taking the fastest on 200 random shapes).
-struct RowTile {
-    int id;
-    double us;
-};
-
-RowTile choose_row_tile(int M, int N, int K) {
+int choose_row_tile(int M, int N, int K) {
     const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
-    RowTile best{0, 0};
+    int best = 0;
+    double best_us = 0;
     for (const TileCost &t : kTileCosts) {
         bool there = false;
         for (const int id : kRowTiles) there |= id == t.id;
         if (!there) continue;
         const double us = tile_us(t, M, N, stages, cus);
-        if (best.id == 0 || us < best.us) best = {t.id, us};
+        if (best == 0 || us < best_us) best = t.id, best_us = us;
     }
     return best;
 }
 
-// Over row-major weights the weight-streaming kernels are priced against the tiles up to 32 tokens; beyond, a tile is the
-// faster one on every shape (1.05 to 2.3 times, 80 random shapes with 33 to 64 tokens; within 2 % where they are level).
-// The prices, in microseconds, are least-squares fits over 100 random shapes: the persistent kernel's within 5 to 6 %; the
-// general one (more than 16 tokens and K > 8192; up to 16 tokens it is always taken where K > 16384) walks all of K in every workgroup, 1.8 us per 1000 k and round of 8192
-// channels.  Choosing by them costs 0.2 % (up to 16 tokens) and 0.7 % on average over always choosing the faster; the
-// streaming kernels alone cost 1.3 % and 6.3 %.  (N = 24896, K = 3296, M = 18: 15.7 us streaming, 11.6 tiled; N = 3200,
-// K = 8160, M = 9: 7.3 and 20.1.)
-constexpr int kRowDecodeMaxM = 32;
-constexpr double kRowOverTiled = 1.2;
-
-double row_decode_us(int M, int N, int K, bool resident) {
-    if (!resident) return 1.8e-3 * K * ((N + 8191) / 8192);
-    const int rows = ((N + compute_units() - 1) / compute_units() + 15) / 16 * 16;
-    const double chunks = rows / 16, w_kb = rows * (K / 2048.0), x_kb = M * (K / 1024.0);
-    const int steps = ((K + 127) / 128 + (M <= 16 ? 7 : 15)) / (M <= 16 ? 8 : 16);
-    return M <= 16 ? 2.696 + 0.2546 * chunks + 0.0505 * w_kb + 0.0177 * x_kb + 0.0003 * steps * chunks
-                   : 2.971 + 0.6039 * chunks + 0.0316 * w_kb + 0.0263 * x_kb + 0.0730 * steps * chunks;
+// Over row-major weights: a weight-streaming kernel, or the tiles.  Measured on 900 shapes (M 1 .. 64, 730 of them random),
+// every byte of the weights cold, as a model's layers find them; a rule of sizes, since where K is no multiple of 128 (rows
+// that start inside a cache line) no price of the tiles comes nearer than 30 %:
+//   up to 16 tokens streaming is the faster one on 94 % of the shapes, and taking it always costs 0.8 % on average (prices
+//   that took the tiles for wide N cost 3.7 %: N = 27648, K = 5120, M = 1: 18.8 us tiled, 16.8 streaming; 57344 x 8192: 51 and
+//   41; only copies that stay in the memory-side cache gain from the tiles, 14.2 against 16.5);
+//   17 to 32 tokens, the persistent kernel where it has a shape (K <= 8192): 1.6 %, the prices 3.4 % (N = 33061, K = 5376,
+//   M = 17: 24.9 us and 31.8 tiled; N = 27648, K = 5120, M = 32: 22.2 and 19.9);
+//   else the general kernel, whose workgroups walk all of K once for every 32 channels of a compute unit: one round up to 32
+//   channels per compute unit, two beyond (N = 8478, K = 15648, M = 47: 86.7 us and 40.2 tiled).  In one round it is the faster
+//   one up to 32 tokens (N = 5120, K = 13824, M = 32: 26.9 and 36.0), with more only on a short K (N = 3746, M = 59: K = 1824 8.0
+//   and 9.1; N = 5948, K = 7488, M = 36: 22.3 and 19.7).  0.1 and 0.3 %.
+bool row_major_streams(int M, int N, int K, bool persistent) {
+    constexpr int kShortK = 2048;
+    if (M <= 16 || persistent) return true;
+    if (N > 32 * compute_units()) return false;
+    return M <= 32 || (M <= kDecodeMaxM && K <= kShortK);
 }
 
 // Whether one launch of the large-M kernel reaches every byte of both operands (32-bit byte offsets)
@@ -456,12 +452,10 @@ int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
     if (pl->tiling == W4A8_TILING_DECODE_RESIDENT_TILED) pl->tiling = W4A8_TILING_DECODE_RESIDENT;
     if (pl->tiling == W4A8_TILING_DECODE_STREAM_TILED) pl->tiling = W4A8_TILING_DECODE_STREAM;
     if (tiling == W4A8_TILING_AUTO) {
-        const bool resident = M <= kRowDecodeMaxM && resident_shape(M, N, K, 0, 0, 0, false, -1, false, &pl->decode);
-        const bool priced = M <= kRowDecodeMaxM && (resident || M > 16);
-        if (M > kRowDecodeMaxM || (priced && row_decode_us(M, N, K, resident) > kRowOverTiled * choose_row_tile(M, N, K).us))
-            pl->tiling = W4A8_TILING_PREFILL;
-        else
-            pl->tiling = resident ? W4A8_TILING_DECODE_RESIDENT : W4A8_TILING_DECODE_STREAM;
+        const bool resident = M <= 32 && resident_shape(M, N, K, 0, 0, 0, false, -1, false, &pl->decode);
+        pl->tiling = !row_major_streams(M, N, K, resident) ? W4A8_TILING_PREFILL
+                     : resident                            ? W4A8_TILING_DECODE_RESIDENT
+                                                           : W4A8_TILING_DECODE_STREAM;
     }
     if (pl->tiling == W4A8_TILING_DECODE_RESIDENT) {
         if (M > kResidentMaxM) return W4A8_ERR_ARG;
@@ -495,7 +489,7 @@ int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
         pl->prefill_tile = variant ? variant : choose_tiled_tile(M, N, K);
     } else {
         if (variant < 0 || variant > kPrefillTileMax) return W4A8_ERR_ARG;
-        pl->prefill_tile = variant ? kRowTiles[variant - 1] : choose_row_tile(M, N, K).id;
+        pl->prefill_tile = variant ? kRowTiles[variant - 1] : choose_row_tile(M, N, K);
     }
     return W4A8_OK;
 }

@@ -138,10 +138,10 @@ def test_prefill_tiling_ragged_shapes(gpu, oracle, M, N, K, tile):
 
 @pytest.mark.parametrize("M,N,K", [(451, 20579, 288), (225, 17008, 544), (129, 19635, 1056),   # 192x256, 128x192, 64x256
                                    (32, 1024, 544), (33, 1024, 544), (17, 1216, 96), (16, 29000, 160), (17, 29000, 160),
-                                   (20, 9000, 8224), (32, 700, 8224)])
+                                   (20, 9000, 8224), (32, 700, 8224), (33, 8193, 96), (64, 8192, 2048), (64, 8191, 2080)])
 def test_row_major_routes(gpu, M, N, K):
     """The library's own choice over row-major weights: the output tiles that cannot be forced, and both sides of the lines
-    between the weight-streaming kernels and the tiles (token count, price, K beyond the persistent kernel's registers)."""
+    between the weight-streaming kernels and the tiles (token count, channels, K beyond the persistent kernel's registers)."""
     xq, wq, s_a, s_w = _codes(M, N, K, tag=43)
     # exact in fp32: |sum| <= 128 * 8 * K < 2^24
     acc_ref = (xq.astype(np.float32) @ wq.astype(np.float32).T).astype(np.int32)

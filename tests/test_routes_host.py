@@ -109,3 +109,16 @@ def test_unsigned_storage_is_priced_for_its_own_tiles():
     for (M, N, K), tile in {(1024, 5120, 5120): 3, (1024, 4096, 11008): 5, (256, 15360, 5120): 5, (64, 57344, 8192): 6,
                             (812, 1168, 9920): 7, (512, 27648, 5120): 1, (16, 27648, 5120): 8}.items():
         assert w4a8_route(ROUTE_UNSIGNED, M, N, K) == (TILING_PREFILL_TILED, tile, 1), (M, N, K)
+
+
+@pytest.mark.parametrize("M,N,K,tiling", [
+    (1, 27648, 5120, TILING_DECODE_RESIDENT), (16, 27648, 5120, TILING_DECODE_RESIDENT), (1, 57344, 8192, TILING_DECODE_RESIDENT),
+    (4, 22016, 4096, TILING_DECODE_RESIDENT), (16, 32000, 4096, TILING_DECODE_RESIDENT), (16, 60829, 16384, TILING_DECODE_RESIDENT),
+    (16, 8192, 16416, TILING_DECODE_STREAM), (17, 33061, 5376, TILING_DECODE_RESIDENT), (32, 57344, 8192, TILING_DECODE_RESIDENT),
+    (17, 8192, 8224, TILING_DECODE_STREAM), (17, 8193, 8224, TILING_PREFILL), (32, 5120, 13824, TILING_DECODE_STREAM),
+    (33, 8192, 2048, TILING_DECODE_STREAM), (33, 8193, 2048, TILING_PREFILL), (64, 8192, 2080, TILING_PREFILL),
+    (64, 3746, 1824, TILING_DECODE_STREAM), (65, 3746, 1824, TILING_PREFILL),
+])
+def test_row_major_weights_are_streamed_where_that_is_the_faster_form_on_cold_weights(M, N, K, tiling):
+    """Both sides of every line of the rule (256 compute units)."""
+    assert w4a8_route(ROUTE_GEMM, M, N, K)[0] == tiling
