@@ -273,8 +273,8 @@ bool one_launch_covers(int M, int N, int K) {
 }
 
 // How a GEMM over tiled int4 weights with more than 16 tokens is run: by the weight-streaming kernel with per-wave
-// staging, K cut into slices, or by the large-M kernel, K cut into slices.  Both are priced
-// and the cheaper one is taken.
+// staging, K cut into slices, or by the large-M kernel, K cut into slices.  Both are priced and the cheaper one is taken, a
+// tile only where its price is 15 % below that of weight streaming.
 struct TiledPlan {
     bool wide;          // weight-streaming kernel, else the large-M kernel
     DecodeShape shape;  // wide: its shape
@@ -283,8 +283,16 @@ struct TiledPlan {
 };
 
 // Price of the weight-streaming kernel in microseconds: what every compute unit brings in (the activations and its
-// weights), a fixed part per chunk of 16 channels, more
-// of it where a wave has more than 8 k steps, and the slabs.  Fitted like the tiles' prices, within 5 %.
+// weights), a fixed part per chunk of 16 channels, more of it where a wave has more than 8 k steps, and the slabs.  Fitted
+// like the tiles' prices, within 5 %.
+// Both prices are off by more than that where the tiles' are too low (K no multiple of 128, wide N), and streaming is the form
+// that such shapes hurt less, so near ties are its own.  On 522 shapes with 17 to 64 tokens (weights cold) that loses 0.5 %
+// on average over always taking the faster with one slice and 1.7 % with several, 1.1 and 2.1 % without the preference; 5
+// shapes are more than 3 % slower than always streaming, 34 without it.  The same from 10 to 15 %, no better beyond.
+// (M = 64: N = 27648, K = 5120 17.9 us streaming, 19.8 tiled; N = 22016, K = 4096 14.0 and 15.3; N = 8544, K = 1824, M = 63 6.6
+// and 7.5.)
+constexpr double kStreamingPreferred = 0.85;
+
 double wide_us(const DecodeShape &s, int M, int N, int K) {
     const double steps = ((K + 127) / 128 + s.k_slices - 1) / s.k_slices;
     const double chunks = (s.rows_per_wg + 15) / 16, mt = (M + 15) / 16, long_walk = s.x_steps > 8 ? s.x_steps - 8 : 0;
@@ -324,7 +332,7 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu, int cus)
             DecodeShape shape{};
             shape.swiglu = swiglu;
             if (!resident_shape(M, N, K, 0, 0, 0, false, -1, true, &shape, s, true) || shape.k_slices != s) continue;
-            const double us = wide_us(shape, M, N, K);
+            const double us = kStreamingPreferred * wide_us(shape, M, N, K);
             if (us < best_us) {
                 best_us = us;
                 best.wide = true;
@@ -434,8 +442,8 @@ int choose_tiled_tile8(int M, int N, int K) {
 int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
     pl->tiling = tiling;
     if (tiling == W4A8_TILING_AUTO_TILED) {
-        // one weight array for every M: the weight-streaming kernels up to M = 16 and, where all of K fits a wave's
-        // registers, up to M = 64; the large-M kernel above
+        // one weight array for every M: the weight-streaming kernels up to M = 16; up to M = 64, where all of K fits a
+        // wave's registers, these or the large-M kernel, by price; the large-M kernel above
         if (M > 16) {
             const TiledPlan t = tiled_plan(M, N, K, false);
             pl->decode = t.shape;
@@ -443,10 +451,10 @@ int choose_plan(int M, int N, int K, int tiling, int variant, Plan *pl) {
             pl->tiling = t.wide ? W4A8_TILING_DECODE_RESIDENT : W4A8_TILING_PREFILL_TILED;
             return W4A8_OK;
         }
-            pl->tiling = (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl->decode, 1, true) ||
-                          resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl->decode))
-                             ? W4A8_TILING_DECODE_RESIDENT_TILED
-                             : W4A8_TILING_DECODE_STREAM_TILED;
+        pl->tiling = (resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl->decode, 1, true) ||
+                      resident_shape(M, N, K, 0, 0, 0, false, -1, true, &pl->decode))
+                         ? W4A8_TILING_DECODE_RESIDENT_TILED
+                         : W4A8_TILING_DECODE_STREAM_TILED;
     }
     const bool decode_tiled = pl->tiling == W4A8_TILING_DECODE_RESIDENT_TILED || pl->tiling == W4A8_TILING_DECODE_STREAM_TILED;
     if (pl->tiling == W4A8_TILING_DECODE_RESIDENT_TILED) pl->tiling = W4A8_TILING_DECODE_RESIDENT;

@@ -122,3 +122,16 @@ def test_unsigned_storage_is_priced_for_its_own_tiles():
 def test_row_major_weights_are_streamed_where_that_is_the_faster_form_on_cold_weights(M, N, K, tiling):
     """Both sides of every line of the rule (256 compute units)."""
     assert w4a8_route(ROUTE_GEMM, M, N, K)[0] == tiling
+
+
+def test_near_ties_go_to_weight_streaming():
+    """Shapes at which the tiles are priced a few per cent below weight streaming and measured slower; and where they are the
+    faster form all the same, or the only one with one slice."""
+    for M, N, K in [(64, 27648, 5120), (64, 22016, 4096), (63, 8544, 1824), (61, 8778, 1888), (50, 33682, 2848), (31, 59552, 5888),
+                    (54, 35603, 3872)]:
+        for entry in (ROUTE_GEMM_TILED, ROUTE_SPLITK):
+            assert w4a8_route(entry, M, N, K) == (TILING_DECODE_RESIDENT_TILED, 0, 1), (M, N, K)
+    assert w4a8_route(ROUTE_SWIGLU, 64, 27648, 5120) == (TILING_DECODE_RESIDENT_TILED, 0, 1)
+    assert w4a8_route(ROUTE_SPLITK, 62, 8219, 14976) == (TILING_DECODE_RESIDENT_TILED, 0, 3)
+    for M, N, K in [(63, 55468, 3520), (52, 47417, 1344), (64, 57344, 8192), (17, 1216, 16416)]:
+        assert w4a8_route(ROUTE_GEMM_TILED, M, N, K)[0] == TILING_PREFILL_TILED, (M, N, K)
