@@ -146,6 +146,9 @@ def test_row_major_routes(gpu, M, N, K):
     # exact in fp32: |sum| <= 128 * 8 * K < 2^24
     acc_ref = (xq.astype(np.float32) @ wq.astype(np.float32).T).astype(np.int32)
     t = gpu
+    expect = {451: (PREFILL, 19), 225: (PREFILL, 15), 129: (PREFILL, 13), 16: (RESIDENT, 0), 17: (RESIDENT, 0), 20: (PREFILL, 8)}
+    if M in expect:
+        assert w4a8.w4a8_route(w4a8.ROUTE_GEMM, M, N, K)[:2] == expect[M]
     wp = ((wq[:, 0::2] & 15) | ((wq[:, 1::2] & 15) << 4)).astype(np.uint8)
     dx, dw, dsa, dsw = (t.from_numpy(a).cuda() for a in (xq, wp, s_a, s_w))
     assert_equal_bits(w4a8.w4a8_gemm_acc_i32(dx, dw).cpu().numpy(), acc_ref, "acc")

@@ -24,9 +24,11 @@ def _linear(t, M, wt, s_w, x, xq, s_a, out, how, ws):
 
 
 # (M, N, K, entry): whole-row staging, fused quantiser, per-wave windows, K slices of the weight-streaming kernel (slabs in a
-# workspace and in the static array), K slices of the large-M kernel, the two-phase large-M launch
+# workspace and in the static array), K slices of the large-M kernel, its 64 x 64 tile with one slice, and its 64 x 192 tile, one
+# of those only the library chooses, with one slice and with four
 CASES = [(3, 520, 2080, "tiled"), (2, 520, 2080, "fused"), (16, 1000, 5120, "tiled"), (48, 300, 13824, "splitk"),
-         (48, 300, 13824, "static"), (130, 520, 8192, "splitk"), (130, 520, 8192, "static"), (300, 17000, 160, "tiled")]
+         (48, 300, 13824, "static"), (130, 520, 8192, "splitk"), (130, 520, 8192, "static"), (300, 17000, 160, "tiled"),
+         (984, 2891, 576, "tiled"), (460, 1315, 6048, "splitk"), (460, 1315, 6048, "static")]
 
 
 @pytest.mark.parametrize("M,N,K,how", CASES)
@@ -67,10 +69,11 @@ def test_graph_replays_match_eager(gpu, oracle, M, N, K, how):
             t.cuda.synchronize()
             assert bool((out.view(t.int16) == eager[i].view(t.int16)).all()), f"replay {rnd}.{i} of {how} M={M} differs from eager"
     # and the eager result is the oracle's
-    xq_o, s_a_o = oracle.quantize_act(xs[3].cpu().numpy())
+    rows = list(range(M)) if M <= 300 else [0, M // 2, M - 1]
+    xq_o, s_a_o = oracle.quantize_act(xs[3].cpu().numpy()[rows])
     wq_o, s_w_o = oracle.quantize_weights_rtn(w.cpu().numpy())
     acc_o, y32, _ = oracle.gemm(xq_o, s_a_o, oracle.pack_w4(wq_o), s_w_o)
-    got = eager[3].cpu().numpy().astype(np.float64)
+    got = eager[3].cpu().numpy()[rows].astype(np.float64)
     y = y32.astype(np.float64)
     assert np.all(np.abs(got - y) <= np.maximum(2.0 ** -10 * np.abs(y), 2.0 ** -24))
 

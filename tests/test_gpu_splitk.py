@@ -62,6 +62,36 @@ def test_library_choice_on_llama13b_shapes(gpu, oracle, M, N, K):
     assert_fp16_close(a.cpu().numpy()[rows], y32, acc_o, f"library split rows M={M} N={N} K={K}")
 
 
+# one ragged shape for every output tile that the library cuts K with, N a multiple of 4 (16-byte stores of raw sums) and not;
+# the last slice is a stage short in some, and the last stage of K partly past the end in all
+@pytest.mark.parametrize("M,N,K,tile,slices", [
+    (490, 869, 4512, 6, 3), (467, 852, 4512, 6, 3), (106, 307, 3424, 7, 2), (104, 312, 3104, 7, 2), (264, 841, 6336, 8, 4),
+    (344, 1128, 4544, 8, 3), (473, 3075, 10080, 12, 4), (452, 3084, 9664, 12, 4), (392, 1731, 6592, 13, 4), (407, 1736, 6560, 13, 4),
+    (510, 2565, 8096, 15, 4), (462, 2564, 8160, 15, 4), (508, 1286, 6080, 16, 4), (451, 1288, 6208, 16, 4), (400, 6250, 11104, 17, 3),
+    (394, 6196, 11072, 17, 3), (334, 5418, 11200, 20, 4), (275, 4412, 13344, 20, 5)])
+def test_librarys_slices_of_every_tile(gpu, oracle, M, N, K, tile, slices):
+    """splits = 0, the workspace of the size asked for and the static array where the slabs fit it: bit for bit the unsliced
+    32 x 128 tile, sampled rows against the oracle."""
+    t = gpu
+    assert w4a8.w4a8_route(w4a8.ROUTE_SPLITK, M, N, K) == (w4a8.TILING_PREFILL_TILED, tile, slices)
+    xq, wq, s_a, s_w = synth.uniform_codes(M, N, K, config_id=84)
+    wp = oracle.pack_w4(wq)
+    need = w4a8.w4a8_gemm_tiled_workspace_bytes(M, N, K)
+    ws = t.empty((need,), dtype=t.uint8, device="cuda")
+    dxq, dsa, dsw = t.from_numpy(xq).cuda(), t.from_numpy(s_a).cuda(), t.from_numpy(s_w).cuda()
+    wt = w4a8.w4a8_tile_weights(t.from_numpy(wp).cuda())
+    ref = w4a8.w4a8_gemm_tuned(dxq, dsa, wt, dsw, w4a8.TILING_PREFILL_TILED, 8, N=N)
+    out = w4a8.w4a8_gemm_tiled_splitk(dxq, dsa, wt, dsw, ws=ws)
+    what = f"sliced tile {tile} M={M} N={N} K={K}"
+    assert_equal_bits(out.cpu().numpy().view(np.uint16), ref.cpu().numpy().view(np.uint16), what)
+    if need <= 16 << 20:
+        static = w4a8.w4a8_gemm_tiled_splitk_static(dxq, dsa, wt, dsw, t.empty_like(out))
+        assert_equal_bits(static.cpu().numpy().view(np.uint16), ref.cpu().numpy().view(np.uint16), what + " static")
+    rows = [0, M // 2, M - 1]
+    acc_o, y32, _ = oracle.gemm(xq[rows], s_a[rows], wp, s_w)
+    assert_fp16_close(out.cpu().numpy()[rows], y32, acc_o, what)
+
+
 def test_workspace_too_small_is_refused(gpu, oracle):
     d, _, _ = _inputs(gpu, oracle, 64, 256, 1024, 82)
     ws = gpu.empty((2 * 64 * 256 * 4 - 16,), dtype=gpu.uint8, device="cuda")

@@ -9,7 +9,7 @@ import pytest
 import paper_2311_09550_amd as w4a8
 from paper_2311_09550_amd import synth
 
-from parity import assert_equal_bits
+from parity import assert_equal_bits, assert_fp16_close
 
 pytestmark = pytest.mark.gpu
 
@@ -51,13 +51,37 @@ def test_swiglu_epilogue_matches_two_calls_and_oracle(gpu, oracle, M, I, K):
     assert np.all(np.abs(gu - y) <= np.maximum(2.0 ** -10 * np.abs(y), 2.0 ** -24))
 
 
-def test_swiglu_two_phase_launch_at_the_13b_shape(gpu, oracle):
-    """M = 1024, I = 13824: 256 x 256 tiles in whole rounds plus 256 x 192 tiles for the columns left over, the second
-    launch writing behind the first one's values of h."""
+def test_swiglu_13b_channels_at_1024_tokens(gpu, oracle):
+    """M = 1024, I = 13824 with a short K: 108 column tiles of 256 channels, the last round of workgroups partly filled."""
     t = gpu
     M, I, K = 1024, 13824, 256
     x, w, gate_up, h_two, h = _case(t, oracle, M, I, K, 92)
-    assert_equal_bits(h.cpu().numpy().view(np.uint16), h_two.cpu().numpy().view(np.uint16), "fused vs two calls, two phases")
+    assert_equal_bits(h.cpu().numpy().view(np.uint16), h_two.cpu().numpy().view(np.uint16), "fused vs two calls")
+
+
+# one ragged shape for every output tile that the library gives the fused form
+@pytest.mark.parametrize("M,I,K,tile", [(969, 7008, 672, 1), (903, 8160, 192, 3), (776, 1024, 288, 6), (86, 512, 32, 7),
+                                        (834, 896, 288, 8), (1089, 2944, 416, 12), (982, 1568, 928, 13), (970, 5664, 288, 14),
+                                        (1093, 1888, 544, 15), (966, 1472, 544, 16), (975, 4128, 416, 17), (1036, 5440, 544, 18),
+                                        (975, 5152, 288, 19), (1089, 3712, 288, 20)])
+def test_swiglu_epilogue_of_every_tile(gpu, oracle, M, I, K, tile):
+    """Bit for bit against the plain GEMM's 32 x 128 tile over the same interleaved channels and silu_mul; sampled rows of
+    that GEMM against the oracle."""
+    t = gpu
+    assert w4a8.w4a8_route(w4a8.ROUTE_SWIGLU, M, 2 * I, K) == (w4a8.TILING_PREFILL_TILED, tile, 1)
+    xq, wq, s_a, s_w = synth.uniform_codes(M, 2 * I, K, config_id=94)
+    wp = oracle.pack_w4(wq)
+    dxq, dsa, dsw = t.from_numpy(xq).cuda(), t.from_numpy(s_a).cuda(), t.from_numpy(s_w).cuda()
+    wt = w4a8.w4a8_tile_weights(t.from_numpy(wp).cuda())
+    h = w4a8.w4a8_gemm_tiled_swiglu(dxq, dsa, wt, dsw)
+    plain = w4a8.w4a8_gemm_tuned(dxq, dsa, wt, dsw, w4a8.TILING_PREFILL_TILED, 8, N=2 * I)
+    pairs = plain.reshape(M, I, 2)
+    two = w4a8.w4a8_silu_mul(t.cat((pairs[:, :, 0], pairs[:, :, 1]), dim=1).contiguous())
+    t.cuda.synchronize()
+    assert_equal_bits(h.cpu().numpy().view(np.uint16), two.cpu().numpy().view(np.uint16), f"fused tile {tile}")
+    rows = [0, M // 2, M - 1]
+    acc_o, y32, _ = oracle.gemm(xq[rows], s_a[rows], wp, s_w)
+    assert_fp16_close(plain.cpu().numpy()[rows], y32, acc_o, f"rows M={M} I={I} K={K}")
 
 
 @pytest.mark.parametrize("M", [1, 2, 3, 4])

@@ -125,12 +125,15 @@ def test_unsigned_storage_variant(gpu, oracle, M, N, K, tile):
     assert_equal_bits(out.cpu().numpy().view(np.uint16), ref.cpu().numpy().view(np.uint16), "unsigned vs signed storage")
 
 
-@pytest.mark.parametrize("M,N,K", [(256, 27648, 160), (512, 15360, 160), (2048, 5120, 160), (1024, 27648, 128)])
-def test_library_tile_choice_exists_for_every_weight_format(gpu, oracle, M, N, K):
-    """Shapes for which the signed int4 format is given one of its own tiles (128 x 256 on 8 waves, 256 x 192, the
-    two-phase launch): the unsigned storage and the int8 weights, which lack those tiles, must be given one they have.
+@pytest.mark.parametrize("M,N,K,own", [(256, 27648, 160, False), (512, 15360, 160, False), (2048, 5120, 160, False),
+                                       (1024, 27648, 128, False), (453, 22911, 288, True), (450, 20537, 288, True)])
+def test_library_tile_choice_exists_for_every_weight_format(gpu, oracle, M, N, K, own):
+    """The three formats choose by prices of their own, among tiles of their own (`own`: the signed int4 format is given one,
+    128 x 384 or 192 x 256, that neither the unsigned storage nor the int8 weights have): each must be given one it has.
     Same codes, so all three outputs have the same bits; sampled rows against the oracle."""
     t = gpu
+    tiles = [w4a8.w4a8_route(entry, M, N, K)[1] for entry in (w4a8.ROUTE_GEMM_TILED, w4a8.ROUTE_UNSIGNED, w4a8.ROUTE_W8A8)]
+    assert tiles[1] <= 8 and tiles[2] in (1, 2, 3, 4, 5, 6, 7, 8, 12, 15, 16, 20) and (tiles[0] in (14, 19)) == own
     xq, wq, s_a, s_w = synth.uniform_codes(M, N, K, config_id=57)
     dxq, dsa, dsw = t.from_numpy(xq).cuda(), t.from_numpy(s_a).cuda(), t.from_numpy(s_w).cuda()
     wp = oracle.pack_w4(wq)
@@ -165,14 +168,16 @@ def test_tiled_llama13b_prefill_sampled(gpu, oracle):
 
 
 # One ragged shape for every output tile the library picks by price beyond those a caller can force (and a few of the
-# others): M and N off the tile, a last stage of K that is partly past the end.
-@pytest.mark.parametrize("M,N,K", [(130, 21127, 800), (453, 22911, 288), (622, 9745, 288), (250, 12122, 416), (387, 19065, 416),
-                                   (647, 16927, 544), (450, 20537, 288), (338, 22148, 288), (516, 23091, 160), (781, 16335, 672),
-                                   (137, 9737, 288), (71, 13592, 160)])
-def test_librarys_choice_on_ragged_shapes_of_every_tile(gpu, oracle, M, N, K):
+# others): M and N off the tile, a last stage of K that is partly past the end.  (The fused form and the form in K slices have
+# lists of their own in test_gpu_swiglu.py and test_gpu_splitk.py.)
+@pytest.mark.parametrize("M,N,K,tile", [(130, 21127, 800, 13), (453, 22911, 288, 14), (622, 9745, 288, 15), (250, 12122, 416, 16),
+                                        (387, 19065, 416, 17), (647, 16927, 544, 18), (450, 20537, 288, 19), (338, 22148, 288, 20),
+                                        (516, 23091, 160, 12), (781, 16335, 672, 1), (137, 9737, 288, 6), (71, 13592, 160, 8)])
+def test_librarys_choice_on_ragged_shapes_of_every_tile(gpu, oracle, M, N, K, tile):
     """Library's choice against the oracle on sampled rows and, on every element, against the bits of the 32 x 128 tile;
     the fused SiLU * up form against the two calls (its bar is equality of bits, as in test_gpu_swiglu.py)."""
     t = gpu
+    assert w4a8.w4a8_route(w4a8.ROUTE_GEMM_TILED, M, N, K) == (TILED, tile, 1)
     xq, wq, s_a, s_w = synth.uniform_codes(M, N, K, config_id=59)
     wp = oracle.pack_w4(wq)
     dxq, dsa, dsw = t.from_numpy(xq).cuda(), t.from_numpy(s_a).cuda(), t.from_numpy(s_w).cuda()

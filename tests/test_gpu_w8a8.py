@@ -70,22 +70,31 @@ def test_w8a8_ragged_shapes(gpu, oracle, M, N, K, tile):
     _run(gpu, oracle, xq, w8, s_a, s_w, tile, f"w8a8 tile={tile} M={M} N={N} K={K}")
 
 
-@pytest.mark.parametrize("M,N,K", [(512, 5120, 13824), (450, 4927, 1056), (330, 12289, 160), (1023, 5120, 288), (512, 15363, 96),
-                                   (130, 32800, 96), (600, 27000, 64)])
-def test_w8a8_chosen_tiles(gpu, oracle, M, N, K):
-    """Sizes at which the library takes its 8-wave tiles (64 x 192, 128 x 192, 192 x 192, 128 x 256), with ragged edges:
-    the bits of the 64 x 64 tile, which the tests above hold against the oracle (integer sums, one rounding)."""
+@pytest.mark.parametrize("M,N,K,tile", [(512, 5120, 13824, 16), (450, 4927, 1056, 7), (330, 12289, 160, 7), (1023, 5120, 288, 15),
+                                        (512, 15363, 96, 7), (130, 32800, 96, 7), (600, 27000, 64, 20), (579, 12355, 288, 12),
+                                        (226, 26289, 3296, 12), (963, 4111, 416, 15), (961, 2929, 832, 16), (1061, 6023, 160, 20),
+                                        (1023, 16371, 288, 1), (1052, 3189, 288, 6), (75, 25319, 416, 8)])
+def test_w8a8_chosen_tiles(gpu, oracle, M, N, K, tile):
+    """The library's own choice, with ragged edges for each of its tiles (12, 15, 16 and 20, which cannot be forced, are
+    128 x 256, 128 x 192, 64 x 192 and 192 x 192 on 8 waves): the bits of another tile, and sampled rows against the oracle."""
     t = gpu
+    assert w4a8.w4a8_route(w4a8.ROUTE_W8A8, M, N, K) == (w4a8.TILING_PREFILL_TILED, tile, 1)
     g = t.Generator(device="cuda").manual_seed(M + N + K)
     xq = t.randint(-128, 128, (M, K), generator=g, device="cuda", dtype=t.int8)
-    wt = w4a8.w8a8_tile_weights(t.randint(-128, 128, (N, K), generator=g, device="cuda", dtype=t.int8))
+    w8 = t.randint(-128, 128, (N, K), generator=g, device="cuda", dtype=t.int8)
+    wt = w4a8.w8a8_tile_weights(w8)
     s_a = t.rand(M, generator=g, device="cuda") * 1e-3
     s_w = t.rand(N, generator=g, device="cuda") * 1e-3
+    other = 8 if tile == 7 else 7
     acc, out = (w4a8.w8a8_gemm_tiled(xq, s_a, wt, s_w, want_acc=a) for a in (True, False))
-    acc64, out64 = (w4a8.w8a8_gemm_tiled(xq, s_a, wt, s_w, variant=7, want_acc=a) for a in (True, False))
+    acc_ref, out_ref = (w4a8.w8a8_gemm_tiled(xq, s_a, wt, s_w, variant=other, want_acc=a) for a in (True, False))
     t.cuda.synchronize()
-    assert t.equal(acc, acc64), "sums"
-    assert t.equal(out.view(t.int16), out64.view(t.int16)), "outputs"
+    assert t.equal(acc, acc_ref), "sums"
+    assert t.equal(out.view(t.int16), out_ref.view(t.int16)), "outputs"
+    rows = [0, M // 2, M - 1]
+    acc_o, y32, _ = oracle.gemm_w8(xq[rows].cpu().numpy(), s_a[rows].cpu().numpy(), w8.cpu().numpy(), s_w.cpu().numpy())
+    assert_equal_bits(acc[rows].cpu().numpy(), acc_o, "sampled rows acc")
+    assert_fp16_close(out[rows].cpu().numpy(), y32, acc_o, "sampled rows out")
 
 
 def test_w8a8_extremes_at_max_k(gpu, oracle):
