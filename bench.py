@@ -19,7 +19,9 @@ GEMM share), the per-GEMM ratios of the W8A8 comparison variant and of the two
 ablation variants (unsigned nibble storage, fine-grained group scales) to W4A8, and
 the CPU oracle's throughput on a bounded sample of the workload.  Except for the
 row-major rows, every GEMM of the run reads the one tiled copy of the weights,
-whatever its M.
+whatever its M.  These sections go to standard error, one JSON object per line; standard
+output is the one JSON line of the headline figure with its roofline, short enough to be
+kept whole where only the end of the output is.
 
 All inputs are seeded synthetic tensors generated on the host and resident in
 HBM before the timed region starts.
@@ -615,7 +617,7 @@ def time_medium_m(torch, w4a8, synth, model="13b", Ms=(32, 64, 128, 256, 512), i
             us = graph_time_us(torch, lambda i: w4a8.w4a8_gemm_tiled_splitk(xq, s_a, wts[i % copies], s_w, ws=ws, out=out),
                                max(copies, 16), iters)
             rows.append({"linear": name, "M": M, **roofline_row(M, N, K, us),
-                         "k_slices": need // (M * N * 4) if need else 1})
+                         "k_slices": w4a8.w4a8_route(w4a8.ROUTE_SPLITK, M, N, K)[2]})
         del wts, wt
         torch.cuda.empty_cache()
     return rows
@@ -905,7 +907,26 @@ def main():
         result["w4a8_vs_w8a8"] = time_w4_vs_w8(torch, w4a8, synth)
     if wanted("cpu", args.no_cpu_baseline):
         result["cpu_baseline"] = cpu_baseline(synth, M, args.cpu_seconds)
-    print(json.dumps(result))
+    emit(result)
+
+
+SUMMARY_ROOFLINE = ("bound", "achieved", "peak", "unit", "frac", "frac_of_achievable", "kernel", "avg_launch_us", "per_linear_us",
+                    "traffic", "traffic_unit", "algorithmic_bytes_per_launch")
+SUMMARY_DECODE = ("achieved", "peak", "unit", "frac", "mean_of_row_fracs", "frac_of_achievable", "traffic")
+
+
+def emit(result):
+    """The headline figure and short rooflines as one line on standard output; every section, the rooflines whole among
+    them, as a line of its own on standard error."""
+    sections = [k for k, v in result.items() if k.startswith("roofline") or (isinstance(v, (dict, list)) and k != "config")]
+    for k in sections:
+        print(json.dumps({k: result[k]}), file=sys.stderr)
+    sys.stderr.flush()
+    line = {k: v for k, v in result.items() if k not in sections}
+    for k, fields in (("roofline", SUMMARY_ROOFLINE), ("roofline_decode", SUMMARY_DECODE)):
+        if k in result:
+            line[k] = {f: result[k][f] for f in fields if f in result[k]}
+    print(json.dumps(line), flush=True)
 
 
 if __name__ == "__main__":

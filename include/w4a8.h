@@ -126,11 +126,12 @@ int w4a8_gemm_acc_i32(const int8_t *xq, const uint8_t *wp, int32_t *acc, int M, 
  * w4a8_tile_weights: wp [N][K/2] (device) in -> wt (device, 16-byte aligned, w4a8_tiled_weight_bytes(N, K)) out.
  * w4a8_gemm_tiled: w4a8_gemm over wt instead of wp (all other arguments as there).  Every M is accepted, and one
  *   copy of the weights, the tiled one, serves them all: up to 16 tokens (token generation) the weight-streaming kernels
- *   read wt directly; so they do from 17 to 64 tokens where all of K fits the registers of a workgroup (K <= 5120 for
- *   49 to 64 tokens, K <= 7168 or 8192 for 17 to 32); above that, and for a longer K, the large-M kernel runs
- *   (w4a8_gemm_tiled_splitk, which has a workspace, serves 17 to 64 tokens with the weight-streaming kernel at any K
- *   and fills the chip with the large-M kernel at a few hundred rows).  w4a8_gemm serves every M from the row-major
- *   array, at up to twice the tiled time for M between 17 and 512.
+ *   read wt directly; from 17 to 64 tokens, where all of K fits the registers of a workgroup (K <= 5120 for 33 to 64
+ *   tokens, K <= 8192 for 17 to 32), one of them or the large-M kernel, whichever is estimated to be the faster;
+ *   above that, and for a longer K, the large-M kernel
+ *   (w4a8_gemm_tiled_splitk, which has a workspace, can cut a longer K into slices that the weight-streaming kernel
+ *   takes, and fills the chip with slices of the large-M kernel at a few hundred rows).  w4a8_gemm serves every M from
+ *   the row-major array, at up to 2.3 times the time of the better of these two for M between 17 and 512.
  */
 size_t w4a8_tiled_weight_bytes(int N, int K);
 int w4a8_tile_weights(const uint8_t *wp, uint8_t *wt, int N, int K, void *stream);
@@ -177,16 +178,23 @@ int w4a8_gemm_tiled_swiglu(const int8_t *xq, const float *s_a, const uint8_t *wt
  * 40 tiles for M = 32, N = 5120): K is cut into slices, every (tile, slice) pair is a workgroup of the same kernel that
  * writes its raw int32 sums to a slab of the workspace, and a second kernel adds the slabs and applies Eq. (6),(7).
  * Integer sums do not depend on the order of addition: the output has the bits w4a8_gemm_tiled gives.
- * With 17 to 64 tokens and no tile forced the slices are slices of the weight-streaming kernel instead (each workgroup
- * streams its channels' share of one K slice, with its slice of the activations in registers): as few slices as let a
- * slice of K fit the registers, often one, and then no slab at all.
+ * With 17 to 64 tokens and no tile forced the slices may be slices of the weight-streaming kernel instead (each workgroup
+ * streams its channels' share of one K slice, with its slice of the activations in registers).
  *   variant : output tile as for W4A8_TILING_PREFILL_TILED, 0 = library's choice;
- *   splits  : number of K slices, 0 = library's choice (1 when the tiles fill the chip: then this is w4a8_gemm_tiled
- *             and the workspace is not touched), at most 64 and at most K / 128 rounded up;
- *   workspace (device, 16-byte aligned), workspace_bytes: at least splits * M * N * 4 bytes when more than one slice is
- *             used, else W4A8_ERR_WORKSPACE; w4a8_gemm_tiled_workspace_bytes(M, N, K) is the size the library's own
- *             choice (splits = 0) needs, 0 if it does not split.  Contents on return: unspecified.
- *   With more than one slice M * K and the tiled weight bytes must each be below 0xF0000000 (W4A8_ERR_SHAPE).
+ *   splits  : number of K slices, 0 = library's choice, at most 64 (more than K / 128 rounded up: that many).
+ *             The library's own choice of tile and slices goes by estimated times.  It stays within the slabs that it asks
+ *             for, and often needs fewer or none, where it is w4a8_gemm_tiled and the workspace is not touched;
+ *   workspace (device, 16-byte aligned), workspace_bytes: W4A8_ERR_NULL or W4A8_ERR_WORKSPACE if the slabs asked for (one is
+ *             M * N * 4 bytes) do not fit, whether or not they are used.  Asked for, nothing if it is one slab:
+ *               splits > 0             : the forced count (slices that would be empty left out);
+ *               splits = 0, variant = 0: w4a8_gemm_tiled_workspace_bytes(M, N, K): nothing up to 16 tokens; up to 64 as few slices (up to
+ *                                        8) as let a slice of K fit the registers of the weight-streaming kernel; else, up
+ *                                        to 512 tokens, where the tiles are few, as many as bring two workgroups to every
+ *                                        compute unit, at most 6;
+ *               splits = 0, a tile     : as many slices by the second rule for that tile, and as many are used.
+ *             Contents on return: unspecified.
+ *   Where slabs of the large-M kernel are asked for, M * K and the tiled weight bytes must each be below 0xF0000000
+ *   (W4A8_ERR_SHAPE).
  */
 size_t w4a8_gemm_tiled_workspace_bytes(int M, int N, int K);
 int w4a8_gemm_tiled_splitk(const int8_t *xq, const float *s_a, const uint8_t *wt, const float *s_w, void *out_fp16,
@@ -250,8 +258,8 @@ int w4a8_linear_tiled_norm_fp16(const void *x_fp16, long long ldx, const void *r
  * same kernels, same output bits.  The slabs of the K slices live in a scratch array inside the library instead:
  * W4A8_STATIC_SCRATCH_BYTES of device memory per GPU, present from the moment the library is loaded until the process
  * ends.  The call allocates and frees nothing (the first call on a device looks up the array's address, as
- * w4a8_init does).  A shape whose slabs (splits * M * N * 4 bytes, splits being the library's choice or the forced
- * count) exceed the array is refused with W4A8_ERR_WORKSPACE and nothing is launched.  All calls on one GPU share the
+ * w4a8_init does).  A call that would ask w4a8_gemm_tiled_splitk for a workspace larger than the array is refused with
+ * W4A8_ERR_WORKSPACE and nothing is launched.  All calls on one GPU share the
  * one array: calls that may overlap in time on the same GPU (different streams, different threads) race on it and
  * must be serialised by the caller; calls on one stream are ordered and safe.  The array's contents carry over from
  * call to call and are never read before they are rewritten.
