@@ -273,8 +273,8 @@ bool one_launch_covers(int M, int N, int K) {
 }
 
 // How a GEMM over tiled int4 weights with more than 16 tokens is run: by the weight-streaming kernel with per-wave
-// staging, K cut into slices, or by the large-M kernel, K cut into slices.  Both are priced and the cheaper one is taken, a
-// tile only where its price is 15 % below that of weight streaming.
+// staging, K cut into slices, or by the large-M kernel, K cut into slices.  Both are priced and the cheaper one is taken, near
+// ties by weight streaming.
 struct TiledPlan {
     bool wide;          // weight-streaming kernel, else the large-M kernel
     DecodeShape shape;  // wide: its shape
@@ -284,15 +284,8 @@ struct TiledPlan {
 
 // Price of the weight-streaming kernel in microseconds: what every compute unit brings in (the activations and its
 // weights), a fixed part per chunk of 16 channels, more of it where a wave has more than 8 k steps, and the slabs.  Fitted
-// like the tiles' prices, within 5 %.
-// Both prices are off by more than that where the tiles' are too low (K no multiple of 128, wide N), and streaming is the form
-// that such shapes hurt less, so near ties are its own.  On 522 shapes with 17 to 64 tokens (weights cold) that loses 0.5 %
-// on average over always taking the faster with one slice and 1.7 % with several, 1.1 and 2.1 % without the preference; 5
-// shapes are more than 3 % slower than always streaming, 34 without it.  The same from 10 to 15 %, no better beyond.
-// (M = 64: N = 27648, K = 5120 17.9 us streaming, 19.8 tiled; N = 22016, K = 4096 14.0 and 15.3; N = 8544, K = 1824, M = 63 6.6
-// and 7.5.)
-constexpr double kStreamingPreferred = 0.85;
-
+// like the tiles' prices, within 5 % of those shapes; on 346 others, with up to 65536 channels, within 9 % with one slice and
+// 13 % too low on average with several.
 double wide_us(const DecodeShape &s, int M, int N, int K) {
     const double steps = ((K + 127) / 128 + s.k_slices - 1) / s.k_slices;
     const double chunks = (s.rows_per_wg + 15) / 16, mt = (M + 15) / 16, long_walk = s.x_steps > 8 ? s.x_steps - 8 : 0;
@@ -301,6 +294,16 @@ double wide_us(const DecodeShape &s, int M, int N, int K) {
     if (s.k_slices > 1) us += slab_us(M, N, s.k_slices);
     return us;
 }
+
+// The tiles' prices are too low where K is no multiple of 128 and where N is wide, and streaming is the form
+// that such shapes hurt less, so near ties are its own: a tile is taken where it is priced 15 % lower, 10 % where K is cut
+// into two or three slices, and simply lower beyond, where streaming's own price is the one that is too low (N = 8192, K =
+// 28672, M = 64: 41.0 us in six slices, priced 30.1; 32.7 with tiles, priced 27.8).  On 522 shapes with 17 to 64 tokens
+// (weights cold) that loses 0.5 % on average over always taking the faster with one slice and 1.7 % with several, 1.4 and 2.4 %
+// without the preference; 6 shapes are more than 3 % slower than always streaming, 34 without it.
+// (M = 64: N = 27648, K = 5120 17.9 us streaming, 19.8 tiled; N = 22016, K = 4096 14.0 and 15.3; N = 8544, K = 1824, M = 63 6.6
+// and 7.5.)
+double streaming_preferred(int slices) { return slices == 1 ? 0.85 : slices <= 3 ? 0.9 : 1.0; }
 
 constexpr int kMaxSlices = 8;
 constexpr int kSplitMaxM = 512;  // the large-M kernel is not split beyond: there its tiles fill the chip or the slabs cost more
@@ -332,7 +335,7 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu, int cus)
             DecodeShape shape{};
             shape.swiglu = swiglu;
             if (!resident_shape(M, N, K, 0, 0, 0, false, -1, true, &shape, s, true) || shape.k_slices != s) continue;
-            const double us = kStreamingPreferred * wide_us(shape, M, N, K);
+            const double us = streaming_preferred(s) * wide_us(shape, M, N, K);
             if (us < best_us) {
                 best_us = us;
                 best.wide = true;

@@ -133,5 +133,7 @@ def test_near_ties_go_to_weight_streaming():
             assert w4a8_route(entry, M, N, K) == (TILING_DECODE_RESIDENT_TILED, 0, 1), (M, N, K)
     assert w4a8_route(ROUTE_SWIGLU, 64, 27648, 5120) == (TILING_DECODE_RESIDENT_TILED, 0, 1)
     assert w4a8_route(ROUTE_SPLITK, 62, 8219, 14976) == (TILING_DECODE_RESIDENT_TILED, 0, 3)
+    for M in (48, 50, 64):  # many slices: streaming is the form that is priced too low
+        assert w4a8_route(ROUTE_SPLITK, M, 8192, 28672) == (TILING_PREFILL_TILED, 13, 6)
     for M, N, K in [(63, 55468, 3520), (52, 47417, 1344), (64, 57344, 8192), (17, 1216, 16416)]:
         assert w4a8_route(ROUTE_GEMM_TILED, M, N, K)[0] == TILING_PREFILL_TILED, (M, N, K)
