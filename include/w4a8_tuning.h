@@ -65,6 +65,8 @@ int w4a8_gemm_tuned(const int8_t *xq, const float *s_a, const uint8_t *wp, const
  *   tiling : out, one of W4A8_TILING_* (never an AUTO one);
  *   tile   : out, output tile of a PREFILL tiling, else 0.  1 .. 12 as for PREFILL_TILED above (for PREFILL as well); 13 = 64 x
  *            256, 14 = 128 x 384, 15 = 128 x 192, 16 = 64 x 192, 17 = 128 x 320, 18 = 192 x 320, 19 = 192 x 256, 20 = 192 x 192;
+ *            of the medium-M kernel over tiled weights: 21 = 32 x 32, 22 and 23 = 32 x 64, 24 = 32 x 96, 25 = 48 x 128, 26 = 64 x 96,
+ *            27 = 64 x 128, 28 = 64 x 160, 29 = 16 x 16, 30 = 16 x 32, 31 = 96 x 128;
  *   slices : out, K slices.
  * Returns what the entry returns for these sizes.
  */

@@ -272,13 +272,64 @@ bool one_launch_covers(int M, int N, int K) {
     return (long long)M * K <= 0xF0000000ll && (long long)tiled_weight_bytes(N, K, 4) <= 0xF0000000ll;
 }
 
+// Price of the medium-M kernel in microseconds: as above, k steps of 128 in place of stages (rounded up to whole stages of `groups`
+// steps), and three terms more: deep, for the share of a compute unit's workgroups that the fullest one holds in the last
+// round; weights, per MB of int4 codes (what the memory needs beside them); ragged, where rows of activations do not begin on
+// a cache line (K % 128 != 0).
+struct StepCost {
+    int id, bm, bn, groups, per_cu;
+    float launch, round, step, last, share, deep, weights, ragged;
+};
+
+double step_us(const StepCost &t, int M, int N, int K, int cus) {
+    const long long n = (long long)((M + t.bm - 1) / t.bm) * ((N + t.bn - 1) / t.bn);
+    const long long slots = (long long)cus * t.per_cu, full = n / slots, rest = n % slots;
+    const double part = (double)rest / (double)slots, deep = (double)((rest + cus - 1) / cus) / t.per_cu;
+    const int steps = ((K + kTiledBlockK - 1) / kTiledBlockK + t.groups - 1) / t.groups * t.groups;
+    double us = t.launch + t.round * (double)(full + (rest != 0)) + t.weights * 0.5e-6 * (double)N * K;
+    us += steps * (t.step * (double)full + (rest != 0 ? t.last + t.share * part + t.deep * deep : 0.0));
+    if (K % kTiledBlockK != 0) us += t.ragged * ((double)full + part) * steps;
+    return us;
+}
+
+bool medium_covers(int M, int N, int K, int wbits) {
+    return (long long)M * K < kMediumMaxActivations && tiled_weight_bytes(N, K, wbits) <= kMediumMaxWeights;
+}
+
+// Its tiles over int4 weights: of eighteen tried, those without which the choice would cost more than 0.3 % on average.  Fits
+// over 552 shapes (420 random, M 17 .. 1024, N 1024 .. 32768, K 1024 .. 16384, and the models' linears; weights cold) within 6 to 9 %.
+// A medium tile is taken where it is priced that much lower than the large-M kernel (below): 1.7 % on average over always taking the fastest, 3 of
+// 216 shapes that were not fitted to are more than 3 % slower than without the kernel, by 9 % at most, and all together take 0.93 of
+// the time: 0.87 from 65 to 512 tokens (N = K = 5120, M = 128: 14.7 us in three slices of K, 10.3 as 32 x 96 tiles; N = 4096, K = 11008:
+// M = 50 17.7 and 11.9, M = 333 28.2 and 24).  Below 17 tokens the weight-streaming kernel holds the activations in registers.
+constexpr StepCost kMediumCosts[] = {
+    {kMedium32x32, 32, 32, 8, 2, 2.018f, 1.159f, 0.142f, 0.000f, 0.016f, 0.138f, 0.066f, 0.010f},
+    {kMedium32x64, 32, 64, 4, 4, 1.504f, 1.200f, 0.359f, 0.037f, 0.059f, 0.292f, 0.086f, 0.022f},
+    {kMedium32x64K8, 32, 64, 8, 2, 2.420f, 1.089f, 0.209f, 0.000f, 0.008f, 0.207f, 0.061f, 0.028f},
+    {kMedium32x96, 32, 96, 4, 3, 1.018f, 1.981f, 0.337f, 0.021f, 0.032f, 0.332f, 0.085f, 0.016f},
+    {kMedium48x128, 48, 128, 4, 2, 0.578f, 3.335f, 0.318f, 0.000f, 0.051f, 0.333f, 0.067f, 0.032f},
+    {kMedium64x96, 64, 96, 4, 2, 0.713f, 3.345f, 0.338f, 0.000f, 0.078f, 0.321f, 0.053f, 0.013f},
+    {kMedium64x128, 64, 128, 4, 1, 1.315f, 3.121f, 0.218f, 0.191f, 0.041f, 0.000f, 0.054f, 0.006f},
+    {kMedium64x160, 64, 160, 4, 1, 0.963f, 3.888f, 0.258f, 0.230f, 0.045f, 0.000f, 0.054f, 0.005f},
+};
+// How much lower it has to be priced than the large-M kernel.  Beyond 512 tokens 15 %: it brings in more bytes per operation, which
+// prices taken from short runs don't show.  N = 5120, K = 13824, M = 1024, as 64 x 160 tiles: 73.5 us against 75.3 by itself, but the
+// layer around it 306 us instead of 299, at the power limit.  (On 60 shapes beyond 512 tokens it then gives 7.0 %, with 3 % 7.1.)
+double medium_over_tiles(int M) { return M <= 512 ? 1.03 : 1.15; }
+
+// Against weight streaming, whose price has its own preference in it (streaming_preferred): 10 % lower where that takes one slice
+// (the two are level there: N = 8544, K = 1824, M = 63 6.44 us and 6.43), up to 8 % higher where it takes several, which its price
+// is too low for and which cost slabs (N = 4096, K = 11008, M = 50: 17.4 us in three slices, 12.2 as 32 x 32 tiles).  On 217 shapes with
+// 17 to 64 tokens that is the faster one of the two but for one shape that loses 2 %.
+double medium_over_streaming(int slices) { return slices == 1 ? 1.10 : 0.92; }
+
 // How a GEMM over tiled int4 weights with more than 16 tokens is run: by the weight-streaming kernel with per-wave
-// staging, K cut into slices, or by the large-M kernel, K cut into slices.  Both are priced and the cheaper one is taken, near
-// ties by weight streaming.
+// staging, K cut into slices, by the large-M kernel, K cut into slices, or by the medium-M kernel.  All are priced and the
+// cheapest one is taken, near ties by weight streaming.
 struct TiledPlan {
     bool wide;          // weight-streaming kernel, else the large-M kernel
     DecodeShape shape;  // wide: its shape
-    int tile;           // else: output tile and K slices
+    int tile;           // else: output tile, of the large-M or the medium-M kernel, and K slices
     int splits, stages_per_split;
 };
 
@@ -343,6 +394,20 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu, int cus)
             }
         }
     }
+    if (medium_covers(M, N, K, 4)) {
+        const double bar = best_us / (best.wide ? medium_over_streaming(best.shape.k_slices) : medium_over_tiles(M));
+        double medium_us = bar;
+        for (const StepCost &t : kMediumCosts) {
+            const double us = step_us(t, M, N, K, cus);
+            if (us < medium_us) {
+                medium_us = us;
+                best = TiledPlan{};
+                best.tile = t.id;
+                best.splits = 1;
+                best.stages_per_split = stages;
+            }
+        }
+    }
     best.splits = best.wide ? best.shape.k_slices : best.splits;
     return best;
 }
@@ -385,6 +450,12 @@ Route tiled_route(int M, int N, int K, RouteKind kind) {
 
 TiledPlan tiled_plan(int M, int N, int K, bool swiglu) { return tiled_route(M, N, K, swiglu ? kSwiglu : kUnsliced).plan; }
 
+// a: one launch's worth of the problem; tile: of either kernel
+hipError_t launch_tile(const PrefillArgs &a, bool acc_out, bool swiglu, int tile, hipStream_t st, int wbits) {
+    if (tile >= kMediumFirst) return launch_gemm_medium(a, acc_out, swiglu, tile, st, wbits);
+    return swiglu ? launch_gemm_prefill_tiled_swiglu(a, tile, st) : launch_gemm_prefill_tiled(a, acc_out, tile, st, wbits);
+}
+
 // d: pointers only
 hipError_t launch_wide(DecodeArgs d, int M, int N, int K, const DecodeShape &s, bool acc_out, hipStream_t st) {
     d.M = M; d.N = N; d.K = K;
@@ -416,14 +487,14 @@ int choose_fine_tile(int M, int N) {
     return best;
 }
 
-// The choice for the int8-weight variant.  Its stages bring in twice the weight bytes, through rings one stage shallower,
+// The large-M kernel's tile for the int8-weight variant.  Its stages bring in twice the weight bytes, through rings one stage shallower,
 // and convert nothing: a launch takes 1.06 to 1.42 times the price of the same tile over int4 weights, most where the weight
 // stream is most of the work.  The factors are geometric means over 36 shapes (29 random, M 1 .. 1024; weights cold).
 // Choosing by them costs 0.6 % on average over always taking the fastest of fourteen tiles; rounds times area over an
 // efficiency on seven tiles, the rule before, cost 11 % (N = 5120, K = 13824, M = 512: 64 x 128 at 81 us, now 64 x 192 at 61;
 // N = 11722, K = 15648, M = 1: 54 us, now 38).  128 x 256 of 4 waves, 128 x 160 and 128 x 128 were never the fastest,
 // 64 x 256 and 192 x 256 neither.
-int choose_tiled_tile8(int M, int N, int K) {
+int choose_ring_tile8(int M, int N, int K) {
     struct Factor { int id; double over_int4; };
     const Factor factors[] = {{kTiled256x256, 1.195}, {kTiled64x128, 1.333},  {kTiled64x64, 1.217},  {kTiled32x128, 1.411},
                               {kTiled128x256W8, 1.252}, {kTiled128x192, 1.173}, {kTiled64x192, 1.277}, {kTiled192x192, 1.060}};
@@ -437,6 +508,43 @@ int choose_tiled_tile8(int M, int N, int K) {
             const double us = f.over_int4 * tile_us(t, M, N, stages, cus, 1, cus);
             if (best == 0 || us < best_us) best = t.id, best_us = us;
         }
+    return best;
+}
+
+// Over int8 weights the medium-M kernel is set against the large-M kernel's tile of the rule above, both by prices of one form:
+// fits over 216 shapes (150 random, M 1 .. 1024, and the models' linears; weights cold) within 8 to 12 %.  It is taken where it is
+// priced lower by medium_over_tiles: 0.5 % on average over always taking the fastest of the fourteen tiles, one of the 216 shapes is more than 3 %
+// slower than without it (by 5 %), and all together take 0.81 of the time: 0.68 up to 16 tokens, 0.79 from 33 to 64, 0.92 from 257
+// to 512 (N = 5120, K = 13824, M = 512: 64 x 192 at 60 us, now 96 x 128 at 46).  By these prices for every tile seven shapes are slower.
+constexpr StepCost kTileCosts8[] = {
+    {kTiled256x256, 256, 256, 1, 1, 0.000f, 5.779f, 1.546f, 1.150f, 0.396f, 0.000f, 0.000f, 0.000f},
+    {kTiled64x128, 64, 128, 1, 2, 2.516f, 0.337f, 0.683f, 0.071f, 0.126f, 0.566f, 0.105f, 0.027f},
+    {kTiled64x64, 64, 64, 1, 2, 2.149f, 0.662f, 0.439f, 0.021f, 0.123f, 0.365f, 0.078f, 0.014f},
+    {kTiled32x128, 32, 128, 1, 2, 1.582f, 0.547f, 0.552f, 0.106f, 0.025f, 0.467f, 0.131f, 0.000f},
+    {kTiled128x256W8, 128, 256, 1, 1, 1.047f, 2.977f, 0.830f, 0.620f, 0.332f, 0.000f, 0.046f, 0.000f},
+    {kTiled128x192, 128, 192, 1, 1, 0.715f, 2.903f, 0.719f, 0.528f, 0.257f, 0.000f, 0.034f, 0.000f},
+    {kTiled64x192, 64, 192, 1, 1, 0.000f, 2.870f, 0.486f, 0.436f, 0.107f, 0.000f, 0.108f, 0.028f},
+    {kTiled192x192, 192, 192, 1, 1, 0.473f, 4.555f, 0.874f, 0.579f, 0.214f, 0.000f, 0.006f, 0.009f},
+    {kMedium16x16, 16, 16, 8, 4, 2.768f, 0.031f, 0.206f, 0.011f, 0.000f, 0.179f, 0.134f, 0.000f},
+    {kMedium16x32, 16, 32, 8, 4, 2.813f, 0.000f, 0.333f, 0.000f, 0.043f, 0.291f, 0.128f, 0.000f},
+    {kMedium32x32, 32, 32, 8, 2, 2.503f, 0.642f, 0.216f, 0.000f, 0.051f, 0.172f, 0.086f, 0.002f},
+    {kMedium32x64, 32, 64, 4, 4, 1.661f, 1.038f, 0.544f, 0.000f, 0.012f, 0.568f, 0.180f, 0.000f},
+    {kMedium64x96, 64, 96, 4, 2, 0.000f, 3.414f, 0.463f, 0.021f, 0.091f, 0.440f, 0.150f, 0.000f},
+    {kMedium96x128, 96, 128, 4, 1, 0.000f, 4.544f, 0.355f, 0.337f, 0.075f, 0.000f, 0.100f, 0.041f},
+};
+
+int choose_tiled_tile8(int M, int N, int K) {
+    int best = choose_ring_tile8(M, N, K);
+    if (!medium_covers(M, N, K, 8)) return best;
+    const int cus = compute_units();
+    double best_us = 0;
+    for (const StepCost &t : kTileCosts8)
+        if (t.id == best) best_us = step_us(t, M, N, K, cus) / medium_over_tiles(M);
+    for (const StepCost &t : kTileCosts8) {
+        if (t.id < kMediumFirst) continue;
+        const double us = step_us(t, M, N, K, cus);
+        if (us < best_us) best = t.id, best_us = us;
+    }
     return best;
 }
 
@@ -525,7 +633,7 @@ int run_gemm(const int8_t *xq, const float *s_a, const uint8_t *wp, const float 
         a.xq = xq; a.s_a = s_a; a.wp = wp; a.s_w = s_w;
         a.out = out_fp16; a.acc_out = acc_i32;
         a.M = M; a.N = N; a.K = K; a.ldc = N;
-        err = launch_gemm_prefill_tiled(a, want_acc, pl.prefill_tile, st);
+        err = launch_tile(a, want_acc, false, pl.prefill_tile, st, 4);
     } else if (pl.tiling != W4A8_TILING_PREFILL) {
         DecodeArgs a{};
         a.xq = xq; a.s_a = s_a; a.wp = wp; a.s_w = s_w;
@@ -644,7 +752,7 @@ int w4a8_gemm_tiled_swiglu(const int8_t *xq, const float *s_a, const uint8_t *wt
     PrefillArgs a{};
     a.xq = xq; a.s_a = s_a; a.wp = wt_gu; a.s_w = s_w_gu; a.out = h_fp16;
     a.M = M; a.N = N; a.K = K; a.ldc = I;
-    return launched(launch_gemm_prefill_tiled_swiglu(a, pl.tile, st));
+    return launched(launch_tile(a, false, true, pl.tile, st, 4));
 }
 
 // ---- K split over workgroups for shapes whose tiles alone leave most of the chip idle (medium M, small N)
@@ -784,7 +892,7 @@ static int splitk_on_route(const SplitRoute &route, const int8_t *xq, const floa
         a.M = M; a.N = N; a.K = K; a.ldc = N;
         a.splits = pl.splits;
         a.stages_per_split = pl.stages_per_split;
-        e = launch_gemm_prefill_tiled(a, sliced, pl.tile, st);
+        e = launch_tile(a, sliced, false, pl.tile, st, 4);
     }
     if (int err = launched(e); err || !sliced) return err;
     return launched(launch_splitk_epilogue(slabs, pl.splits, s_a, s_w, out_fp16, M, N, st));
@@ -944,6 +1052,7 @@ int w4a8_init(void) {
     (void)compute_units();
     if (int e = launched(prepare_tiled_kernels())) return e;
     if (int e = launched(prepare_row_kernels())) return e;
+    if (int e = launched(prepare_medium_kernels())) return e;
     return launched(prepare_decode_kernels());
 }
 
@@ -1014,7 +1123,7 @@ static int gemm_tiled_variant(const int8_t *xq, const float *s_a, const uint8_t 
     a.M = M; a.N = N; a.K = K; a.ldc = N;
     const int tile = variant ? variant
                              : wfmt == 8 ? choose_tiled_tile8(M, N, K) : choose_unsigned_tile(M, N, K);
-    return launched(launch_gemm_prefill_tiled(a, want_acc, tile, static_cast<hipStream_t>(stream), wfmt));
+    return launched(launch_tile(a, want_acc, false, tile, static_cast<hipStream_t>(stream), wfmt));
 }
 
 int w4a8_quantize_weights(const void *w_fp16, uint8_t *wp, float *s_w, int N, int K, void *stream) {

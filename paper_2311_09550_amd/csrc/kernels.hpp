@@ -178,7 +178,28 @@ hipError_t prepare_tiled_kernels();
 hipError_t launch_splitk_epilogue(const int *part, int splits, const float *s_a, const float *s_w, void *out, int M, int N,
                                   hipStream_t stream);
 
-// The same kernel over weights in the packed row-major storage format.  Its tiles, the first kPrefillTileMax of which a
+// Output tiles of the medium-M kernel (gemm_medium.hpp), numbered behind the large-M kernel's; rows x channels, 4 groups of waves
+// along K, or 8.  int4 weights: 32 x 32 .. 64 x 160; int8: 16 x 16, 16 x 32, 32 x 32, 32 x 64, 64 x 96, 96 x 128.
+constexpr int kMedium32x32 = 21;    // 8 groups
+constexpr int kMedium32x64 = 22;
+constexpr int kMedium32x64K8 = 23;  // 8 groups
+constexpr int kMedium32x96 = 24;
+constexpr int kMedium48x128 = 25;
+constexpr int kMedium64x96 = 26;
+constexpr int kMedium64x128 = 27;
+constexpr int kMedium64x160 = 28;
+constexpr int kMedium16x16 = 29;    // 8 groups
+constexpr int kMedium16x32 = 30;    // 8 groups
+constexpr int kMedium96x128 = 31;
+constexpr int kMediumFirst = kMedium32x32, kMediumLast = kMedium96x128;
+// its activation offsets mark rows and steps that do not exist by their two highest bits; its weight offsets have 32 bits
+constexpr long long kMediumMaxActivations = 1ll << 30;
+constexpr size_t kMediumMaxWeights = 0xF0000000u;
+// p.out: fp16, or h = fp16(silu(gate) * up) over interleaved channels (swiglu; p.ldc = its pitch); acc_out: raw sums.  No slices of K.
+hipError_t launch_gemm_medium(const PrefillArgs &p, bool acc_out, bool swiglu, int tile, hipStream_t stream, int wbits);
+hipError_t prepare_medium_kernels();
+
+// The large-M kernel over weights in the packed row-major storage format.  Its tiles, the first kPrefillTileMax of which a
 // caller can force by number; without 192 x 320 the choice would cost 1.1 % more on average over random shapes, without
 // 64 x 256 and 128 x 192 half a percent each, and three more of the tiles above would gain nothing.
 constexpr int kRowTiles[] = {kTiled256x256, kTiled192x320, kTiled192x192, kTiled128x256, kTiled64x192, kTiled64x128,

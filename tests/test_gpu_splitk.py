@@ -65,10 +65,10 @@ def test_library_choice_on_llama13b_shapes(gpu, oracle, M, N, K):
 # one ragged shape for every output tile that the library cuts K with, N a multiple of 4 (16-byte stores of raw sums) and not;
 # the last slice is a stage short in some, and the last stage of K partly past the end in all
 @pytest.mark.parametrize("M,N,K,tile,slices", [
-    (490, 869, 4512, 6, 3), (467, 852, 4512, 6, 3), (106, 307, 3424, 7, 2), (104, 312, 3104, 7, 2), (264, 841, 6336, 8, 4),
-    (344, 1128, 4544, 8, 3), (473, 3075, 10080, 12, 4), (452, 3084, 9664, 12, 4), (392, 1731, 6592, 13, 4), (407, 1736, 6560, 13, 4),
-    (510, 2565, 8096, 15, 4), (462, 2564, 8160, 15, 4), (508, 1286, 6080, 16, 4), (451, 1288, 6208, 16, 4), (400, 6250, 11104, 17, 3),
-    (394, 6196, 11072, 17, 3), (334, 5418, 11200, 20, 4), (275, 4412, 13344, 20, 5)])
+    (457, 551, 9152, 6, 6), (436, 580, 9120, 6, 6), (71, 206, 8352, 7, 5), (101, 204, 8640, 7, 5), (66, 839, 9280, 8, 6),
+    (74, 732, 10912, 8, 6), (403, 2389, 15936, 12, 6), (349, 4120, 14368, 12, 5), (484, 1041, 12832, 13, 6), (394, 1276, 12192, 13, 6),
+    (453, 2099, 13856, 15, 5), (494, 2060, 14528, 15, 5), (410, 902, 12960, 16, 6), (399, 912, 12864, 16, 6), (400, 6250, 11104, 17, 3),
+    (394, 6196, 11072, 17, 3), (323, 7191, 10688, 20, 3), (340, 7668, 10272, 20, 3)])
 def test_librarys_slices_of_every_tile(gpu, oracle, M, N, K, tile, slices):
     """splits = 0, the workspace of the size asked for and the static array where the slabs fit it: bit for bit the unsliced
     32 x 128 tile, sampled rows against the oracle."""
