@@ -116,26 +116,61 @@ __device__ __forceinline__ float absmax_packed_value(unsigned m2) {
 // Pieces of the residual addition + RMSNorm in front of a quantiser, shared by the row-wise kernel and the linear that
 // takes them in, so that both apply the same arithmetic to an element: eight sums fp16(fp32(a) + fp32(b)); the fp32
 // sum of eight squares added to a running sum; eight values fp16(fp32(r) * inv * fp32(g)).
+// The sum is one packed fp16 addition: fp32 has 2 * 11 + 2 bits, so rounding the fp32 sum again gives the correctly rounded
+// fp16 sum.  A square of an fp16 value is exact in fp32, so adding it by an FMA rounds as adding the product does.
 __device__ __forceinline__ v4u add_halves8(v4u a, v4u b) {
+    typedef _Float16 f16x2 __attribute__((ext_vector_type(2)));
     v4u o;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = pack_f16x2(lo_half(a[j]) + lo_half(b[j]), hi_half(a[j]) + hi_half(b[j]));
+    for (int j = 0; j < 4; ++j) {
+        const unsigned aj = a[j], bj = b[j];  // a bit cast of a vector's element would take its first one
+        o[j] = __builtin_bit_cast(unsigned, __builtin_bit_cast(f16x2, aj) + __builtin_bit_cast(f16x2, bj));
+    }
     return o;
 }
 __device__ __forceinline__ float add_squares8(v4u r, float ss) {
 #pragma unroll
     for (int j = 0; j < 4; ++j) {
         const float a = lo_half(r[j]), b = hi_half(r[j]);
-        ss += a * a;
-        ss += b * b;
+        ss = fmaf(a, a, ss);
+        ss = fmaf(b, b, ss);
     }
     return ss;
+}
+// a * b rounded to fp32 as fma(a, b, -0): with an fp16 operand that is one v_fma_mix_f32 instead of a conversion and a
+// multiplication.  The compiler does not see the constant, or it would turn the FMA back into a product.
+__device__ __forceinline__ float mul_mix(float a, float b) {
+    float z = -0.0f;
+    asm("" : "+s"(z));
+    return fmaf(a, b, z);
 }
 __device__ __forceinline__ v4u norm_scale8(v4u r, float inv, v4u g) {
     v4u o;
 #pragma unroll
-    for (int j = 0; j < 4; ++j) o[j] = pack_f16x2(lo_half(r[j]) * inv * lo_half(g[j]), hi_half(r[j]) * inv * hi_half(g[j]));
+    for (int j = 0; j < 4; ++j)
+        o[j] = pack_f16x2(mul_mix(mul_mix(lo_half(r[j]), inv), lo_half(g[j])), mul_mix(mul_mix(hi_half(r[j]), inv), hi_half(g[j])));
     return o;
+}
+// Running maximum of |r g| as a bit pattern (non-negative floats order like theirs, NaN above all), eight products at a time; a
+// product of two fp16 values is exact in fp32.
+__device__ __forceinline__ unsigned absmax_products8(v4u r, v4u g, unsigned m) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+        const unsigned a = __float_as_uint(mul_mix(lo_half(r[j]), lo_half(g[j]))) & 0x7FFFFFFFu;
+        const unsigned b = __float_as_uint(mul_mix(hi_half(r[j]), hi_half(g[j]))) & 0x7FFFFFFFu;
+        m = max(m, max(a, b));
+    }
+    return m;
+}
+// The largest |y| of a row, y = fp16(fl(fl(r inv) g)), from top = max |r g|, without forming a y: the value that every element is
+// rounded from is |r g| inv within 2^-23, two roundings, and top * inv, as computed, within 2^-24.  So when top inv (1 - 2^-21) and
+// top inv (1 + 2^-21) round to the same fp16 value, the element at the top gives that value and none gives more.  Else, and for NaN,
+// false: about one row in two thousand has to look at its values.
+__device__ __forceinline__ bool absmax_of_norm(float top, float inv, float *amax) {
+    const float v = top * inv;
+    const float lo = half_bits_to_float(f32_to_f16_bits(v * (1.0f - 0x1p-21f))), hi = half_bits_to_float(f32_to_f16_bits(v * (1.0f + 0x1p-21f)));
+    *amax = lo;
+    return lo == hi;
 }
 // 1 / sqrt(sum / count + eps): correctly rounded division, square root and division
 __device__ __forceinline__ float rms_inverse(float sum, int count, float eps) {

@@ -144,10 +144,10 @@ __device__ __forceinline__ void wait_vmcnt_at_most() {
 // instead of the 2 I outputs (Sec. 6.1: glue operators folded into their neighbours).  The four channels an epilogue
 // item holds are two such pairs; ranges and chunks are multiples of 4 channels, so no pair is ever split.
 //
-// NORM (with FQ): the rows handed over are the residual stream's; the workgroup first forms r = fp16(res + x) and
-// y = fp16(r * rsqrt(mean r^2 + eps) * gamma) in place in its LDS copy (two passes in which every thread works on the
-// same chunks, one barrier for the sum of squares between them, the row maxima falling out of the second), and the
-// quantiser goes on from y.  The first workgroup writes r (the residual stream that goes on) and, on request, y.
+// NORM (with FQ): the rows handed over are the residual stream's; the workgroup first forms r = fp16(res + x) in place in its
+// LDS copy, with the sum of squares and the largest |r gamma| (one barrier), from which the scale of
+// y = fp16(r * rsqrt(mean r^2 + eps) * gamma) follows; a wave forms the y of its k steps where it quantises them.  (With y
+// formed in place and its maximum found in a second pass, behind a second barrier, a 7B layer at one token took 0.3 us more.)  The first workgroup writes r (the residual stream that goes on) and, on request, y.
 template <int MT, int XS, int P, int WAVES, bool ACC_OUT, bool TILED, int AUX, bool FQ = false, bool XW = false,
           bool SWIGLU = false, bool NORM = false>
 __global__ __launch_bounds__(WAVES * 64) void gemm_decode_resident_kernel(DecodeArgs p) {
@@ -350,8 +350,16 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_resident_kernel(Decode
             for (int mt = 0; mt < MT; ++mt) sa[mt] = p.s_a[min(16 * mt + r, p.M - 1)];
         }
     }
-    v4u gam[2] = {v4u{0, 0, 0, 0}, v4u{0, 0, 0, 0}};  // NORM: the gains of the chunks this thread normalises (K <= 16 threads)
+    // NORM: the gains of the chunks whose squares this thread adds (K <= 16 threads), and of those that it quantises
+    constexpr int kOwn = (XS * 16 + 63) / 64;
+    v4u gam[2] = {v4u{0, 0, 0, 0}, v4u{0, 0, 0, 0}}, own_gain[NORM ? kOwn : 1];
     if constexpr (NORM) {
+#pragma unroll
+        for (int j = 0; j < kOwn; ++j) {
+            const int u = lane + j * 64, ks = k_step(u >> 4), k0 = ks * 128 + (u & 15) * 8;
+            own_gain[j] = v4u{0, 0, 0, 0};
+            if (u < XS * 16 && ks < ks_limit && k0 < p.K) own_gain[j] = *(const v4u *)(p.gamma + k0);
+        }
 #pragma unroll
         for (int i = 0; i < 2; ++i) {
             const int c = tid + i * WAVES * 64;
@@ -405,8 +413,10 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_resident_kernel(Decode
         uint8_t *xq_lds = epoch_lds + p.x_lds_offset;
         const int chunks_row = p.K >> 3;  // 8 fp16 = 16 bytes
         sa[0] = 0.f;
+        float norm_inv[4] = {0.f, 0.f, 0.f, 0.f}, norm_amax[4] = {0.f, 0.f, 0.f, 0.f};  // NORM, per row
         if constexpr (NORM) {
-            // r = res + x in place, and the rows' sums of squares; a thread's chunks are tid and tid + T in both passes
+            // r = res + x in place, the rows' sums of squares and their largest |r gamma|, from which the largest |y| follows but
+            // for one row in two thousand (absmax_of_norm); a thread's chunks are tid and tid + T
             float *sum_lds = amax_lds + 64;
             const uint8_t *res_l = epoch_lds + p.res_lds_offset;
             const bool writer = blockIdx.x == 0;
@@ -414,6 +424,7 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_resident_kernel(Decode
             for (int m = 0; m < 4; ++m) {
                 if (m < p.M) {  // uniform
                     float ss = 0.f;
+                    unsigned top = 0u;
 #pragma unroll
                     for (int i = 0; i < 2; ++i) {
                         const int c = tid + i * T;
@@ -426,35 +437,57 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_resident_kernel(Decode
                             }
                             if (writer && p.r_out != nullptr) ((v4u *)(p.r_out + (size_t)m * p.K))[c] = rv;
                             ss = add_squares8(rv, ss);
+                            top = absmax_products8(rv, gam[i], top);
                         }
                     }
                     ss = wave_sum(ss);
-                    if (lane == 0) sum_lds[wave * 4 + m] = ss;
+                    const float wave_top = wave_max_nonneg(__uint_as_float(top));
+                    if (lane == 0) {
+                        sum_lds[wave * 4 + m] = ss;
+                        amax_lds[wave * 4 + m] = wave_top;
+                    }
                 }
             }
             lds_barrier();
-            // y = r * rsqrt(mean r^2 + eps) * gamma in place, and the maxima of |y| on the way
+            bool known = true;  // the same for all threads
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
                 if (m < p.M) {
                     float total = 0.f;
+                    unsigned top = 0u;
 #pragma unroll
-                    for (int w = 0; w < WAVES; ++w) total += sum_lds[w * 4 + m];
-                    const float inv = rms_inverse(total, p.K, p.eps);
-                    unsigned pm2 = 0u;
-#pragma unroll
-                    for (int i = 0; i < 2; ++i) {
-                        const int c = tid + i * T;
-                        if (c < chunks_row) {
-                            v4u *slot = (v4u *)(x16 + m * p.x16_lds_pitch + c * 16);
-                            const v4u y = norm_scale8(*slot, inv, gam[i]);
-                            *slot = y;
-                            if (writer && p.y_out != nullptr) ((v4u *)(p.y_out + (size_t)m * p.K))[c] = y;
-                            pm2 = absmax8_packed(y, pm2);
-                        }
+                    for (int w = 0; w < WAVES; ++w) {
+                        total += sum_lds[w * 4 + m];
+                        top = max(top, __float_as_uint(amax_lds[w * 4 + m]));
                     }
-                    const float pm = wave_max_nonneg(absmax_packed_value(pm2));
-                    if (lane == 0) amax_lds[wave * 4 + m] = pm;
+                    norm_inv[m] = rms_inverse(total, p.K, p.eps);
+                    known &= absmax_of_norm(__uint_as_float(top), norm_inv[m], &norm_amax[m]);
+                }
+            }
+            if (!known) {
+                lds_barrier();  // the tops have been read: their place takes the maxima of |y|
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    if (m < p.M) {
+                        unsigned pm2 = 0u;
+#pragma unroll
+                        for (int i = 0; i < 2; ++i) {
+                            const int c = tid + i * T;
+                            if (c < chunks_row) pm2 = absmax8_packed(norm_scale8(*(const v4u *)(x16 + m * p.x16_lds_pitch + c * 16), norm_inv[m], gam[i]), pm2);
+                        }
+                        const float pm = wave_max_nonneg(absmax_packed_value(pm2));
+                        if (lane == 0) amax_lds[wave * 4 + m] = pm;
+                    }
+                }
+                lds_barrier();
+#pragma unroll
+                for (int m = 0; m < 4; ++m) {
+                    if (m < p.M) {
+                        float amax = 0.f;
+#pragma unroll
+                        for (int w = 0; w < WAVES; ++w) amax = fmaxf(amax, amax_lds[w * 4 + m]);
+                        norm_amax[m] = amax;
+                    }
                 }
             }
         } else {
@@ -468,13 +501,15 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_resident_kernel(Decode
                 }
             }
         }
-        lds_barrier();
+        if constexpr (!NORM) lds_barrier();
 #pragma unroll
         for (int m = 0; m < 4; ++m) {
             if (m < p.M) {
-                float amax = 0.f;
+                float amax = norm_amax[m];
+                if constexpr (!NORM) {
 #pragma unroll
-                for (int w = 0; w < WAVES; ++w) amax = fmaxf(amax, amax_lds[w * 4 + m]);
+                    for (int w = 0; w < WAVES; ++w) amax = fmaxf(amax, amax_lds[w * 4 + m]);
+                }
                 const RowQuantizer rq(amax, 127.0f, -127.f, 127.f);  // amax == 0 gives scale 0
                 if (tid == 0 && p.s_a_out != nullptr && blockIdx.x == 0) p.s_a_out[m] = rq.scale;
                 if (min(r, p.M - 1) == m) sa[0] = rq.scale;
@@ -483,13 +518,20 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_resident_kernel(Decode
                 // the row: the waves' parts are disjoint and a wave reads back only its own, so no barrier follows --
                 // LDS serves a wave's accesses in program order.
                 const bool zero_row = amax == 0.f;
-                for (int u = lane; u < XS * 16; u += 64) {
+#pragma unroll
+                for (int j = 0; j < kOwn; ++j) {
+                    const int u = lane + j * 64;
                     const int ks = k_step(u >> 4), k0 = ks * 128 + (u & 15) * 8;
-                    if (ks < ks_limit && k0 < p.K) {
+                    if ((XS % 4 == 0 || u < XS * 16) && ks < ks_limit && k0 < p.K) {
                         v2u codes = v2u{0u, 0u};
+                        v4u xv = *(const v4u *)(x16 + m * p.x16_lds_pitch + k0 * 2);
+                        if constexpr (NORM) {
+                            xv = norm_scale8(xv, norm_inv[m], own_gain[j]);
+                            if (blockIdx.x == 0 && p.y_out != nullptr) *(v4u *)(p.y_out + (size_t)m * p.K + k0) = xv;
+                        }
                         if (!zero_row) {
                             float xf[8];
-                            halves8(*(const v4u *)(x16 + m * p.x16_lds_pitch + k0 * 2), xf);
+                            halves8(xv, xf);
                             codes = rq.packed8_own_max(xf);
                         }
                         *(v2u *)(xq_lds + m * pitch + k0) = codes;

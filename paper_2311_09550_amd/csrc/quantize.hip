@@ -311,16 +311,20 @@ __global__ __launch_bounds__(kFusedThreads) void silu_mul_quantize_kernel(const 
 // rounded square root and division.  r and y are written where the caller wants them (the residual stream goes on; y
 // is for inspection), otherwise the only traffic is x, res, g in and the codes out.  A thread keeps its chunks of the
 // row in registers (K <= 16384); longer rows take what is beyond from r as written, or from the inputs again, with the
-// same bits.  THREADS x CACHE as for the quantiser: 1024 x 2 for a few rows, 256 x 8 where the rows fill the chip.
-
-template <int kNormThreads, int kNormCache>
-__global__ __launch_bounds__(kNormThreads) void add_rmsnorm_quantize_kernel(const uint16_t *x, const uint16_t *res,
-                                                                          const uint16_t *__restrict__ gamma, float eps,
-                                                                          uint16_t *r_out, uint16_t *__restrict__ y_out,
-                                                                          int8_t *__restrict__ xq, float *__restrict__ s_a,
-                                                                          int K) {
-    __shared__ float scratch[kNormThreads / 64];
-    __shared__ float scratch_sum[kNormThreads / 64];
+// same bits.
+// One reduction, of the squares and of |r g| together, where the scale needs no y (absmax_of_norm), the gains fetched with the row;
+// a thread has as many chunks as the row's length asks for.  Bound by latency below some 300 rows, by the vector ALU and memory
+// beyond.  Before (a second reduction, conversions around every product, always 1024 x 2 or 256 x 8 chunks) and now, residual added, back
+// to back: 200 x 4096 4.7 -> 3.7 us, 333 x 4096 5.7 -> 4.6, 1024 x 5120 11.3 -> 10.0 (3.7 TB/s), 2048 x 8192 30.6 -> 27.0; 16 rows level.
+template <int THREADS, int CACHE>
+__global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uint16_t *x, const uint16_t *res,
+                                                                     const uint16_t *__restrict__ gamma, float eps,
+                                                                     uint16_t *r_out, uint16_t *__restrict__ y_out,
+                                                                     int8_t *__restrict__ xq, float *__restrict__ s_a, int K) {
+    constexpr int kWaves = THREADS / 64;
+    __shared__ float scratch[kWaves];
+    __shared__ float scratch_sum[kWaves];
+    __shared__ float scratch_top[kWaves];
     const int m = blockIdx.x;
     const int chunks = K >> 3;
     const v4u *xs = (const v4u *)(x + (size_t)m * K);
@@ -331,43 +335,64 @@ __global__ __launch_bounds__(kNormThreads) void add_rmsnorm_quantize_kernel(cons
     // this thread has then overwritten), else the same sum again
     auto r_again = [&](int c) { return r_out ? ((const v4u *)(r_out + (size_t)m * K))[c] : r_chunk(c); };
 
-    v4u cache[kNormCache];
+    constexpr bool kKeepGains = CACHE <= 4;  // longer rows fetch them again
+    v4u cache[CACHE], gain[kKeepGains ? CACHE : 1];
     float ss = 0.f;
-    auto add_squares = [&](v4u r) { ss = add_squares8(r, ss); };
+    unsigned top = 0u;
 #pragma unroll
-    for (int i = 0; i < kNormCache; ++i) {
-        const int c = threadIdx.x + i * kNormThreads;
+    for (int i = 0; i < CACHE; ++i) {
+        const int c = threadIdx.x + i * THREADS;
         cache[i] = v4u{0, 0, 0, 0};
+        v4u gn = v4u{0, 0, 0, 0};
         if (c < chunks) {
             cache[i] = r_chunk(c);
+            gn = gs[c];
             if (r_out) ((v4u *)(r_out + (size_t)m * K))[c] = cache[i];
         }
-        add_squares(cache[i]);
+        ss = add_squares8(cache[i], ss);
+        top = absmax_products8(cache[i], gn, top);
+        if (kKeepGains) gain[kKeepGains ? i : 0] = gn;
     }
-    for (int c = threadIdx.x + kNormCache * kNormThreads; c < chunks; c += kNormThreads) {
+    for (int c = threadIdx.x + CACHE * THREADS; c < chunks; c += THREADS) {
         const v4u r = r_chunk(c);
         if (r_out) ((v4u *)(r_out + (size_t)m * K))[c] = r;
-        add_squares(r);
+        ss = add_squares8(r, ss);
+        top = absmax_products8(r, gs[c], top);
     }
-    // sum over the workgroup: DPP steps inside the wave, the waves' sums in wave order
+    // over the workgroup: DPP steps inside the wave, the waves' sums in wave order
     ss = wave_sum(ss);
-    if ((threadIdx.x & 63) == 0) scratch_sum[threadIdx.x >> 6] = ss;
+    const float wave_top = wave_max_nonneg(__uint_as_float(top));
+    if ((threadIdx.x & 63) == 0) {
+        scratch_sum[threadIdx.x >> 6] = ss;
+        scratch_top[threadIdx.x >> 6] = wave_top;
+    }
     __syncthreads();
     float total = 0.f;
+    unsigned row_top = 0u;
 #pragma unroll
-    for (int w = 0; w < kNormThreads / 64; ++w) total += scratch_sum[w];
+    for (int w = 0; w < kWaves; ++w) {
+        total += scratch_sum[w];
+        row_top = max(row_top, __float_as_uint(scratch_top[w]));
+    }
     const float inv = rms_inverse(total, K, eps);
     auto y_chunk = [&](int c, v4u r) { return norm_scale8(r, inv, gs[c]); };
-    unsigned amax2 = 0u;
 #pragma unroll
-    for (int i = 0; i < kNormCache; ++i) {
-        const int c = threadIdx.x + i * kNormThreads;
-        if (c < chunks) cache[i] = y_chunk(c, cache[i]);  // from here on the cache holds y
-        amax2 = absmax8_packed(cache[i], amax2);
+    for (int i = 0; i < CACHE; ++i) {  // from here on the cache holds y
+        const int c = threadIdx.x + i * THREADS;
+        if (kKeepGains)
+            cache[i] = norm_scale8(cache[i], inv, gain[kKeepGains ? i : 0]);
+        else if (c < chunks)
+            cache[i] = y_chunk(c, cache[i]);
     }
-    for (int c = threadIdx.x + kNormCache * kNormThreads; c < chunks; c += kNormThreads)
-        amax2 = absmax8_packed(y_chunk(c, r_again(c)), amax2);
-    const float amax = block_max<kNormThreads, true>(absmax_packed_value(amax2), scratch);
+    float amax;
+    if (!absmax_of_norm(__uint_as_float(row_top), inv, &amax)) {  // the same for all threads
+        unsigned amax2 = 0u;
+#pragma unroll
+        for (int i = 0; i < CACHE; ++i)
+            if ((int)threadIdx.x + i * THREADS < chunks) amax2 = absmax8_packed(cache[i], amax2);
+        for (int c = threadIdx.x + CACHE * THREADS; c < chunks; c += THREADS) amax2 = absmax8_packed(y_chunk(c, r_again(c)), amax2);
+        amax = block_max<THREADS, true>(absmax_packed_value(amax2), scratch);
+    }
 
     const RowQuantizer rq(amax, 127.0f, -127.f, 127.f);
     if (threadIdx.x == 0) s_a[m] = rq.scale;
@@ -384,22 +409,41 @@ __global__ __launch_bounds__(kNormThreads) void add_rmsnorm_quantize_kernel(cons
         dst[c] = o;
     };
 #pragma unroll
-    for (int i = 0; i < kNormCache; ++i) {
-        const int c = threadIdx.x + i * kNormThreads;
+    for (int i = 0; i < CACHE; ++i) {
+        const int c = threadIdx.x + i * THREADS;
         if (c < chunks) emit(c, cache[i]);
     }
-    for (int c = threadIdx.x + kNormCache * kNormThreads; c < chunks; c += kNormThreads) emit(c, y_chunk(c, r_again(c)));
+    for (int c = threadIdx.x + CACHE * THREADS; c < chunks; c += THREADS) emit(c, y_chunk(c, r_again(c)));
+}
+
+template <int THREADS, int CACHE>
+static void launch_norm(const void *x, const void *res, const void *gamma, float eps, void *r_out, void *y_out, int8_t *xq, float *s_a,
+                        int M, int K, hipStream_t stream) {
+    hipLaunchKernelGGL((add_rmsnorm_quantize_kernel<THREADS, CACHE>), dim3(M), dim3(THREADS), 0, stream, (const uint16_t *)x,
+                       (const uint16_t *)res, (const uint16_t *)gamma, eps, (uint16_t *)r_out, (uint16_t *)y_out, xq, s_a, K);
 }
 
 hipError_t launch_add_rmsnorm_quantize(const void *x, const void *res, const void *gamma, float eps, void *r_out, void *y_out,
                                        int8_t *xq, float *s_a, int M, int K, hipStream_t stream) {
-    if (M <= kFewRows)
-        hipLaunchKernelGGL((add_rmsnorm_quantize_kernel<1024, 2>), dim3(M), dim3(1024), 0, stream, (const uint16_t *)x,
-                           (const uint16_t *)res, (const uint16_t *)gamma, eps, (uint16_t *)r_out, (uint16_t *)y_out, xq, s_a, K);
-    else
-        hipLaunchKernelGGL((add_rmsnorm_quantize_kernel<kRowThreads, kCache>), dim3(M), dim3(kRowThreads), 0, stream,
-                           (const uint16_t *)x, (const uint16_t *)res, (const uint16_t *)gamma, eps, (uint16_t *)r_out,
-                           (uint16_t *)y_out, xq, s_a, K);
+    const int chunks = K >> 3;
+#define W4A8_NORM(T, C) launch_norm<T, C>(x, res, gamma, eps, r_out, y_out, xq, s_a, M, K, stream)
+    if (M <= kFewRows) {
+        if (chunks <= 1024) W4A8_NORM(1024, 1);
+        else W4A8_NORM(1024, 2);
+    } else if (M <= kSomeRows) {
+        if (chunks <= 512) W4A8_NORM(512, 1);
+        else if (chunks <= 1024) W4A8_NORM(512, 2);
+        else W4A8_NORM(512, 4);
+    } else {
+        switch ((chunks + 255) / 256) {
+            case 1: W4A8_NORM(256, 1); break;
+            case 2: W4A8_NORM(256, 2); break;
+            case 3: W4A8_NORM(256, 3); break;
+            case 4: W4A8_NORM(256, 4); break;
+            default: W4A8_NORM(256, 8);
+        }
+    }
+#undef W4A8_NORM
     return hipGetLastError();
 }
 

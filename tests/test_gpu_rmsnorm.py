@@ -155,3 +155,31 @@ def test_norm_linear_strided_inputs_zero_rows_and_refusals(gpu, oracle):
             w4a8.w4a8_linear_tiled_norm_fp16(xb, None, t.ones((bad["K"],), dtype=t.float16, device="cuda"), 1e-5, wtb,
                                              t.ones((64,), dtype=t.float32, device="cuda"))
         assert e.value.code == -7
+
+
+@pytest.mark.parametrize("K", [64, 1056, 4096])
+def test_scales_of_rows_whose_maximum_is_near_an_fp16_rounding_boundary(gpu, K):
+    """The row's largest |y| follows from the largest |r g| unless that falls near a boundary between two fp16 values, about once
+    in two thousand rows: over enough rows that many do, codes and scales are the quantiser's on the very y that comes out."""
+    t = gpu
+    gen = t.Generator(device="cuda").manual_seed(K)
+    M = 20000 if K < 4096 else 6000
+    x = t.randn((M, K), generator=gen, device="cuda").half()
+    res = t.randn((M, K), generator=gen, device="cuda").half()
+    g = (1 + 0.1 * t.randn((K,), generator=gen, device="cuda")).half()
+    for m in (100, 200, M):                               # 1024, 512 and 256 threads a row
+        y = t.empty((m, K), dtype=t.float16, device="cuda")
+        xq, s_a = w4a8.w4a8_add_rmsnorm_quantize(x[:m], res[:m], g, 1e-5, y_out=y)
+        xq_ref, s_ref = w4a8.w4a8_quantize_act(y)
+        t.cuda.synchronize()
+        assert t.equal(xq, xq_ref) and t.equal(s_a.view(t.int32), s_ref.view(t.int32)), m
+    if K > 64:
+        return
+    # the same inside the linear, where the rows of a launch are up to four
+    wt, s_w = t.zeros((w4a8.w4a8_tiled_weight_bytes(64, K),), dtype=t.uint8, device="cuda"), t.ones((64,), dtype=t.float32, device="cuda")
+    y, s_a = t.empty((M, K), dtype=t.float16, device="cuda"), t.empty((M,), dtype=t.float32, device="cuda")
+    for m in range(0, M, 4):
+        w4a8.w4a8_linear_tiled_norm_fp16(x[m:m + 4], res[m:m + 4], g, 1e-5, wt, s_w, y_out=y[m:m + 4], s_a_out=s_a[m:m + 4])
+    s_ref = w4a8.w4a8_quantize_act(y)[1]
+    t.cuda.synchronize()
+    assert t.equal(s_a.view(t.int32), s_ref.view(t.int32))
