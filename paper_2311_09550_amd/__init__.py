@@ -9,6 +9,7 @@ has not been built (``python -m paper_2311_09550_amd.build`` or
 from __future__ import annotations
 
 import ctypes
+import functools
 import os
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
@@ -117,33 +118,48 @@ def _check(code: int):
         raise W4A8Error(code, lib().w4a8_strerror(code).decode() + detail)
 
 
+_torch_module = None
+_current_device = None  # () -> ordinal of torch's current device
+_raw_stream = None      # ordinal -> handle of torch's current stream on that device
+
+
 def _torch():
-    import torch
-    return torch
+    """torch, imported on first use.  The two queries that every call makes go to torch's own C functions where it has them:
+    torch.cuda.current_stream builds a Stream object for each answer, most of what a small call used to cost."""
+    global _torch_module, _current_device, _raw_stream
+    if _torch_module is None:
+        import torch
+        _current_device = getattr(torch._C, "_cuda_getDevice", None) or torch.cuda.current_device
+        _raw_stream = (getattr(torch._C, "_cuda_getCurrentRawStream", None)
+                       or (lambda index: torch.cuda.current_stream(index).cuda_stream))
+        _torch_module = torch
+    return _torch_module
 
 
 def _stream():
     """torch's current stream on the current device: the library launches on the device that is current when it is
     called, and `_on_current_device` holds every tensor argument to that device."""
-    torch = _torch()
-    return ctypes.c_void_p(torch.cuda.current_stream(torch.cuda.current_device()).cuda_stream)
+    _torch_module or _torch()
+    return _raw_stream(_current_device())
 
 
 def _on_current_device(t, what):
-    torch = _torch()
+    _torch()
     if not t.is_cuda:
         raise TypeError(f"{what}: expected a device tensor")
-    if t.device.index != torch.cuda.current_device():
-        raise ValueError(f"{what} is on {t.device} but the current device is cuda:{torch.cuda.current_device()}: "
+    current = _current_device()
+    if t.get_device() != current:
+        raise ValueError(f"{what} is on {t.device} but the current device is cuda:{current}: "
                          "call under torch.cuda.device(...) of the tensors' device")
 
 
 def _dev(t, dtype, what):
-    torch = _torch()
+    torch = _torch_module or _torch()
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()):
         raise TypeError(f"{what}: expected a contiguous device tensor of {dtype}")
-    _on_current_device(t, what)
-    return ctypes.c_void_p(t.data_ptr())
+    if t.get_device() != _current_device():
+        _on_current_device(t, what)
+    return t.data_ptr()
 
 
 def _shaped(t, shape, what):
@@ -169,10 +185,10 @@ def bound_call(name: str, *args):
         raise ValueError(f"{name}: the tensors are on different devices")
     device = keep[0].device if keep else torch.device("cuda", torch.cuda.current_device())
     cargs = [ctypes.c_void_p(a.data_ptr()) if isinstance(a, torch.Tensor) else a for a in args]
-    current_stream = torch.cuda.current_stream
+    raw_stream, index = _raw_stream, device.index
 
     def call(_keep=keep):
-        code = fn(*cargs, ctypes.c_void_p(current_stream(device).cuda_stream))
+        code = fn(*cargs, raw_stream(index))
         if code != 0:
             _check(code)
     return call
@@ -231,7 +247,7 @@ def workspace(M: int, N: int, K: int, device=None):
     torch = _torch()
     device = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
     need = max(w4a8_gemm_workspace_bytes(M, N, K), 256)
-    key = (device.index, torch.cuda.current_stream(device).cuda_stream)
+    key = (device.index, _raw_stream(device.index))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < need:
         ws = torch.zeros(need, dtype=torch.uint8, device=device)
@@ -326,6 +342,7 @@ def w4a8_gemm_tuned(xq, s_a, wp, s_w, tiling: int, variant: int = 0, want_acc: b
     return out
 
 
+@functools.lru_cache(maxsize=256)  # a function of the shape alone, asked for on every call over tiled weights
 def w4a8_tiled_weight_bytes(N: int, K: int) -> int:
     return int(lib().w4a8_tiled_weight_bytes(N, K))
 
@@ -359,6 +376,7 @@ def w4a8_gemm_tiled(xq, s_a, wt, s_w, out=None):
     return out
 
 
+@functools.lru_cache(maxsize=256)
 def w8a8_tiled_weight_bytes(N: int, K: int) -> int:
     return int(lib().w8a8_tiled_weight_bytes(N, K))
 
@@ -486,7 +504,8 @@ def w4a8_linear_tiled_fp16(x, wt, s_w, out=None, s_a_out=None):
     torch = _torch()
     M, K = x.shape
     N = s_w.shape[0]
-    if not (x.is_cuda and x.dtype == torch.float16 and x.stride(1) == 1):
+    ldx, unit = x.stride()
+    if not (x.is_cuda and x.dtype == torch.float16 and unit == 1):
         raise TypeError("x: expected a device fp16 view with unit column stride")
     _on_current_device(x, "x")
     if wt.numel() != w4a8_tiled_weight_bytes(N, K):
@@ -496,7 +515,7 @@ def w4a8_linear_tiled_fp16(x, wt, s_w, out=None, s_a_out=None):
         raise ValueError("out shape mismatch")
     if s_a_out is not None and tuple(s_a_out.shape) != (M,):
         raise ValueError("s_a_out shape mismatch")
-    _check(lib().w4a8_linear_tiled_fp16(ctypes.c_void_p(x.data_ptr()), x.stride(0), _dev(wt, torch.uint8, "wt"),
+    _check(lib().w4a8_linear_tiled_fp16(x.data_ptr(), ldx, _dev(wt, torch.uint8, "wt"),
                                         _dev(s_w, torch.float32, "s_w"), _dev(out, torch.float16, "out"),
                                         None if s_a_out is None else _dev(s_a_out, torch.float32, "s_a_out"), M, N, K,
                                         _stream()))

@@ -1047,13 +1047,19 @@ int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *til
 unsigned long long w4a8_plans_made(void) { return plans_made; }
 
 int w4a8_init(void) {
+    // some four hundred kernels, each asked for once per device: a caller may call this before every set-up of a layer
+    static std::atomic<bool> done[kMaxDevices];
+    int dev = 0;
+    if (hipGetDevice(&dev) == hipSuccess && dev >= 0 && dev < kMaxDevices && done[dev].load(std::memory_order_acquire)) return W4A8_OK;
     void *ws = nullptr;
     if (int e = static_scratch(&ws)) return e;
     (void)compute_units();
     if (int e = launched(prepare_tiled_kernels())) return e;
     if (int e = launched(prepare_row_kernels())) return e;
     if (int e = launched(prepare_medium_kernels())) return e;
-    return launched(prepare_decode_kernels());
+    if (int e = launched(prepare_decode_kernels())) return e;
+    done[dev].store(true, std::memory_order_release);  // static_scratch has seen to the device's number
+    return W4A8_OK;
 }
 
 // ---- W8A8 comparison variant: int8 weight codes in the tiled layout, the same kernels without the int4 conversion
