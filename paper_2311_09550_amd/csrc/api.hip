@@ -94,14 +94,28 @@ bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool
 //              (measured on LLaMA-7B/13B/70B shapes, cold weights: within 4 % of the best grid everywhere; ranges of
 //              20 or 24 channels, i.e. chunks of 12, lose up to 13 % to ranges of 32 on fewer compute units);
 //   prefetch : chunks of weight loads a wave keeps in flight, 0 = library's choice: one, since a compute unit takes
-//              only some 40 to 50 outstanding wave-wide loads and one chunk per wave already is that many; two where a
-//              range is exactly two chunks and M <= 8 (everything is then requested at once: 4 to 5 % on 13B's O;
-//              level at 16 tokens, slower on every other shape tried);
+//              only some 40 to 50 outstanding wave-wide loads and one chunk per wave mostly is that many; two by
+//              two_chunks_ahead, among others where a range is exactly two chunks and M <= 8 (everything is then requested at
+//              once: 4 to 5 % on 13B's O; level at 16 tokens);
 //   whole16  : chunks of 16 channels even where the range does not divide evenly;
 //   aux      : cache policy of the weight loads, -1 = library's choice (non-temporal: 5 to 10 % faster);
 //   k_slices : workgroups along K (raw sums only when more than one);
 //   x_window : every wave stages its own k steps (tiled weights, 17 to 64 tokens).  Then waves = 0 means 16 waves for
 //              two column tiles when their k steps fit, else 8.
+// Whether a wave asks for two chunks ahead.  One chunk of all waves should be the 32 or more loads that keep a compute unit
+// busy; where it is fewer, a second one is worth the slot that it wastes at the end of an odd number of chunks.  Tiled weights, one
+// token, cold, one chunk ahead and two: 32768 x 1024 8.06 us and 5.66, 32000 x 2048 9.17 and 7.35, 24576 x 3072 8.50 and 7.93,
+// 22016 x 4096 9.29 and 9.08; but 12288 x 4096 (three chunks) 6.12 and 6.49, 27648 x 5120 12.96 and 13.54.  Row-major 32768 x 1024
+// 8.75 and 6.07, 32000 x 2048 10.3 and 8.3, but 17216 x 4000 11.5 and 11.9.  With three and four column tiles 64 tokens of 24576 x 3072 take 11.4 and 12.6, 32000 x 2048
+// 12.4 and 11.1.  The norm in front takes long enough for two chunks to arrive: 12288 x 4096 7.70 and 7.30, 22016 x 4096 10.8 and 9.9
+// (10240 x 8192, eight steps a wave: 10.6 and 11.4).
+bool two_chunks_ahead(const DecodeShape &s, int chunks, int M, int mt) {
+    const int loads = s.waves * s.x_steps;
+    if (chunks == 2 && M <= 8) return true;
+    if (chunks >= 2 && (loads <= 8 || (s.norm && loads <= 32))) return true;
+    return chunks >= 4 && loads <= (mt <= 2 && s.tiled ? 32 : 16);
+}
+
 bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool whole16, int aux, bool tiled, DecodeShape *out,
                     int k_slices, bool x_window) {
     const int mt = (M + 15) / 16;
@@ -146,7 +160,7 @@ bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool
     s.chunk_rows = whole16 ? 16 : (((rows + chunks - 1) / chunks + 3) & ~3);
     s.prefetch = prefetch;
     if (prefetch == 0) {
-        s.prefetch = (chunks == 2 && M <= 8) ? 2 : 1;
+        s.prefetch = two_chunks_ahead(s, chunks, M, mt) ? 2 : 1;
         if (s.prefetch == 2 && !decode_resident_supported(M, N, K, s)) s.prefetch = 1;
     }
     if (!decode_resident_supported(M, N, K, s)) return false;
