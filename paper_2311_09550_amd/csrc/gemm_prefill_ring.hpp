@@ -338,7 +338,7 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
 
     // Two schedules.  Ring of two: stage st + 2 can only be requested once stage st has been read, i.e. in one burst
     // behind the barrier of stage st.  Ring of three or more (kSpread): the slot freed by the barrier of stage st - 1
-    // is refilled with stage st + STAGES - 1 load by load, between the MFMAs of stage st; a burst of loads right
+    // is refilled with stage st + STAGES - 1 load by load, between the MFMAs up to the next barrier; a burst of loads right
     // behind the barrier holds up the issuing wave for as long as the address unit needs to take them (measured: a
     // fifth of the loop time), spread out they cost an issue slot each.
     // Loads return in order, so "at most n outstanding" means all but the youngest n have landed; waiting for fewer
@@ -406,9 +406,15 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
         // One stage: kBlocks blocks of MFMAs, each reading the activation fragments of the block behind it; the scheduling
         // fences keep those reads in front of the MFMAs they overlap with (left alone the compiler sinks them next to
         // their first use and every block then starts with an exposed LDS wait).  A weight fragment is replaced by its
-        // successor right behind its last MFMAs.  TARGET: there is a stage left to request.
-        auto stage = [&](int st, auto target_c) {
-            constexpr bool TARGET = decltype(target_c)::value;
+        // successor right behind its last MFMAs.  TARGET: there is a stage left to request; EARLY: behind the barrier, one more.
+        // Where load j of a target stage is issued: places 0 .. NT - 1 are the channel tiles of the last block, behind the barrier,
+        // then come those of the other blocks.  With two blocks both take loads (N = 5120, K = 13824, M = 1024 as 128 x 192: 71.5 us
+        // with all of them in the first, 69.2 so; N = 15360, K = 5120, M = 128 as 64 x 128: 17.5 and 16.7); with four, three are enough
+        // (256 x 256 level, 192 x 320 over row-major weights 1 % slower).
+        constexpr int kFirstPlace = kBlocks == 2 ? 0 : NT;
+        constexpr auto place = [](int j) { return kFirstPlace + j * (kBlocks * NT - kFirstPlace) / kLoads; };
+        auto stage = [&](int st, auto target_c, auto early_c) {
+            constexpr bool TARGET = decltype(target_c)::value, EARLY = decltype(early_c)::value;
             const int next = slot + 1 == STAGES ? 0 : slot + 1;
             const int prev = slot == 0 ? STAGES - 1 : slot - 1;
 #pragma unroll
@@ -432,13 +438,12 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
                 __builtin_amdgcn_sched_barrier(0);
                 const bool step_ends = m0 + XF == MT;
                 mfma_block(x, xn, w, h, m0, FG && h == 0, m0 == 0, step_ends ? 1 - h : -1, [&](int t) {
-                    // loads of the target stage, evenly over the channel tiles of every block but the last
-                    if constexpr (kSpread && TARGET) {
-                        constexpr int kPlaces = (kBlocks - 1) * NT;
-                        if (!last) {
+                    // Loads of a target stage, evenly between two barriers: the last block's has freed this stage's slot.
+                    if constexpr (kSpread) {
 #pragma unroll
-                            for (int j = 0; j < kLoads; ++j)
-                                if (j * kPlaces / kLoads == b * NT + t) issue(st + STAGES - 1, prev, j, kLoads);
+                        for (int j = 0; j < kLoads; ++j) {
+                            if (last ? EARLY && place(j) == t : TARGET && place(j) == (b + 1) * NT + t)
+                                issue(last ? st + STAGES : st + STAGES - 1, last ? slot : prev, j, kLoads);
                         }
                     }
                     if (step_ends) {
@@ -464,8 +469,16 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
         };
         const int with_target = st_total - (kSpread ? STAGES - 1 : STAGES);
         int st = 0;
-        for (; st < with_target; ++st) stage(st, std::true_type{});
-        for (; st < st_total; ++st) stage(st, std::false_type{});
+        if constexpr (kSpread) {
+            if (with_target > 0) {  // what a stage before the first would have requested behind its barrier
+#pragma unroll
+                for (int j = 0; j < kLoads; ++j)
+                    if (place(j) < NT) issue(STAGES - 1, STAGES - 1, j, kLoads);
+            }
+            for (; st + 1 < with_target; ++st) stage(st, std::true_type{}, std::true_type{});
+        }
+        for (; st < with_target; ++st) stage(st, std::true_type{}, std::false_type{});
+        for (; st < st_total; ++st) stage(st, std::false_type{}, std::false_type{});
     }
     wait_vmcnt<0>();
 
