@@ -669,8 +669,8 @@ def time_paper_table5(torch, w4a8, synth, iters=5):
 def time_w4_vs_w8(torch, w4a8, synth, model="13b", Ms=(16, 1024), iters=4):
     """The paper sets its W4A8 against its own W8A8 (Table 4) and its signed storage against the vanilla unsigned one
     ("Asym GEMM", Sec. 7.2) and the fine-grained recipe (group scales, Eq. (5)).  Here, per GEMM: the same large-M kernel
-    over tiled int4 (signed), tiled unsigned int4, signed int4 with group scales, and tiled int8 weights of the same
-    fp16 matrix, every launch on a different weight copy (copies exceed the last-level
+    over tiled int4 (signed), tiled unsigned int4, signed int4 with group scales, and, by its entry's own choice (the large-M
+    kernel at 1024 tokens, the medium-M kernel at 16 for the narrower outputs), tiled int8 weights of the same fp16 matrix, every launch on a different weight copy (copies exceed the last-level
     cache three times, so weights come from HBM), batches replayed from a HIP graph."""
     rows = []
     for name, (N, K) in synth.LLAMA_SHAPES[model].items():
@@ -691,7 +691,7 @@ def time_w4_vs_w8(torch, w4a8, synth, model="13b", Ms=(16, 1024), iters=4):
             x = torch.from_numpy(synth.activations_fp16(M, K, config_id=3, tag=4)).cuda()
             xq, s_a = w4a8.w4a8_quantize_act(x)
             out = torch.empty((M, N), dtype=torch.float16, device="cuda")
-            # all four through the same kernel (the large-M one with the library's tile for the shape), also at M = 16,
+            # the int4 formats through the same kernel (the large-M one with the library's tile for the shape), also at M = 16,
             # where w4a8_gemm_tiled itself would hand the signed format to the weight-streaming kernel
             calls = {4: lambda t: w4a8.w4a8_gemm_tuned(xq, s_a, t, s_w4, w4a8.TILING_PREFILL_TILED, 0, N=N, out=out),
                      "u4": lambda t: w4a8.w4a8_gemm_tiled_unsigned(xq, s_a, t, s_w4, out=out),

@@ -127,10 +127,10 @@ int w4a8_gemm_acc_i32(const int8_t *xq, const uint8_t *wp, int32_t *acc, int M, 
  * w4a8_gemm_tiled: w4a8_gemm over wt instead of wp (all other arguments as there).  Every M is accepted, and one
  *   copy of the weights, the tiled one, serves them all: up to 16 tokens (token generation) the weight-streaming kernels
  *   read wt directly; from 17 to 64 tokens, where all of K fits the registers of a workgroup (K <= 5120 for 33 to 64
- *   tokens, K <= 8192 for 17 to 32), one of them or the large-M kernel, whichever is estimated to be the faster;
- *   above that, and for a longer K, the large-M kernel
+ *   tokens, K <= 8192 for 17 to 32), one of them, the medium-M kernel or the large-M kernel, whichever is estimated to be the
+ *   fastest; above that, and for a longer K, the medium-M or the large-M kernel
  *   (w4a8_gemm_tiled_splitk, which has a workspace, can cut a longer K into slices that the weight-streaming kernel
- *   takes, and fills the chip with slices of the large-M kernel at a few hundred rows).  w4a8_gemm serves every M from
+ *   takes, or into slices of the large-M kernel at a few hundred rows).  w4a8_gemm serves every M from
  *   the row-major array, at up to 2.3 times the time of the better of these two for M between 17 and 512.
  */
 size_t w4a8_tiled_weight_bytes(int N, int K);
@@ -280,7 +280,7 @@ int w4a8_init(void);
  * W8A8 comparison variant (the paper sets its W4A8 against its own W8A8, Table 4): the same contraction and the
  * same epilogue (Eq. (6),(7)) with int8 weight codes,
  *   O[m][n] = fp16( float( sum_k Xq[m][k] * W8[n][k] ) * (s_a[m] * s_w[n]) ),   W8 in [-128, 127],
- * run by the large-M kernel without the int4 conversion.  Per-channel 8-bit weights (Eq. (8),(9) with 8 bits,
+ * run by the medium-M and large-M kernels without the int4 conversion.  Per-channel 8-bit weights (Eq. (8),(9) with 8 bits,
  * gamma = beta = 1: s_w = absmax / 127) are what w4a8_quantize_act computes when given the weight matrix as its
  * rows, so there is no separate weight quantiser.
  *   Layout of wt: 4096-byte blocks; block (nb, kb), nb = n / 32, kb = k / 128, starts at ((nb * KB) + kb) * 4096,

@@ -50,8 +50,9 @@ extern "C" {
 #define W4A8_TILING_PREFILL_TILED 4   /* the same over the tiled weight layout (any M; meant for large M)  */
 #define W4A8_TILING_DECODE_RESIDENT_TILED 5 /* tilings 1 and 2 reading the TILED weight array (`wp` = wt);        */
 #define W4A8_TILING_DECODE_STREAM_TILED 6   /* same limits and variants as 1 and 2                                 */
-#define W4A8_TILING_AUTO_TILED 7      /* library's choice over the TILED array: 5 or 6 up to M = 16, 5 with flag 16
-                                         or 4 up to M = 64 where K allows both, 4 otherwise                  */
+#define W4A8_TILING_AUTO_TILED 7      /* library's choice over the TILED array: 5 or 6 up to M = 16, beyond, the
+                                         cheapest by estimate of 5 with flag 16 (up to M = 64, where K allows
+                                         it), 4 and the medium-M kernel, which cannot be forced              */
 int w4a8_gemm_tuned(const int8_t *xq, const float *s_a, const uint8_t *wp, const float *s_w,
                     void *out_fp16, int32_t *acc_i32, int M, int N, int K,
                     int tiling, int variant,
