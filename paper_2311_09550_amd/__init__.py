@@ -345,7 +345,9 @@ def w4a8_gemm_tuned(xq, s_a, wp, s_w, tiling: int, variant: int = 0, want_acc: b
     return out
 
 
-@functools.lru_cache(maxsize=256)  # a function of the shape alone, asked for on every call over tiled weights
+# A function of the shape alone, asked for on every call over tiled weights.  typed: 4096.0 equals 4096, and must not be answered
+# from its entry when ctypes refuses it.
+@functools.lru_cache(maxsize=256, typed=True)
 def w4a8_tiled_weight_bytes(N: int, K: int) -> int:
     return int(lib().w4a8_tiled_weight_bytes(N, K))
 
@@ -379,7 +381,7 @@ def w4a8_gemm_tiled(xq, s_a, wt, s_w, out=None):
     return out
 
 
-@functools.lru_cache(maxsize=256)
+@functools.lru_cache(maxsize=256, typed=True)
 def w8a8_tiled_weight_bytes(N: int, K: int) -> int:
     return int(lib().w8a8_tiled_weight_bytes(N, K))
 

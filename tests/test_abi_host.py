@@ -189,6 +189,17 @@ def test_tiled_weight_bytes_counts_whole_blocks(L):
     assert f(16, 48) == 0 and f(0, 128) == 0              # outside the contract
 
 
+@pytest.mark.parametrize("f", [w4a8.w4a8_tiled_weight_bytes, w4a8.w8a8_tiled_weight_bytes])
+def test_tiled_weight_bytes_refuses_what_is_no_whole_number_also_after_it_was_asked(L, f):
+    """The sizes are remembered, and 4096.0 equals 4096: what was refused before the first call stays refused behind it."""
+    for asked in (False, True):
+        if asked:
+            assert f(4096, 4096) == f(N=4096, K=4096) == f(np.int64(4096), 4096)
+        for bad in ((4096.0, 4096), (4096, 4096.0), ("4096", 4096), (None, 4096)):
+            with pytest.raises(ctypes.ArgumentError):
+                f(*bad)
+
+
 def test_host_packing_matches_oracle_and_rejects_bad_codes(L, oracle):
     _, wq, _, _ = synth.uniform_codes(2, 64, 96)
     assert np.array_equal(w4a8.w4a8_pack_weights_host(wq), oracle.pack_w4(wq))
