@@ -307,23 +307,27 @@ __global__ __launch_bounds__(kFusedThreads) void silu_mul_quantize_kernel(const 
 // front of it, Sec. 6.1; the norm is LLaMA's):
 //   r = fp16(fp32(res) + fp32(x))  (r = x without a residual),  y = fp16(fp32(r) * rsqrt(mean r^2 + eps) * fp32(g)),
 //   (xq, s_a) = the per-token quantiser of quantize_act_kernel applied to y.
-// The mean of squares is an fp32 sum (per thread, then over the workgroup), the reciprocal square root a correctly
-// rounded square root and division.  r and y are written where the caller wants them (the residual stream goes on; y
+// The mean of squares is an fp32 sum (per thread, then over the workgroup), the reciprocal square root the hardware's
+// square root (within one ulp) and a correctly rounded division.  r and y are written where the caller wants them (the residual stream goes on; y
 // is for inspection), otherwise the only traffic is x, res, g in and the codes out.  A thread keeps its chunks of the
 // row in registers (K <= 16384); longer rows take what is beyond from r as written, or from the inputs again, with the
 // same bits.
-// One reduction, of the squares and of |r g| together, where the scale needs no y (absmax_of_norm), the gains fetched with the row;
-// a thread has as many chunks as the row's length asks for.  Bound by latency below some 300 rows, by the vector ALU and memory
-// beyond.  Before (a second reduction, conversions around every product, always 1024 x 2 or 256 x 8 chunks) and now, residual added, back
-// to back: 200 x 4096 4.7 -> 3.7 us, 333 x 4096 5.7 -> 4.6, 1024 x 5120 11.3 -> 10.0 (3.7 TB/s), 2048 x 8192 30.6 -> 27.0; 16 rows level.
-template <int THREADS, int CACHE>
+// One reduction, of the squares and of |r g| together, where the scale needs no y (absmax_of_norm), the gain requested behind the
+// chunk it belongs to; a thread has as many chunks as the row's length asks for.  Bound by latency below some 300 rows, by the vector
+// ALU and memory beyond.  With two reductions, conversions around every product and always 1024 x 2 or 256 x 8 chunks, and now,
+// residual added, back to back: 200 x 4096 4.7 -> 3.6 us, 333 x 4096 5.6 -> 4.5, 1024 x 5120 11.2 -> 9.9 (3.7 TB/s), 2048 x 8192 30.6 -> 27.0.
+// Few rows: the order of the sum is that of 1024 threads, but up to K = 8192 on 512 of them, chain q of a thread being the thread
+// 512 q further on; half the waves, and none with nothing to do.  On 1024 threads one reduction was slower than two, without a residual
+// above all (16 x 8192 3.8 us with two, 4.1 with one, 3.6 so; 1 x 8192 3.5, 3.85, 3.3; with the residual 16 x 5120 3.8, 3.8, 3.5).
+// Tried: requesting x, residual and gains of all chunks ahead of the first sum: level up to 128 rows, 3 to 6 % slower beyond.
+template <int THREADS, int CACHE, int CHAINS = 1>
 __global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uint16_t *x, const uint16_t *res,
                                                                      const uint16_t *__restrict__ gamma, float eps,
                                                                      uint16_t *r_out, uint16_t *__restrict__ y_out,
                                                                      int8_t *__restrict__ xq, float *__restrict__ s_a, int K) {
     constexpr int kWaves = THREADS / 64;
     __shared__ float scratch[kWaves];
-    __shared__ float scratch_sum[kWaves];
+    __shared__ float scratch_sum[CHAINS * kWaves];
     __shared__ float scratch_top[kWaves];
     const int m = blockIdx.x;
     const int chunks = K >> 3;
@@ -335,9 +339,12 @@ __global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uin
     // this thread has then overwritten), else the same sum again
     auto r_again = [&](int c) { return r_out ? ((const v4u *)(r_out + (size_t)m * K))[c] : r_chunk(c); };
 
-    constexpr bool kKeepGains = CACHE <= 4;  // longer rows fetch them again
+    constexpr bool kKeepGains = CACHE <= 6;  // longer rows fetch them again
+    // Waves past the row's end skip the arithmetic, which leaves its issue slots to the others, where the rows are few (16 x 12288
+    // 4.5 -> 4.3 us); with many rows the branches cost 20 % at K = 9216.
+    constexpr bool kSkip = CHAINS > 1 || THREADS == 1024;
     v4u cache[CACHE], gain[kKeepGains ? CACHE : 1];
-    float ss = 0.f;
+    float ss[CHAINS] = {};
     unsigned top = 0u;
 #pragma unroll
     for (int i = 0; i < CACHE; ++i) {
@@ -349,36 +356,44 @@ __global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uin
             gn = gs[c];
             if (r_out) ((v4u *)(r_out + (size_t)m * K))[c] = cache[i];
         }
-        ss = add_squares8(cache[i], ss);
+        if (kSkip && c >= chunks) continue;
+        ss[i % CHAINS] = add_squares8(cache[i], ss[i % CHAINS]);
         top = absmax_products8(cache[i], gn, top);
         if (kKeepGains) gain[kKeepGains ? i : 0] = gn;
     }
-    for (int c = threadIdx.x + CACHE * THREADS; c < chunks; c += THREADS) {
-        const v4u r = r_chunk(c);
-        if (r_out) ((v4u *)(r_out + (size_t)m * K))[c] = r;
-        ss = add_squares8(r, ss);
-        top = absmax_products8(r, gs[c], top);
-    }
-    // over the workgroup: DPP steps inside the wave, the waves' sums in wave order
-    ss = wave_sum(ss);
+    for (int c0 = threadIdx.x + CACHE * THREADS; c0 < chunks; c0 += CHAINS * THREADS)
+#pragma unroll
+        for (int q = 0; q < CHAINS; ++q) {
+            const int c = c0 + q * THREADS;
+            if (c < chunks) {
+                const v4u r = r_chunk(c);
+                if (r_out) ((v4u *)(r_out + (size_t)m * K))[c] = r;
+                ss[q] = add_squares8(r, ss[q]);
+                top = absmax_products8(r, gs[c], top);
+            }
+        }
+    // over the workgroup: DPP steps inside the wave, the waves' sums in wave order, chain by chain
+#pragma unroll
+    for (int q = 0; q < CHAINS; ++q) ss[q] = wave_sum(ss[q]);
     const float wave_top = wave_max_nonneg(__uint_as_float(top));
     if ((threadIdx.x & 63) == 0) {
-        scratch_sum[threadIdx.x >> 6] = ss;
+#pragma unroll
+        for (int q = 0; q < CHAINS; ++q) scratch_sum[q * kWaves + (threadIdx.x >> 6)] = ss[q];
         scratch_top[threadIdx.x >> 6] = wave_top;
     }
     __syncthreads();
     float total = 0.f;
     unsigned row_top = 0u;
 #pragma unroll
-    for (int w = 0; w < kWaves; ++w) {
-        total += scratch_sum[w];
-        row_top = max(row_top, __float_as_uint(scratch_top[w]));
-    }
+    for (int w = 0; w < CHAINS * kWaves; ++w) total += scratch_sum[w];
+#pragma unroll
+    for (int w = 0; w < kWaves; ++w) row_top = max(row_top, __float_as_uint(scratch_top[w]));
     const float inv = rms_inverse(total, K, eps);
     auto y_chunk = [&](int c, v4u r) { return norm_scale8(r, inv, gs[c]); };
 #pragma unroll
     for (int i = 0; i < CACHE; ++i) {  // from here on the cache holds y
         const int c = threadIdx.x + i * THREADS;
+        if (kSkip && c >= chunks) continue;
         if (kKeepGains)
             cache[i] = norm_scale8(cache[i], inv, gain[kKeepGains ? i : 0]);
         else if (c < chunks)
@@ -416,19 +431,20 @@ __global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uin
     for (int c = threadIdx.x + CACHE * THREADS; c < chunks; c += THREADS) emit(c, y_chunk(c, r_again(c)));
 }
 
-template <int THREADS, int CACHE>
+template <int THREADS, int CACHE, int CHAINS = 1>
 static void launch_norm(const void *x, const void *res, const void *gamma, float eps, void *r_out, void *y_out, int8_t *xq, float *s_a,
                         int M, int K, hipStream_t stream) {
-    hipLaunchKernelGGL((add_rmsnorm_quantize_kernel<THREADS, CACHE>), dim3(M), dim3(THREADS), 0, stream, (const uint16_t *)x,
+    hipLaunchKernelGGL((add_rmsnorm_quantize_kernel<THREADS, CACHE, CHAINS>), dim3(M), dim3(THREADS), 0, stream, (const uint16_t *)x,
                        (const uint16_t *)res, (const uint16_t *)gamma, eps, (uint16_t *)r_out, (uint16_t *)y_out, xq, s_a, K);
 }
 
 hipError_t launch_add_rmsnorm_quantize(const void *x, const void *res, const void *gamma, float eps, void *r_out, void *y_out,
                                        int8_t *xq, float *s_a, int M, int K, hipStream_t stream) {
     const int chunks = K >> 3;
-#define W4A8_NORM(T, C) launch_norm<T, C>(x, res, gamma, eps, r_out, y_out, xq, s_a, M, K, stream)
+#define W4A8_NORM(...) launch_norm<__VA_ARGS__>(x, res, gamma, eps, r_out, y_out, xq, s_a, M, K, stream)
     if (M <= kFewRows) {
-        if (chunks <= 1024) W4A8_NORM(1024, 1);
+        if (chunks <= 512) W4A8_NORM(512, 1);
+        else if (chunks <= 1024) W4A8_NORM(512, 2, 2);
         else W4A8_NORM(1024, 2);
     } else if (M <= kSomeRows) {
         if (chunks <= 512) W4A8_NORM(512, 1);
@@ -440,6 +456,8 @@ hipError_t launch_add_rmsnorm_quantize(const void *x, const void *res, const voi
             case 2: W4A8_NORM(256, 2); break;
             case 3: W4A8_NORM(256, 3); break;
             case 4: W4A8_NORM(256, 4); break;
+            case 5: W4A8_NORM(256, 5); break;
+            case 6: W4A8_NORM(256, 6); break;
             default: W4A8_NORM(256, 8);
         }
     }

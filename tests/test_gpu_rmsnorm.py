@@ -183,3 +183,48 @@ def test_scales_of_rows_whose_maximum_is_near_an_fp16_rounding_boundary(gpu, K):
     s_ref = w4a8.w4a8_quantize_act(y)[1]
     t.cuda.synchronize()
     assert t.equal(s_a.view(t.int32), s_ref.view(t.int32))
+
+
+def _sum_of_squares(r, threads):
+    """The fp32 sum of squares of a row in the kernel's order for `threads` threads: a thread's chunks of eight one after the other
+    (a square of an fp16 value added to an fp32 sum rounds once), six DPP steps inside a wave, the waves in order."""
+    K = r.shape[0]
+    per = -(-K // (8 * threads))
+    v = np.zeros(per * threads * 8)
+    v[:K] = r.astype(np.float64)
+    v = v.reshape(per, threads, 8)
+    ss = np.zeros(threads, np.float32)
+    for i in range(per):
+        for e in range(8):
+            ss = (ss.astype(np.float64) + v[i, :, e] ** 2).astype(np.float32)
+    x = ss.reshape(-1, 4, 16)  # wave, row of lanes, lane
+    for step in (1, 2, 4, 8):
+        x = x + np.concatenate((np.zeros_like(x[:, :, :step]), x[:, :, :-step]), axis=2)
+    x[:, 1::2] += x[:, 0::2, 15:]
+    x[:, 2:] += x[:, 1, 15][:, None, None]
+    total = np.float32(0)
+    for w in x[:, 3, 15]:
+        total = np.float32(total + w)
+    return total
+
+
+@pytest.mark.parametrize("M,threads", [(5, 1024), (128, 1024), (129, 512), (257, 256)])
+@pytest.mark.parametrize("K", [32, 4096, 4128, 8192, 8224, 9216, 12288, 12320, 16384, 16416, 24608])
+def test_the_sum_of_squares_has_one_order_for_each_number_of_rows(gpu, M, threads, K):
+    """However a row is spread over threads, its sum is the documented one: the order of 1024 threads up to 128 rows, of 512 up to
+    256, of 256 beyond.  The rows are ones with a few values of 4096, whose squares swallow the ones added to them, so that another
+    order is another sum (many ulp); the square root is the hardware's, within one ulp."""
+    t = gpu
+    rng = np.random.default_rng(M + K)
+    x = rng.choice([np.float16(-1), np.float16(1)], size=(M, K))
+    x[rng.random((M, K)) < 0.005] = np.float16(4096)
+    gain = (1 + 0.1 * rng.standard_normal(K)).astype(np.float16)
+    y = t.empty((M, K), dtype=t.float16, device="cuda")
+    w4a8.w4a8_add_rmsnorm_quantize(t.from_numpy(x).cuda(), None, t.from_numpy(gain).cuda(), 1e-5, y_out=y)
+    t.cuda.synchronize()
+    for m in sorted({0, M // 2, M - 1}):
+        root = np.sqrt(np.float32(np.float32(_sum_of_squares(x[m], threads) / np.float32(K)) + np.float32(1e-5)))
+        got = y[m].cpu().numpy().view(np.uint16)
+        want = [((x[m].astype(np.float32) * (np.float32(1) / s)) * gain.astype(np.float32)).astype(np.float16).view(np.uint16)
+                for s in (root, np.nextafter(root, np.float32(0)), np.nextafter(root, np.float32(np.inf)))]
+        assert any(np.array_equal(got, w) for w in want), f"M={M} K={K} row {m}: {[int((got != w).sum()) for w in want]} values differ"
