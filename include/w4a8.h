@@ -353,8 +353,8 @@ int w4a8_silu_mul_quantize(const void *gate_up_fp16, int8_t *xq, float *s_a, int
  *   r[m][k] = fp16( fp32(res[m][k]) + fp32(x[m][k]) )                     r = x when res_fp16 is NULL
  *   y[m][k] = fp16( fp32(r[m][k]) * rsqrt( mean_k r[m][k]^2 + eps ) * fp32(gamma[k]) )
  *   (xq, s_a) = w4a8_quantize_act(y)                                      Eq. (2), z = 0, per token
- * in one pass over the row: the mean of squares is an fp32 sum, the reciprocal square root a correctly rounded square
- * root and division, the products are taken in the order written.  xq and s_a are, bit for bit, what
+ * in one pass over the row: the mean of squares is an fp32 sum, the reciprocal square root the hardware's square root (within one
+ * ulp) and a correctly rounded division, the products are taken in the order written.  xq and s_a are, bit for bit, what
  * w4a8_quantize_act gives on the y this call computes; r is exactly defined; y is within an fp16 rounding of the
  * real-number formula.
  *   x_fp16 [M][K] in;  res_fp16 [M][K] in or NULL;  gamma_fp16 [K] in;  eps >= 0 (W4A8_ERR_ARG otherwise; an all-zero

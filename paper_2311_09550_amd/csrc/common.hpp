@@ -172,7 +172,7 @@ __device__ __forceinline__ bool absmax_of_norm(float top, float inv, float *amax
     *amax = lo;
     return lo == hi;
 }
-// 1 / sqrt(sum / count + eps): correctly rounded division, square root and division
+// 1 / sqrt(sum / count + eps): correctly rounded divisions, the hardware's square root (within one ulp) between them
 __device__ __forceinline__ float rms_inverse(float sum, int count, float eps) {
     return __fdiv_rn(1.0f, __fsqrt_rn(__fdiv_rn(sum, (float)count) + eps));
 }
