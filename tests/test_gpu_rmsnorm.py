@@ -185,6 +185,58 @@ def test_scales_of_rows_whose_maximum_is_near_an_fp16_rounding_boundary(gpu, K):
     assert t.equal(s_a.view(t.int32), s_ref.view(t.int32))
 
 
+def _rows_whose_maximum_lies_at_a_boundary(t, K, want):
+    """(x, res, gain) of `want` rows whose largest |r g| / rms, in fp64, lies within 2^-22 of a value halfway between two fp16
+    neighbours: well inside the 2^-21 within which the kernel has to look at its values, whatever it rounds on the way."""
+    gen = t.Generator(device="cuda").manual_seed(K)
+    gain = (1 + 0.1 * t.randn((K,), generator=gen, device="cuda")).half()
+    found = []
+    for _ in range(400):
+        x, res = (t.randn((500, K), generator=gen, device="cuda").half() for _ in range(2))
+        r = (x.float() + res.float()).half().double()
+        v = (r * gain.double()).abs().amax(1) / (r.square().mean(1) + 1e-5).sqrt()
+        h = v.half()
+        low = t.where(h.double() > v, (h.view(t.int16) - 1).view(t.float16), h)
+        edge = (low.double() + (low.view(t.int16) + 1).view(t.float16).double()) / 2
+        found += [(x[i], res[i]) for i in t.nonzero((v / edge - 1).abs() < 2.0 ** -22).flatten().tolist()]
+        if len(found) >= want:
+            break
+    assert len(found) >= want
+    return t.stack([f[0] for f in found[:want]]), t.stack([f[1] for f in found[:want]]), gain
+
+
+@pytest.mark.parametrize("swiglu", [False, True])
+@pytest.mark.parametrize("K", [64, 2080, 4096, 5120])
+def test_linear_over_rows_whose_maximum_lies_at_a_boundary(gpu, K, swiglu):
+    """Here the linear finds its maxima in y after all.  The scales and the output are those of the plain linear on the y that this
+    call wrote, with chunks of the row in every wave and several k steps a wave, for all rows of a launch and for one among others,
+    with and without r and y written."""
+    t = gpu
+    N, most = 320, 4 if K <= 4096 else 3
+    x, res, gain = _rows_whose_maximum_lies_at_a_boundary(t, K, 8)
+    gen = t.Generator(device="cuda").manual_seed(N)
+    plain = t.randn((2, 2, 8, K), generator=gen, device="cuda").half()
+    w = (0.02 * t.randn((N, K), generator=gen, device="cuda")).half()
+    wp, s_w = w4a8.w4a8_quantize_weights(w)
+    wt = w4a8.w4a8_tile_weights(wp)
+    linear = w4a8.w4a8_linear_tiled_swiglu_fp16 if swiglu else w4a8.w4a8_linear_tiled_fp16
+    for i in range(8):
+        M = 1 + i % most
+        dx, dres = plain[0, 0, :M].clone(), plain[0, 1, :M].clone()
+        rows = range(M) if i < 4 else [i % M]
+        for j in rows:
+            dx[j], dres[j] = x[(i + j) % 8], res[(i + j) % 8]
+        r, y, s_a = t.empty_like(dx), t.empty_like(dx), t.empty((M,), dtype=t.float32, device="cuda")
+        out = w4a8.w4a8_linear_tiled_norm_fp16(dx, dres, gain, 1e-5, wt, s_w, swiglu=swiglu, r_out=r, y_out=y, s_a_out=s_a)
+        bare = w4a8.w4a8_linear_tiled_norm_fp16(dx, dres, gain, 1e-5, wt, s_w, swiglu=swiglu)
+        ref, s_ref = linear(y, wt, s_w), w4a8.w4a8_quantize_act(y)[1]
+        t.cuda.synchronize()
+        assert t.equal(r.view(t.int16), (dx.float() + dres.float()).half().view(t.int16)), (i, "r")
+        assert t.equal(s_a.view(t.int32), s_ref.view(t.int32)), (i, "scales")
+        assert bool(out.any()) and t.equal(out.view(t.int16), ref.view(t.int16)), (i, "output")
+        assert t.equal(bare.view(t.int16), ref.view(t.int16)), (i, "output without r and y")
+
+
 def _sum_of_squares(r, threads):
     """The fp32 sum of squares of a row in the kernel's order for `threads` threads: a thread's chunks of eight one after the other
     (a square of an fp16 value added to an fp32 sum rounds once), six DPP steps inside a wave, the waves in order."""
