@@ -449,20 +449,25 @@ __global__ __launch_bounds__(WAVES * 64) void gemm_decode_resident_kernel(Decode
                 }
             }
             lds_barrier();
-            bool known = true;  // the same for all threads
+            // Lane l works out row l % 4: one chain of divisions and a square root for all rows instead of one chain a row behind the
+            // other, with which two tokens at K <= 2048 took longer than with two reductions (8192 x 1504, two tokens: 5.85 us with two,
+            // 6.13 with a chain a row, 5.9 so; 12288 x 4096, four tokens 11.7, 10.4, 9.8).  Rows past M have whatever lies in LDS there.
+            const int own_row = lane & 3;
+            float total = 0.f;
+            unsigned top = 0u;
+#pragma unroll
+            for (int w = 0; w < WAVES; ++w) {
+                total += sum_lds[w * 4 + own_row];
+                top = max(top, __float_as_uint(amax_lds[w * 4 + own_row]));
+            }
+            const float row_inv = rms_inverse(total, p.K, p.eps);
+            float row_amax;
+            const bool row_known = absmax_of_norm(__uint_as_float(top), row_inv, &row_amax);
+            const bool known = __all(own_row >= p.M || row_known);  // the same for all threads
 #pragma unroll
             for (int m = 0; m < 4; ++m) {
-                if (m < p.M) {
-                    float total = 0.f;
-                    unsigned top = 0u;
-#pragma unroll
-                    for (int w = 0; w < WAVES; ++w) {
-                        total += sum_lds[w * 4 + m];
-                        top = max(top, __float_as_uint(amax_lds[w * 4 + m]));
-                    }
-                    norm_inv[m] = rms_inverse(total, p.K, p.eps);
-                    known &= absmax_of_norm(__uint_as_float(top), norm_inv[m], &norm_amax[m]);
-                }
+                norm_inv[m] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(row_inv), m));
+                norm_amax[m] = __int_as_float(__builtin_amdgcn_readlane(__float_as_int(row_amax), m));
             }
             if (!known) {
                 lds_barrier();  // the tops have been read: their place takes the maxima of |y|
