@@ -37,7 +37,7 @@ constexpr int medium_lds_bytes(int mt, int nt, int nw, int kg) {
 // What bounds it: the bytes a compute unit brings in, (BM + BN / 2) K, at about 60 KB/us while the weights come from
 // memory and 95 where everything hits in L2; that is the reason for the shapes (near square in bytes, one per compute unit)
 // and the launch, exchange and epilogue, 4 to 5 us.
-template <int MT, int NT, int NW, int KG, bool ACC_OUT, int WBITS, bool SWIGLU>
+template <int MT, int NT, int NW, int KG, bool ACC_OUT, int WBITS, bool SWIGLU, bool NOT_KEPT>
 __global__ __launch_bounds__(64 * NW * KG, MT * NT <= 12 && WBITS == 4 ? 4 : 2) void gemm_medium_kernel(PrefillArgs p) {
     static_assert(!SWIGLU || (WBITS == 4 && !ACC_OUT), "fused SiLU * up: int4 weights, fp16 output");
     constexpr bool W8 = WBITS == 8;
@@ -48,9 +48,7 @@ __global__ __launch_bounds__(64 * NW * KG, MT * NT <= 12 && WBITS == 4 ? 4 : 2) 
     constexpr int A_LOADS = KG * MT * 2 / WAVES, W_LOADS = NT * WV;
     static_assert(A_LOADS * WAVES == KG * MT * 2, "every wave issues the same number of activation loads: the waits count on it");
     static_assert(WAVES * 64 >= BM && WAVES * 64 >= BN, "one thread per row and per channel of the tile");
-    // weights read by one or two workgroups only are not kept (3 % at N = 4096, K = 11008, M = 50); the wider shapes serve
-    // larger M, where the hint costs up to 20 %
-    constexpr int kWeightPolicy = KG == 8 ? 2 : 0;
+    constexpr int kWeightPolicy = NOT_KEPT ? 2 : 0;  // non-temporal, where launch_medium_one says so
     extern __shared__ __attribute__((aligned(1024))) uint8_t lds[];
 
     const int tid = threadIdx.x;
@@ -252,19 +250,37 @@ __global__ __launch_bounds__(64 * NW * KG, MT * NT <= 12 && WBITS == 4 ? 4 : 2) 
 
 namespace {
 
-template <int MT, int NT, int NW, int KG, bool ACC_OUT, int WBITS, bool SWIGLU>
-hipError_t launch_medium_one(PrefillArgs p, hipStream_t stream) {
-    constexpr int BM = 16 * MT, BN = 16 * NT * NW;
-    constexpr int kLds = medium_lds_bytes(MT, NT, NW, KG) + 4 * (BM + BN);
+template <int MT, int NT, int NW, int KG, bool ACC_OUT, int WBITS, bool SWIGLU, bool NOT_KEPT>
+hipError_t launch_medium_as(const PrefillArgs &p, hipStream_t stream) {
+    constexpr int kLds = medium_lds_bytes(MT, NT, NW, KG) + 4 * (16 * MT + 16 * NT * NW);
     static_assert(kLds <= 160 * 1024, "a workgroup's stages and exchange must fit the compute unit's LDS");
-    constexpr auto kernel = gemm_medium_kernel<MT, NT, NW, KG, ACC_OUT, WBITS, SWIGLU>;
+    constexpr auto kernel = gemm_medium_kernel<MT, NT, NW, KG, ACC_OUT, WBITS, SWIGLU, NOT_KEPT>;
     if (const hipError_t e = allow_lds<kernel>(kLds); e != hipSuccess) return e;
     if (p.prepare_only) return hipSuccess;
-    p.tiles_m = (p.M + BM - 1) / BM;
-    p.tiles_n = (p.N + BN - 1) / BN;
     const int total = p.tiles_m * p.tiles_n;
     hipLaunchKernelGGL(kernel, dim3(8 * ((total + 7) / 8)), dim3(64 * NW * KG), kLds, stream, p);
     return hipGetLastError();
+}
+
+template <int MT, int NT, int NW, int KG, bool ACC_OUT, int WBITS, bool SWIGLU>
+hipError_t launch_medium_one(PrefillArgs p, hipStream_t stream) {
+    constexpr int BM = 16 * MT, BN = 16 * NT * NW;
+    p.tiles_m = (p.M + BM - 1) / BM;
+    p.tiles_n = (p.N + BN - 1) / BN;
+    // With eight k groups the weights are loaded with the non-temporal hint where the tile rows of a column all lie on one XCD, which
+    // then fetches them once for its own L2 alone; a column that is cut between two XCDs is wanted again by the second.  Cold weights,
+    // hint and none: N = 4351, K = 9888, M = 25 (one tile row) 10.4 us and 11.1; N = 1519, K = 12160, M = 53 (two, whole columns) 10.9 and
+    // 11.5; N = 2076, K = 10528, M = 41 (two, cut) 11.2 and 10.65; N = 1082, K = 11104, M = 161 (six, cut) 11.2 and 10.75.  Over 260 shapes with one
+    // to sixteen tile rows, int4 and int8, the rule takes the faster of the two each time (within 1 %).  The shapes with four k groups serve
+    // larger M, where the hint costs up to 20 %.
+    if constexpr (KG == 8) {
+        if (p.prepare_only) {
+            if (const hipError_t e = launch_medium_as<MT, NT, NW, KG, ACC_OUT, WBITS, SWIGLU, true>(p, stream); e != hipSuccess) return e;
+        } else if ((p.tiles_m * p.tiles_n + 7) / 8 % p.tiles_m == 0) {
+            return launch_medium_as<MT, NT, NW, KG, ACC_OUT, WBITS, SWIGLU, true>(p, stream);
+        }
+    }
+    return launch_medium_as<MT, NT, NW, KG, ACC_OUT, WBITS, SWIGLU, false>(p, stream);
 }
 
 }  // namespace

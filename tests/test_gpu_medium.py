@@ -84,6 +84,25 @@ def test_int8_tiles(gpu, oracle, M, N, K, tile):
     assert_fp16_close(out[rows].cpu().numpy(), y32, acc_o, "sampled rows out")
 
 
+# with eight k groups: columns of tiles whole on an XCD (weights loaded with the non-temporal hint) and cut between two (without)
+@pytest.mark.parametrize("entry,M,N,K,tile,whole", [
+    ("tiled", 110, 245, 1984, 21, True), ("tiled", 127, 1857, 1952, 21, False), ("tiled", 33, 4432, 5888, 23, True), ("tiled", 36, 4212, 5760, 23, False),
+    ("swiglu", 151, 1024, 1984, 21, True), ("swiglu", 126, 192, 1952, 21, False), ("swiglu", 35, 4480, 6144, 23, True), ("swiglu", 42, 4288, 5760, 23, False),
+    ("w8a8", 183, 1266, 2880, 21, True), ("w8a8", 91, 1896, 3744, 21, False), ("w8a8", 76, 511, 3072, 29, True), ("w8a8", 44, 706, 2080, 29, False),
+    ("w8a8", 150, 756, 3552, 30, True), ("w8a8", 57, 1809, 2048, 30, False)])
+def test_columns_of_tiles_whole_on_an_xcd_and_cut(gpu, oracle, entry, M, N, K, tile, whole):
+    """The same comparisons as above on both sides of the rule for the cache policy of the weights."""
+    bm, bn = {21: (32, 32), 23: (32, 64), 29: (16, 16), 30: (16, 32)}[tile]
+    rows, columns = -(-M // bm), -(-N // bn)
+    assert rows > 1 and (-(-rows * columns // 8) % rows == 0) == whole
+    if entry == "tiled":
+        test_int4_tiles(gpu, oracle, M, N, K, tile)
+    elif entry == "swiglu":
+        test_swiglu_form(gpu, oracle, M, N // 2, K, tile)
+    else:
+        test_int8_tiles(gpu, oracle, M, N, K, tile)
+
+
 def test_graph_replays(gpu, oracle):
     """Captured once, replayed with new inputs between eager work: the bits of the eager call every time."""
     t = gpu
