@@ -315,7 +315,8 @@ bool medium_covers(int M, int N, int K, int wbits) {
 // A medium tile is taken where it is priced that much lower than the large-M kernel (below): 1.7 % on average over always taking the fastest, 3 of
 // 216 shapes that were not fitted to are more than 3 % slower than without the kernel, by 9 % at most, and all together take 0.93 of
 // the time: 0.87 from 65 to 512 tokens (N = K = 5120, M = 128: 14.7 us in three slices of K, 10.3 as 32 x 96 tiles; N = 4096, K = 11008:
-// M = 50 17.7 and 11.9, M = 333 28.2 and 24).  Below 17 tokens the weight-streaming kernel holds the activations in registers.
+// M = 50 17.7 and 11.9, M = 333 28.2 and 24).  Of 903 more shapes with 65 to 512 tokens 21 take over 3 % longer than without it, all
+// with K up to 3072 and priced close to the large-M kernel (N = 16320, K = 1888, M = 167: 13.15 us, 12.0 without).  Below 17 tokens the weight-streaming kernel holds the activations in registers.
 constexpr StepCost kMediumCosts[] = {
     {kMedium32x32, 32, 32, 8, 2, 2.018f, 1.159f, 0.142f, 0.000f, 0.016f, 0.138f, 0.066f, 0.010f},
     {kMedium32x64, 32, 64, 4, 4, 1.504f, 1.200f, 0.359f, 0.037f, 0.059f, 0.292f, 0.086f, 0.022f},
@@ -331,11 +332,11 @@ constexpr StepCost kMediumCosts[] = {
 // layer around it 306 us instead of 299, at the power limit.  (On 60 shapes beyond 512 tokens it then gives 7.0 %, with 3 % 7.1.)
 double medium_over_tiles(int M) { return M <= 512 ? 1.03 : 1.15; }
 
-// Against weight streaming, whose price has its own preference in it (streaming_preferred): 10 % lower where that takes one slice
-// (the two are level there: N = 8544, K = 1824, M = 63 6.44 us and 6.43), up to 8 % higher where it takes several, which its price
-// is too low for and which cost slabs (N = 4096, K = 11008, M = 50: 17.4 us in three slices, 12.2 as 32 x 32 tiles).  On 217 shapes with
-// 17 to 64 tokens that is the faster one of the two but for one shape that loses 2 %.
-double medium_over_streaming(int slices) { return slices == 1 ? 1.10 : 0.92; }
+// Against weight streaming: 10 % lower than its price, preference included (streaming_preferred), where that takes one slice
+// (the two are level there: N = 8544, K = 1824, M = 63 6.44 us and 6.43); 7 % lower than sliced_us where it takes several.  (By the price
+// of one slice and 8 % more for the slabs it was taken for N = 1600, K = 11264, M = 59, 10.8 us, where three slices take 9.4; of 715
+// shapes with several slices 22 took over 3 % longer than without the medium-M kernel, by up to 15 %, now 3.)
+constexpr double kMediumOverStreaming = 1.10, kMediumOverSlices = 1.07;
 
 // How a GEMM over tiled int4 weights with more than 16 tokens is run: by the weight-streaming kernel with per-wave
 // staging, K cut into slices, by the large-M kernel, K cut into slices, or by the medium-M kernel.  All are priced and the
@@ -350,7 +351,7 @@ struct TiledPlan {
 // Price of the weight-streaming kernel in microseconds: what every compute unit brings in (the activations and its
 // weights), a fixed part per chunk of 16 channels, more of it where a wave has more than 8 k steps, and the slabs.  Fitted
 // like the tiles' prices, within 5 % of those shapes; on 346 others, with up to 65536 channels, within 9 % with one slice and
-// 13 % too low on average with several.
+// 13 % too low on average with several.  Older than two_chunks_ahead: where that asks for two, the kernel takes 2 to 30 % less.
 double wide_us(const DecodeShape &s, int M, int N, int K) {
     const double steps = ((K + 127) / 128 + s.k_slices - 1) / s.k_slices;
     const double chunks = (s.rows_per_wg + 15) / 16, mt = (M + 15) / 16, long_walk = s.x_steps > 8 ? s.x_steps - 8 : 0;
@@ -358,6 +359,18 @@ double wide_us(const DecodeShape &s, int M, int N, int K) {
     double us = 2.215 + 0.01676 * x_kb + 0.01376 * w_kb + chunks * (0.630 + 0.0551 * mt + 0.1122 * long_walk);
     if (s.k_slices > 1) us += slab_us(M, N, s.k_slices);
     return us;
+}
+
+// The same for several slices, where the medium-M kernel is set against them: fitted over 4275 such launches (17 to 64 tokens, N
+// up to 32768, two to four slices, weights cold) within 6.2 %.  It knows two things more: ranges rounded to whole chunks can make more
+// workgroups than there are compute units, and the few beyond take a round of their own (N = 4096, K = 11008, M = 50: 86 ranges
+// in three slices, 16.5 us); and the slabs of an N that is no multiple of four are stored and read value by value.
+double sliced_us(const DecodeShape &s, int M, int N, int K, int cus) {
+    const int ranges = (N + s.rows_per_wg - 1) / s.rows_per_wg, rounds = (ranges * s.k_slices + cus - 1) / cus;
+    const double steps = ((K + 127) / 128 + s.k_slices - 1) / s.k_slices, mt = (M + 15) / 16, slab_mb = 4e-6 * M * (double)N * s.k_slices;
+    const double x_kb = M * steps * 0.125, w_kb = s.rows_per_wg * steps * 0.0625, chunks = (s.rows_per_wg + 15) / 16;
+    return 3.603 + rounds * (0.00901 * x_kb + 0.03258 * w_kb + 0.0757 * chunks) + 0.2753 * mt + 0.2278 * s.k_slices +
+           (N % 4 ? 1.445 : 0.6046) * slab_mb;
 }
 
 // The tiles' prices are too low where K is no multiple of 128 and where N is wide, and streaming is the form
@@ -409,7 +422,9 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu, int cus)
         }
     }
     if (medium_covers(M, N, K, 4)) {
-        const double bar = best_us / (best.wide ? medium_over_streaming(best.shape.k_slices) : medium_over_tiles(M));
+        const double bar = !best.wide                  ? best_us / medium_over_tiles(M)
+                           : best.shape.k_slices == 1 ? best_us / kMediumOverStreaming
+                                                      : sliced_us(best.shape, M, N, K, cus) / kMediumOverSlices;
         double medium_us = bar;
         for (const StepCost &t : kMediumCosts) {
             const double us = step_us(t, M, N, K, cus);

@@ -137,3 +137,16 @@ def test_near_ties_go_to_weight_streaming():
         assert w4a8_route(ROUTE_SPLITK, M, 8192, 28672) == (TILING_PREFILL_TILED, 13, 6)
     for M, N, K in [(63, 55468, 3520), (52, 47417, 1344), (64, 57344, 8192), (17, 1216, 16416)]:
         assert w4a8_route(ROUTE_GEMM_TILED, M, N, K)[0] == TILING_PREFILL_TILED, (M, N, K)
+
+
+def test_several_slices_are_kept_where_they_are_faster_than_the_medium_m_kernel():
+    """Slices of weight streaming against the medium-M kernel, each shape measured on cold weights: narrow outputs whose slabs are
+    few and stored four values at a time are the slices', an odd N and wider outputs the medium-M kernel's."""
+    for M, N, K in [(59, 1600, 11264), (63, 2944, 14976), (62, 1664, 10752), (48, 1024, 7488), (42, 1152, 6976), (32, 4160, 10176),
+                    (38, 2432, 10240), (39, 1088, 6656)]:
+        tiling, tile, slices = w4a8_route(ROUTE_SPLITK, M, N, K)
+        assert (tiling, tile) == (TILING_DECODE_RESIDENT_TILED, 0) and slices > 1, (M, N, K)
+        assert w4a8_route(ROUTE_GEMM_TILED, M, N, K) == (TILING_PREFILL_TILED, 21, 1), (M, N, K)  # no workspace, no slices
+    for M, N, K in [(50, 4096, 11008), (62, 4096, 5760), (54, 3745, 9248), (62, 1359, 5920), (58, 8877, 6144), (51, 3520, 5760)]:
+        tiling, tile, slices = w4a8_route(ROUTE_SPLITK, M, N, K)
+        assert tiling == TILING_PREFILL_TILED and tile >= 21 and slices == 1, (M, N, K)
