@@ -447,13 +447,14 @@ struct Route {
     size_t need;      // bytes of workspace, 0 when one slice is asked for
     bool one_launch;  // refused where one launch cannot address the problem (slabs are whole M x N matrices)
 };
-enum RouteKind { kUnsliced, kSliced, kSwiglu };
+enum RouteKind { kUnsliced, kSliced, kSwiglu, kInt8 };  // kInt8: over int8 weights, a tile
 
 Route make_route(int M, int N, int K, RouteKind kind, int cus);
 
 thread_local unsigned long long plans_made = 0;
 
-// The library's own choice for more than 16 tokens, remembered per thread: it is a pure function of its arguments (and of the
+// The library's own choice for more than 16 tokens, over int8 weights for any number (pricing its tiles takes longer than the rest
+// of a call's checks: 0.5 us), remembered per thread: it is a pure function of its arguments (and of the
 // device's compute units), and a loop over a model's layers asks for the same few again and again.  16 sets of four, the
 // oldest of a set replaced; the set comes from all bits of the shape (a sum or XOR of products with its top bits taken put
 // two linears of one layer into one place for every M).
@@ -850,6 +851,10 @@ SlabRule slab_rule(int M, int N, int K, int variant, int cus) {
 
 Route make_route(int M, int N, int K, RouteKind kind, int cus) {
     Route r{};
+    if (kind == kInt8) {
+        r.plan.tile = choose_tiled_tile8(M, N, K);
+        return r;
+    }
     if (kind == kSliced) {
         const SlabRule rule = slab_rule(M, N, K, 0, cus);
         r.need = rule.slices > 1 ? rule.slices * ((size_t)M * (size_t)N * sizeof(int32_t)) : 0;
@@ -1067,7 +1072,7 @@ int w4a8_route(int entry, int M, int N, int K, int variant, int splits, int *til
         case W4A8_ROUTE_W8A8:
         case W4A8_ROUTE_UNSIGNED:
             *tiling = W4A8_TILING_PREFILL_TILED;
-            *tile = entry == W4A8_ROUTE_W8A8 ? choose_tiled_tile8(M, N, K) : choose_unsigned_tile(M, N, K);
+            *tile = entry == W4A8_ROUTE_W8A8 ? tiled_route(M, N, K, kInt8).plan.tile : choose_unsigned_tile(M, N, K);
             return W4A8_OK;
         default: return W4A8_ERR_ARG;
     }
@@ -1157,7 +1162,7 @@ static int gemm_tiled_variant(const int8_t *xq, const float *s_a, const uint8_t 
     a.out = out_fp16; a.acc_out = acc_i32;
     a.M = M; a.N = N; a.K = K; a.ldc = N;
     const int tile = variant ? variant
-                             : wfmt == 8 ? choose_tiled_tile8(M, N, K) : choose_unsigned_tile(M, N, K);
+                             : wfmt == 8 ? tiled_route(M, N, K, kInt8).plan.tile : choose_unsigned_tile(M, N, K);
     return launched(launch_tile(a, want_acc, false, tile, static_cast<hipStream_t>(stream), wfmt));
 }
 

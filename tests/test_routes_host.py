@@ -103,6 +103,26 @@ def test_plans_of_a_models_layers_are_remembered(model):
             assert not again or made() == before, M
 
 
+@pytest.mark.parametrize("model", ["7b", "13b", "70b"])
+def test_tiles_over_int8_weights_are_remembered_too(model):
+    """Every token count of the sizes in use, token generation among them; the forms over int4 weights keep plans of their own."""
+    from paper_2311_09550_amd.synth import LLAMA_SHAPES
+    made = w4a8.lib().w4a8_plans_made
+    for M in [1, 4, 16, 17, 64, 128, 333, 512, 1024, 2048]:
+        first = {name: w4a8_route(ROUTE_W8A8, M, N, K) for name, (N, K) in LLAMA_SHAPES[model].items()}
+        before = made()
+        for name, (N, K) in LLAMA_SHAPES[model].items():
+            assert w4a8_route(ROUTE_W8A8, M, N, K) == first[name], (M, name)
+        assert made() == before, M
+        if M > 16:
+            N, K = LLAMA_SHAPES[model]["qkv"]
+            assert w4a8_route(ROUTE_SPLITK, M, N, K) == w4a8_route(ROUTE_GEMM_TILED, M, N, K)
+    N, K = LLAMA_SHAPES[model]["down"]
+    before = made()
+    w4a8_route(ROUTE_W8A8, 77, N, K)
+    assert made() == before + 1  # asked for the first time
+
+
 def test_unsigned_storage_is_priced_for_its_own_tiles():
     """It has eight tiles, runs 64 x 128 on four waves and converts at twice the cost: the taller tiles pay earlier than over
     signed weights, 128 x 128 among them."""
