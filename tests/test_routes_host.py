@@ -114,9 +114,9 @@ def test_tiles_over_int8_weights_are_remembered_too(model):
         for name, (N, K) in LLAMA_SHAPES[model].items():
             assert w4a8_route(ROUTE_W8A8, M, N, K) == first[name], (M, name)
         assert made() == before, M
-        if M > 16:
-            N, K = LLAMA_SHAPES[model]["qkv"]
-            assert w4a8_route(ROUTE_SPLITK, M, N, K) == w4a8_route(ROUTE_GEMM_TILED, M, N, K)
+        N, K = LLAMA_SHAPES[model]["qkv"]
+        int4 = w4a8_route(ROUTE_GEMM_TILED, M, N, K)
+        assert w4a8_route(ROUTE_W8A8, M, N, K) == first["qkv"] and w4a8_route(ROUTE_GEMM_TILED, M, N, K) == int4
     N, K = LLAMA_SHAPES[model]["down"]
     before = made()
     w4a8_route(ROUTE_W8A8, 77, N, K)
