@@ -106,12 +106,15 @@ __global__ __launch_bounds__(64 * NW * KG, MT * NT <= 12 && WBITS == 4 ? 4 : 2) 
     };
     // A lane's weights of a k step: chunk g of its channel's row of the block (int4: the codes of both MFMA steps), or chunks
     // 2 g and 2 g + 1 (int8).  Step h of the two multiplies k = 32 g + 16 h .. + 15, piece 2 g + h of an activation row.
+    // Channels that do not exist lie beyond the buffer with either piece's offset added.
+    constexpr unsigned kNoChannel = kNowhere - 512u * (WV - 1);
+    static_assert(kNoChannel + 512u * (WV - 1) + 15u >= kNoChannel && kNoChannel >= kMediumMaxWeights, "offsets must not come round to the buffer's start");
     unsigned w_off[NT];
 #pragma unroll
     for (int t = 0; t < NT; ++t) {
         const int n = bn0 + 16 * (wn * NT + t), nb = n >> 5;
         w_off[t] = nb < nb_total ? (unsigned)nb * (unsigned)(steps * kBlock) + (unsigned)((n & 16) + idx) * 16u + (unsigned)g * (512u * WV)
-                                 : kNowhere;
+                                 : kNoChannel;
     }
     v4u wreg[NT][WV];
     auto w_load = [&](int s, int t) {
