@@ -62,13 +62,23 @@ def test_library_choice_on_llama13b_shapes(gpu, oracle, M, N, K):
     assert_fp16_close(a.cpu().numpy()[rows], y32, acc_o, f"library split rows M={M} N={N} K={K}")
 
 
+# Shapes that the library cut into slices of a tile before the medium-M kernel served them whole: that tile, its slices, and the
+# medium-M kernel's tile.  Their ids name the slices.
+FORMERLY_SLICED = [
+    (490, 869, 4512, 6, 3, 22), (467, 852, 4512, 6, 3, 22), (106, 307, 3424, 7, 2, 21), (104, 312, 3104, 7, 2, 21),
+    (264, 841, 6336, 8, 4, 21), (344, 1128, 4544, 8, 3, 22), (473, 3075, 10080, 12, 4, 25), (452, 3084, 9664, 12, 4, 25),
+    (392, 1731, 6592, 13, 4, 24), (407, 1736, 6560, 13, 4, 24), (510, 2565, 8096, 15, 4, 26), (462, 2564, 8160, 15, 4, 26),
+    (508, 1286, 6080, 16, 4, 24), (451, 1288, 6208, 16, 4, 24), (334, 5418, 11200, 20, 4, 28), (275, 4412, 13344, 20, 5, 26)]
+
+
 # one ragged shape for every output tile that the library cuts K with, N a multiple of 4 (16-byte stores of raw sums) and not;
 # the last slice is a stage short in some, and the last stage of K partly past the end in all
 @pytest.mark.parametrize("M,N,K,tile,slices", [
     (457, 551, 9152, 6, 6), (436, 580, 9120, 6, 6), (71, 206, 8352, 7, 5), (101, 204, 8640, 7, 5), (66, 839, 9280, 8, 6),
     (74, 732, 10912, 8, 6), (403, 2389, 15936, 12, 6), (349, 4120, 14368, 12, 5), (484, 1041, 12832, 13, 6), (394, 1276, 12192, 13, 6),
     (453, 2099, 13856, 15, 5), (494, 2060, 14528, 15, 5), (410, 902, 12960, 16, 6), (399, 912, 12864, 16, 6), (400, 6250, 11104, 17, 3),
-    (394, 6196, 11072, 17, 3), (323, 7191, 10688, 20, 3), (340, 7668, 10272, 20, 3)])
+    (394, 6196, 11072, 17, 3), (323, 7191, 10688, 20, 3), (340, 7668, 10272, 20, 3)]
+    + [pytest.param(M, N, K, now, 1, id=f"{M}-{N}-{K}-{tile}-{slices}") for M, N, K, tile, slices, now in FORMERLY_SLICED])
 def test_librarys_slices_of_every_tile(gpu, oracle, M, N, K, tile, slices):
     """splits = 0, the workspace of the size asked for and the static array where the slabs fit it: bit for bit the unsliced
     32 x 128 tile, sampled rows against the oracle."""
@@ -90,6 +100,22 @@ def test_librarys_slices_of_every_tile(gpu, oracle, M, N, K, tile, slices):
     rows = [0, M // 2, M - 1]
     acc_o, y32, _ = oracle.gemm(xq[rows], s_a[rows], wp, s_w)
     assert_fp16_close(out.cpu().numpy()[rows], y32, acc_o, what)
+
+
+@pytest.mark.parametrize("M,N,K,tile,slices", [r[:5] for r in FORMERLY_SLICED if r[3] <= 12])
+def test_slices_of_a_tile_asked_for_where_the_library_takes_the_medium_kernel(gpu, oracle, M, N, K, tile, slices):
+    """The slices that such a shape had, forced where a tile can be forced: the bits of the library's choice, every sum written by one
+    slice or another (the workspace starts from other values)."""
+    t = gpu
+    assert w4a8.w4a8_route(w4a8.ROUTE_SPLITK, M, N, K, tile, slices) == (w4a8.TILING_PREFILL_TILED, tile, slices)
+    xq, wq, s_a, s_w = synth.uniform_codes(M, N, K, config_id=84)
+    dxq, dsa, dsw = t.from_numpy(xq).cuda(), t.from_numpy(s_a).cuda(), t.from_numpy(s_w).cuda()
+    wt = w4a8.w4a8_tile_weights(t.from_numpy(oracle.pack_w4(wq)).cuda())
+    ws = t.full((slices * M * N * 4,), 85, dtype=t.uint8, device="cuda")
+    forced = w4a8.w4a8_gemm_tiled_splitk(dxq, dsa, wt, dsw, variant=tile, splits=slices, ws=ws)
+    choice = w4a8.w4a8_gemm_tiled_splitk(dxq, dsa, wt, dsw)
+    t.cuda.synchronize()
+    assert_equal_bits(forced.cpu().numpy().view(np.uint16), choice.cpu().numpy().view(np.uint16), f"tile {tile} in {slices} slices")
 
 
 def test_workspace_too_small_is_refused(gpu, oracle):

@@ -63,7 +63,9 @@ def test_swiglu_13b_channels_at_1024_tokens(gpu, oracle):
 @pytest.mark.parametrize("M,I,K,tile", [(969, 7008, 672, 1), (903, 8160, 192, 3), (1028, 1504, 32, 6), (1036, 512, 32, 7),
                                         (898, 1664, 32, 8), (1089, 2944, 416, 12), (982, 1568, 928, 13), (970, 5664, 288, 14),
                                         (1093, 1888, 544, 15), (966, 1472, 544, 16), (975, 4128, 416, 17), (1036, 5440, 544, 18),
-                                        (975, 5152, 288, 19), (1089, 3712, 288, 20)])
+                                        (975, 5152, 288, 19), (1089, 3712, 288, 20), (776, 1024, 288, 6)]
+                         # the tile in the id before the medium-M kernel, whose tile it is now
+                         + [pytest.param(86, 512, 32, 22, id="86-512-32-7"), pytest.param(834, 896, 288, 22, id="834-896-288-8")])
 def test_swiglu_epilogue_of_every_tile(gpu, oracle, M, I, K, tile):
     """Bit for bit against the plain GEMM's 32 x 128 tile over the same interleaved channels and silu_mul; sampled rows of
     that GEMM against the oracle."""

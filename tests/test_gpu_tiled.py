@@ -172,7 +172,9 @@ def test_tiled_llama13b_prefill_sampled(gpu, oracle):
 # lists of their own in test_gpu_swiglu.py and test_gpu_splitk.py.)
 @pytest.mark.parametrize("M,N,K,tile", [(130, 21127, 800, 13), (453, 22911, 288, 14), (622, 9745, 288, 15), (250, 12122, 416, 16),
                                         (387, 19065, 416, 17), (647, 16927, 544, 18), (450, 20537, 288, 19), (338, 22148, 288, 20),
-                                        (516, 23091, 160, 12), (781, 16335, 672, 1), (1049, 2946, 160, 6), (1039, 2887, 160, 8)])
+                                        (516, 23091, 160, 12), (781, 16335, 672, 1), (1049, 2946, 160, 6), (1039, 2887, 160, 8)]
+                         # the tile in the id before the medium-M kernel, whose tile it is now
+                         + [pytest.param(137, 9737, 288, 22, id="137-9737-288-6"), pytest.param(71, 13592, 160, 22, id="71-13592-160-8")])
 def test_librarys_choice_on_ragged_shapes_of_every_tile(gpu, oracle, M, N, K, tile):
     """Library's choice against the oracle on sampled rows and, on every element, against the bits of the 32 x 128 tile;
     the fused SiLU * up form against the two calls (its bar is equality of bits, as in test_gpu_swiglu.py)."""

@@ -73,7 +73,9 @@ def test_w8a8_ragged_shapes(gpu, oracle, M, N, K, tile):
 @pytest.mark.parametrize("M,N,K,tile", [(988, 2951, 1088, 16), (450, 4927, 1056, 7), (330, 12289, 160, 7), (1023, 5120, 288, 15),
                                         (512, 15363, 96, 7), (130, 32800, 96, 7), (600, 27000, 64, 20), (579, 12355, 288, 12),
                                         (226, 26289, 3296, 12), (963, 4111, 416, 15), (961, 2929, 832, 16), (1061, 6023, 160, 20),
-                                        (1023, 16371, 288, 1), (1052, 3189, 288, 6), (75, 25319, 416, 8)])
+                                        (1023, 16371, 288, 1), (1052, 3189, 288, 6), (75, 25319, 416, 8)]
+                         # the tile in the id before the medium-M kernel, whose tile it is now
+                         + [pytest.param(512, 5120, 13824, 31, id="512-5120-13824-16")])
 def test_w8a8_chosen_tiles(gpu, oracle, M, N, K, tile):
     """The library's own choice, with ragged edges for each of its tiles (12, 15, 16 and 20, which cannot be forced, are
     128 x 256, 128 x 192, 64 x 192 and 192 x 192 on 8 waves): the bits of another tile, and sampled rows against the oracle."""
