@@ -246,13 +246,16 @@ def workspace(M: int, N: int, K: int, device=None):
     """A zero-filled workspace tensor large enough for (M, N, K), cached per device and stream."""
     torch = _torch()
     device = torch.device("cuda", torch.cuda.current_device()) if device is None else torch.device(device)
-    if device.type != "cuda":
-        raise ValueError(f"workspace: expected a cuda device, got {device}")
-    index = torch.cuda.current_device() if device.index is None else device.index  # "cuda" names the current device
+    index = device.index
+    if index is None:  # "cuda" names the current device
+        index = torch.cuda.current_device()
+        device = torch.device(device.type, index)
     need = max(w4a8_gemm_workspace_bytes(M, N, K), 256)
-    key = (index, _raw_stream(index))
+    key = (device, _raw_stream(index))
     ws = _workspaces.get(key)
     if ws is None or ws.numel() < need:
+        if device.type != "cuda":
+            raise ValueError(f"workspace: expected a cuda device, got {device}")
         ws = torch.zeros(need, dtype=torch.uint8, device=device)
         _workspaces[key] = ws
     return ws

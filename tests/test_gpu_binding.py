@@ -15,5 +15,6 @@ def test_workspace_takes_every_name_of_the_current_device(gpu):
     assert first.device == t.device("cuda", 0) and first.dtype == t.uint8 and not bool(first.any())
     with t.cuda.stream(t.cuda.Stream()):
         assert w4a8.workspace(4, 64, 256, device="cuda") is not first
-    with pytest.raises(ValueError):
-        w4a8.workspace(4, 64, 256, device="cpu")
+    for name in ("cpu", "cpu:0"):
+        with pytest.raises(ValueError):
+            w4a8.workspace(4, 64, 256, device=name)
