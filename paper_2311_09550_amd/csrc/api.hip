@@ -107,7 +107,9 @@ bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool
 // token, cold, one chunk ahead and two: 32768 x 1024 8.06 us and 5.66, 32000 x 2048 9.17 and 7.35, 24576 x 3072 8.50 and 7.93,
 // 22016 x 4096 9.29 and 9.08; but 12288 x 4096 (three chunks) 6.12 and 6.49, 27648 x 5120 12.96 and 13.54.  Row-major 32768 x 1024
 // 8.75 and 6.07, 32000 x 2048 10.3 and 8.3, but 17216 x 4000 11.5 and 11.9.  With three and four column tiles 64 tokens of 24576 x 3072 take 11.4 and 12.6, 32000 x 2048
-// 12.4 and 11.1.  The norm in front takes long enough for two chunks to arrive: 12288 x 4096 7.70 and 7.30, 22016 x 4096 10.8 and 9.9
+// 12.4 and 11.1.  So do two column tiles, also over row-major weights, whose rows then no longer fit LDS beside the sums and are
+// read in operand order: row-major 17 tokens of 32768 x 1024 10.5 and 7.9, 32 tokens 11.1 and 8.4, 32000 x 2048 12.45 and 9.8, 13.1 and
+// 10.7; tiled 32 tokens of 24576 x 3072 9.5 and 9.05.  The norm in front takes long enough for two chunks to arrive: 12288 x 4096 7.70 and 7.30, 22016 x 4096 10.8 and 9.9
 // (10240 x 8192, eight steps a wave: 10.6 and 11.4).
 bool two_chunks_ahead(const DecodeShape &s, int chunks, int M, int mt) {
     const int loads = s.waves * s.x_steps;
