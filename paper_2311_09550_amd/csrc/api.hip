@@ -103,19 +103,20 @@ bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool
 //   x_window : every wave stages its own k steps (tiled weights, 17 to 64 tokens).  Then waves = 0 means 16 waves for
 //              two column tiles when their k steps fit, else 8.
 // Whether a wave asks for two chunks ahead.  One chunk of all waves should be the 32 or more loads that keep a compute unit
-// busy; where it is fewer, a second one is worth the slot that it wastes at the end of an odd number of chunks.  Tiled weights, one
-// token, cold, one chunk ahead and two: 32768 x 1024 8.06 us and 5.66, 32000 x 2048 9.17 and 7.35, 24576 x 3072 8.50 and 7.93,
-// 22016 x 4096 9.29 and 9.08; but 12288 x 4096 (three chunks) 6.12 and 6.49, 27648 x 5120 12.96 and 13.54.  Row-major 32768 x 1024
-// 8.75 and 6.07, 32000 x 2048 10.3 and 8.3, but 17216 x 4000 11.5 and 11.9.  With three and four column tiles 64 tokens of 24576 x 3072 take 11.4 and 12.6, 32000 x 2048
-// 12.4 and 11.1.  So do two column tiles, also over row-major weights, whose rows then no longer fit LDS beside the sums and are
-// read in operand order: row-major 17 tokens of 32768 x 1024 10.5 and 7.9, 32 tokens 11.1 and 8.4, 32000 x 2048 12.45 and 9.8, 13.1 and
-// 10.7; tiled 32 tokens of 24576 x 3072 9.5 and 9.05.  The norm in front takes long enough for two chunks to arrive: 12288 x 4096 7.70 and 7.30, 22016 x 4096 10.8 and 9.9
-// (10240 x 8192, eight steps a wave: 10.6 and 11.4).
+// busy; where it is fewer, a second one is worth the slot that it wastes at the end of an odd number of chunks, but not where one is
+// nearly enough.  Cold, one chunk ahead and two: tiled weights, one token, 32768 x 1024 8.06 us and 5.66, 32000 x 2048 9.17 and 7.35,
+// 24576 x 3072 8.50 and 7.93, 22016 x 4096 (six chunks) 9.29 and 9.08; but 20480 x 4096 (five) 8.70 and 8.96, with 32 tokens 10.1 and 10.5,
+// 12288 x 4096 (three) 6.12 and 6.49, 27648 x 5120 12.96 and 13.54.  Row-major 32768 x 1024 8.75 and 6.07, 32000 x 2048 10.3 and 8.3, but
+// 17216 x 4000 11.5 and 11.9; with 17 to 32 tokens, whose rows then no longer fit LDS beside the sums and are read in operand order,
+// still 11.1 and 8.4, 13.1 and 10.7.  With three and four column tiles 64 tokens of 24576 x 3072 take 11.4 and 12.6, 32000 x 2048 12.4 and 11.1.
+// The norm in front takes long enough for two chunks to arrive: 12288 x 4096 7.70 and 7.30, 22016 x 4096 10.8 and 9.9 (10240 x 8192, eight
+// steps a wave: 10.6 and 11.4).
 bool two_chunks_ahead(const DecodeShape &s, int chunks, int M, int mt) {
     const int loads = s.waves * s.x_steps;
     if (chunks == 2 && M <= 8) return true;
     if (chunks >= 2 && (loads <= 8 || (s.norm && loads <= 32))) return true;
-    return chunks >= 4 && loads <= (mt <= 2 && s.tiled ? 32 : 16);
+    const int few = !s.tiled || mt > 2 ? 16 : chunks % 2 != 0 ? 24 : 32;
+    return chunks >= 4 && loads <= few;
 }
 
 bool resident_shape(int M, int N, int K, int waves, int grid, int prefetch, bool whole16, int aux, bool tiled, DecodeShape *out,
