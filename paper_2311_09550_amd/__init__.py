@@ -173,12 +173,16 @@ def _on_current_device(t, what):
                          "call under torch.cuda.device(...) of the tensors' device")
 
 
-def _dev(t, dtype, what):
+def _dev(t, dtype, what, least=0):
+    """Address of a contiguous device tensor of dtype; least: as many elements as the kernels read from it, or write into it, where
+    its shape is not held to one above."""
     torch = _torch_module or _torch()
     if not (isinstance(t, torch.Tensor) and t.is_cuda and t.dtype == dtype and t.is_contiguous()):
         raise TypeError(f"{what}: expected a contiguous device tensor of {dtype}")
     if t.get_device() != _current_device():
         _on_current_device(t, what)
+    if t.numel() < least:
+        raise ValueError(f"{what}: expected {least} elements or more, got {t.numel()}")
     return t.data_ptr()
 
 
@@ -373,7 +377,7 @@ def w4a8_gemm_tuned(xq, s_a, wp, s_w, tiling: int, variant: int = 0, want_acc: b
     else:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device) if out is None else out
         o16, o32 = _dev(out, torch.float16, "out"), None
-        sa, sw = _dev(s_a, torch.float32, "s_a"), _dev(s_w, torch.float32, "s_w")
+        sa, sw = _dev(s_a, torch.float32, "s_a", M), _dev(s_w, torch.float32, "s_w", N)
     if out.shape != (M, N):
         raise ValueError("out shape mismatch")
     _check(lib().w4a8_gemm_tuned(_dev(xq, torch.int8, "xq"), sa, _dev(wp, torch.uint8, "wp"), sw, o16, o32, M, N, K,
@@ -418,7 +422,7 @@ def w4a8_gemm_tiled(xq, s_a, wt, s_w, out=None):
     out = torch.empty((M, N), dtype=torch.float16, device=xq.device) if out is None else out
     if out.shape != (M, N):
         raise ValueError("out shape mismatch")
-    _check(lib().w4a8_gemm_tiled(_dev(xq, torch.int8, "xq"), _dev(s_a, torch.float32, "s_a"), _dev(wt, torch.uint8, "wt"),
+    _check(lib().w4a8_gemm_tiled(_dev(xq, torch.int8, "xq"), _dev(s_a, torch.float32, "s_a", M), _dev(wt, torch.uint8, "wt"),
                                  _dev(s_w, torch.float32, "s_w"), _dev(out, torch.float16, "out"), M, N, K, _stream()))
     return out
 
@@ -460,7 +464,7 @@ def w8a8_gemm_tiled(xq, s_a, wt, s_w, N=None, variant: int = 0, want_acc: bool =
     else:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device) if out is None else out
         o16, o32 = _dev(out, torch.float16, "out"), None
-        sa, sw = _dev(s_a, torch.float32, "s_a"), _dev(s_w, torch.float32, "s_w")
+        sa, sw = _dev(s_a, torch.float32, "s_a", M), _dev(s_w, torch.float32, "s_w", N)
     if out.shape != (M, N):
         raise ValueError("out shape mismatch")
     _check(lib().w8a8_gemm_tiled(_dev(xq, torch.int8, "xq"), sa, _dev(wt, torch.uint8, "wt"), sw, o16, o32, M, N, K, variant,
@@ -483,7 +487,7 @@ def w4a8_gemm_tiled_unsigned(xq, s_a, ut, s_w, N=None, variant: int = 0, want_ac
     else:
         out = torch.empty((M, N), dtype=torch.float16, device=xq.device) if out is None else out
         o16, o32 = _dev(out, torch.float16, "out"), None
-        sa, sw = _dev(s_a, torch.float32, "s_a"), _dev(s_w, torch.float32, "s_w")
+        sa, sw = _dev(s_a, torch.float32, "s_a", M), _dev(s_w, torch.float32, "s_w", N)
     if out.shape != (M, N):
         raise ValueError("out shape mismatch")
     _check(lib().w4a8_gemm_tiled_unsigned(_dev(xq, torch.int8, "xq"), sa, _dev(ut, torch.uint8, "ut"), sw, o16, o32, M, N, K,
@@ -523,7 +527,7 @@ def w4a8_gemm_tiled_splitk(xq, s_a, wt, s_w, variant: int = 0, splits: int = 0, 
     if ws is None:
         need = w4a8_gemm_tiled_workspace_bytes(M, N, K) if splits == 0 else max(splits, 1) * M * N * 4
         ws = torch.empty((max(need, 16),), dtype=torch.uint8, device=xq.device)
-    _check(lib().w4a8_gemm_tiled_splitk(_dev(xq, torch.int8, "xq"), _dev(s_a, torch.float32, "s_a"), _dev(wt, torch.uint8, "wt"),
+    _check(lib().w4a8_gemm_tiled_splitk(_dev(xq, torch.int8, "xq"), _dev(s_a, torch.float32, "s_a", M), _dev(wt, torch.uint8, "wt"),
                                         _dev(s_w, torch.float32, "s_w"), _dev(out, torch.float16, "out"), M, N, K, variant,
                                         splits, _dev(ws, torch.uint8, "ws"), ws.numel(), _stream()))
     return out
@@ -609,6 +613,8 @@ def w4a8_linear_tiled_norm_fp16(x, res, gamma, eps: float, wt, s_w, swiglu: bool
         if t is not None and not (t.is_cuda and t.dtype == torch.float16 and t.stride(1) == 1 and tuple(t.shape) == (M, K)):
             raise TypeError(f"{name}: expected a device fp16 [M][K] view with unit column stride")
     _on_current_device(x, "x")
+    if res is not None:
+        _on_current_device(res, "res")
     if wt.numel() != w4a8_tiled_weight_bytes(N, K):
         raise ValueError("tiled weight array does not match (N, K)")
     cols = N // 2 if swiglu else N
@@ -623,7 +629,7 @@ def w4a8_linear_tiled_norm_fp16(x, res, gamma, eps: float, wt, s_w, swiglu: bool
     opt = lambda t, dt, name: None if t is None else _dev(t, dt, name)
     _check(lib().w4a8_linear_tiled_norm_fp16(ctypes.c_void_p(x.data_ptr()), x.stride(0),
                                              None if res is None else ctypes.c_void_p(res.data_ptr()),
-                                             0 if res is None else res.stride(0), _dev(gamma, torch.float16, "gamma"),
+                                             0 if res is None else res.stride(0), _dev(gamma, torch.float16, "gamma", K),
                                              float(eps), opt(r_out, torch.float16, "r_out"), opt(y_out, torch.float16, "y_out"),
                                              _dev(wt, torch.uint8, "wt"), _dev(s_w, torch.float32, "s_w"),
                                              _dev(out, torch.float16, "out"), opt(s_a_out, torch.float32, "s_a_out"), M, N, K,
@@ -674,7 +680,7 @@ def w4a8_gemm_tiled_splitk_static(xq, s_a, wt, s_w, out, variant: int = 0, split
         raise ValueError("tiled weight array does not match (N, K)")
     if out.shape != (M, N):
         raise ValueError("out shape mismatch")
-    _check(lib().w4a8_gemm_tiled_splitk_static(_dev(xq, torch.int8, "xq"), _dev(s_a, torch.float32, "s_a"),
+    _check(lib().w4a8_gemm_tiled_splitk_static(_dev(xq, torch.int8, "xq"), _dev(s_a, torch.float32, "s_a", M),
                                                _dev(wt, torch.uint8, "wt"), _dev(s_w, torch.float32, "s_w"),
                                                _dev(out, torch.float16, "out"), M, N, K, variant, splits, _stream()))
     return out
@@ -694,7 +700,7 @@ def w4a8_gemm_fine_grained(xq, s_a, wt, s_g, N=None, variant: int = 0, out=None)
     out = torch.empty((M, N), dtype=torch.float16, device=xq.device) if out is None else out
     if out.shape != (M, N):
         raise ValueError("out shape mismatch")
-    _check(lib().w4a8_gemm_fine_grained(_dev(xq, torch.int8, "xq"), _dev(s_a, torch.float32, "s_a"), _dev(wt, torch.uint8, "wt"),
+    _check(lib().w4a8_gemm_fine_grained(_dev(xq, torch.int8, "xq"), _dev(s_a, torch.float32, "s_a", M), _dev(wt, torch.uint8, "wt"),
                                         _dev(s_g, torch.float32, "s_g"), ldg, _dev(out, torch.float16, "out"), M, N, K,
                                         variant, _stream()))
     return out
@@ -709,8 +715,8 @@ def w4a8_quantize_weights(w, wp=None, s_w=None):
     N, K = w.shape
     wp = torch.empty((N, K // 2), dtype=torch.uint8, device=w.device) if wp is None else wp
     s_w = torch.empty((N,), dtype=torch.float32, device=w.device) if s_w is None else s_w
-    _check(lib().w4a8_quantize_weights(_dev(w, torch.float16, "w"), _dev(wp, torch.uint8, "wp"),
-                                       _dev(s_w, torch.float32, "s_w"), N, K, _stream()))
+    _check(lib().w4a8_quantize_weights(_dev(w, torch.float16, "w"), _dev(wp, torch.uint8, "wp", N * (K // 2)),
+                                       _dev(s_w, torch.float32, "s_w", N), N, K, _stream()))
     return wp, s_w
 
 
@@ -726,7 +732,7 @@ def w4a8_quantize_weights_clipped(w, gamma=None, beta=None, wp=None, s_w=None):
     _check(lib().w4a8_quantize_weights_clipped(_dev(w, torch.float16, "w"),
                                                None if gamma is None else _dev(gamma, torch.float32, "gamma"),
                                                None if beta is None else _dev(beta, torch.float32, "beta"),
-                                               _dev(wp, torch.uint8, "wp"), _dev(s_w, torch.float32, "s_w"), N, K, _stream()))
+                                               _dev(wp, torch.uint8, "wp", N * (K // 2)), _dev(s_w, torch.float32, "s_w", N), N, K, _stream()))
     return wp, s_w
 
 
@@ -736,7 +742,7 @@ def w4a8_silu_mul(gate_up, h=None):
     M, I2 = gate_up.shape
     I = I2 // 2
     h = torch.empty((M, I), dtype=torch.float16, device=gate_up.device) if h is None else h
-    _check(lib().w4a8_silu_mul(_dev(gate_up, torch.float16, "gate_up"), _dev(h, torch.float16, "h"), M, I, _stream()))
+    _check(lib().w4a8_silu_mul(_dev(gate_up, torch.float16, "gate_up"), _dev(h, torch.float16, "h", M * I), M, I, _stream()))
     return h
 
 
@@ -747,8 +753,8 @@ def w4a8_silu_mul_quantize(gate_up, xq=None, s_a=None):
     I = I2 // 2
     xq = torch.empty((M, I), dtype=torch.int8, device=gate_up.device) if xq is None else xq
     s_a = torch.empty((M,), dtype=torch.float32, device=gate_up.device) if s_a is None else s_a
-    _check(lib().w4a8_silu_mul_quantize(_dev(gate_up, torch.float16, "gate_up"), _dev(xq, torch.int8, "xq"),
-                                        _dev(s_a, torch.float32, "s_a"), M, I, _stream()))
+    _check(lib().w4a8_silu_mul_quantize(_dev(gate_up, torch.float16, "gate_up"), _dev(xq, torch.int8, "xq", M * I),
+                                        _dev(s_a, torch.float32, "s_a", M), M, I, _stream()))
     return xq, s_a
 
 
