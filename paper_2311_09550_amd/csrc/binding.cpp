@@ -21,6 +21,7 @@
 #include <cstddef>
 #include <cstdint>
 #include <cstring>
+#include <exception>
 #include <memory>
 #include <tuple>
 #include <type_traits>
@@ -86,10 +87,22 @@ at::Tensor output(PyObject *o, const Here &here, at::ScalarType type, at::IntArr
     return t;
 }
 
-PyObject *returned(PyObject *given, const at::Tensor &t) {
-    if (given == Py_None) return THPVariable_Wrap(t);
-    Py_INCREF(given);
-    return given;
+// A reference given up with its scope unless it is handed on
+struct Owned {
+    PyObject *object;
+    explicit Owned(PyObject *o) : object(o) {
+        if (!o) throw NotServed{};
+    }
+    Owned(const Owned &) = delete;
+    ~Owned() { Py_XDECREF(object); }
+    PyObject *release() { return std::exchange(object, nullptr); }
+};
+
+// What a call returns, made before its launch: nothing behind a launch may fail, or the Python function would launch once more
+PyObject *returned(PyObject *given, const at::Tensor &t) { return given == Py_None ? THPVariable_Wrap(t) : Py_NewRef(given); }
+PyObject *returned(PyObject *given0, const at::Tensor &t0, PyObject *given1, const at::Tensor &t1) {
+    const Owned r0(returned(given0, t0)), r1(returned(given1, t1));
+    return PyTuple_Pack(2, r0.object, r1.object);
 }
 
 // The call itself, with the interpreter's lock given back as ctypes would (a launch waits where the queue is full).  False: the
@@ -117,10 +130,11 @@ PyObject *serve(Py_ssize_t nargs, Py_ssize_t want, Body body) {
     if (nargs != want || !check || at::impl::torch_function_mode_enabled() || c10::impl::dispatch_mode_enabled()) Py_RETURN_NONE;
     try {
         return body();
-    } catch (...) {  // NotServed, or an exception of torch's, which the Python function will meet again and pass on
-        if (PyErr_Occurred()) PyErr_Clear();
-        Py_RETURN_NONE;
+    } catch (const NotServed &) {
+    } catch (const std::exception &) {  // of torch's, which the Python function will meet again and pass on
     }
+    PyErr_Clear();
+    Py_RETURN_NONE;
 }
 
 template <class T>
@@ -142,13 +156,10 @@ PyObject *quantize_act(PyObject *, PyObject *const *a, Py_ssize_t n) {
         float *const ps = ptr<float>(s_a);
         const long long ldx = x.stride(0);
         void *const stream = here.stream();
+        Owned both(returned(a[1], xq, a[2], s_a));
         if (!launched([=] { return STRIDED ? entries.quantize_act_strided(px, ldx, pq, ps, M, K, stream) : entries.quantize_act(px, pq, ps, M, K, stream); }))
             return nullptr;
-        PyObject *q = returned(a[1], xq), *s = returned(a[2], s_a);
-        PyObject *both = q && s ? PyTuple_Pack(2, q, s) : nullptr;
-        Py_XDECREF(q);
-        Py_XDECREF(s);
-        return both;
+        return both.release();
     });
 }
 
@@ -175,8 +186,9 @@ PyObject *gemm_with(const Operands &o, PyObject *out_given, Call call) {
     const int8_t *const xq = ptr<int8_t>(o.xq);
     const float *const s_a = ptr<float>(o.s_a), *const s_w = ptr<float>(o.s_w);
     void *const po = ptr<void>(out), *const stream = o.here.stream();
+    Owned result(returned(out_given, out));
     if (!launched([&] { return call(xq, s_a, s_w, po, stream); })) return nullptr;
-    return returned(out_given, out);
+    return result.release();
 }
 
 // (xq, s_a, wp, s_w, out); the entry point makes no use of a workspace
@@ -245,8 +257,9 @@ PyObject *linear_tiled_fp16(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const float *const ps = ptr<float>(s_w);
         void *const po = ptr<void>(out), *const stream = here.stream();
         const long long ldx = x.stride(0);
+        Owned result(returned(a[3], out));
         if (!launched([=] { return entries.linear_tiled_fp16(px, ldx, pw, ps, po, scales, M, N, K, stream); })) return nullptr;
-        return returned(a[3], out);
+        return result.release();
     });
 }
 
@@ -261,12 +274,9 @@ PyObject *quantize_weights(PyObject *, PyObject *const *a, Py_ssize_t n) {
         uint8_t *const pp = ptr<uint8_t>(wp);
         float *const ps = ptr<float>(s_w);
         void *const stream = here.stream();
+        Owned both(returned(a[1], wp, a[2], s_w));
         if (!launched([=] { return entries.quantize_weights(pw, pp, ps, N, K, stream); })) return nullptr;
-        PyObject *p = returned(a[1], wp), *s = returned(a[2], s_w);
-        PyObject *both = p && s ? PyTuple_Pack(2, p, s) : nullptr;
-        Py_XDECREF(p);
-        Py_XDECREF(s);
-        return both;
+        return both.release();
     });
 }
 
@@ -282,8 +292,9 @@ PyObject *tile_weights(PyObject *, PyObject *const *a, Py_ssize_t n) {
         const uint8_t *const pp = ptr<uint8_t>(wp);
         uint8_t *const pt = ptr<uint8_t>(wt);
         void *const stream = here.stream();
+        Owned result(returned(a[1], wt));
         if (!launched([=] { return entries.tile_weights(pp, pt, N, K, stream); })) return nullptr;
-        return returned(a[1], wt);
+        return result.release();
     });
 }
 
@@ -347,7 +358,7 @@ std::unique_ptr<Marshalled> marshal(int (*)(A...), void *address, PyObject *valu
 
 std::unique_ptr<Marshalled> marshal_by_name(const char *name, void *address, PyObject *values) {
 #define W4A8_ENTRY(entry) \
-    if (std::strcmp(name, #entry) == 0) return marshal(&::entry, address, values);
+    if (std::strcmp(name, #entry) == 0) return marshal((decltype(&::entry))nullptr, address, values);  /* its type only */
     W4A8_ENTRY(w4a8_quantize_act) W4A8_ENTRY(w4a8_quantize_act_strided) W4A8_ENTRY(w4a8_gemm) W4A8_ENTRY(w4a8_gemm_acc_i32)
     W4A8_ENTRY(w4a8_tile_weights) W4A8_ENTRY(w4a8_gemm_tiled) W4A8_ENTRY(w4a8_quantize_weights) W4A8_ENTRY(w4a8_quantize_weights_clipped)
     W4A8_ENTRY(w4a8_gemm_tiled_swiglu) W4A8_ENTRY(w4a8_gemm_tiled_splitk) W4A8_ENTRY(w4a8_gemm_tiled_splitk_static)
