@@ -374,6 +374,8 @@ struct BoundCall {
     vectorcallfunc vectorcall;
     Marshalled *call;
     PyObject *keep;  // the tensors behind the pointers
+    PyObject *dict;  // attributes, __name__ and the like among them, and weak references, as a Python function has them
+    PyObject *weak;
     c10::DeviceIndex device;
 };
 
@@ -396,20 +398,28 @@ PyObject *bound_run(PyObject *self, PyObject *const *, size_t nargsf, PyObject *
 
 int bound_traverse(PyObject *self, visitproc visit, void *arg) {
     Py_VISIT(((BoundCall *)self)->keep);
+    Py_VISIT(((BoundCall *)self)->dict);
     return 0;
 }
 
 int bound_clear(PyObject *self) {
     Py_CLEAR(((BoundCall *)self)->keep);
+    Py_CLEAR(((BoundCall *)self)->dict);
     return 0;
 }
 
 void bound_dealloc(PyObject *self) {
     PyObject_GC_UnTrack(self);
+    if (((BoundCall *)self)->weak) PyObject_ClearWeakRefs(self);
     bound_clear(self);
     delete ((BoundCall *)self)->call;
     PyObject_GC_Del(self);
 }
+
+// copy.copy, copy.deepcopy: itself, as of a function
+PyObject *bound_copied(PyObject *self, PyObject *) { return Py_NewRef(self); }
+PyMethodDef bound_methods[] = {{"__copy__", bound_copied, METH_NOARGS, nullptr}, {"__deepcopy__", bound_copied, METH_O, nullptr}, {nullptr, nullptr, 0, nullptr}};
+PyGetSetDef bound_attributes[] = {{"__dict__", PyObject_GenericGetDict, PyObject_GenericSetDict, nullptr, nullptr}, {nullptr, nullptr, nullptr, nullptr, nullptr}};
 
 PyTypeObject bound_type = {PyVarObject_HEAD_INIT(nullptr, 0)};
 
@@ -426,8 +436,14 @@ PyObject *bound(PyObject *, PyObject *args) {
         PyErr_Clear();
         Py_RETURN_NONE;
     }
-    BoundCall *const b = PyObject_GC_New(BoundCall, &bound_type);
-    if (!b) return nullptr;
+    PyObject *const dict = Py_BuildValue("{ssssss}", "__name__", "call", "__qualname__", "bound_call.<locals>.call", "__module__", "paper_2311_09550_amd");
+    BoundCall *const b = dict ? PyObject_GC_New(BoundCall, &bound_type) : nullptr;
+    if (!b) {
+        Py_XDECREF(dict);
+        return nullptr;
+    }
+    b->dict = dict;
+    b->weak = nullptr;
     b->vectorcall = bound_run;
     b->call = call.release();
     b->keep = Py_NewRef(keep);
@@ -494,6 +510,12 @@ PyMODINIT_FUNC PyInit__binding() {
     bound_type.tp_flags = Py_TPFLAGS_DEFAULT | Py_TPFLAGS_HAVE_GC | Py_TPFLAGS_HAVE_VECTORCALL;
     bound_type.tp_vectorcall_offset = offsetof(BoundCall, vectorcall);
     bound_type.tp_call = PyVectorcall_Call;
+    bound_type.tp_dictoffset = offsetof(BoundCall, dict);
+    bound_type.tp_weaklistoffset = offsetof(BoundCall, weak);
+    bound_type.tp_methods = bound_methods;
+    bound_type.tp_getset = bound_attributes;
+    bound_type.tp_getattro = PyObject_GenericGetAttr;
+    bound_type.tp_setattro = PyObject_GenericSetAttr;
     bound_type.tp_traverse = bound_traverse;
     bound_type.tp_clear = bound_clear;
     bound_type.tp_dealloc = bound_dealloc;

@@ -1,5 +1,11 @@
 """The native short way of the binding's calls without a GPU: it serves nothing that is not on the device, and the checks written out
 in Python answer as they do without it."""
+import copy
+import ctypes
+import functools
+import gc
+import weakref
+
 import pytest
 
 import paper_2311_09550_amd as w4a8
@@ -48,3 +54,29 @@ def test_bind_wants_every_address(short):
         short.bind(w4a8._check, {})
     with pytest.raises(TypeError):
         short.bind(w4a8._check, None)
+
+
+def test_a_bound_call_has_what_a_function_has(short):
+    """Weak references, attributes, a name, and copies that are itself: what bound_call returned before it was native, and still returns
+    where its arguments are left to ctypes."""
+    class Tensor:  # stands for what is kept alive
+        pass
+    kept = Tensor()
+    alive = weakref.ref(kept)
+    address = ctypes.cast(w4a8.lib().w4a8_quantize_act, ctypes.c_void_p).value
+    bound = short.bound("w4a8_quantize_act", address, (0, 0, 0, 1, 64), 0, [kept])
+    assert bound is not None and callable(bound)
+    assert (bound.__name__, bound.__qualname__, bound.__module__) == ("call", "bound_call.<locals>.call", "paper_2311_09550_amd")
+    bound.note = "down projection"
+    assert vars(bound)["note"] == bound.note
+    assert copy.copy(bound) is bound and copy.deepcopy([bound])[0] is bound
+    wrapped = functools.wraps(bound)(lambda: bound())
+    assert wrapped.__name__ == "call" and wrapped.note == bound.note and wrapped.__wrapped__ is bound
+    assert {weakref.ref(bound)} and weakref.WeakSet([bound])
+    with pytest.raises(TypeError):
+        type(bound)()
+    bound.me = bound  # a cycle through its attributes is collected
+    gone = weakref.ref(bound)
+    del bound, wrapped, kept
+    gc.collect()
+    assert gone() is None and alive() is None
