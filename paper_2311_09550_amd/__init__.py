@@ -10,7 +10,10 @@ from __future__ import annotations
 
 import ctypes
 import functools
+import importlib.machinery
+import importlib.util
 import os
+import warnings
 
 _HERE = os.path.dirname(os.path.abspath(__file__))
 LIB_PATH = os.path.join(_HERE, "libw4a8.so")
@@ -24,7 +27,7 @@ _lib = None
 
 
 class _NothingLoaded:
-    """In the place of the native short way until the library is loaded: serves no call."""
+    """In the place of the native short way until the library is loaded, and where the short way is not to be had: serves no call."""
 
     def __getattr__(self, name):
         return lambda *args: None
@@ -41,15 +44,34 @@ class W4A8Error(RuntimeError):
         self.code = code
 
 
+def _native_short_way():
+    """_binding.so, or None with a warning: every call has its whole path in Python, and the same kernels behind it; small calls then
+    take two to three microseconds longer on the host."""
+    import torch
+    path, why = BINDING_PATH, None
+    if not os.path.exists(path):
+        why = "is missing"
+    else:
+        loader = importlib.machinery.ExtensionFileLoader(f"{__name__}._binding", path)
+        try:
+            module = importlib.util.module_from_spec(importlib.util.spec_from_loader(loader.name, loader))
+            loader.exec_module(module)
+            if module.built_for == torch.__version__:
+                return module
+            why = f"is built for torch {module.built_for}, not {torch.__version__}"  # whose tensors it could misread
+        except ImportError as e:  # another torch, or another Python
+            why = f"cannot be loaded ({e})"
+    warnings.warn(f"{path} {why}: calls go by way of ctypes (python -m paper_2311_09550_amd.build builds it)", RuntimeWarning, stacklevel=3)
+    return None
+
+
 def lib():
-    """Load libw4a8.so (once).  Fails loudly when it, or the binding's native part, is missing."""
+    """Load libw4a8.so (once).  Fails loudly when it is missing, and says so when the binding's native part is."""
     global _lib, _short
     if _lib is None:
-        for path in (LIB_PATH, BINDING_PATH):
-            if os.path.exists(path):
-                continue
+        if not os.path.exists(LIB_PATH):
             raise ImportError(
-                f"{path} is missing: build the HIP library first "
+                f"{LIB_PATH} is missing: build the HIP library first "
                 "(python -m paper_2311_09550_amd.build); there is no fallback path")
         # torch first: it ships its own HIP runtime, and the one loaded first serves the whole process.  Loaded the
         # other way round, this library's kernels are registered with a runtime that torch's streams and memory do
@@ -123,12 +145,14 @@ def lib():
                      "w4a8_tile_weights", "w4a8_gemm_tiled"):
             getattr(L, name).restype = i
         L.w4a8_last_hip_error.restype = ctypes.c_char_p
-        from . import _binding
-        _binding.bind(_check, {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
-            "w4a8_quantize_act", "w4a8_quantize_act_strided", "w4a8_gemm", "w4a8_gemm_tiled", "w4a8_gemm_tiled_splitk",
-            "w8a8_gemm_tiled", "w4a8_linear_tiled_fp16", "w4a8_tiled_weight_bytes", "w8a8_tiled_weight_bytes",
-            "w4a8_quantize_weights", "w4a8_tile_weights")})
-        _short, _lib = _binding, L
+        short = _native_short_way()
+        if short is not None:
+            short.bind(_check, {name: ctypes.cast(getattr(L, name), ctypes.c_void_p).value for name in (
+                "w4a8_quantize_act", "w4a8_quantize_act_strided", "w4a8_gemm", "w4a8_gemm_tiled", "w4a8_gemm_tiled_splitk",
+                "w8a8_gemm_tiled", "w4a8_linear_tiled_fp16", "w4a8_tiled_weight_bytes", "w8a8_tiled_weight_bytes",
+                "w4a8_quantize_weights", "w4a8_tile_weights")})
+            _short = short
+        _lib = L
     return _lib
 
 

@@ -1,6 +1,7 @@
-"""Builds libw4a8.so (gfx950 only) next to this file with hipcc, and _binding.so with g++."""
+"""Builds libw4a8.so (gfx950 only) next to this file with hipcc, and _binding.so with g++ where torch is installed."""
 from __future__ import annotations
 
+import importlib.util
 import os
 import subprocess
 import sys
@@ -57,24 +58,23 @@ def binding_command() -> list:
     home = os.path.dirname(torch.__file__)
     rocm = os.path.dirname(os.path.dirname(hipcc())) if os.path.isabs(hipcc()) else "/opt/rocm"
     return ["g++", "-O2", "-std=c++17", "-fPIC", "-shared", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
-            f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(home, "include"),
+            f'-DW4A8_BUILT_FOR_TORCH="{torch.__version__}"', f"-D_GLIBCXX_USE_CXX11_ABI={int(torch._C._GLIBCXX_USE_CXX11_ABI)}", "-I" + os.path.join(home, "include"),
             "-I" + sysconfig.get_paths()["include"], "-I" + os.path.join(rocm, "include"), os.path.join(CSRC, "binding.cpp"), "-o", BINDING,
             "-L" + os.path.join(home, "lib"), "-ltorch_python", "-ltorch_cpu", "-lc10", "-lc10_hip"]
 
 
 def build_library(force: bool = True, verbose: bool = False) -> str:
-    """Compile every HIP source for gfx950 and link the shared library, and the binding's native part beside it."""
+    """Compile every HIP source for gfx950 and link the shared library.  Users of the C interface need no more; where torch can be
+    imported the binding's native part is built afterwards."""
     srcs = [os.path.join(CSRC, s) for s in SOURCES]
-    deps = srcs + [os.path.join(CSRC, h) for h in HEADERS] + [os.path.join(CSRC, "binding.cpp")]
-    if not force and all(os.path.exists(built) and os.path.getmtime(built) >= max(map(os.path.getmtime, deps)) for built in (LIB, BINDING)):
+    with_binding = importlib.util.find_spec("torch") is not None
+    deps = srcs + [os.path.join(CSRC, h) for h in HEADERS] + ([os.path.join(CSRC, "binding.cpp")] if with_binding else [])
+    built = (LIB, BINDING) if with_binding else (LIB,)
+    if not force and all(os.path.exists(b) and os.path.getmtime(b) >= max(map(os.path.getmtime, deps)) for b in built):
         return LIB
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
-    cmd = binding_command()
-    if verbose:
-        print(" ".join(cmd), flush=True)
-    procs = [(cmd, subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT, text=True))]
-    objs = []
+    procs, objs = [], []
     for s in srcs:
         o = os.path.join(objdir, os.path.basename(s) + ".o")
         objs.append(o)
@@ -89,6 +89,11 @@ def build_library(force: bool = True, verbose: bool = False) -> str:
             raise RuntimeError("compilation failed: " + " ".join(cmd))
     cmd = [hipcc(), "--offload-arch=gfx950", "-shared", "-fPIC", "-o", LIB, *objs]
     subprocess.run(cmd, check=True)
+    if with_binding:
+        cmd = binding_command()
+        if verbose:
+            print(" ".join(cmd), flush=True)
+        subprocess.run(cmd, check=True)
     return LIB
 
 

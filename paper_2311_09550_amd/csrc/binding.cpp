@@ -519,5 +519,11 @@ PyMODINIT_FUNC PyInit__binding() {
     bound_type.tp_traverse = bound_traverse;
     bound_type.tp_clear = bound_clear;
     bound_type.tp_dealloc = bound_dealloc;
-    return PyType_Ready(&bound_type) < 0 ? nullptr : PyModule_Create(&module);
+    if (PyType_Ready(&bound_type) < 0) return nullptr;
+    PyObject *const m = PyModule_Create(&module);
+    if (m && PyModule_AddStringConstant(m, "built_for", W4A8_BUILT_FOR_TORCH) < 0) {
+        Py_DECREF(m);
+        return nullptr;
+    }
+    return m;
 }

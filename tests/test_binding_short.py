@@ -49,6 +49,53 @@ def test_what_is_no_tensor_is_not_served(short, args):
         assert getattr(short, name)(*args) is None
 
 
+@pytest.mark.parametrize("how", ["missing", "unreadable", "another torch"])
+def test_without_the_short_way_calls_go_by_ctypes(short, monkeypatch, tmp_path, how):
+    """A missing, broken or foreign _binding.so takes no call away: the library loads, says so once, and bound_call still binds."""
+    import torch
+    if how != "another torch":
+        path = tmp_path / "_binding.so"
+        if how == "unreadable":
+            path.write_bytes(b"no library")
+        monkeypatch.setattr(w4a8, "BINDING_PATH", str(path))
+    else:
+        monkeypatch.setattr(torch, "__version__", "1.0")
+    monkeypatch.setattr(w4a8, "_lib", None)
+    monkeypatch.setattr(w4a8, "_short", w4a8._NothingLoaded())
+    with pytest.warns(RuntimeWarning, match="_binding.so"):
+        assert w4a8.lib().w4a8_version() > 0
+    assert isinstance(w4a8._short, w4a8._NothingLoaded) and w4a8._short.quantize_act(None, None, None) is None
+    with pytest.raises(TypeError):
+        w4a8.w4a8_quantize_act(torch.zeros((2, 64), dtype=torch.float16))
+    assert w4a8.w4a8_tiled_weight_bytes(32, 128) == 2048
+
+
+def test_the_library_is_built_without_torch(monkeypatch, tmp_path):
+    """hipcc is all that the C interface needs: no torch, no C++ compiler of the host, no CPython headers."""
+    import subprocess
+    import sys
+
+    from paper_2311_09550_amd import build
+    ran = []
+
+    class Done:
+        returncode = 0
+
+        def communicate(self):
+            return "", None
+    monkeypatch.setattr(build, "HERE", str(tmp_path))
+    monkeypatch.setattr(build, "LIB", str(tmp_path / "libw4a8.so"))
+    monkeypatch.setattr(build, "BINDING", str(tmp_path / "_binding.so"))
+    monkeypatch.setattr(subprocess, "Popen", lambda cmd, **kw: ran.append(cmd) or Done())
+    monkeypatch.setattr(subprocess, "run", lambda cmd, **kw: ran.append(cmd))
+    build.build_library()
+    assert any("binding.cpp" in part for cmd in ran for part in cmd) and len(ran) == len(build.SOURCES) + 2
+    ran.clear()
+    monkeypatch.setitem(sys.modules, "torch", None)  # as where it is not installed
+    build.build_library()
+    assert len(ran) == len(build.SOURCES) + 1 and all("hipcc" in cmd[0] for cmd in ran)
+
+
 def test_bind_wants_every_address(short):
     with pytest.raises(KeyError):
         short.bind(w4a8._check, {})
