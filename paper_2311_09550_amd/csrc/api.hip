@@ -202,15 +202,18 @@ constexpr TileCost kTileCosts[] = {
     {kTiled192x192, 192, 192, 1, 5.91f, 0.00f, 0.802f, 0.620f, 0.141f, 0.000f},
 };
 
-// The same for more than 512 tokens with K >= 1024, where the prices above are extrapolated for the most part: a round costs some
+// The same for more than 512 tokens with K >= 1536, where the prices above are extrapolated for the most part: a round costs some
 // 5 to 8 us beside its stages, and the chip is at its power limit.  Fits over 600 shapes (380 random, 220 of whole tiles, the models' linears
-// among them; M 513 .. 2300, N 1024 .. 65536, K 1024 .. 28672; weights cold, the chip warm; about 9 % off, but alike for all tiles), then
-// moved a little towards the choices that measured best.  Choosing by them costs 0.3 % on average over always taking the fastest of the
-// sixteen, the prices above on fourteen tiles 2.5 %; one shape takes over 3 % longer than by those.  Two tiles are in here alone, worth
-// 0.3 % each: 256 x 320 (N = 10240, K = 8192, M = 2048, one round where 192 x 256 takes two: 126.8 -> 111.2 us) and 192 x 384
-// (N = 21888, K = 13184, M = 718: 169 -> 148).  More of the output per operand byte is what counts at the power limit:
+// among them; M 513 .. 2300, N 1024 .. 65536, K 1024 .. 28672; weights cold, the chip warm; about 9 % off, but alike for all tiles), their
+// shares and shorter terms then moved by hand towards the choices that measured best.  On 670 other random shapes (M 513 .. 2300, K from
+// 1024) choosing by them costs 0.8 % on average over always taking the fastest of the sixteen, the prices above on fourteen tiles 1.3 %;
+// 3 of the 670 take over 3 % longer than by those, by 5 % at most.  (64 x 256 had been fitted cheaper than 64 x 192 where both take one
+// round: N = 4224, K = 15808, M = 689 56.6 us, 52.5 as 64 x 192.)  On a shorter K these prices choose better on average, but now and
+// then much worse: N = 1000, K = 1024, M = 2000 6.1 us and 6.6.  Two tiles are in here alone, worth 0.3 % each: 256 x 320 (N = 10240,
+// K = 8192, M = 2048, one round where 192 x 256 takes two: 126.8 -> 111.2 us) and 192 x 384 (N = 21888, K = 13184, M = 718: 169 -> 148).
+// More of the output per operand byte is what counts at the power limit:
 // the matrix instructions alone hold 2.35 GHz, with the LDS reads of 256 x 256 2.1, with operands coming from L2 as well 1.9.
-constexpr int kManyTokens = 512, kManyTokensMinK = 1024;
+constexpr int kManyTokens = 512, kManyTokensMinK = 1536;
 constexpr TileCost kManyTokensTileCosts[] = {
     {kTiled256x256, 256, 256, 1, 2.318f, 6.822f, 1.311f, 0.866f, 0.424f, 0.000f},
     {kTiled128x256, 128, 256, 2, 1.304f, 7.124f, 1.324f, 1.017f, 0.430f, 0.468f},
@@ -218,7 +221,7 @@ constexpr TileCost kManyTokensTileCosts[] = {
     {kTiled64x64, 64, 64, 3, 4.730f, 0.000f, 0.543f, 0.136f, 0.399f, 0.000f},
     {kTiled32x128, 32, 128, 3, 4.842f, 0.291f, 0.481f, 0.152f, 0.359f, 0.000f},
     {kTiled128x256W8, 128, 256, 1, 2.584f, 4.417f, 0.736f, 0.482f, 0.216f, 0.000f},
-    {kTiled64x256, 64, 256, 1, 2.946f, 2.444f, 0.466f, 0.288f, 0.136f, 0.000f},
+    {kTiled64x256, 64, 256, 1, 2.946f, 2.444f, 0.466f, 0.318f, 0.136f, 0.000f},
     {kTiled128x384, 128, 384, 1, 2.736f, 5.661f, 1.040f, 0.682f, 0.301f, 0.000f},
     {kTiled128x192, 128, 192, 1, 2.613f, 4.036f, 0.597f, 0.398f, 0.166f, 0.000f},
     {kTiled64x192, 64, 192, 1, 2.677f, 2.228f, 0.444f, 0.317f, 0.108f, 0.000f},
@@ -256,7 +259,7 @@ TileCosts signed_tile_costs(int M, int K) {
     return {std::begin(kTileCosts), std::end(kTileCosts)};
 }
 
-int cheapest_tile(TileCosts costs, int M, int N, int K) {
+int cheapest_tile(TileCosts costs, int M, int N, int K, double *price = nullptr) {
     const int stages = (K + kTiledBlockK - 1) / kTiledBlockK, cus = compute_units();
     int best = 0;
     double best_us = 0;
@@ -264,6 +267,7 @@ int cheapest_tile(TileCosts costs, int M, int N, int K) {
         const double us = tile_us(t, M, N, stages, cus);
         if (best == 0 || us < best_us) best = t.id, best_us = us;
     }
+    if (price) *price = best_us;
     return best;
 }
 
@@ -370,7 +374,10 @@ constexpr StepCost kMediumCosts[] = {
 };
 // How much lower it has to be priced than the large-M kernel.  Beyond 512 tokens 15 %: it brings in more bytes per operation, which
 // prices taken from short runs don't show.  N = 5120, K = 13824, M = 1024, as 64 x 160 tiles: 73.5 us against 75.3 by itself, but the
-// layer around it 306 us instead of 299, at the power limit.  (On 60 shapes beyond 512 tokens it then gives 7.0 %, with 3 % 7.1.)
+// layer around it 306 us instead of 299, at the power limit.  (On 60 shapes beyond 512 tokens it then gives 7.0 %, with 3 % 7.1.)  The
+// prices it is set against there are kTileCosts', not kManyTokensTileCosts', which ask more for few and small tiles and less for a long K:
+// against those, on the 670 shapes above, 11 more take over 3 % longer (N = 3072, K = 1024, M = 586 as 32 x 64 tiles 1.28 times as long,
+// N = 3264, K = 3680, M = 768 16.0 us as 64 x 256 tiles where 64 x 160 take 13.9).
 double medium_over_tiles(int M) { return M <= 512 ? 1.03 : 1.15; }
 
 // Against weight streaming: 10 % lower than its price, preference included (streaming_preferred), where that takes one slice
@@ -463,6 +470,8 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu, int cus)
         }
     }
     if (medium_covers(M, N, K, 4)) {
+        // beyond 512 tokens on the scale of the prices that medium_over_tiles was measured with
+        if (M > kManyTokens) cheapest_tile({std::begin(kTileCosts), std::end(kTileCosts)}, M, N, K, &best_us);
         const double bar = !best.wide                  ? best_us / medium_over_tiles(M)
                            : best.shape.k_slices == 1 ? best_us / kMediumOverStreaming
                                                       : sliced_us(best.shape, M, N, K, cus) / kMediumOverSlices;
