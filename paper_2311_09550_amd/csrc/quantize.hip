@@ -327,9 +327,11 @@ __global__ __launch_bounds__(kFusedThreads) void silu_mul_quantize_kernel(const 
 // Few rows: the order of the sum is that of 1024 threads, but up to K = 8192 on 512 of them, chain q of a thread being the thread
 // 512 q further on; half the waves, and none with nothing to do.  On 1024 threads one reduction was slower than two, without a residual
 // above all (16 x 8192 3.8 us with two, 4.1 with one, 3.6 so; 1 x 8192 3.5, 3.85, 3.3; with the residual 16 x 5120 3.8, 3.8, 3.5).
-// Up to six chunks a thread x, residual and gains of all of them are asked for ahead of the first sum, as buffer loads with no branch between
-// (with a branch around each chunk the gain of a chunk was asked for behind its x, the next chunk behind both): 16 x 5120 3.43 -> 3.14 us,
-// 333 x 4096 4.65 -> 4.53, 1024 x 5120 10.15 -> 9.67, 2048 x 8192 25.5 -> 23.8.
+// From two to six chunks a thread x, residual and gains of all of them are asked for ahead of the first sum, as buffer loads with no branch
+// between (with a branch around each chunk the gain of a chunk was asked for behind its x, the next chunk behind both): 16 x 5120 3.43 ->
+// 3.14 us, 333 x 4096 4.65 -> 4.53, 1024 x 5120 10.15 -> 9.67, 2048 x 8192 25.5 -> 23.8.  With one chunk there is nothing to gather, the
+// waves past a short row's end load nothing, and the margin of the row maximum is the shorter chain: 1 x 2048 2.33 us where loads without
+// branches and a margin per value take 2.50, 64 x 2048 2.66 and 2.82, 128 x 1024 2.67 and 2.85; 64 x 4096 level.
 template <int THREADS, int CACHE, int CHAINS = 1>
 __global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uint16_t *x, const uint16_t *res,
                                                                      const uint16_t *__restrict__ gamma, float eps,
@@ -356,7 +358,7 @@ __global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uin
     v4u cache[CACHE], gain[kKeepGains ? CACHE : 1];
     float ss[CHAINS] = {};
     unsigned top = 0u;
-    if constexpr (kKeepGains) {
+    if constexpr (kKeepGains && CACHE > 1) {
         const __amdgpu_buffer_rsrc_t x_row = row_buffer(xs, chunks), res_row = row_buffer(rs, rs ? chunks : 0), g_row = row_buffer(gs, chunks);
         v4u res_chunk[CACHE];
 #pragma unroll
@@ -394,6 +396,7 @@ __global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uin
             if (kSkip && c >= chunks) continue;
             ss[i % CHAINS] = add_squares8(cache[i], ss[i % CHAINS]);
             top = absmax_products8(cache[i], gn, top);
+            if (kKeepGains) gain[kKeepGains ? i : 0] = gn;
         }
     }
     for (int c0 = threadIdx.x + CACHE * THREADS; c0 < chunks; c0 += CHAINS * THREADS)
@@ -454,7 +457,7 @@ __global__ __launch_bounds__(THREADS) void add_rmsnorm_quantize_kernel(const uin
         if (!zero_row) {
             float yf[8];
             halves8(y, yf);
-            o = rq.packed8_own_max<true>(yf);
+            o = rq.packed8_own_max<(CACHE > 1)>(yf);
         }
         dst[c] = o;
     };
