@@ -202,18 +202,17 @@ constexpr TileCost kTileCosts[] = {
     {kTiled192x192, 192, 192, 1, 5.91f, 0.00f, 0.802f, 0.620f, 0.141f, 0.000f},
 };
 
-// The same for more than 512 tokens with K >= 1536, where the prices above are extrapolated for the most part: a round costs some
+// The same for more than 512 tokens with K >= 1024, where the prices above are extrapolated for the most part: a round costs some
 // 5 to 8 us beside its stages, and the chip is at its power limit.  Fits over 600 shapes (380 random, 220 of whole tiles, the models' linears
 // among them; M 513 .. 2300, N 1024 .. 65536, K 1024 .. 28672; weights cold, the chip warm; about 9 % off, but alike for all tiles), their
 // shares and shorter terms then moved by hand towards the choices that measured best.  On 670 other random shapes (M 513 .. 2300, K from
-// 1024) choosing by them costs 0.8 % on average over always taking the fastest of the sixteen, the prices above on fourteen tiles 1.3 %;
-// 3 of the 670 take over 3 % longer than by those, by 5 % at most.  (64 x 256 had been fitted cheaper than 64 x 192 where both take one
-// round: N = 4224, K = 15808, M = 689 56.6 us, 52.5 as 64 x 192.)  On a shorter K these prices choose better on average, but now and
-// then much worse: N = 1000, K = 1024, M = 2000 6.1 us and 6.6.  Two tiles are in here alone, worth 0.3 % each: 256 x 320 (N = 10240,
+// 1024) choosing by them costs 0.8 % on average over always taking the fastest of the sixteen, the prices above on fourteen tiles 1.6 %;
+// 2 of the 670 take over 3 % longer than by those, by 5 % at most.  (64 x 256 had been fitted cheaper than 64 x 192 where both take one
+// round: N = 4224, K = 15808, M = 689 56.6 us, 52.5 as 64 x 192.)  Two tiles are in here alone, worth 0.3 % each: 256 x 320 (N = 10240,
 // K = 8192, M = 2048, one round where 192 x 256 takes two: 126.8 -> 111.2 us) and 192 x 384 (N = 21888, K = 13184, M = 718: 169 -> 148).
 // More of the output per operand byte is what counts at the power limit:
 // the matrix instructions alone hold 2.35 GHz, with the LDS reads of 256 x 256 2.1, with operands coming from L2 as well 1.9.
-constexpr int kManyTokens = 512, kManyTokensMinK = 1536;
+constexpr int kManyTokens = 512, kManyTokensMinK = 1024;
 constexpr TileCost kManyTokensTileCosts[] = {
     {kTiled256x256, 256, 256, 1, 2.318f, 6.822f, 1.311f, 0.866f, 0.424f, 0.000f},
     {kTiled128x256, 128, 256, 2, 1.304f, 7.124f, 1.324f, 1.017f, 0.430f, 0.468f},
@@ -376,7 +375,7 @@ constexpr StepCost kMediumCosts[] = {
 // prices taken from short runs don't show.  N = 5120, K = 13824, M = 1024, as 64 x 160 tiles: 73.5 us against 75.3 by itself, but the
 // layer around it 306 us instead of 299, at the power limit.  (On 60 shapes beyond 512 tokens it then gives 7.0 %, with 3 % 7.1.)  The
 // prices it is set against there are kTileCosts', not kManyTokensTileCosts', which ask more for few and small tiles and less for a long K:
-// against those, on the 670 shapes above, 11 more take over 3 % longer (N = 3072, K = 1024, M = 586 as 32 x 64 tiles 1.28 times as long,
+// against those, on the 670 shapes above, 9 more take over 3 % longer (N = 3072, K = 1024, M = 586 as 32 x 64 tiles 1.28 times as long,
 // N = 3264, K = 3680, M = 768 16.0 us as 64 x 256 tiles where 64 x 160 take 13.9).
 double medium_over_tiles(int M) { return M <= 512 ? 1.03 : 1.15; }
 
