@@ -175,7 +175,7 @@ def test_several_slices_are_kept_where_they_are_faster_than_the_medium_m_kernel(
 def test_tiles_for_many_tokens_are_those_that_measured_faster():
     """Beyond 512 tokens: on the border between the large-M kernel and the medium-M kernel (21 .. 31), and between 64 x 192 (16) and
     64 x 256 (13), where choices by kManyTokensTileCosts alone took 4 to 28 % longer on cold weights."""
-    for (M, N, K), tile in {(586, 3072, 1024): 6, (1263, 2240, 1024): 16, (1138, 2048, 1024): 7, (768, 3264, 3680): 28, (520, 3865, 3200): 28,
+    for (M, N, K), tile in {(586, 3072, 1024): 6, (1263, 2240, 1024): 16, (1138, 2048, 1024): 16, (768, 3264, 3680): 28, (520, 3865, 3200): 28,
                             (689, 4224, 15808): 16, (629, 4331, 8128): 16,
                             (1085, 2880, 8416): 16, (615, 4296, 5792): 16}.items():
         for entry in (ROUTE_GEMM_TILED, ROUTE_SPLITK):
