@@ -205,9 +205,9 @@ constexpr TileCost kTileCosts[] = {
 // The same for more than 512 tokens with K >= 1024, where the prices above are extrapolated for the most part: a round costs some
 // 5 to 8 us beside its stages, and the chip is at its power limit.  Fits over 600 shapes (380 random, 220 of whole tiles, the models' linears
 // among them; M 513 .. 2300, N 1024 .. 65536, K 1024 .. 28672; weights cold, the chip warm; about 9 % off, but alike for all tiles), their
-// shares and shorter terms then moved by hand towards the choices that measured best.  On 670 other random shapes (M 513 .. 2300, K from
-// 1024) choosing by them costs 0.8 % on average over always taking the fastest of the sixteen, the prices above on fourteen tiles 1.6 %;
-// 2 of the 670 take over 3 % longer than by those, by 5 % at most.  (64 x 256 had been fitted cheaper than 64 x 192 where both take one
+// shares and shorter terms then moved by hand towards the choices that measured best.  On 870 other random shapes (M 513 .. 2300, K from
+// 1024) choosing by them costs 0.8 % on average over always taking the fastest of the sixteen, the prices above on fourteen tiles 1.5 %;
+// 4 of the 870 take over 3 % longer than by those, by 6 % at most.  (64 x 256 had been fitted cheaper than 64 x 192 where both take one
 // round: N = 4224, K = 15808, M = 689 56.6 us, 52.5 as 64 x 192.)  Two tiles are in here alone, worth 0.3 % each: 256 x 320 (N = 10240,
 // K = 8192, M = 2048, one round where 192 x 256 takes two: 126.8 -> 111.2 us) and 192 x 384 (N = 21888, K = 13184, M = 718: 169 -> 148).
 // More of the output per operand byte is what counts at the power limit:
@@ -373,11 +373,14 @@ constexpr StepCost kMediumCosts[] = {
 };
 // How much lower it has to be priced than the large-M kernel.  Beyond 512 tokens 15 %: it brings in more bytes per operation, which
 // prices taken from short runs don't show.  N = 5120, K = 13824, M = 1024, as 64 x 160 tiles: 73.5 us against 75.3 by itself, but the
-// layer around it 306 us instead of 299, at the power limit.  (On 60 shapes beyond 512 tokens it then gives 7.0 %, with 3 % 7.1.)  The
-// prices it is set against there are kTileCosts', not kManyTokensTileCosts', which ask more for few and small tiles and less for a long K:
-// against those, on the 670 shapes above, 9 more take over 3 % longer (N = 3072, K = 1024, M = 586 as 32 x 64 tiles 1.28 times as long,
-// N = 3264, K = 3680, M = 768 16.0 us as 64 x 256 tiles where 64 x 160 take 13.9).
+// layer around it 306 us instead of 299, at the power limit.  (On 60 shapes beyond 512 tokens it then gives 7.0 %, with 3 % 7.1.)
 double medium_over_tiles(int M) { return M <= 512 ? 1.03 : 1.15; }
+// Over int4 weights beyond 512 tokens 12 %, and against the prices of kTileCosts, not those of kManyTokensTileCosts, which ask more for few and
+// small tiles and less for a long K.  On 870 random shapes (M 513 .. 2300) the choice then costs 1.1 % on average over always taking the fastest of
+// all tiles, and 5 shapes take over 3 % longer than by kTileCosts and 15 % alone (1.9 %), by 6 % at most; 15 % cost 1.3 %.  Against
+// kManyTokensTileCosts 15 % cost 1.2 %, but 15 shapes take over 3 % longer (N = 3072, K = 1024, M = 586 as 32 x 64 tiles 1.34 times as long,
+// N = 3264, K = 3680, M = 768 16.0 us as 64 x 256 tiles where 64 x 160 take 13.9).
+constexpr double kMediumOverManyTokens = 1.12;
 
 // Against weight streaming: 10 % lower than its price, preference included (streaming_preferred), where that takes one slice
 // (the two are level there: N = 8544, K = 1824, M = 63 6.44 us and 6.43); 7 % lower than sliced_us where it takes several.  (By the price
@@ -469,9 +472,8 @@ TiledPlan plan_tiled(int M, int N, int K, size_t max_slab, bool swiglu, int cus)
         }
     }
     if (medium_covers(M, N, K, 4)) {
-        // beyond 512 tokens on the scale of the prices that medium_over_tiles was measured with
         if (M > kManyTokens) cheapest_tile({std::begin(kTileCosts), std::end(kTileCosts)}, M, N, K, &best_us);
-        const double bar = !best.wide                  ? best_us / medium_over_tiles(M)
+        const double bar = !best.wide                  ? best_us / (M > kManyTokens ? kMediumOverManyTokens : medium_over_tiles(M))
                            : best.shape.k_slices == 1 ? best_us / kMediumOverStreaming
                                                       : sliced_us(best.shape, M, N, K, cus) / kMediumOverSlices;
         double medium_us = bar;

@@ -124,8 +124,9 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
     const int idx = lane & 15;  // row of a 16-row operand tile
     const int g = lane >> 4;    // K group
 
-    // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs; consecutive tiles of one XCD share
-    // their weight panel, so it is fetched into that XCD's L2 once
+    // XCD-aware tile order: workgroup ids go round-robin over the 8 XCDs, and an XCD takes a run of consecutive tiles, column of tiles
+    // by column within a group of tile rows: those that it has in flight share weight panels and activation rows in its L2.  A
+    // panel is fetched once per group.
     const int total = p.tiles_m * p.tiles_n;
     const int per_xcd = (total + 7) >> 3;
     const int logical = (blockIdx.x & 7) * per_xcd + (blockIdx.x >> 3);
@@ -134,8 +135,10 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
     // n BN WBITS / 8 of weights per k: least for m near kBestRows.  With more tile rows than that they are taken in groups.  Bytes
     // from the memory-side cache cost the clock at the power limit about three times what bytes from L2 do: N = 57344, K = 8192, M = 2048
     // 1175 MB and 940, N = 10240 319 and 151 (with the taller tile), N = 5120, M = 1024 as 128 x 192 108 and 93; the 70B layer 1207 us and
-    // 1197, with nothing slower.
-    constexpr int kAtOnce = 32 * (kWaves <= 4 ? 2 : 1);
+    // 1197.  kAtOnce: what the LDS of 32 compute units holds, three of the smallest tiles each.  (With two for every workgroup of
+    // four waves 64 x 64 tiles of unsigned weights took nine tile rows in two groups: N = 3679, K = 6720, M = 521 32.5 us before there were
+    // groups, then 38.0, now 32.2.)
+    constexpr int kAtOnce = 32 * (160 * 1024 / (kEpiScales + 4 * (BM + BN)));
     constexpr int kBestRows = [] {
         int m = 1;
         while (m * m * BM * 8 < kAtOnce * BN * WBITS) ++m;
