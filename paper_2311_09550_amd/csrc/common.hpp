@@ -212,18 +212,20 @@ __device__ __forceinline__ float wave_sum(float v) {
 
 // Symmetric quantisation of one row (Eq. (2) with zero point 0): code = clamp(rne(fl32(x / scale)), lo, hi).
 //
-// The definition divides.  A correctly rounded fp32 division costs about ten instructions, so the common case
-// takes a shortcut that provably gives the same integer: with r = fl32(1/scale) and q' = fl32(x * r),
-// |q' - x/scale| <= |x/scale| * (2^-23 + 2^-48) < 1.6e-5 for |x/scale| <= 128, and the definition's quotient
-// fl32(x/scale) lies within 3.9e-6 of x/scale.  So when q' is at least 1e-4 away from the nearest half-integer,
-// both quotients round to the same integer; otherwise (about 2 in 10^4 elements, or rows whose quotients are
-// exact halves) the eight values of the chunk are redone with the division.
+// The definition divides.  A correctly rounded fp32 division costs about ten instructions, so the common case takes a shortcut that
+// provably gives the same integer: a product with r = fl32(1/scale), kept wherever it lies far enough from a half-integer that the
+// definition's quotient must round alike; otherwise (or in rows whose quotients are exact halves) the eight values of the chunk are
+// redone with the division.
+constexpr float kTieMargin = 0x1.4p-23f, kTieRest = 0x1p-22f;  // of packed8_own_max, below
 struct RowQuantizer {
     float scale, recip, lo, hi, margin;
-    __device__ __forceinline__ RowQuantizer(float amax, float qmax, float lo_, float hi_) : lo(lo_), hi(hi_), margin(qmax * 0x1.4p-23f) {
+    __device__ __forceinline__ RowQuantizer(float amax, float qmax, float lo_, float hi_) : lo(lo_), hi(hi_), margin(qmax * kTieMargin) {
         scale = __fdiv_rn(amax, qmax);
         recip = __fdiv_rn(1.0f, scale);  // unused when amax == 0
     }
+    // Any range of codes and any scale.  q' = fl32(x * r): |q' - x/scale| <= |x/scale| * (2^-23 + 2^-48) < 1.6e-5 for |x/scale| <= 128,
+    // and the definition's quotient fl32(x/scale) lies within 3.9e-6 of x/scale: from 1e-4 off a half-integer both round to the same
+    // integer (about 2 in 10^4 elements are nearer).
     __device__ __forceinline__ void codes8(const float (&x)[8], int (&q)[8]) const {
         bool near_tie = false;
 #pragma unroll
@@ -245,7 +247,7 @@ struct RowQuantizer {
     //
     // q' being the exact product x * recip here, it is within |q'| 2^-24 of x / scale (recip is rounded once), and the definition's
     // quotient is within as much of it: beyond |q'| 2^-23 of a half-integer both round alike.  The distance's own roundings are below 2^-24.
-    // Taken is qmax 1.25 2^-23 for every value, or, PER_VALUE, |n| 1.25 2^-23 + 2^-22 with n = rne(q'), |q'| <= |n| + 1/2: one more operation
+    // Taken is qmax 1.25 2^-23 (kTieMargin) for every value, or, PER_VALUE, |n| 1.25 2^-23 + 2^-22 with n = rne(q'), |q'| <= |n| + 1/2: one more operation
     // each, and a division for one value in a million where most are small, as they are behind outliers.  With 1e-4 for every value
     // one wave in ten took the division per eight values of a lane, and nearly every launch waited for one that did: 16 x 5120
     // 2.58 -> 2.32 us, 1024 x 13824 9.8 -> 9.3; SiLU * up, 333 x 11008 6.3 -> 5.9 and, PER_VALUE, 5.8.  Inside the linear, where every
@@ -261,10 +263,10 @@ struct RowQuantizer {
             // inputs each is one v_fma_mix_f32, which converts its operand on the way in.
             const float t = fmaf(x[j], recip, kShift);
             const float distance = fabsf(fmaf(x[j], recip, kShift - t));
-            off = fmaxf(off, PER_VALUE ? fmaf(fabsf(kShift - t), 0x1.4p-23f, distance) : distance);
+            off = fmaxf(off, PER_VALUE ? fmaf(fabsf(kShift - t), kTieMargin, distance) : distance);
             b[j] = __float_as_uint(t);
         }
-        if (off > 0.5f - (PER_VALUE ? 0x1p-22f : margin)) {
+        if (off > 0.5f - (PER_VALUE ? kTieRest : margin)) {
 #pragma unroll
             for (int j = 0; j < 8; ++j) b[j] = (unsigned)(int)fminf(fmaxf(rintf(__fdiv_rn(x[j], scale)), lo), hi);
         }
