@@ -36,7 +36,7 @@ extern "C" {
  *                    9, 10 = the tiles of 4, 5 run by two sets of waves that split every 128-k stage between
  *                    them and add their integer sums before the epilogue (same bits; never the library's choice);
  *                    11 = 256 x 192 as 4 x 2 waves; 12 = 128 x 256 as 8 waves with a four-stage ring, one workgroup
- *                    per compute unit.  The library chooses among some of these and eight further tiles of its own.
+ *                    per compute unit.  The library chooses among some of these and ten further tiles of its own.
  * Exactly one of out_fp16 / acc_i32 must be non-NULL (s_a and s_w may be NULL
  * when acc_i32 is requested).
  */
@@ -65,7 +65,8 @@ int w4a8_gemm_tuned(const int8_t *xq, const float *s_a, const uint8_t *wp, const
  *   variant, splits : as in w4a8_gemm_tiled_splitk, for SPLITK and SPLITK_STATIC only;
  *   tiling : out, one of W4A8_TILING_* (never an AUTO one);
  *   tile   : out, output tile of a PREFILL tiling, else 0.  1 .. 12 as for PREFILL_TILED above (for PREFILL as well); 13 = 64 x
- *            256, 14 = 128 x 384, 15 = 128 x 192, 16 = 64 x 192, 17 = 128 x 320, 18 = 192 x 320, 19 = 192 x 256, 20 = 192 x 192;
+ *            256, 14 = 128 x 384, 15 = 128 x 192, 16 = 64 x 192, 17 = 128 x 320, 18 = 192 x 320, 19 = 192 x 256, 20 = 192 x 192,
+ *            32 = 256 x 320, 33 = 192 x 384 (these two over tiled int4 weights, beyond 512 tokens);
  *            of the medium-M kernel over tiled weights: 21 = 32 x 32, 22 and 23 = 32 x 64, 24 = 32 x 96, 25 = 48 x 128, 26 = 64 x 96,
  *            27 = 64 x 128, 28 = 64 x 160, 29 = 16 x 16, 30 = 16 x 32, 31 = 96 x 128;
  *   slices : out, K slices.

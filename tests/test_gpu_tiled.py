@@ -203,3 +203,22 @@ def test_librarys_choice_on_ragged_shapes_of_every_tile(gpu, oracle, M, N, K, ti
 @pytest.mark.parametrize("M,N,K,tile", [(770, 19617, 1056, 32), (641, 21770, 1056, 33)])  # a row, a channel and a K group past a tile
 def test_librarys_choice_of_the_tiles_for_many_tokens(gpu, oracle, M, N, K, tile):
     test_librarys_choice_on_ragged_shapes_of_every_tile(gpu, oracle, M, N, K, tile)
+
+
+@pytest.mark.parametrize("M,N,K,tile", [(770, 19617, 1056, 32), (770, 19616, 1056, 32), (641, 21770, 1056, 33), (641, 21772, 1056, 33)])
+def test_raw_sums_of_the_tiles_for_many_tokens(gpu, oracle, M, N, K, tile):
+    """The form that returns int32 sums, stored four at a time where N allows it and one by one elsewhere: every element against the
+    32 x 128 tile, sampled rows against the oracle."""
+    t = gpu
+    assert w4a8.w4a8_route(w4a8.ROUTE_GEMM_TILED, M, N, K) == (TILED, tile, 1)
+    xq, wq, _, _ = synth.uniform_codes(M, N, K, config_id=59)
+    wp = oracle.pack_w4(wq)
+    dxq, wt = t.from_numpy(xq).cuda(), w4a8.w4a8_tile_weights(t.from_numpy(wp).cuda())
+    acc = w4a8.w4a8_gemm_tuned(dxq, None, wt, None, TILED, 0, want_acc=True, N=N)
+    ref = w4a8.w4a8_gemm_tuned(dxq, None, wt, None, TILED, 8, want_acc=True, N=N)
+    t.cuda.synchronize()
+    assert t.equal(acc, ref)
+    rows = [0, M // 2, M - 1]
+    ones = np.ones(max(M, N), np.float32)
+    acc_o, _, _ = oracle.gemm(xq[rows], ones[:3], wp, ones[:N])
+    assert_equal_bits(acc.cpu().numpy()[rows], acc_o, f"raw sums M={M} N={N} K={K}")

@@ -169,7 +169,7 @@ def test_several_slices_are_kept_where_they_are_faster_than_the_medium_m_kernel(
         assert w4a8_route(ROUTE_GEMM_TILED, M, N, K) == (TILING_PREFILL_TILED, 21, 1), (M, N, K)  # no workspace, no slices
     for M, N, K in [(50, 4096, 11008), (62, 4096, 5760), (54, 3745, 9248), (62, 1359, 5920), (58, 8877, 6144), (51, 3520, 5760)]:
         tiling, tile, slices = w4a8_route(ROUTE_SPLITK, M, N, K)
-        assert tiling == TILING_PREFILL_TILED and tile >= 21 and slices == 1, (M, N, K)
+        assert tiling == TILING_PREFILL_TILED and 21 <= tile <= 31 and slices == 1, (M, N, K)
 
 
 def test_tiles_for_many_tokens_are_those_that_measured_faster():
