@@ -206,10 +206,11 @@ constexpr TileCost kTileCosts[] = {
 // 5 to 8 us beside its stages, and the chip is at its power limit.  Fits over 600 shapes (380 random, 220 of whole tiles, the models' linears
 // among them; M 513 .. 2300, N 1024 .. 65536, K 1024 .. 28672; weights cold, the chip warm; about 9 % off, but alike for all tiles), their
 // shares and shorter terms then moved by hand towards the choices that measured best.  On 870 other random shapes (M 513 .. 2300, K from
-// 1024) choosing by them costs 0.8 % on average over always taking the fastest of the sixteen, the prices above on fourteen tiles 1.5 %;
-// 4 of the 870 take over 3 % longer than by those, by 6 % at most.  (64 x 256 had been fitted cheaper than 64 x 192 where both take one
-// round: N = 4224, K = 15808, M = 689 56.6 us, 52.5 as 64 x 192.)  Two tiles are in here alone, worth 0.3 % each: 256 x 320 (N = 10240,
-// K = 8192, M = 2048, one round where 192 x 256 takes two: 126.8 -> 111.2 us) and 192 x 384 (N = 21888, K = 13184, M = 718: 169 -> 148).
+// 1024; every weight byte cold) choosing by them costs 0.7 % on average over always taking the fastest of the sixteen, the prices above on
+// fourteen tiles 1.3 %; 4 of the 870 take over 3 % longer than by those, by 6 % at most.  (64 x 256 had been fitted cheaper than
+// 64 x 192 where both take one round: N = 4224, K = 15808, M = 689 56.8 us, 51.8 as 64 x 192.)  Two tiles are in here alone, worth 0.3 %
+// each: 256 x 320 (N = 10240, K = 8192, M = 2048, one round where 192 x 256 takes two: 126.8 -> 111.2 us) and 192 x 384 (N = 21888,
+// K = 13184, M = 718: 169 -> 148).
 // More of the output per operand byte is what counts at the power limit:
 // the matrix instructions alone hold 2.35 GHz, with the LDS reads of 256 x 256 2.1, with operands coming from L2 as well 1.9.
 constexpr int kManyTokens = 512, kManyTokensMinK = 1024;
@@ -376,10 +377,10 @@ constexpr StepCost kMediumCosts[] = {
 // layer around it 306 us instead of 299, at the power limit.  (On 60 shapes beyond 512 tokens it then gives 7.0 %, with 3 % 7.1.)
 double medium_over_tiles(int M) { return M <= 512 ? 1.03 : 1.15; }
 // Over int4 weights beyond 512 tokens 12 %, and against the prices of kTileCosts, not those of kManyTokensTileCosts, which ask more for few and
-// small tiles and less for a long K.  On 870 random shapes (M 513 .. 2300) the choice then costs 1.1 % on average over always taking the fastest of
-// all tiles, and 5 shapes take over 3 % longer than by kTileCosts and 15 % alone (1.9 %), by 6 % at most; 15 % cost 1.3 %.  Against
-// kManyTokensTileCosts 15 % cost 1.2 %, but 15 shapes take over 3 % longer (N = 3072, K = 1024, M = 586 as 32 x 64 tiles 1.34 times as long,
-// N = 3264, K = 3680, M = 768 16.0 us as 64 x 256 tiles where 64 x 160 take 13.9).
+// small tiles and less for a long K.  On the same 870 shapes the choice among all tiles then costs 1.2 % on average over always taking the
+// fastest, and 4 shapes take over 3 % longer than by kTileCosts and 15 % alone (2.0 %), by 5 % at most; 15 % cost 1.4 %.  Against
+// kManyTokensTileCosts 15 % cost 1.1 %, but 13 shapes take over 3 % longer (N = 3072, K = 1024, M = 586 7.3 us as 32 x 64 tiles, 5.8 as
+// 64 x 128; N = 3264, K = 3680, M = 768 17.1 as 64 x 256, 14.1 as 64 x 160).
 constexpr double kMediumOverManyTokens = 1.12;
 
 // Against weight streaming: 10 % lower than its price, preference included (streaming_preferred), where that takes one slice

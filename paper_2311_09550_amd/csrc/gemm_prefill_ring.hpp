@@ -136,8 +136,8 @@ __global__ __launch_bounds__(64 * WM * WN * KS, 2) void gemm_prefill_tiled_kerne
     // from the memory-side cache cost the clock at the power limit about three times what bytes from L2 do: N = 57344, K = 8192, M = 2048
     // 1175 MB and 940, N = 10240 319 and 151 (with the taller tile), N = 5120, M = 1024 as 128 x 192 108 and 93; the 70B layer 1207 us and
     // 1197.  kAtOnce: what the LDS of 32 compute units holds, three of the smallest tiles each.  (With two for every workgroup of
-    // four waves 64 x 64 tiles of unsigned weights took nine tile rows in two groups: N = 3679, K = 6720, M = 521 32.5 us before there were
-    // groups, then 38.0, now 32.2.)
+    // four waves 64 x 64 tiles of unsigned weights took nine tile rows in two groups: N = 3679, K = 6720, M = 521 32.1 us before there were
+    // groups, then 37.8, now 31.8.)
     constexpr int kAtOnce = 32 * (160 * 1024 / (kEpiScales + 4 * (BM + BN)));
     constexpr int kBestRows = [] {
         int m = 1;

@@ -53,7 +53,9 @@ hipError_t launch_tile_swiglu(PrefillArgs p, hipStream_t stream) {
 // What bounds it is latency: a thread has four channels of a row, one load from each slab.  SPLITS slabs, known at compile time, are
 // asked for at once; 0: any number, one behind the other (a loop that waits at every slab, which this kernel was for any number, with a
 // 64-bit division per thread in front: GEMM and sum of N = 5120, K = 13824, M = 128 in six slices 21.0 -> 20.8 us, of N = 1502,
-// K = 12032, M = 50, whose channels are read one by one, 10.7 -> 9.4).
+// K = 12032, M = 50, whose channels are read one by one, 10.7 -> 9.4).  A row takes whole workgroups of 1024 channels: a narrow output leaves
+// most of one idle and is no slower for it (before and now, with the GEMM: N = 64, K = 16736, M = 123 11.4 us and 10.2, N = 1232,
+// K = 29376, M = 499 30.4 and 29.5, N = 1056, K = 13824, M = 16 level).
 template <int SPLITS>
 __global__ __launch_bounds__(256) void splitk_epilogue_kernel(const int *__restrict__ part, const float *__restrict__ s_a,
                                                               const float *__restrict__ s_w, unsigned short *__restrict__ out, int M, int N,
