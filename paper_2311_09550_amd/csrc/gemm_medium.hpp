@@ -34,10 +34,10 @@ constexpr int medium_lds_bytes(int mt, int nt, int nw, int kg) {
 // loaded into the registers of the one wave that uses it (a lane's 16 bytes of a tiled block are an operand of both MFMA
 // steps of a k step), its successor being requested as soon as it has been converted; and an output too narrow for a tile
 // per compute unit is cut finer instead of along K over workgroups, which costs slabs of sums and a second launch.
-// What bounds it: the bytes a compute unit brings in, (BM + BN / 2) K, at 61 to 74 KB/us while the weights come from memory and 72 to
-// 84 from the memory-side cache, which is the reason for the shapes (near square in bytes, one per compute unit); and 3.5 to 6 us of
-// launch, exchange and epilogue.  That rate is no limit of the memory (2.5 TB/s): a fragment is requested one stage ahead of its
-// use, and a stage, 64 KB for 64 x 128, lasts as long as its loads take to arrive, 1.07 us.
+// What bounds it: the bytes a compute unit brings in, (BM + BN / 2) K, at 56 to 77 KB/us while the weights come from memory and 79 to
+// 90 from the memory-side cache, which is the reason for the shapes (near square in bytes, one per compute unit); and 3 to 5 us of
+// launch, exchange and epilogue.  That rate is no limit of the memory (3.3 TB/s): a fragment is requested one stage ahead of its
+// use, and a stage, 64 KB for 64 x 128, lasts as long as its loads take to arrive, 1.17 us.
 template <int MT, int NT, int NW, int KG, bool ACC_OUT, int WBITS, bool SWIGLU, bool NOT_KEPT>
 __global__ __launch_bounds__(64 * NW * KG, MT * NT <= 12 && WBITS == 4 ? 4 : 2) void gemm_medium_kernel(W4A8_PREFILL_PARAMS) {
     const PrefillArgs p = prefill_args<16 * MT, 16 * NT * NW>(W4A8_PREFILL_PARAM_NAMES);
