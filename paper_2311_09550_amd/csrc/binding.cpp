@@ -23,6 +23,7 @@
 #include <cstring>
 #include <exception>
 #include <memory>
+#include <new>
 #include <tuple>
 #include <type_traits>
 #include <utility>
@@ -431,7 +432,12 @@ PyObject *bound(PyObject *, PyObject *args) {
     if (!PyArg_ParseTuple(args, "sO!O!iO", &name, &PyLong_Type, &address, &PyTuple_Type, &values, &device, &keep)) return nullptr;
     void *const entry = PyLong_AsVoidPtr(address);
     if (!entry || !check) return PyErr_Occurred() ? nullptr : Py_NewRef(Py_None);
-    std::unique_ptr<Marshalled> call = marshal_by_name(name, entry, values);
+    std::unique_ptr<Marshalled> call;
+    try {
+        call = marshal_by_name(name, entry, values);
+    } catch (const std::bad_alloc &) {
+        return PyErr_NoMemory();
+    }
     if (!call) {
         PyErr_Clear();
         Py_RETURN_NONE;
